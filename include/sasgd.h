@@ -155,7 +155,7 @@ int sasgd_sumGradients(sasgd_ctx* ctx, int32_t* out_pending);
  * overwritten holds a version some learner has pulled but not yet used.
  * Deferred launch: when every gradient of the window was computed by the library's learners (pushGradient) and the
  * window has fewer than 25 gradients, the host bookkeeping is done at once but the kernels are enqueued later --
- * at the next calcGradient, evaluate, getter, sasgd_flush or sasgd_destroy, or when 8 updates or 64 gradients have
+ * at the next calcGradient, evaluate, getter, sasgd_flush or sasgd_destroy, or when 32 updates or 64 gradients have
  * gathered -- so that consecutive updates become ONE pass over theta and v: they are read once, the steps are applied
  * in order in registers (the arithmetic of the separate launches, bit for bit) and written once, and every step still
  * writes its weight version.  With n = lambda (one gradient per update) this is most of the server's memory traffic.

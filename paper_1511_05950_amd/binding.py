@@ -1,4 +1,5 @@
-"""ctypes binding of libsasgd.so: argument marshalling only, same names as the C ABI (include/sasgd.h).
+"""Binding of libsasgd.so: argument marshalling only, same names as the C ABI (include/sasgd.h).  ctypes, and for the calls
+made once per gradient or update the CPython module _fastcalls (same calls, cheaper conversions).
 
 Device buffers are passed as torch CUDA tensors (their data_ptr is forwarded) or raw integer addresses.
 The library is required: there is no fallback path, loading fails loudly when it has not been built.
@@ -63,11 +64,12 @@ class SasgdError(RuntimeError):
 
 
 _lib = None
+_fast = None
 
 
 def load():
-    """Load libsasgd.so (built by paper_1511_05950_amd.build); raises if it is missing."""
-    global _lib
+    """Load libsasgd.so (built by paper_1511_05950_amd.build); raises if it or the CPython module is missing."""
+    global _lib, _fast
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(
@@ -107,6 +109,9 @@ def load():
         for name in EXPORTS:
             if name not in ("sasgd_last_error", "sasgd_version"):
                 getattr(lib, name).restype = ctypes.c_int
+        from . import _fastcalls                # links against the library loaded above
+        _fastcalls.set_error_class(SasgdError)
+        _fast = _fastcalls
         _lib = lib
     return _lib
 
@@ -136,10 +141,7 @@ class Sasgd:
         cfg.num_params = num_params
         cfg.flags = flags
         cfg.alpha0, cfg.momentum, cfg.weight_decay = alpha0, momentum, weight_decay
-        if stream is None:
-            import torch
-            stream = torch.cuda.current_stream().cuda_stream
-        cfg.stream = stream
+        cfg.stream = current_stream() if stream is None else stream
         self._layers = None
         if net is None:
             cfg.net = NET_NONE
@@ -197,26 +199,19 @@ class Sasgd:
 
     # -- learner side
     def getMinibatch(self, learner, images_dev, labels_dev):
-        self._check(load().sasgd_getMinibatch(self._h, learner, _addr(images_dev), _addr(labels_dev)))
+        _fast.get_minibatch(self._h.value, learner, images_dev, labels_dev)
 
     def pullWeights(self, learner, staleness_request=0):
-        ts = ctypes.c_int64()
-        self._check(load().sasgd_pullWeights(self._h, learner, staleness_request, ctypes.byref(ts)))
-        return ts.value
+        return _fast.pull_weights(self._h.value, learner, staleness_request)
 
     def calcGradient(self, learners, out_loss_dev=None):
-        arr = (ctypes.c_int32 * len(learners))(*learners)
-        self._check(load().sasgd_calcGradient(self._h, arr, len(learners), _addr(out_loss_dev)))
+        _fast.calc_gradient(self._h.value, learners, out_loss_dev)
 
     def pushGradient(self, learner):
-        tau = ctypes.c_int32()
-        self._check(load().sasgd_pushGradient(self._h, learner, ctypes.byref(tau)))
-        return tau.value
+        return _fast.push_gradient(self._h.value, learner)
 
     def pushGradientExternal(self, grad_dev, timestamp):
-        tau = ctypes.c_int32()
-        self._check(load().sasgd_pushGradientExternal(self._h, _addr(grad_dev), timestamp, ctypes.byref(tau)))
-        return tau.value
+        return _fast.push_gradient_external(self._h.value, grad_dev, timestamp)
 
     # -- training-loop pieces around the hot path
     def evaluate(self, learners, out_loss_dev, out_rank_dev):
@@ -232,23 +227,17 @@ class Sasgd:
 
     # -- server side
     def sumGradients(self):
-        pending = ctypes.c_int32()
-        self._check(load().sasgd_sumGradients(self._h, ctypes.byref(pending)))
-        return pending.value
+        return _fast.sum_gradients(self._h.value)
 
     def applyUpdate(self):
-        ts = ctypes.c_int64()
-        self._check(load().sasgd_applyUpdate(self._h, ctypes.byref(ts)))
-        return ts.value
+        return _fast.apply_update(self._h.value)
 
     def flush(self):
         self._check(load().sasgd_flush(self._h))
 
     # -- getters
     def timestamp(self):
-        ts = ctypes.c_int64()
-        self._check(load().sasgd_timestamp(self._h, ctypes.byref(ts)))
-        return ts.value
+        return _fast.timestamp(self._h.value)
 
     def numParams(self):
         p = ctypes.c_int64()
@@ -306,22 +295,20 @@ def applyUpdateNoAlloc(theta_in_dev, theta_out_dev, v_dev, grads_dev, staleness,
                        momentum=0.0, weight_decay=0.0, shadow_out_dev=None, num_params=None, stream=None):
     """sasgd_applyUpdateNoAlloc: the context-free server update that allocates nothing (see include/sasgd.h).
     grads_dev: sequence of device tensors / addresses; staleness: sequence of ints."""
-    lib = load()
-    c = len(grads_dev)
+    load()
     if num_params is None:
-        num_params = int(theta_in_dev.numel())
+        num_params = theta_in_dev.numel()
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
-    ptrs = (ctypes.c_void_p * max(c, 1))(*[_addr(g) for g in grads_dev])
-    taus = (ctypes.c_int32 * max(c, 1))(*[int(t) for t in staleness])
-    err = ctypes.create_string_buffer(256)
-    rc = lib.sasgd_applyUpdateNoAlloc(_addr(theta_in_dev), _addr(theta_out_dev), _addr(v_dev), _addr(shadow_out_dev), num_params, c,
-                                      ptrs, taus, LR_MODES[lr_mode] if isinstance(lr_mode, str) else lr_mode, alpha0, momentum,
-                                      weight_decay, stream, err, len(err))
-    if rc != OK:
-        raise SasgdError(rc, err.value.decode())
-    return rc
+        stream = current_stream()
+    return _fast.apply_update_no_alloc(theta_in_dev, theta_out_dev, v_dev, shadow_out_dev, num_params, grads_dev, staleness,
+                                       LR_MODES[lr_mode] if isinstance(lr_mode, str) else lr_mode, alpha0, momentum, weight_decay, stream)
+
+
+def current_stream():
+    """Handle of torch's current stream on the current device (without the Stream object around it where torch offers that)."""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(torch.cuda.current_device()) if raw is not None and torch.cuda.is_initialized() else torch.cuda.current_stream().cuda_stream
 
 
 def version():

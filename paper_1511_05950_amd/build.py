@@ -1,16 +1,19 @@
-"""Compile the HIP sources under csrc/ into libsasgd.so for gfx950 (run: python -m paper_1511_05950_amd.build)."""
+"""Compile the HIP sources under csrc/ into libsasgd.so for gfx950 and the CPython module beside it (run: python -m paper_1511_05950_amd.build)."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsasgd.so")
+PYEXT_SRC = os.path.join(HERE, "pyext", "fastcalls.c")
+PYEXT = os.path.join(HERE, "_fastcalls.so")
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-x", "hip",
@@ -51,7 +54,17 @@ def build(force=True, verbose=False):
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    build_pyext()
     return LIB
+
+
+def build_pyext():
+    """The CPython module of the per-gradient and per-update calls (host code only), linked against libsasgd.so beside it."""
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"], PYEXT_SRC, "-o", PYEXT,
+           "-L", HERE, "-l:libsasgd.so", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("building %s failed:\n%s" % (PYEXT, r.stderr))
 
 
 if __name__ == "__main__":

@@ -154,6 +154,7 @@ hipError_t enqueue_updates(sasgd_ctx* ctx, int n) {
   u.v = ctx->v;
   u.sum_buf = ctx->sum_buf;
   u.reverse = (int)(i0 & 1);   // consecutive single updates walk in opposite directions (last-level cache reuse)
+  u.reuse = 1;
   u.theta_in = bf ? ctx->ring_f32 : ctx->ring_f32 + (size_t)slot_of(ctx, i0) * ctx->slot_elems_f32;
   u.theta_out = bf ? ctx->ring_f32 : ctx->ring_f32 + (size_t)slot_of(ctx, i0 + 1) * ctx->slot_elems_f32;
   u.shadow_out = st.shadow_out[0];
@@ -636,6 +637,7 @@ int sasgd_applyUpdateNoAlloc(const float* theta_in_dev, float* theta_out_dev, fl
   u.momentum = momentum;
   u.decay = abar * weight_decay;
   u.reverse = 0;
+  u.reuse = 0;
   u.sum_buf = sums;
   e = launch_apply_update(u, (hipStream_t)stream);
   if (e != hipSuccess) return refuse(SASGD_EHIP, hipGetErrorString(e));

@@ -27,13 +27,14 @@ struct UpdateLaunch {
   float momentum;
   float decay;             // (sum_l coef_l) * weight_decay
   int reverse;             // walk the vector from its end (same result; see apply_update_kernel)
+  int reuse;               // the caller's passes over this vector follow each other in alternating directions
   float* sum_buf;          // kSumStretch floats for the two-pass form of long windows, or nullptr: always one pass
 };
 // Several consecutive updates in ONE pass over the vector ("fused steps"): theta and v are read once, the steps are applied
 // one after the other in registers -- the arithmetic of the single launches in the same order, bit-identical -- and
 // written once; every step still writes its own weight version (ring slot / bf16 copy).  Step t owns the gradient-table
 // entries [first[t], first[t + 1]).
-constexpr int kMaxFusedSteps = 8;
+constexpr int kMaxFusedSteps = 32;
 struct StepTable {
   int32_t steps;
   int32_t first[kMaxFusedSteps + 1];
@@ -41,7 +42,8 @@ struct StepTable {
   float* theta_out[kMaxFusedSteps];     // fp32 weights after step t (ring slot), or nullptr: not kept (fp32 master in place)
   bf16_t* shadow_out[kMaxFusedSteps];   // bf16 copy of the weights after step t, or nullptr
 };
-// Windows of at least kTwoPassMinC gradients are applied in two passes per stretch of kSumStretch parameters.
+// Windows of at least kTwoPassMinC gradients go alone (never fused with other steps) and may be applied in two passes per
+// stretch of kSumStretch parameters.
 constexpr int kTwoPassMinC = 25;
 constexpr int64_t kSumStretch = (int64_t)1 << 21;   // 8 MiB of sums: 512 workgroups of 4 096 parameters
 hipError_t launch_apply_update(const UpdateLaunch& u, hipStream_t stream);

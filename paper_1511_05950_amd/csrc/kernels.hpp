@@ -120,7 +120,7 @@ struct PackTable {
   int64_t total;
 };
 // Several weight versions in one launch (blockIdx.y): flat bf16 vector and packed-filter region of each.
-constexpr int kMaxPackVersions = 8;
+constexpr int kMaxPackVersions = 32;
 struct PackVersions {
   const void* flat[kMaxPackVersions];
   void* packed[kMaxPackVersions];

@@ -7,17 +7,18 @@
 //     theta' = theta_i - v'
 // Reads c gradients, theta_i and v once, writes theta_{i+1} and v once (plus an optional bf16
 // copy of theta_{i+1}): 4 (c + 4) bytes per parameter, nothing else touches HBM.  The kernel is
-// bandwidth bound; each lane moves 16-byte vectors, gradients are read with non-temporal loads
-// because they are never read again.
+// bandwidth bound (latency bound below a million parameters); each lane moves 16-byte vectors,
+// gradients are read with non-temporal loads because they are never read again.
 //
-// Long windows (c >= kTwoPassMinC) take the same arithmetic in two launches per stretch of kSumStretch parameters:
+// Long windows over long vectors (c >= kTwoPassLaunchC, P >= kTwoPassLaunchP) take the same arithmetic in two launches per
+// stretch of kSumStretch parameters:
 // sum_gradients_kernel writes s for the stretch to a small buffer, apply_update_kernel then runs on the stretch with
 // that buffer as its one "gradient" of coefficient 1 (fma(1, s, 0) = s: the result is bit-identical).  A pass that
 // only reads streams c gradients at the rate of a pure read (7.07 TB/s measured); in the single pass the two written
-// streams are interleaved with the 54 read ones all the time and the whole runs at copy speed (5.7 TB/s).  The
+// streams are interleaved with the 54 read ones all the time.  The
 // buffer is 8 MiB and is read back right after it was written (it passes the L2s' memory interface both ways, 8 bytes
-// per parameter of counted traffic, and fits the memory-side cache many times over).  P = 60 M, c = 54:
-// 2.43 -> 2.15 ms; the two forms cross at c of about 24.
+// per parameter of counted traffic, and fits the memory-side cache many times over).  P = 62 M with a bf16 copy: c = 54
+// 2.27 ms against 2.42 ms in one pass; the two forms cross at c of about 30 (1.41 against 1.40 ms).
 #include "ctx.hpp"
 #include "dev_common.hpp"
 
@@ -59,46 +60,73 @@ struct GradTable {
   float coef[kMaxLearners];
 };
 
+typedef float float4v __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float4 ldg_nt(const float4* p) {
-  float4 r;
-  r.x = __builtin_nontemporal_load(&p->x);
-  r.y = __builtin_nontemporal_load(&p->y);
-  r.z = __builtin_nontemporal_load(&p->z);
-  r.w = __builtin_nontemporal_load(&p->w);
-  return r;
+  const float4v r = __builtin_nontemporal_load(reinterpret_cast<const float4v*>(p));
+  return make_float4(r.x, r.y, r.z, r.w);
 }
-
 __device__ __forceinline__ void stg_nt(float4* p, float4 v) {
-  __builtin_nontemporal_store(v.x, &p->x);
-  __builtin_nontemporal_store(v.y, &p->y);
-  __builtin_nontemporal_store(v.z, &p->z);
-  __builtin_nontemporal_store(v.w, &p->w);
+  const float4v r = {v.x, v.y, v.z, v.w};
+  __builtin_nontemporal_store(r, reinterpret_cast<float4v*>(p));
+}
+__device__ __forceinline__ uint2 pack_bf4(float4 a) {
+  uint2 o;
+  o.x = (uint32_t)f2bf(a.x) | ((uint32_t)f2bf(a.y) << 16);
+  o.y = (uint32_t)f2bf(a.z) | ((uint32_t)f2bf(a.w) << 16);
+  return o;
+}
+__device__ __forceinline__ void fma4(float4& s, float cf, const float4& g) {
+  s.x = fmaf(cf, g.x, s.x);
+  s.y = fmaf(cf, g.y, s.y);
+  s.z = fmaf(cf, g.z, s.z);
+  s.w = fmaf(cf, g.w, s.w);
+}
+// v' = m v + s + decay theta, theta' = theta - v': the one place the four-wide update is written down
+__device__ __forceinline__ void update4(float4& a, float4& b, const float4& s, float m, float decay) {
+  b.x = fmaf(m, b.x, s.x) + decay * a.x;
+  b.y = fmaf(m, b.y, s.y) + decay * a.y;
+  b.z = fmaf(m, b.z, s.z) + decay * a.z;
+  b.w = fmaf(m, b.w, s.w) + decay * a.w;
+  a.x -= b.x;
+  a.y -= b.y;
+  a.z -= b.z;
+  a.w -= b.w;
 }
 
-// One-shot grid: a workgroup of 256 lanes owns ILP consecutive 4 KiB pieces of every stream, so each
-// lane keeps ILP * U 16-byte gradient loads in flight.  Measured on MI355X at P = 60 M this shape
-// (ILP 4, U 3, non-temporal loads and stores) gave the highest rate of the shapes tried; grid-stride
-// loops with fewer, longer-lived workgroups were 5-10 % slower.
+// One-wavefront workgroups, ILP pieces of 16 bytes per lane and stream, U gradients in flight.  Two things decide the rate:
+// the loads a lane has outstanding (a window's gradients are requested U at a time, the rest of the window in one go as
+// well), and how many lanes are resident at once.  Fewer resident wavefronts with more loads each keep the c + 2 streams
+// more sequential in DRAM: the launcher bounds the residency by giving a workgroup LDS that it never touches (10 wavefronts
+// per compute unit at 16 KiB, 8 at 20 KiB).  Measured at P = 62 M with the bf16 copy against blocks of 256 lanes with four
+// pieces and three gradients each: c = 18 1 046 -> 875 us (5.4 -> 6.4 TB/s), c = 8 574 -> 459 us, c = 1 249 -> 193 us; at
+// P = 89 578, c = 30 15.5 -> 5.9 us (350 wavefronts instead of 22 blocks).
 // reverse: workgroups take the pieces from the far end first.  A server that applies updates back to back
 // alternates the direction, so each pass starts on the theta and v lines the previous pass touched last, which
-// the 256 MB last-level cache still holds (P = 60 M, c = 1: 204 -> 175 us per update).  NT bit 0 / bit 1: theta
-// and v are read / written with non-temporal hints, which lose that reuse (gradients always are: nobody reads
-// them again).
-// GPLAIN: the gradients are read with ordinary loads (the second pass of a long window reads the sums just written).
-template <int ILP, int U, bool EARLY, bool SHADOW, int NT, bool GPLAIN = false>
-__global__ __launch_bounds__(256) void apply_update_kernel(const float4* theta_in, float4* theta_out, float4* v,
-                                                           uint2* __restrict__ shadow, int64_t n4, int c,
-                                                           GradTable t, float m, float decay, int reverse) {
+// the 256 MB last-level cache still holds (P = 40 M, c = 1: 136 -> 108 us per update).
+// MODE: kCached  theta and v by ordinary loads and stores (vectors that stay in the caches from call to call);
+//       kReuse   ordinary loads, non-temporal stores (the last-level cache serves part of the next pass);
+//       kStream  non-temporal both ways: nothing of theta and v survives until the next pass.
+// A vector length that is no multiple of 4 leaves at most 3 elements to the lane behind the last piece.
+enum { kCached = 0, kReuse = 1, kStream = 2 };
+constexpr int kUpdThreads = 64;
+template <int ILP, int U, bool SHADOW, int MODE>
+__global__ __launch_bounds__(kUpdThreads) void apply_update_kernel(const float* theta_in, float* theta_out, float* v,
+                                                                   bf16_t* __restrict__ shadow, int64_t P, int c, GradTable t, float m,
+                                                                   float decay, int reverse) {
   const int64_t blk = reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
-  const int64_t base = blk * (256 * ILP) + threadIdx.x;
+  const int64_t base = blk * (kUpdThreads * ILP) + threadIdx.x, n4 = P >> 2;
+  const float4* th4 = reinterpret_cast<const float4*>(theta_in);
+  float4* v4 = reinterpret_cast<float4*>(v);
   float4 s[ILP], th[ILP], vv[ILP];
+  bool in[ILP];
 #pragma unroll
-  for (int e = 0; e < ILP; e++) s[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (EARLY) {
-#pragma unroll
-    for (int e = 0; e < ILP; e++) {
-      const int64_t i = base + e * 256;
-      if (i < n4) { if (NT & 1) { th[e] = ldg_nt(theta_in + i); vv[e] = ldg_nt(v + i); } else { th[e] = theta_in[i]; vv[e] = v[i]; } }
+  for (int e = 0; e < ILP; e++) {
+    const int64_t i = base + e * kUpdThreads;
+    in[e] = i < n4;
+    s[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (in[e]) {
+      th[e] = MODE == kStream ? ldg_nt(th4 + i) : th4[i];
+      vv[e] = MODE == kStream ? ldg_nt(v4 + i) : v4[i];
     }
   }
   int l = 0;
@@ -107,66 +135,57 @@ __global__ __launch_bounds__(256) void apply_update_kernel(const float4* theta_i
 #pragma unroll
     for (int u = 0; u < U; u++)
 #pragma unroll
-      for (int e = 0; e < ILP; e++) {
-        const int64_t i = base + e * 256;
-        if (i < n4) g[u][e] = GPLAIN ? reinterpret_cast<const float4*>(t.g[l + u])[i] : ldg_nt(reinterpret_cast<const float4*>(t.g[l + u]) + i);
-      }
+      for (int e = 0; e < ILP; e++)
+        if (in[e]) g[u][e] = ldg_nt(reinterpret_cast<const float4*>(t.g[l + u]) + base + e * kUpdThreads);
 #pragma unroll
-    for (int u = 0; u < U; u++) {           // arrival order l, l+1, ... within every element
-      const float cf = t.coef[l + u];
+    for (int u = 0; u < U; u++)             // arrival order l, l+1, ... within every element
 #pragma unroll
-      for (int e = 0; e < ILP; e++) {
-        s[e].x = fmaf(cf, g[u][e].x, s[e].x);
-        s[e].y = fmaf(cf, g[u][e].y, s[e].y);
-        s[e].z = fmaf(cf, g[u][e].z, s[e].z);
-        s[e].w = fmaf(cf, g[u][e].w, s[e].w);
-      }
-    }
+      for (int e = 0; e < ILP; e++) fma4(s[e], t.coef[l + u], g[u][e]);
   }
-  for (; l < c; l++) {
-    const float cf = t.coef[l];
+  if (l < c) {
+    float4 g[U][ILP];
 #pragma unroll
-    for (int e = 0; e < ILP; e++) {
-      const int64_t i = base + e * 256;
-      if (i < n4) {
-        float4 g = ldg_nt(reinterpret_cast<const float4*>(t.g[l]) + i);
-        s[e].x = fmaf(cf, g.x, s[e].x);
-        s[e].y = fmaf(cf, g.y, s[e].y);
-        s[e].z = fmaf(cf, g.z, s[e].z);
-        s[e].w = fmaf(cf, g.w, s[e].w);
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int e = 0; e < ILP; e++)
+        if (in[e] && l + u < c) g[u][e] = ldg_nt(reinterpret_cast<const float4*>(t.g[l + u]) + base + e * kUpdThreads);
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (l + u < c) {
+#pragma unroll
+        for (int e = 0; e < ILP; e++) fma4(s[e], t.coef[l + u], g[u][e]);
       }
-    }
   }
 #pragma unroll
   for (int e = 0; e < ILP; e++) {
-    const int64_t i = base + e * 256;
-    if (i < n4) {
-      if (!EARLY) { if (NT & 1) { th[e] = ldg_nt(theta_in + i); vv[e] = ldg_nt(v + i); } else { th[e] = theta_in[i]; vv[e] = v[i]; } }
-      float4 a = th[e], b = vv[e];
-      b.x = fmaf(m, b.x, s[e].x) + decay * a.x;
-      b.y = fmaf(m, b.y, s[e].y) + decay * a.y;
-      b.z = fmaf(m, b.z, s[e].z) + decay * a.z;
-      b.w = fmaf(m, b.w, s[e].w) + decay * a.w;
-      a.x -= b.x;
-      a.y -= b.y;
-      a.z -= b.z;
-      a.w -= b.w;
-      if (NT & 2) { stg_nt(v + i, b); stg_nt(theta_out + i, a); } else { v[i] = b; theta_out[i] = a; }
+    const int64_t i = base + e * kUpdThreads;
+    if (in[e]) {
+      update4(th[e], vv[e], s[e], m, decay);
+      float4* to = reinterpret_cast<float4*>(theta_out) + i;
+      if (MODE == kCached) { v4[i] = vv[e]; *to = th[e]; } else { stg_nt(v4 + i, vv[e]); stg_nt(to, th[e]); }
       if (SHADOW) {
-        uint2 o;
-        o.x = (uint32_t)f2bf(a.x) | ((uint32_t)f2bf(a.y) << 16);
-        o.y = (uint32_t)f2bf(a.z) | ((uint32_t)f2bf(a.w) << 16);
-        shadow[i] = o;
+        const uint2 o = pack_bf4(th[e]);
+        if (MODE == kReuse) __builtin_nontemporal_store(((uint64_t)o.y << 32) | o.x, reinterpret_cast<uint64_t*>(shadow) + i);
+        else reinterpret_cast<uint2*>(shadow)[i] = o;
+      }
+    } else if (i == n4) {
+      for (int64_t k = n4 * 4; k < P; k++) {
+        float sum = 0.f;
+        for (int q = 0; q < c; q++) sum = fmaf(t.coef[q], t.g[q][k], sum);
+        const float a = theta_in[k], b = fmaf(m, v[k], sum) + decay * a;
+        v[k] = b;
+        theta_out[k] = a - b;
+        if (SHADOW) shadow[k] = f2bf(a - b);
       }
     }
   }
 }
 
 // First pass of a long window: s = sum_l coef_l g_l for one stretch, the FMA chain of apply_update_kernel, written
-// with ordinary stores.
+// with ordinary stores.  Blocks of 256 lanes, ILP pieces each (a pass that only reads is at 7.07 TB/s this way).
 template <int ILP, int U>
-__global__ __launch_bounds__(256) void sum_gradients_kernel(float4* __restrict__ out, int64_t n4, int c, GradTable t) {
-  const int64_t base = (int64_t)blockIdx.x * (256 * ILP) + threadIdx.x;
+__global__ __launch_bounds__(256) void sum_gradients_kernel(float* __restrict__ out, int64_t len, int c, GradTable t) {
+  const int64_t base = (int64_t)blockIdx.x * (256 * ILP) + threadIdx.x, n4 = len >> 2;
   float4 s[ILP];
 #pragma unroll
   for (int e = 0; e < ILP; e++) s[e] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -181,232 +200,171 @@ __global__ __launch_bounds__(256) void sum_gradients_kernel(float4* __restrict__
         if (i < n4) g[u][e] = ldg_nt(reinterpret_cast<const float4*>(t.g[l + u]) + i);
       }
 #pragma unroll
-    for (int u = 0; u < U; u++) {           // arrival order l, l+1, ... within every element
-      const float cf = t.coef[l + u];
+    for (int u = 0; u < U; u++)             // arrival order l, l+1, ... within every element
 #pragma unroll
-      for (int e = 0; e < ILP; e++) {
-        s[e].x = fmaf(cf, g[u][e].x, s[e].x);
-        s[e].y = fmaf(cf, g[u][e].y, s[e].y);
-        s[e].z = fmaf(cf, g[u][e].z, s[e].z);
-        s[e].w = fmaf(cf, g[u][e].w, s[e].w);
-      }
-    }
+      for (int e = 0; e < ILP; e++) fma4(s[e], t.coef[l + u], g[u][e]);
   }
-  for (; l < c; l++) {
-    const float cf = t.coef[l];
+  for (; l < c; l++)
 #pragma unroll
     for (int e = 0; e < ILP; e++) {
       const int64_t i = base + e * 256;
-      if (i < n4) {
-        float4 g = ldg_nt(reinterpret_cast<const float4*>(t.g[l]) + i);
-        s[e].x = fmaf(cf, g.x, s[e].x);
-        s[e].y = fmaf(cf, g.y, s[e].y);
-        s[e].z = fmaf(cf, g.z, s[e].z);
-        s[e].w = fmaf(cf, g.w, s[e].w);
-      }
+      if (i < n4) fma4(s[e], t.coef[l], ldg_nt(reinterpret_cast<const float4*>(t.g[l]) + i));
     }
-  }
-#pragma unroll
-  for (int e = 0; e < ILP; e++) {
-    const int64_t i = base + e * 256;
-    if (i < n4) out[i] = s[e];
-  }
-}
-
-// Fused steps over a flat stretch (see StepTable): per element the operations of apply_update_kernel, step after step.
-template <int ILP>
-__global__ __launch_bounds__(256) void apply_updates_fused_kernel(const float4* theta_in, float4* theta_final, float4* v, int64_t n4,
-                                                                  GradTable t, StepTable st, float m) {
-  const int64_t base = (int64_t)blockIdx.x * (256 * ILP) + threadIdx.x;
-  float4 th[ILP], vv[ILP];
-#pragma unroll
-  for (int e = 0; e < ILP; e++) {
-    const int64_t i = base + e * 256;
-    if (i < n4) { th[e] = ldg_nt(theta_in + i); vv[e] = ldg_nt(v + i); }
-  }
-  for (int step = 0; step < st.steps; step++) {
-    float4 s[ILP];
-#pragma unroll
-    for (int e = 0; e < ILP; e++) s[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int l = st.first[step]; l < st.first[step + 1]; l++) {   // arrival order
-      const float cf = t.coef[l];
-      float4 g[ILP];
-#pragma unroll
-      for (int e = 0; e < ILP; e++) {
-        const int64_t i = base + e * 256;
-        if (i < n4) g[e] = ldg_nt(reinterpret_cast<const float4*>(t.g[l]) + i);
-      }
-#pragma unroll
-      for (int e = 0; e < ILP; e++) {
-        s[e].x = fmaf(cf, g[e].x, s[e].x);
-        s[e].y = fmaf(cf, g[e].y, s[e].y);
-        s[e].z = fmaf(cf, g[e].z, s[e].z);
-        s[e].w = fmaf(cf, g[e].w, s[e].w);
-      }
-    }
-    const float decay = st.decay[step];
-    float4* tout = reinterpret_cast<float4*>(st.theta_out[step]);
-    uint2* shadow = reinterpret_cast<uint2*>(st.shadow_out[step]);
-#pragma unroll
-    for (int e = 0; e < ILP; e++) {
-      const int64_t i = base + e * 256;
-      if (i < n4) {
-        float4 a = th[e], b = vv[e];
-        b.x = fmaf(m, b.x, s[e].x) + decay * a.x;
-        b.y = fmaf(m, b.y, s[e].y) + decay * a.y;
-        b.z = fmaf(m, b.z, s[e].z) + decay * a.z;
-        b.w = fmaf(m, b.w, s[e].w) + decay * a.w;
-        a.x -= b.x;
-        a.y -= b.y;
-        a.z -= b.z;
-        a.w -= b.w;
-        th[e] = a;
-        vv[e] = b;
-        if (tout) stg_nt(tout + i, a);
-        if (shadow) {
-          uint2 o;
-          o.x = (uint32_t)f2bf(a.x) | ((uint32_t)f2bf(a.y) << 16);
-          o.y = (uint32_t)f2bf(a.z) | ((uint32_t)f2bf(a.w) << 16);
-          shadow[i] = o;
-        }
-      }
-    }
-  }
 #pragma unroll
   for (int e = 0; e < ILP; e++) {
     const int64_t i = base + e * 256;
     if (i < n4) {
-      stg_nt(v + i, vv[e]);
-      if (theta_final) stg_nt(theta_final + i, th[e]);
+      reinterpret_cast<float4*>(out)[i] = s[e];
+    } else if (i == n4) {
+      for (int64_t k = n4 * 4; k < len; k++) {
+        float sum = 0.f;
+        for (int q = 0; q < c; q++) sum = fmaf(t.coef[q], t.g[q][k], sum);
+        out[k] = sum;
+      }
     }
   }
 }
 
-// Scalar tail of the fused steps (P not a multiple of 4): at most 3 elements.
-__global__ void apply_updates_fused_tail_kernel(const float* theta_in, float* theta_final, float* v, int64_t begin, int64_t P, GradTable t,
-                                                StepTable st, float m) {
-  const int64_t i = begin + threadIdx.x;
-  if (i >= P) return;
-  float th = theta_in[i], vv = v[i];
-  for (int step = 0; step < st.steps; step++) {
-    float s = 0.f;
-    for (int l = st.first[step]; l < st.first[step + 1]; l++) s = fmaf(t.coef[l], t.g[l][i], s);
-    vv = fmaf(m, vv, s) + st.decay[step] * th;
-    th = th - vv;
-    if (st.theta_out[step]) st.theta_out[step][i] = th;
-    if (st.shadow_out[step]) st.shadow_out[step][i] = f2bf(th);
+// Fused steps over a flat stretch (see StepTable): per element the operations of apply_update_kernel, step after step.
+// The gradients of all steps are one list, requested U at a time whatever step they belong to: the chain of steps waits
+// for memory once per U gradients instead of once per step (P = 89 578, 8 steps of one gradient: 13.7 + 6.5 us for the
+// pass and its scalar tail with one dependent read per step -> 5 us).
+template <int U, bool NT>
+__global__ __launch_bounds__(kUpdThreads) void apply_updates_fused_kernel(const float* theta_in, float* theta_final, float* v, int64_t P, int c,
+                                                                          GradTable t, StepTable st, float m) {
+  const int64_t i = (int64_t)blockIdx.x * kUpdThreads + threadIdx.x, n4 = P >> 2;
+  if (i < n4) {
+    const float4* th4 = reinterpret_cast<const float4*>(theta_in) + i;
+    float4* v4 = reinterpret_cast<float4*>(v) + i;
+    float4 a = NT ? ldg_nt(th4) : *th4, b = NT ? ldg_nt(v4) : *v4;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    int step = 0, end = st.first[1];
+    for (int l0 = 0; l0 < c; l0 += U) {
+      float4 g[U];
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        if (l0 + u < c) g[u] = ldg_nt(reinterpret_cast<const float4*>(t.g[l0 + u]) + i);
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        if (l0 + u >= c) continue;
+        fma4(s, t.coef[l0 + u], g[u]);      // arrival order
+        if (l0 + u + 1 == end) {            // the step's window is complete
+          update4(a, b, s, m, st.decay[step]);
+          s = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (st.theta_out[step]) {
+            float4* to = reinterpret_cast<float4*>(st.theta_out[step]) + i;
+            if (NT) stg_nt(to, a); else *to = a;
+          }
+          if (st.shadow_out[step]) reinterpret_cast<uint2*>(st.shadow_out[step])[i] = pack_bf4(a);
+          step++;
+          if (step < st.steps) end = st.first[step + 1];
+        }
+      }
+    }
+    if (NT) stg_nt(v4, b); else *v4 = b;
+    if (theta_final) {
+      float4* to = reinterpret_cast<float4*>(theta_final) + i;
+      if (NT) stg_nt(to, a); else *to = a;
+    }
+  } else if (i == n4) {                      // at most 3 elements behind the last whole piece
+    for (int64_t k = n4 * 4; k < P; k++) {
+      float a = theta_in[k], b = v[k];
+      for (int step = 0; step < st.steps; step++) {
+        float s = 0.f;
+        for (int l = st.first[step]; l < st.first[step + 1]; l++) s = fmaf(t.coef[l], t.g[l][k], s);
+        b = fmaf(m, b, s) + st.decay[step] * a;
+        a = a - b;
+        if (st.theta_out[step]) st.theta_out[step][k] = a;
+        if (st.shadow_out[step]) st.shadow_out[step][k] = f2bf(a);
+      }
+      v[k] = b;
+      if (theta_final) theta_final[k] = a;
+    }
   }
-  v[i] = vv;
-  if (theta_final) theta_final[i] = th;
 }
 
-// Scalar tail (P not a multiple of 4): at most 3 elements.
-__global__ void apply_update_tail_kernel(const float* theta_in, float* theta_out, float* v, bf16_t* shadow,
-                                         int64_t begin, int64_t P, int c, GradTable t, float m, float decay) {
-  int64_t i = begin + threadIdx.x;
-  if (i >= P) return;
-  float s = 0.f;
-  for (int l = 0; l < c; l++) s = fmaf(t.coef[l], t.g[l][i], s);
-  float vv = fmaf(m, v[i], s) + decay * theta_in[i];
-  float th = theta_in[i] - vv;
-  v[i] = vv;
-  theta_out[i] = th;
-  if (shadow) shadow[i] = f2bf(th);
-}
-
-template <int ILP, int U, bool EARLY, int NT>
-static void launch_shape_nt(const UpdateLaunch& u, const GradTable& t, int64_t n4, hipStream_t stream) {
-  const int blocks = (int)((n4 + 256 * ILP - 1) / (256 * ILP));
-  const float4* tin = reinterpret_cast<const float4*>(u.theta_in);
-  float4* tout = reinterpret_cast<float4*>(u.theta_out);
-  float4* vv = reinterpret_cast<float4*>(u.v);
-  uint2* sh = reinterpret_cast<uint2*>(u.shadow_out);
+template <int ILP, int U, int MODE>
+static void launch_update(const UpdateLaunch& u, const GradTable& t, int residency_lds, hipStream_t stream) {
+  const int64_t pieces = (u.P + 3) / 4;
+  const dim3 grid((unsigned)((pieces + kUpdThreads * ILP - 1) / (kUpdThreads * ILP)));
   if (u.shadow_out)
-    hipLaunchKernelGGL((apply_update_kernel<ILP, U, EARLY, true, NT>), dim3(blocks), dim3(256), 0, stream, tin, tout, vv, sh, n4, u.c, t, u.momentum, u.decay, u.reverse);
+    hipLaunchKernelGGL((apply_update_kernel<ILP, U, true, MODE>), grid, dim3(kUpdThreads), residency_lds, stream, u.theta_in, u.theta_out, u.v,
+                       u.shadow_out, u.P, u.c, t, u.momentum, u.decay, u.reverse);
   else
-    hipLaunchKernelGGL((apply_update_kernel<ILP, U, EARLY, false, NT>), dim3(blocks), dim3(256), 0, stream, tin, tout, vv, sh, n4, u.c, t, u.momentum, u.decay, u.reverse);
+    hipLaunchKernelGGL((apply_update_kernel<ILP, U, false, MODE>), grid, dim3(kUpdThreads), residency_lds, stream, u.theta_in, u.theta_out, u.v,
+                       u.shadow_out, u.P, u.c, t, u.momentum, u.decay, u.reverse);
 }
-// theta and v take ordinary loads and stores for windows of up to kKeepMaxC gradients, so that the next update
-// finds their tail in the last-level cache; behind longer gradient sweeps nothing of them survives and the
-// streaming hints are the faster choice (P = 60 M, c = 54, after other updates: 2.45 against 2.61 ms in one pass).
-constexpr int kKeepMaxC = kTwoPassMinC - 1;
-template <int ILP, int U, bool EARLY>
-static void launch_shape(const UpdateLaunch& u, const GradTable& t, int64_t n4, hipStream_t stream) {
-  if (u.c <= kKeepMaxC) launch_shape_nt<ILP, U, EARLY, 0>(u, t, n4, stream);
-  else launch_shape_nt<ILP, U, EARLY, 3>(u, t, n4, stream);
-}
+
+constexpr int kTwoPassLaunchC = 32;                       // see the head of this file
+constexpr int64_t kTwoPassLaunchP = (int64_t)1 << 24;     // shorter vectors: one pass (P = 10 M, c = 54: 380 against 390 us)
 
 hipError_t launch_apply_update(const UpdateLaunch& u, hipStream_t stream) {
   if (u.P <= 0) return hipSuccess;
-  if (u.P / 4 > (int64_t)0x7fffffff * 256) return hipErrorInvalidValue;
+  if (u.P / 4 > (int64_t)0x7fffff00 * kUpdThreads) return hipErrorInvalidValue;
   GradTable t;
   for (int l = 0; l < kMaxLearners; l++) {
     t.g[l] = l < u.c ? u.grads[l] : nullptr;
     t.coef[l] = l < u.c ? u.coef[l] : 0.f;
   }
-  const int64_t n4 = u.P / 4;
-  if (u.P >= kSumStretch && u.c >= kTwoPassMinC && u.sum_buf) {   // shorter vectors: one launch, nothing to separate
-    // stretches of 512 workgroups (two per compute unit; 256-1024 measured within 4 %, other counts slower)
-    constexpr int64_t stretch4 = kSumStretch / 4;
-    float4* sums = reinterpret_cast<float4*>(u.sum_buf);
+  if (u.P >= kTwoPassLaunchP && u.c >= kTwoPassLaunchC && u.sum_buf) {
+    // stretches of 512 summing workgroups (two per compute unit; 256-1024 measured within 4 %, other counts slower)
+    UpdateLaunch r = u;
+    r.c = 1;
+    r.reverse = 0;
     GradTable tb;
     for (int l = 0; l < kMaxLearners; l++) { tb.g[l] = nullptr; tb.coef[l] = 0.f; }
     tb.g[0] = u.sum_buf;
     tb.coef[0] = 1.0f;
-    for (int64_t off = 0; off < n4; off += stretch4) {
-      const int64_t len = std::min(stretch4, n4 - off);
-      const int blocks = (int)((len + 256 * 4 - 1) / (256 * 4));
+    for (int64_t off = 0; off < u.P; off += kSumStretch) {
+      const int64_t len = std::min(kSumStretch, u.P - off);
+      const int64_t pieces = (len + 3) / 4;
       GradTable ta = t;
-      for (int l = 0; l < u.c; l++) ta.g[l] = t.g[l] + off * 4;
-      hipLaunchKernelGGL((sum_gradients_kernel<4, 3>), dim3(blocks), dim3(256), 0, stream, sums, len, u.c, ta);
-      const float4* tin = reinterpret_cast<const float4*>(u.theta_in) + off;
-      float4* tout = reinterpret_cast<float4*>(u.theta_out) + off;
-      float4* vv = reinterpret_cast<float4*>(u.v) + off;
-      uint2* sh = u.shadow_out ? reinterpret_cast<uint2*>(u.shadow_out) + off : nullptr;
-      if (sh)
-        hipLaunchKernelGGL((apply_update_kernel<4, 1, true, true, 3, true>), dim3(blocks), dim3(256), 0, stream, tin, tout, vv, sh, len, 1, tb, u.momentum, u.decay, 0);
-      else
-        hipLaunchKernelGGL((apply_update_kernel<4, 1, true, false, 3, true>), dim3(blocks), dim3(256), 0, stream, tin, tout, vv, sh, len, 1, tb, u.momentum, u.decay, 0);
+      for (int l = 0; l < u.c; l++) ta.g[l] = t.g[l] + off;
+      hipLaunchKernelGGL((sum_gradients_kernel<4, 3>), dim3((unsigned)((pieces + 1023) / 1024)), dim3(256), 0, stream, u.sum_buf, len, u.c, ta);
+      r.theta_in = u.theta_in + off;
+      r.theta_out = u.theta_out + off;
+      r.v = u.v + off;
+      r.shadow_out = u.shadow_out ? u.shadow_out + off : nullptr;
+      r.P = len;
+      launch_update<2, 8, kStream>(r, tb, 0, stream);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  } else if (n4 > 0) {
-    if (u.c == 1) launch_shape<4, 1, true>(u, t, n4, stream);
-    else if (u.c == 2 || u.c == 4) launch_shape<4, 2, true>(u, t, n4, stream);
-    else launch_shape<4, 3, false>(u, t, n4, stream);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (n4 * 4 < u.P) {
-    hipLaunchKernelGGL(apply_update_tail_kernel, dim3(1), dim3(64), 0, stream, u.theta_in, u.theta_out, u.v,
-                       u.shadow_out, n4 * 4, u.P, u.c, t, u.momentum, u.decay);
     return hipGetLastError();
   }
-  return hipSuccess;
+  // The lines between the shapes are where their times crossed in sweeps over P = 20 k .. 62 M and c = 1 .. 54 (residency in
+  // wavefronts per compute unit: 10 at 16 KiB of LDS each, 8 at 20 KiB, otherwise bounded by registers):
+  //   up to 0.6 M parameters the chip is not full: one piece per lane and as many loads in flight as registers allow;
+  //   above, short windows want two pieces per lane, long ones fewer resident wavefronts;
+  //   beyond 32 M parameters theta and v (8 bytes each) no longer fit the last-level cache: unless the passes alternate in
+  //   direction (u.reuse), nothing of them can be reused and the streaming hints win.
+  const bool stream_mode = !u.reuse && u.P > ((int64_t)1 << 25);
+  if (u.P <= 600000) launch_update<1, 16, kCached>(u, t, 0, stream);
+  else if (u.P <= 1500000) launch_update<2, 8, kCached>(u, t, 0, stream);
+  else if (stream_mode && u.c <= 4) launch_update<1, 16, kStream>(u, t, 0, stream);
+  else if (stream_mode) launch_update<1, 8, kStream>(u, t, 20 * 1024, stream);
+  else if (u.c <= 4) launch_update<2, 8, kReuse>(u, t, 0, stream);
+  else if (u.P <= 6000000 || u.c > 24) launch_update<2, 4, kReuse>(u, t, 20 * 1024, stream);
+  else launch_update<1, 8, kReuse>(u, t, 16 * 1024, stream);
+  return hipGetLastError();
 }
 
 hipError_t launch_apply_updates_fused(const UpdateLaunch& u, const StepTable& st, float* final_theta, hipStream_t stream) {
   if (u.P <= 0) return hipSuccess;
   if (st.steps < 1 || st.steps > kMaxFusedSteps || st.first[0] != 0 || st.first[st.steps] != u.c || u.c > kMaxLearners) return hipErrorInvalidValue;
-  if (u.P / 4 > (int64_t)0x7fffffff * 256) return hipErrorInvalidValue;
+  for (int k = 0; k < st.steps; k++)
+    if (st.first[k + 1] <= st.first[k]) return hipErrorInvalidValue;   // the kernel closes a step with its last gradient
+  if (u.P / 4 > (int64_t)0x7fffff00 * kUpdThreads) return hipErrorInvalidValue;
   GradTable t;
   for (int l = 0; l < kMaxLearners; l++) {
     t.g[l] = l < u.c ? u.grads[l] : nullptr;
     t.coef[l] = l < u.c ? u.coef[l] : 0.f;
   }
-  const int64_t n4 = u.P / 4;
-  if (n4 > 0) {
-    const int blocks = (int)((n4 + 256 * 4 - 1) / (256 * 4));
-    hipLaunchKernelGGL((apply_updates_fused_kernel<4>), dim3(blocks), dim3(256), 0, stream, reinterpret_cast<const float4*>(u.theta_in),
-                       reinterpret_cast<float4*>(final_theta), reinterpret_cast<float4*>(u.v), n4, t, st, u.momentum);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (n4 * 4 < u.P) {
-    hipLaunchKernelGGL(apply_updates_fused_tail_kernel, dim3(1), dim3(64), 0, stream, u.theta_in, final_theta, u.v, n4 * 4, u.P, t, st, u.momentum);
-    return hipGetLastError();
-  }
-  return hipSuccess;
+  const int64_t pieces = (u.P + 3) / 4;
+  const dim3 grid((unsigned)((pieces + kUpdThreads - 1) / kUpdThreads));
+  if (u.P >= 1500000)
+    hipLaunchKernelGGL((apply_updates_fused_kernel<8, true>), grid, dim3(kUpdThreads), 0, stream, u.theta_in, final_theta, u.v, u.P, u.c, t, st, u.momentum);
+  else
+    hipLaunchKernelGGL((apply_updates_fused_kernel<16, false>), grid, dim3(kUpdThreads), 0, stream, u.theta_in, final_theta, u.v, u.P, u.c, t, st, u.momentum);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ update of a fully connected layer from factors

@@ -8,6 +8,11 @@ at the start).  This realises the server-view update of the paper's Section 3 fo
 from __future__ import annotations
 
 
+def _rows(schedule):
+    """The schedule as lists of Python integers (an array element costs several times as much to fetch)."""
+    return schedule.tolist() if hasattr(schedule, "tolist") else [[int(t) for t in row] for row in schedule]
+
+
 def run_softsync(ctx, schedule, batch_of, lam, loss_out=None, on_gradient=None, first_update=0, base_rates=None):
     """Run len(schedule) server updates.
 
@@ -22,6 +27,7 @@ def run_softsync(ctx, schedule, batch_of, lam, loss_out=None, on_gradient=None, 
     """
     c = ctx.c
     log = []
+    schedule = _rows(schedule)
     for k in range(len(schedule)):
         i = first_update + k
         assert ctx.timestamp() == i
@@ -31,7 +37,7 @@ def run_softsync(ctx, schedule, batch_of, lam, loss_out=None, on_gradient=None, 
             learner = (i * c + l) % lam
             x, y = batch_of(i, l)
             ctx.getMinibatch(learner, x, y)
-            stamps.append(ctx.pullWeights(learner, int(schedule[k][l])))
+            stamps.append(ctx.pullWeights(learner, schedule[k][l]))
             learners.append(learner)
         ctx.calcGradient(learners, loss_out)
         for l in range(c):
@@ -58,20 +64,22 @@ def run_softsync_batched(ctx, schedule, batch_of, lam, loss_out=None, first_upda
     """
     c = ctx.c
     K = len(schedule)
+    stale = [t for row in _rows(schedule) for t in row]      # gradient id -> requested staleness
     done = {}                                   # gradient id -> (learner, timestamp j)
     log = []
     calls = 0
+    timestamp, push, close, apply = ctx.timestamp, ctx.pushGradient, ctx.sumGradients, ctx.applyUpdate
     for k in range(K):
         i = first_update + k
-        assert ctx.timestamp() == i
-        if any((k * c + l) not in done for l in range(c)):
+        assert timestamp() == i
+        first = k * c
+        if any(g not in done for g in range(first, first + c)):
             learners = []
-            for g in range(k * c, min(K * c, k * c + lam)):
+            for g in range(first, min(K * c, first + lam)):
                 if g in done:
                     continue
-                k2, l2 = divmod(g, c)
-                i2 = first_update + k2
-                j = i2 - min(int(schedule[k2][l2]), i2)
+                i2, l2 = first_update + g // c, g % c
+                j = i2 - min(stale[g], i2)
                 if j > i:
                     continue                    # its weights do not exist yet
                 learner = (i2 * c + l2) % lam
@@ -84,11 +92,10 @@ def run_softsync_batched(ctx, schedule, batch_of, lam, loss_out=None, first_upda
             ctx.calcGradient(learners, loss_out if len(learners) == c else None)
             calls += 1
         for l in range(c):
-            learner, j = done.pop(k * c + l)
-            tau = ctx.pushGradient(learner)
-            log.append((i, l, learner, j, tau))
-        ctx.sumGradients()
-        ctx.applyUpdate()
+            learner, j = done.pop(first + l)
+            log.append((i, l, learner, j, push(learner)))
+        close()
+        apply()
     ctx.flush()
     return log, calls
 
