@@ -93,28 +93,56 @@ __device__ __forceinline__ void update4(float4& a, float4& b, const float4& s, f
   a.w -= b.w;
 }
 
+// sum_l coef_l g_l of one element over gradients [begin, end), U loads in flight: the chain of fma4 in the same order.
+template <int U>
+__device__ __forceinline__ float sum_element(const GradTable& t, int begin, int end, int64_t k) {
+  float s = 0.f;
+  for (int l = begin; l < end; l += U) {
+    float g[U];
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (l + u < end) g[u] = t.g[l + u][k];
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (l + u < end) s = fmaf(t.coef[l + u], g[u], s);
+  }
+  return s;
+}
+
 // One-wavefront workgroups, ILP pieces of 16 bytes per lane and stream, U gradients in flight.  Two things decide the rate:
 // the loads a lane has outstanding (a window's gradients are requested U at a time, the rest of the window in one go as
 // well), and how many lanes are resident at once.  Fewer resident wavefronts with more loads each keep the c + 2 streams
 // more sequential in DRAM: the launcher bounds the residency by giving a workgroup LDS that it never touches (10 wavefronts
 // per compute unit at 16 KiB, 8 at 20 KiB).  Measured at P = 62 M with the bf16 copy against blocks of 256 lanes with four
 // pieces and three gradients each: c = 18 1 046 -> 875 us (5.4 -> 6.4 TB/s), c = 8 574 -> 459 us, c = 1 249 -> 193 us; at
-// P = 89 578, c = 30 15.5 -> 5.9 us (350 wavefronts instead of 22 blocks).
+// P = 89 578, c = 30 18 -> 6 us (350 wavefronts instead of 22 blocks and a second launch for the last elements).
 // reverse: workgroups take the pieces from the far end first.  A server that applies updates back to back
 // alternates the direction, so each pass starts on the theta and v lines the previous pass touched last, which
 // the 256 MB last-level cache still holds (P = 40 M, c = 1: 136 -> 108 us per update).
 // MODE: kCached  theta and v by ordinary loads and stores (vectors that stay in the caches from call to call);
 //       kReuse   ordinary loads, non-temporal stores (the last-level cache serves part of the next pass);
 //       kStream  non-temporal both ways: nothing of theta and v survives until the next pass.
-// A vector length that is no multiple of 4 leaves at most 3 elements to the lane behind the last piece.
+// A vector length that is no multiple of 4 leaves at most 3 elements to a workgroup of their own, one lane each (left to a
+// lane of the last whole workgroup, their loads come after that wavefront's own: 11.3 instead of 6 us at P = 89 578, c = 30).
 enum { kCached = 0, kReuse = 1, kStream = 2 };
 constexpr int kUpdThreads = 64;
 template <int ILP, int U, bool SHADOW, int MODE>
 __global__ __launch_bounds__(kUpdThreads) void apply_update_kernel(const float* theta_in, float* theta_out, float* v,
                                                                    bf16_t* __restrict__ shadow, int64_t P, int c, GradTable t, float m,
                                                                    float decay, int reverse) {
-  const int64_t blk = reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
-  const int64_t base = blk * (kUpdThreads * ILP) + threadIdx.x, n4 = P >> 2;
+  const int64_t n4 = P >> 2, whole = (n4 + kUpdThreads * ILP - 1) / (kUpdThreads * ILP);
+  if (blockIdx.x >= whole) {
+    const int64_t k = n4 * 4 + threadIdx.x;
+    if (k >= P) return;
+    const float s = sum_element<U>(t, 0, c, k);
+    const float a = theta_in[k], b = fmaf(m, v[k], s) + decay * a;
+    v[k] = b;
+    theta_out[k] = a - b;
+    if (SHADOW) shadow[k] = f2bf(a - b);
+    return;
+  }
+  const int64_t blk = reverse ? whole - 1 - blockIdx.x : blockIdx.x;
+  const int64_t base = blk * (kUpdThreads * ILP) + threadIdx.x;
   const float4* th4 = reinterpret_cast<const float4*>(theta_in);
   float4* v4 = reinterpret_cast<float4*>(v);
   float4 s[ILP], th[ILP], vv[ILP];
@@ -168,15 +196,6 @@ __global__ __launch_bounds__(kUpdThreads) void apply_update_kernel(const float* 
         if (MODE == kReuse) __builtin_nontemporal_store(((uint64_t)o.y << 32) | o.x, reinterpret_cast<uint64_t*>(shadow) + i);
         else reinterpret_cast<uint2*>(shadow)[i] = o;
       }
-    } else if (i == n4) {
-      for (int64_t k = n4 * 4; k < P; k++) {
-        float sum = 0.f;
-        for (int q = 0; q < c; q++) sum = fmaf(t.coef[q], t.g[q][k], sum);
-        const float a = theta_in[k], b = fmaf(m, v[k], sum) + decay * a;
-        v[k] = b;
-        theta_out[k] = a - b;
-        if (SHADOW) shadow[k] = f2bf(a - b);
-      }
     }
   }
 }
@@ -186,6 +205,11 @@ __global__ __launch_bounds__(kUpdThreads) void apply_update_kernel(const float* 
 template <int ILP, int U>
 __global__ __launch_bounds__(256) void sum_gradients_kernel(float* __restrict__ out, int64_t len, int c, GradTable t) {
   const int64_t base = (int64_t)blockIdx.x * (256 * ILP) + threadIdx.x, n4 = len >> 2;
+  if (blockIdx.x >= (n4 + 256 * ILP - 1) / (256 * ILP)) {
+    const int64_t k = n4 * 4 + threadIdx.x;
+    if (k < len) out[k] = sum_element<16>(t, 0, c, k);
+    return;
+  }
   float4 s[ILP];
 #pragma unroll
   for (int e = 0; e < ILP; e++) s[e] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -213,15 +237,7 @@ __global__ __launch_bounds__(256) void sum_gradients_kernel(float* __restrict__ 
 #pragma unroll
   for (int e = 0; e < ILP; e++) {
     const int64_t i = base + e * 256;
-    if (i < n4) {
-      reinterpret_cast<float4*>(out)[i] = s[e];
-    } else if (i == n4) {
-      for (int64_t k = n4 * 4; k < len; k++) {
-        float sum = 0.f;
-        for (int q = 0; q < c; q++) sum = fmaf(t.coef[q], t.g[q][k], sum);
-        out[k] = sum;
-      }
-    }
+    if (i < n4) reinterpret_cast<float4*>(out)[i] = s[e];
   }
 }
 
@@ -232,7 +248,7 @@ __global__ __launch_bounds__(256) void sum_gradients_kernel(float* __restrict__ 
 template <int U, bool NT>
 __global__ __launch_bounds__(kUpdThreads) void apply_updates_fused_kernel(const float* theta_in, float* theta_final, float* v, int64_t P, int c,
                                                                           GradTable t, StepTable st, float m) {
-  const int64_t i = (int64_t)blockIdx.x * kUpdThreads + threadIdx.x, n4 = P >> 2;
+  const int64_t i = (int64_t)blockIdx.x * kUpdThreads + threadIdx.x, n4 = P >> 2, whole = (n4 + kUpdThreads - 1) / kUpdThreads;
   if (i < n4) {
     const float4* th4 = reinterpret_cast<const float4*>(theta_in) + i;
     float4* v4 = reinterpret_cast<float4*>(v) + i;
@@ -266,27 +282,42 @@ __global__ __launch_bounds__(kUpdThreads) void apply_updates_fused_kernel(const 
       float4* to = reinterpret_cast<float4*>(theta_final) + i;
       if (NT) stg_nt(to, a); else *to = a;
     }
-  } else if (i == n4) {                      // at most 3 elements behind the last whole piece
-    for (int64_t k = n4 * 4; k < P; k++) {
-      float a = theta_in[k], b = v[k];
-      for (int step = 0; step < st.steps; step++) {
-        float s = 0.f;
-        for (int l = st.first[step]; l < st.first[step + 1]; l++) s = fmaf(t.coef[l], t.g[l][k], s);
-        b = fmaf(m, b, s) + st.decay[step] * a;
-        a = a - b;
-        if (st.theta_out[step]) st.theta_out[step][k] = a;
-        if (st.shadow_out[step]) st.shadow_out[step][k] = f2bf(a);
+  } else if (blockIdx.x >= whole) {          // at most 3 elements behind the last whole piece, one lane each
+    const int64_t k = n4 * 4 + threadIdx.x;
+    if (k >= P) return;
+    float a = theta_in[k], b = v[k], s = 0.f;
+    int step = 0, end = st.first[1];
+    for (int l0 = 0; l0 < c; l0 += U) {
+      float g[U];
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        if (l0 + u < c) g[u] = t.g[l0 + u][k];
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        if (l0 + u >= c) continue;
+        s = fmaf(t.coef[l0 + u], g[u], s);
+        if (l0 + u + 1 == end) {
+          b = fmaf(m, b, s) + st.decay[step] * a;
+          a = a - b;
+          s = 0.f;
+          if (st.theta_out[step]) st.theta_out[step][k] = a;
+          if (st.shadow_out[step]) st.shadow_out[step][k] = f2bf(a);
+          step++;
+          if (step < st.steps) end = st.first[step + 1];
+        }
       }
-      v[k] = b;
-      if (theta_final) theta_final[k] = a;
     }
+    v[k] = b;
+    if (theta_final) theta_final[k] = a;
   }
 }
 
+// Workgroups for n4 pieces, `per` each, plus the one of the remaining elements.
+static unsigned update_grid(int64_t P, int64_t per) { return (unsigned)((P / 4 + per - 1) / per + (P % 4 ? 1 : 0)); }
+
 template <int ILP, int U, int MODE>
 static void launch_update(const UpdateLaunch& u, const GradTable& t, int residency_lds, hipStream_t stream) {
-  const int64_t pieces = (u.P + 3) / 4;
-  const dim3 grid((unsigned)((pieces + kUpdThreads * ILP - 1) / (kUpdThreads * ILP)));
+  const dim3 grid(update_grid(u.P, kUpdThreads * ILP));
   if (u.shadow_out)
     hipLaunchKernelGGL((apply_update_kernel<ILP, U, true, MODE>), grid, dim3(kUpdThreads), residency_lds, stream, u.theta_in, u.theta_out, u.v,
                        u.shadow_out, u.P, u.c, t, u.momentum, u.decay, u.reverse);
@@ -317,10 +348,9 @@ hipError_t launch_apply_update(const UpdateLaunch& u, hipStream_t stream) {
     tb.coef[0] = 1.0f;
     for (int64_t off = 0; off < u.P; off += kSumStretch) {
       const int64_t len = std::min(kSumStretch, u.P - off);
-      const int64_t pieces = (len + 3) / 4;
       GradTable ta = t;
       for (int l = 0; l < u.c; l++) ta.g[l] = t.g[l] + off;
-      hipLaunchKernelGGL((sum_gradients_kernel<4, 3>), dim3((unsigned)((pieces + 1023) / 1024)), dim3(256), 0, stream, u.sum_buf, len, u.c, ta);
+      hipLaunchKernelGGL((sum_gradients_kernel<4, 3>), dim3(update_grid(len, 1024)), dim3(256), 0, stream, u.sum_buf, len, u.c, ta);
       r.theta_in = u.theta_in + off;
       r.theta_out = u.theta_out + off;
       r.v = u.v + off;
@@ -358,8 +388,7 @@ hipError_t launch_apply_updates_fused(const UpdateLaunch& u, const StepTable& st
     t.g[l] = l < u.c ? u.grads[l] : nullptr;
     t.coef[l] = l < u.c ? u.coef[l] : 0.f;
   }
-  const int64_t pieces = (u.P + 3) / 4;
-  const dim3 grid((unsigned)((pieces + kUpdThreads - 1) / kUpdThreads));
+  const dim3 grid(update_grid(u.P, kUpdThreads));
   if (u.P >= 1500000)
     hipLaunchKernelGGL((apply_updates_fused_kernel<8, true>), grid, dim3(kUpdThreads), 0, stream, u.theta_in, final_theta, u.v, u.P, u.c, t, st, u.momentum);
   else
