@@ -195,4 +195,99 @@ hipError_t launch_fc_save_factors(const PtrTab& ws, const PtrTab& grads, size_t 
                                   int64_t b_off, int N, int in, int out, int NP, int count, hipStream_t s);
 hipError_t launch_fc_expand_factors(const void* fx, const void* fdy, float* dw, int N, int in, int out, int NP, hipStream_t s);
 
+// ---- small networks and mini-batches in few launches (compact.hip)
+// Division by a number known at launch: floor(n / d) for n d < 2^32.
+struct FastDiv {
+  uint32_t d, m;
+  __host__ void set(int div) { d = (uint32_t)div; m = magic_u32(div); }
+#ifdef __HIPCC__
+  __device__ __forceinline__ int operator()(int n) const { return d <= 1u ? n : (int)__umulhi((uint32_t)n, m); }
+#endif
+};
+// Where a layer's input comes from.
+enum { CSRC_TENSOR = 0, CSRC_IMAGES = 1, CSRC_MAXPOOL = 2, CSRC_AVGPOOL = 3, CSRC_FLAT = 4 };
+struct CompactSrc {
+  int kind;
+  int C, H, W;                 // the input as the layer sees it (behind the pooling)
+  size_t off;                  // tensor that is read (elements)
+  int YH, YW, pks, pst, relu;  // pooled sources: size of that tensor, window, stride, ReLU behind the pooling
+  size_t out_off, arg_off;     // pooled sources: where the pooled tensor (elements) and its winners (bytes) are kept
+  FastDiv by_c, by_c4;         // C and C / 4
+};
+// Gradient of a convolution's output: stored (masked), or behind the pooling layer that follows the convolution.
+enum { CGRAD_PLAIN = 0, CGRAD_MAXPOOL = 1, CGRAD_AVGPOOL = 2 };
+struct CompactGrad {
+  int kind;
+  int use_mask;                // pooled kinds: zero where the convolution's output (at mask_off) is not positive
+  int OH, OW, K, PH, PW, pks, pst;
+  size_t off, mask_off, arg_off;
+  FastDiv by_k, by_k4, by_pst;
+};
+struct CompactConv {
+  int N, C, H, W, K, OH, OW, ks, stride, pad;
+  int64_t w_off, b_off;
+  FastDiv by_ow, by_w, by_cols, by_dcols;   // OW, W, patch columns of the forward pass and of the input gradient
+};
+struct CompactBwd {
+  int dgrad_blocks, col_groups, blocks_per_group, tile;   // set by the launcher
+  int splits;
+  size_t dx_off, mask_off;        // elements
+  int use_mask;
+  size_t part_off;                // bytes from the workspace base: `splits` partial gradients of part_elems floats, [K][ks ks C + 1]
+  int64_t part_elems;
+};
+struct CompactHead {
+  int N, in, K;
+  int64_t w_off, b_off;
+  size_t flat_off, dz_off, dx_off, loss_off;   // elements; loss_off bytes
+  int use_mask, need_dx;
+  int C, HW;                   // the input in front of a flattening: channels, pixels (HW = 1, C = in: none)
+  FastDiv by_hw;
+};
+struct CompactFc {
+  int N, in, out, relu, use_mask;
+  int HW;                      // pixels of the input in front of a flattening (1: none)
+  FastDiv by_hw;
+  int64_t w_off, b_off;
+  size_t x_off, y_off, dy_off, dx_off;
+  int splits, aligned;         // set by the launcher
+  size_t part_off;             // bytes: partial tiles [splits][N][columns]
+};
+enum { CJOB_SUM = 0, CJOB_FC = 1, CJOB_LOSS = 2 };
+struct CompactJob {
+  int kind, first_block, splits, groups;
+  int64_t elems, w_off;
+  size_t part_off;
+  int K, C, taps;
+  int in, out;
+  size_t x_off, dy_off;
+};
+constexpr int kMaxCompactJobs = 16;
+struct CompactFinish {
+  CompactJob job[kMaxCompactJobs];
+  int count;
+};
+// Floats per pixel of an LDS patch: room for C rounded up to a multiple of four, and 4 (mod 8).
+__host__ __device__ inline int compact_pixel_stride(int C) { return (((C + 3) & ~3) & ~7) + ((((C + 3) & ~3) & 7) > 4 ? 12 : 4); }
+// Wavefronts of a weight-gradient workgroup side by side across its column blocks (a power of two).
+__host__ __device__ inline int wgrad_waves_across(int blocks, int waves) {
+  int w = 1;
+  while (w < blocks && w < waves) w *= 2;
+  return w;
+}
+bool compact_conv_ok(const CompactConv& v, bool need_dx);
+bool compact_head_ok(int in, int K);
+bool compact_fc_ok(int in, int out);
+int compact_splits(const CompactConv& v, bool need_dx, int count, int most);
+hipError_t launch_compact_fwd(bool is_bf16, const PtrTab& ws, const CPtrTab& wts, const CPtrTab& imgs, const CompactConv& v, const CompactSrc& src,
+                              bool relu, size_t y_off, const float* mean, int count, hipStream_t s);
+hipError_t launch_compact_bwd(bool is_bf16, const PtrTab& ws, const CPtrTab& wts, const CPtrTab& imgs, const CompactConv& v,
+                              const CompactSrc& x, const CompactGrad& gr, const CompactBwd& bw, const float* mean, bool need_dx, int count, hipStream_t s);
+hipError_t launch_compact_flatten(bool is_bf16, const PtrTab& ws, const CompactSrc& src, size_t flat_off, int N, int count, hipStream_t s);
+hipError_t launch_compact_head(bool is_bf16, const PtrTab& ws, const CPtrTab& wts, const CPtrTab& labels, const CompactSrc& src, const CompactHead& hd,
+                               int32_t* rank_out, int count, hipStream_t s);
+hipError_t launch_compact_fc(bool is_bf16, const PtrTab& ws, const CPtrTab& wts, const CompactFc& f, bool dgrad, size_t part_bytes, int count, hipStream_t s);
+hipError_t launch_compact_finish(bool is_bf16, const PtrTab& ws, const PtrTab& grads, const CompactFinish& fin, size_t loss_off, int N, float* loss_out,
+                                 int count, hipStream_t s);
+
 }  // namespace sasgd

@@ -52,8 +52,27 @@ struct Tensor {
   bool relu = false;           // values are post-ReLU (a gradient flowing into it must be masked)
 };
 
+// The network as the compact kernels run it (compact.hip): convolutions with the pooling layer behind each, then fully
+// connected layers.  Indices into ops.
+struct CompactStage {
+  int conv = -1, pool = -1;
+  CompactConv v{};
+  size_t part_off = 0;         // bytes: partial weight gradients
+  int most_splits = 1;
+};
+struct CompactPlan {
+  bool ok = false;             // the network fits
+  bool always = false;         // no other path is worth taking; otherwise small calls only
+  int64_t macs = 0;            // multiply-adds of an image's forward pass
+  std::vector<CompactStage> stages;
+  int flatten = -1;            // OP_FLATTEN in front of the first fully connected layer, if any
+  std::vector<int> fcs;
+  std::vector<size_t> fc_dy;   // element offset of every fully connected layer's output gradient
+};
+
 struct Net {
   int mu = 0;
+  CompactPlan compact;
   bool bf16 = false;
   int classes = 0;
   bool scores_f32 = false;
@@ -78,6 +97,45 @@ struct Net {
   void* ws[kMaxLearners] = {nullptr};
   const float* pixel_mean = nullptr;   // optional [C][H][W] fp32, subtracted while the input is re-laid out
 };
+
+// Recognises networks the compact kernels take: conv (pool)? repeated, (flatten)?, fc repeated.
+static CompactPlan compact_plan(const Net* net) {
+  CompactPlan cp;
+  const std::vector<Op>& ops = net->ops;
+  const int n = (int)ops.size();
+  int i = 0;
+  while (i < n && ops[(size_t)i].kind == OP_CONV && !ops[(size_t)i].is_fc) {
+    CompactStage st;
+    st.conv = i;
+    const ConvShape& cs = ops[(size_t)i].cs;
+    st.v = CompactConv{cs.N, cs.C, cs.H, cs.W, cs.K, cs.OH, cs.OW, cs.ks, cs.stride, cs.pad, ops[(size_t)i].w_off, ops[(size_t)i].b_off, {}, {}, {}, {}};
+    st.v.by_ow.set(cs.OW);
+    st.v.by_w.set(cs.W);
+    st.v.by_cols.set((cs.OW - 1) * cs.stride + cs.ks);
+    st.v.by_dcols.set(cs.W - 1 + cs.ks);
+    if (!compact_conv_ok(st.v, !cp.stages.empty())) return cp;
+    i++;
+    if (i < n && (ops[(size_t)i].kind == OP_POOL_MAX || ops[(size_t)i].kind == OP_POOL_AVG)) {
+      if (ops[(size_t)i].ps.ks > 2 * ops[(size_t)i].ps.stride) return cp;      // more than two windows per direction reach a position
+      st.pool = i++;
+    }
+    cp.stages.push_back(st);
+  }
+  if (cp.stages.empty()) return cp;
+  if (i < n && ops[(size_t)i].kind == OP_FLATTEN) cp.flatten = i++;
+  for (; i < n; i++) {
+    if (!ops[(size_t)i].is_fc) return cp;
+    cp.fcs.push_back(i);
+  }
+  if (cp.fcs.empty() || cp.stages.size() + cp.fcs.size() + 1 > (size_t)kMaxCompactJobs) return cp;
+  for (size_t k = 0; k < cp.fcs.size(); k++) {
+    const ConvShape& cs = ops[(size_t)cp.fcs[k]].cs;
+    if (k + 1 == cp.fcs.size() ? !compact_head_ok(cs.C, cs.K) : !compact_fc_ok(cs.C, cs.K)) return cp;
+  }
+  for (const Op& op : ops) cp.macs += (int64_t)op.cs.K * op.cs.C * op.cs.ks * op.cs.ks * op.cs.OH * op.cs.OW;
+  cp.ok = true;
+  return cp;
+}
 
 static int pool_out_size(int n, int k, int s) {
   int o = (n - k + s - 1) / s + 1;
@@ -276,6 +334,23 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
     net->scores_f32 = true;
     if (net->bf16) { new_tensor(net->tensors[(size_t)cur].elems); }   // room for the wider elements (tensor is last in the arena)
   }
+  // small networks and mini-batches: the compact kernels.  They are the only good path where a layer does not fit the other
+  // matrix-instruction kernels (channel counts that are no multiple of 8); otherwise they serve small calls.
+  net->compact = compact_plan(net);
+  if (net->compact.ok) {
+    CompactPlan& cp = net->compact;
+    bool any_factored = false;
+    for (size_t k = 0; k < net->ops.size(); k++) {
+      const Op& op = net->ops[k];
+      if (op.kind == OP_CONV && !op.mfma && (int)k != cp.fcs.back()) cp.always = true;
+      any_factored = any_factored || op.factored;
+    }
+    if (cp.always)
+      for (Op& op : net->ops) op.factored = op.grouped = false;
+    else if (any_factored) cp.ok = false;
+    if (cp.ok)
+      for (int f : cp.fcs) cp.fc_dy.push_back(net->tensors[(size_t)new_tensor((size_t)N * net->ops[(size_t)f].cs.K)].off);
+  }
   for (Op& op : net->ops) {
     if (!op.factored) continue;
     op.fx_off = net->tensors[(size_t)new_tensor((size_t)op.cs.C * op.NP)].off;
@@ -311,7 +386,7 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
   cursor += 256;
   for (Op& op : net->ops) op.gf.zero_off = op.gd.zero_off = net->zero_off;
   for (const Op& op : net->ops) {
-    if (!op.mfma || op.pack_fwd < 0) continue;
+    if (!op.mfma || op.pack_fwd < 0 || (net->compact.ok && net->compact.always)) continue;
     if (net->pack.count == kMaxPackJobs) { delete net; err = "too many convolution layers for the MFMA path"; return SASGD_EINVAL; }
     PackJob& jb = net->pack.job[net->pack.count++];
     jb.v = op.vc;
@@ -340,9 +415,21 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
     need = wg > need ? wg : need;
     need = dg > need ? dg : need;
   }
-  if (need > 0) {
+  size_t compact_parts = 0;                        // partial weight gradients of all convolutions side by side
+  if (net->compact.ok)
+    for (CompactStage& st : net->compact.stages) {
+      // one tile of 32 positions per workgroup where that costs little memory
+      const int64_t elems = (int64_t)st.v.K * st.v.C * st.v.ks * st.v.ks + st.v.K;
+      st.most_splits = (int)std::min<int64_t>(std::min<int64_t>(256, std::max<int64_t>(32, ((int64_t)1 << 20) / elems)),
+                                              (int64_t)st.v.N * ((st.v.OH * st.v.OW + 31) / 32));
+      st.part_off = compact_parts;
+      compact_parts += ((size_t)st.most_splits * ((size_t)st.v.K * st.v.C * st.v.ks * st.v.ks + st.v.K) * 4 + 255) & ~(size_t)255;
+    }
+  if (need > 0 || compact_parts > 0) {
     size_t sb = need * 8;
     if (sb > ((size_t)128 << 20)) sb = need > ((size_t)128 << 20) ? need : ((size_t)128 << 20);
+    if (net->compact.ok && net->compact.always) sb = 0;
+    sb = std::max(sb, compact_parts);
     net->scratch_off = (bytes + 255) & ~(size_t)255;
     net->scratch_bytes = sb;
     bytes = net->scratch_off + sb;
@@ -355,7 +442,7 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
     size_t g = 256, max_in = 0, max_out = 0;
     net->g_zero_off = 0;
     for (Op& op : net->ops) {
-      if (!(op.is_fc && op.mfma) || op.grouped) continue;
+      if (!(op.is_fc && op.mfma) || op.grouped || (net->compact.ok && net->compact.always)) continue;
       const size_t in = (size_t)op.cs.C, outn = (size_t)op.cs.K;
       if ((N * in * 2) % 16 || (N * outn * (op.out_f32 ? 4 : 2)) % 16 || R * std::max(in, outn) * 4 >= ((size_t)1 << 31)) continue;
       op.stacked = true;
@@ -442,6 +529,156 @@ int net_factored_layers(const Net* net, FactoredLayer* out, int max) {
 void net_set_pixel_mean(Net* net, const float* mean_dev) { net->pixel_mean = mean_dev; }
 void net_input_shape(const Net* net, int* C, int* H, int* W) { *C = net->inC; *H = net->inH; *W = net->inW; }
 
+// Multiply-adds of a call's forward passes up to which the compact kernels serve networks that the layer-by-layer kernels
+// take as well.  Measured on the CIFAR-shaped net (12.3 M an image), compact against layer by layer: fp32 at 4 / 64 / 128 / 480
+// images 62 / 162 / 274 / 874 us against 139 / 256 / 358 / 952; bf16 at 8 / 32 / 64 images 86 / 125 / 217 against 123 / 149 /
+// 169.  fp32 with 93 M an image at 12 / 128 images: 272 / 2 034 against 371 / 2 203.
+constexpr int64_t kCompactMacs[2] = {(int64_t)1600 << 20, (int64_t)400 << 20};   // fp32, bf16
+
+static CompactSrc compact_src(const Net* net, const CompactStage* st) {
+  CompactSrc s;
+  memset(&s, 0, sizeof(s));
+  if (!st) {
+    s.kind = CSRC_IMAGES;
+    s.C = net->inC; s.H = net->inH; s.W = net->inW;
+    s.by_c.set(s.C);
+    return s;
+  }
+  const Op& conv = net->ops[(size_t)st->conv];
+  s.off = net->tensors[(size_t)conv.out_t].off;
+  s.C = conv.cs.K; s.H = conv.cs.OH; s.W = conv.cs.OW;
+  s.by_c.set(s.C);
+  s.by_c4.set(s.C / 4);
+  if (st->pool < 0) return s;                        // CSRC_TENSOR
+  const Op& pool = net->ops[(size_t)st->pool];
+  s.kind = pool.kind == OP_POOL_MAX ? CSRC_MAXPOOL : CSRC_AVGPOOL;
+  s.YH = s.H; s.YW = s.W;
+  s.H = pool.ps.OH; s.W = pool.ps.OW;
+  s.pks = pool.ps.ks; s.pst = pool.ps.stride; s.relu = pool.relu ? 1 : 0;
+  s.out_off = net->tensors[(size_t)pool.out_t].off;
+  s.arg_off = pool.arg_off;
+  return s;
+}
+
+static hipError_t compact_gradient(Net* net, const PtrTab& ws, const CPtrTab& wts, const CPtrTab& imgs, const CPtrTab& labs, const PtrTab& grads,
+                                   int count, float* out_loss_dev, int32_t* out_rank_dev, hipStream_t stream) {
+  const bool bf = net->bf16;
+  const CompactPlan& cp = net->compact;
+  const std::vector<Tensor>& T = net->tensors;
+  const std::vector<Op>& ops = net->ops;
+  const int ns = (int)cp.stages.size(), nf = (int)cp.fcs.size();
+  // ---- forward
+  for (int k = 0; k < ns; k++) {
+    const CompactStage& st = cp.stages[(size_t)k];
+    const Op& op = ops[(size_t)st.conv];
+    TRY(launch_compact_fwd(bf, ws, wts, imgs, st.v, compact_src(net, k ? &cp.stages[(size_t)k - 1] : nullptr), op.relu, T[(size_t)op.out_t].off,
+                           net->pixel_mean, count, stream));
+  }
+  const CompactStage& last = cp.stages.back();
+  const size_t flat_off = T[(size_t)ops[(size_t)cp.fcs[0]].in_t].off;        // input of the first fully connected layer, (C, H, W) order
+  const bool pooled_relu = last.pool >= 0 && ops[(size_t)last.pool].relu;
+  const CompactSrc flat_src = compact_src(net, &last);
+  const int flat_hw = flat_src.H * flat_src.W;
+  auto fc_of = [&](int k) {
+    const Op& op = ops[(size_t)cp.fcs[(size_t)k]];
+    CompactFc f;
+    memset(&f, 0, sizeof(f));
+    f.N = net->mu; f.in = op.cs.C; f.out = op.cs.K;
+    f.relu = op.relu ? 1 : 0;
+    f.w_off = op.w_off; f.b_off = op.b_off;
+    f.x_off = T[(size_t)op.in_t].off;
+    f.y_off = T[(size_t)op.out_t].off;
+    f.dy_off = cp.fc_dy[(size_t)k];
+    f.dx_off = k ? cp.fc_dy[(size_t)k - 1] : net->grad_a;
+    f.use_mask = (k ? T[(size_t)op.in_t].relu : pooled_relu) ? 1 : 0;
+    f.HW = k ? 1 : flat_hw;
+    f.by_hw.set(f.HW);
+    f.part_off = net->scratch_off;
+    return f;
+  };
+  if (nf > 1) {
+    TRY(launch_compact_flatten(bf, ws, compact_src(net, &last), flat_off, net->mu, count, stream));
+    for (int k = 0; k + 1 < nf; k++) TRY(launch_compact_fc(bf, ws, wts, fc_of(k), false, net->scratch_bytes, count, stream));
+  }
+  // ---- last fully connected layer, loss, its input gradient
+  {
+    const CompactFc f = fc_of(nf - 1);
+    CompactSrc s = compact_src(net, &last);
+    if (nf > 1) {
+      memset(&s, 0, sizeof(s));
+      s.kind = CSRC_FLAT;
+      s.off = f.x_off;
+    }
+    CompactHead hd;
+    memset(&hd, 0, sizeof(hd));
+    hd.N = net->mu; hd.in = f.in; hd.K = f.out;
+    hd.w_off = f.w_off; hd.b_off = f.b_off;
+    hd.flat_off = flat_off; hd.dz_off = f.dy_off; hd.dx_off = f.dx_off; hd.loss_off = net->loss_off;
+    hd.use_mask = f.use_mask;
+    hd.need_dx = 1;
+    hd.HW = f.HW; hd.C = f.in / f.HW;
+    hd.by_hw = f.by_hw;
+    TRY(launch_compact_head(bf, ws, wts, labs, s, hd, out_rank_dev, count, stream));
+  }
+  CompactFinish fin;
+  memset(&fin, 0, sizeof(fin));
+  if (out_loss_dev) fin.job[fin.count++].kind = CJOB_LOSS;
+  if (!out_rank_dev) {
+    // ---- backward
+    for (int k = nf - 2; k >= 0; k--) TRY(launch_compact_fc(bf, ws, wts, fc_of(k), true, net->scratch_bytes, count, stream));
+    size_t dy = net->grad_a, dx = net->grad_b;
+    for (int k = ns - 1; k >= 0; k--) {
+      const CompactStage& st = cp.stages[(size_t)k];
+      const Op& op = ops[(size_t)st.conv];
+      CompactGrad g;
+      memset(&g, 0, sizeof(g));
+      g.off = dy;
+      g.OH = op.cs.OH; g.OW = op.cs.OW; g.K = op.cs.K;
+      g.by_k.set(g.K);
+      g.by_k4.set(g.K / 4);
+      if (st.pool >= 0) {
+        const Op& pool = ops[(size_t)st.pool];
+        g.kind = pool.kind == OP_POOL_MAX ? CGRAD_MAXPOOL : CGRAD_AVGPOOL;
+        g.PH = pool.ps.OH; g.PW = pool.ps.OW; g.pks = pool.ps.ks; g.pst = pool.ps.stride;
+        g.arg_off = pool.arg_off;
+      } else if (k == ns - 1) {                       // flattened as it is: a window of one element
+        g.kind = CGRAD_AVGPOOL;
+        g.PH = g.OH; g.PW = g.OW; g.pks = g.pst = 1;
+      }
+      g.by_pst.set(g.pst);
+      g.use_mask = op.relu ? 1 : 0;                   // plain gradients were masked by their producer
+      g.mask_off = T[(size_t)op.out_t].off;
+      // the layer's input as kept by the forward pass
+      CompactSrc x = compact_src(net, k ? &cp.stages[(size_t)k - 1] : nullptr);
+      if (k && x.kind != CSRC_TENSOR) {
+        x.kind = CSRC_TENSOR;
+        x.off = x.out_off;
+      }
+      CompactBwd bw;
+      memset(&bw, 0, sizeof(bw));
+      bw.splits = compact_splits(st.v, k > 0, count, st.most_splits);
+      bw.dx_off = dx;
+      bw.mask_off = x.off;
+      bw.use_mask = k && T[(size_t)op.in_t].relu ? 1 : 0;
+      bw.part_off = net->scratch_off + st.part_off;
+      bw.part_elems = (int64_t)st.v.K * st.v.C * st.v.ks * st.v.ks + st.v.K;
+      TRY(launch_compact_bwd(bf, ws, wts, imgs, st.v, x, g, bw, net->pixel_mean, k > 0, count, stream));
+      CompactJob& jb = fin.job[fin.count++];
+      jb.kind = CJOB_SUM;
+      jb.splits = bw.splits; jb.elems = bw.part_elems; jb.w_off = st.v.w_off; jb.part_off = bw.part_off;
+      jb.K = st.v.K; jb.C = st.v.C; jb.taps = st.v.ks * st.v.ks;
+      std::swap(dy, dx);
+    }
+    for (int k = 0; k < nf; k++) {
+      const CompactFc f = fc_of(k);
+      CompactJob& jb = fin.job[fin.count++];
+      jb.kind = CJOB_FC;
+      jb.in = f.in; jb.out = f.out; jb.w_off = f.w_off; jb.x_off = f.x_off; jb.dy_off = f.dy_off;
+    }
+  }
+  return launch_compact_finish(bf, ws, grads, fin, net->loss_off, net->mu, out_loss_dev, count, stream);
+}
+
 // Forward pass, loss and (unless out_rank_dev is given, which makes this an evaluation pass) backward pass.
 hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* binds, int count, float* out_loss_dev,
                              int32_t* out_rank_dev, hipStream_t stream) {
@@ -458,6 +695,8 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
   }
   const bool bf = net->bf16;
   const std::vector<Tensor>& T = net->tensors;
+  if (net->compact.ok && (net->compact.always || count * net->mu * net->compact.macs <= kCompactMacs[bf]))
+    return compact_gradient(net, ws, wts, imgs, labs, grads, count, out_loss_dev, out_rank_dev, stream);
   // Learners that read the same weight version: the stacked fully connected layers take each such group (two members
   // and more) as one matrix product; `single` lists the others.  Groups lie one after the other in the staging area.
   struct Group { int first_row_block; std::vector<int> idx; };
