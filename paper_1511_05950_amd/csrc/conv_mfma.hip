@@ -1424,6 +1424,69 @@ hipError_t launch_igemm(const PtrTab& ws, const CPtrTab& wts, const IGemm& g_in,
 }
 
 // ------------------------------------------------------------------ weight gradient
+// A wavefront's piece of the weight-gradient tile: 32 TM output channels from n_base, 32 TN im2col columns from k_base.
+template <int TM, int TN>
+__device__ __forceinline__ void wgrad_write(const floatx16 (&acc)[TM][TN], const PtrTab& ws, const PtrTab& grads, const IGemm& g, const VConv& v,
+                                            int64_t w_off, int64_t b_off, int partial, int z, int sp, int n_base, int k_base, int lane) {
+  const int kcols = g.Kchunks * 8;
+  if (partial) {   // fp32 partial [split][n][kcols + 8]; wgrad_finish_kernel adds and writes the flat gradient in its order
+    const int ldk = kcols + 8;
+    float* part = reinterpret_cast<float*>((char*)ws.p[z] + g.scratch_off) + (int64_t)sp * g.Ncols * ldk;
+#pragma unroll
+    for (int j = 0; j < TN; j++) {
+      const int k = k_base + 32 * j + (lane & 31);
+      if (k > kcols) continue;
+#pragma unroll
+      for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          const int n = n_base + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          if (n < g.Ncols) part[(int64_t)n * ldk + k] = acc[i][j][r];
+        }
+    }
+    return;
+  }
+  float* dw = (float*)grads.p[z] + w_off;
+  float* db = (float*)grads.p[z] + b_off;
+  if (v.ks == 1 && v.s2d == 1 && v.C == v.Creal) {
+    // fully connected layer: dW[n][k] is the tile itself, row length C; 32 lanes write 128 contiguous bytes
+#pragma unroll
+    for (int j = 0; j < TN; j++) {
+      const int k = k_base + 32 * j + (lane & 31);
+      if (k > kcols) continue;
+#pragma unroll
+      for (int i = 0; i < TM; i++) {
+        const int nb = n_base + 32 * i + 4 * (lane >> 5);
+        float* row = dw + (int64_t)nb * v.C + k;
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          const int dn = 8 * (r >> 2) + (r & 3);
+          if (nb + dn >= g.Ncols) continue;
+          if (k == kcols) db[nb + dn] = acc[i][j][r];
+          else row[(int64_t)dn * v.C] = acc[i][j][r];
+        }
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < TN; j++) {
+    const int k = k_base + 32 * j + (lane & 31);       // im2col column = tap * C + cp; column kcols = bias
+    if (k > kcols) continue;
+    const int tap = k / g.C, cp = k - tap * g.C;
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int n = n_base + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        if (n >= g.Ncols) continue;
+        if (k == kcols) { db[n] = acc[i][j][r]; continue; }
+        const int64_t dst = filter_src(v, n, tap, cp);
+        if (dst >= 0) dw[dst] = acc[i][j][r];
+      }
+  }
+}
+
 // dW tile [BMG output channels][BNG im2col columns], contraction over output positions m in steps of 32.
 // dy tile  [32 m][BMG n]  and  im2col tile [32 m][BNG k]  are staged as they lie in memory (rows = m) and
 // read with the transpose load.  The result is scattered into the flat fp32 gradient through filter_src().
@@ -1612,65 +1675,162 @@ __global__ __launch_bounds__(256) void igemm_wgrad_kernel(PtrTab ws, PtrTab grad
   }
   if (ms < msteps) step(0, false, false);
 
-  const int kcols = g.Kchunks * 8;
-  if (partial) {   // fp32 partial [split][n][kcols + 8]; wgrad_finish_kernel adds and writes the flat gradient in its order
-    const int ldk = kcols + 8;
-    float* part = reinterpret_cast<float*>((char*)ws.p[z] + g.scratch_off) + (int64_t)sp * g.Ncols * ldk;
+  wgrad_write<TM, TN>(acc, ws, grads, g, v, w_off, b_off, partial, z, sp, n0 + wm0, k0 + wn0, lane);
+}
+
+// The same product for more than 64 output channels, with the tiles going from memory to LDS without passing through
+// registers.  Tiles are stored as panels of 32 columns, [panel][32 m][32 columns]: the 64 lanes of an LDS-direct load fill half
+// a panel (16 rows of 64 bytes, a piece the vector L1 serves at its full rate), a panel is the operand of one 32-wide MFMA
+// block, and four neighbouring rows lie 16 banks apart, so that the transpose load meets no conflict and needs no padding.
+// Three buffers: the tiles of step s + 2 are requested before the MFMAs of step s and waited for by count at the end of step
+// s + 1; one barrier a step.  Every step issues the same number of loads; rows behind the split's last one are out of range
+// and arrive as zeros.  The buffers are arrays of their own and the step is written out once per buffer: only then does the
+// compiler know that an LDS read of one does not wait for the loads into another.
+// What bounds it: the transposing LDS reads (32 KiB a step at 82 B/clk per compute unit) and the arriving tiles.  AlexNet-shaped
+// net, 288 images, average of its five layers: 147 us against 173 us with staging registers and two buffers.  128 x 256 tiles
+// (64 x 128 per wavefront) read a quarter less but leave two wavefronts a SIMD and too few tiles: 152 us.
+template <bool INCR>
+__global__ __launch_bounds__(256, 3) void wgrad_panel_kernel(PtrTab ws, PtrTab grads, IGemm g, VConv v, size_t dy_off, int64_t w_off,
+                                                             int64_t b_off, int partial) {
+  constexpr int BMG = 128, BNG = 128, TM = 2, TN = BNG / 64;
+  constexpr int PA = BMG / 32, PB = BNG / 32, PANEL = BK * 32;
+  __shared__ __attribute__((aligned(16))) bf16_t buf0[(PA + PB) * PANEL], buf1[(PA + PB) * PANEL], buf2[(PA + PB) * PANEL];
+
+  const TileIdx tile = xcd_tile(1);
+  const int z = tile.z / g.splits, sp = tile.z % g.splits;
+  const bf16_t* x = (const bf16_t*)ws.p[z] + g.a_off;
+  const bf16_t* dy = (const bf16_t*)ws.p[z] + dy_off;
+  const int n0 = tile.x * BMG, k0 = tile.y * BNG;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * (BNG / 2);
+
+  const int all_steps = (g.M + BK - 1) / BK;
+  const int per = (all_steps + g.splits - 1) / g.splits;
+  const int ms_begin = __builtin_amdgcn_readfirstlane(sp * per);
+  const int ms_end = __builtin_amdgcn_readfirstlane(min(all_steps, ms_begin + per));
+  const int m_end = min(g.M, ms_end * BK);
+
+  // the bias column is an im2col column of ones: its chunk {1, 0, ...} comes from the constant block of the workspace, which
+  // only the workgroups that hold this column can reach
+  const int one_off = (int)((g.zero_off + 128 - g.a_off) * 2);
+  const bool has_bias = g.Kchunks * 8 >= k0 && g.Kchunks * 8 < k0 + BNG;
+  const __amdgpu_buffer_rsrc_t rsrc_dy = __builtin_amdgcn_make_buffer_rsrc((void*)dy, 0, (int)((int64_t)m_end * g.Ncols * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc((void*)x, 0, has_bias ? one_off + 16 : (int)g.a_bytes, 0x00020000);
+  const int row = lane >> 2, ch = lane & 3;
+  uint32_t a_off[2];
+  const uint32_t a_step = (uint32_t)(BK * g.Ncols * 2);
 #pragma unroll
-    for (int j = 0; j < TN; j++) {
-      const int k = k0 + wn0 + 32 * j + (lane & 31);
-      if (k > kcols) continue;
+  for (int h = 0; h < 2; h++) {
+    const int n = n0 + wave * 32 + ch * 8;
+    a_off[h] = n < g.Ncols ? (uint32_t)((((int64_t)ms_begin * BK + 16 * h + row) * g.Ncols + n) * 2) : kOutOfRange;
+  }
+  const int q = k0 / 8 + wave * 4 + ch;                  // this lane's im2col chunk: one tap, 8 channels
+  const uint32_t tap = fastdiv((uint32_t)q, g.CPT, g.mg_cpt);
+  const int c8 = q - (int)tap * g.CPT;
+  const int kh = (int)fastdiv(tap, g.ks, g.mg_ks), kw = (int)tap - kh * g.ks;
+  const int b_dkh = q < g.Kchunks ? kh - g.pad : (int)kOutOfRange;      // a row that no input has
+  const int b_dkw = kw - g.pad;
+  const int b_koff = ((kh - g.pad) * g.W * g.C + (kw - g.pad) * g.C + c8 * 8) * 2;
+  const int b_else = q == g.Kchunks ? one_off : (int)kOutOfRange;
+  // position of the rows that `issue` fetches next
+  int r_m[2], r_oh[2], r_ow[2], r_off[2];
+  auto decode_row = [&](int h) {
+    const uint32_t mm = r_m[h] < g.M ? (uint32_t)r_m[h] : 0u;
+    const uint32_t rest = fastdiv(mm, g.OW, g.mg_ow);
+    const uint32_t n = fastdiv(rest, g.OH, g.mg_oh);
+    r_ow[h] = (int)(mm - rest * (uint32_t)g.OW);
+    r_oh[h] = (int)(rest - n * (uint32_t)g.OH);
+    r_off[h] = (int)(((n * (uint32_t)g.H + (uint32_t)r_oh[h]) * (uint32_t)g.W + (uint32_t)r_ow[h]) * (uint32_t)g.C * 2u);
+  };
+#pragma unroll
+  for (int h = 0; h < 2; h++) {
+    r_m[h] = ms_begin * BK + 16 * h + row;
+    decode_row(h);
+  }
+  const int d_ow = BK / g.OW, m_ow = BK - d_ow * g.OW;
+  const int inc0 = (d_ow * g.W + m_ow) * g.C * 2;
+  const int inc_w = (g.W - g.OW) * g.C * 2;
+  const int inc_h = (g.H - g.OH) * g.W * g.C * 2;
+
+  auto issue = [&](bf16_t* S) {
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_dy, (__attribute__((address_space(3))) void*)(S + wave * PANEL + h * (PANEL / 2)), 16, (int)a_off[h], 0, 0, 0);
+      a_off[h] += a_step;
+      const bool ok = r_m[h] < m_end && (unsigned)(r_oh[h] + b_dkh) < (unsigned)g.H && (unsigned)(r_ow[h] + b_dkw) < (unsigned)g.W;
+      const int off = ok ? r_off[h] + b_koff : b_else;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_x, (__attribute__((address_space(3))) void*)(S + (PA + wave) * PANEL + h * (PANEL / 2)), 16,
+                                               off, 0, 0, 0);
+      r_m[h] += BK;
+      if (INCR) {
+        r_ow[h] += m_ow;
+        const bool c1 = r_ow[h] >= g.OW;
+        r_ow[h] -= c1 ? g.OW : 0;
+        r_oh[h] += d_ow + (c1 ? 1 : 0);
+        const bool c2 = r_oh[h] >= g.OH;
+        r_oh[h] -= c2 ? g.OH : 0;
+        r_off[h] += inc0 + (c1 ? inc_w : 0) + (c2 ? inc_h : 0);
+      } else {
+        decode_row(h);
+      }
+    }
+  };
+
+  floatx16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
+
+  const int j16 = lane & 15;
+  const int lane_off = (8 * (lane >> 5) + (j16 >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (j16 & 3);
+  const int pa_off = (wm0 / 32) * PANEL + lane_off, pb_off = (PA + wn0 / 32) * PANEL + lane_off;
+  auto read_frag = [&](const bf16_t* p) {
+    union { bf16x8 v; shortx4 h[2]; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((shortx4 __attribute__((address_space(3)))*)(p));
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((shortx4 __attribute__((address_space(3)))*)(p + 4 * 32));
+    return u.v;
+  };
+  auto multiply = [&](const bf16_t* S) {
+#pragma unroll
+    for (int kk = 0; kk < 2; kk++) {
+      bf16x8 a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; i++) a[i] = read_frag(S + pa_off + i * PANEL + kk * 16 * 32);
+#pragma unroll
+      for (int j = 0; j < TN; j++) b[j] = read_frag(S + pb_off + j * PANEL + kk * 16 * 32);
 #pragma unroll
       for (int i = 0; i < TM; i++)
 #pragma unroll
-        for (int r = 0; r < 16; r++) {
-          const int n = n0 + wm0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (n < g.Ncols) part[(int64_t)n * ldk + k] = acc[i][j][r];
-        }
+        for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
-    return;
-  }
-  float* dw = (float*)grads.p[z] + w_off;
-  float* db = (float*)grads.p[z] + b_off;
-  if (v.ks == 1 && v.s2d == 1 && v.C == v.Creal) {
-    // fully connected layer: dW[n][k] is the tile itself, row length C; 32 lanes write 128 contiguous bytes
-#pragma unroll
-    for (int j = 0; j < TN; j++) {
-      const int k = k0 + wn0 + 32 * j + (lane & 31);
-      if (k > kcols) continue;
-#pragma unroll
-      for (int i = 0; i < TM; i++) {
-        const int nb = n0 + wm0 + 32 * i + 4 * (lane >> 5);
-        float* row = dw + (int64_t)nb * v.C + k;
-#pragma unroll
-        for (int r = 0; r < 16; r++) {
-          const int dn = 8 * (r >> 2) + (r & 3);
-          if (nb + dn >= g.Ncols) continue;
-          if (k == kcols) db[nb + dn] = acc[i][j][r];
-          else row[(int64_t)dn * v.C] = acc[i][j][r];
-        }
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < TN; j++) {
-    const int k = k0 + wn0 + 32 * j + (lane & 31);       // im2col column = tap * C + cp; column kcols = bias
-    if (k > kcols) continue;
-    const int tap = k / g.C, cp = k - tap * g.C;
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const int n = n0 + wm0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (n >= g.Ncols) continue;
-        if (k == kcols) { db[n] = acc[i][j][r]; continue; }
-        const int64_t dst = filter_src(v, n, tap, cp);
-        if (dst >= 0) dw[dst] = acc[i][j][r];
-      }
-  }
-}
+  };
+  // The older of two steps' loads has landed (each wavefront waits for its own, the barrier for everyone's), and this
+  // wavefront's LDS reads are done, so that the buffer it leaves may be overwritten.
+  auto turn = [&]() {
+    asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // four loads a step and wavefront
+  };
 
+  const int steps = ms_end - ms_begin;
+  issue(buf0);
+  issue(buf1);
+  turn();
+  int s = 0;
+  for (; s + 3 <= steps; s += 3) {
+    issue(buf2); multiply(buf0); turn();
+    issue(buf0); multiply(buf1); turn();
+    issue(buf1); multiply(buf2); turn();
+  }
+  if (s < steps) {
+    issue(buf2); multiply(buf0); turn();
+    if (s + 1 < steps) multiply(buf1);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no load is left on its way to this workgroup's LDS
+  wgrad_write<TM, TN>(acc, ws, grads, g, v, w_off, b_off, partial, z, sp, n0 + wm0, k0 + wn0, lane);
+}
 // One workgroup per output channel n: the row of partial sums is added in split order into LDS (coalesced reads),
 // then written to the flat gradient in ITS order (coalesced writes), the im2col column of each filter element
 // being looked up on the way.
@@ -1745,7 +1905,13 @@ hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm
     SASGD_WGRAD(64, 128, 32, 64);
   } else {
     dim3 grid((unsigned)((g.Ncols + 127) / 128), (unsigned)((cols + 127) / 128), (unsigned)(count * g.splits));
-    SASGD_WGRAD(128, 128, 64, 64);
+    // the constant block has to lie within a 31-bit byte offset from the layer's input
+    if (g.zero_off >= g.a_off && (g.zero_off - g.a_off + 256) * 2 < ((size_t)1 << 31)) {
+      if (incr) hipLaunchKernelGGL((wgrad_panel_kernel<true>), grid, dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off, partial);
+      else hipLaunchKernelGGL((wgrad_panel_kernel<false>), grid, dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off, partial);
+    } else {
+      SASGD_WGRAD(128, 128, 64, 64);
+    }
   }
 #undef SASGD_WGRAD
   if (partial) {

@@ -1,0 +1,41 @@
+"""Weight gradients at the edges of the kernels' tiles, bf16, against the CPU
+oracle: contractions of one and a few steps and of no whole number of them, image rows shorter and longer than a step, filter
+taps that change inside a 32-column panel, the bias column alone in a tile, partly filled column tiles, and a fully connected
+layer whose gradient is written out.  The networks hold no ReLU and no max-pooling: a sign or a winner that rounding decides
+moves single elements by as much as they are, whichever way the sums are ordered."""
+import pytest
+
+import workloads as wl
+from test_gpu_net import check_gradient, one_gradient
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def net(c, h, w, *layers):
+    return {"name": "tiles", "input": (c, h, w), "classes": 8, "layers": list(layers) + [("fc", 24), ("fc", 8)]}
+
+
+CASES = {
+    # name: (network, mini-batch size, learners)
+    "one_step": (net(3, 5, 5, ("conv", 72, 3, 1, 0), ("conv", 136, 2, 1, 0)), 1, 1),
+    "steps_2_to_4": (net(3, 8, 8, ("conv", 80, 3, 1, 0), ("conv", 72, 2, 1, 0)), 3, 2),
+    "ragged": (net(3, 12, 11, ("conv", 128, 3, 1, 1), ("conv", 72, 3, 1, 1), ("avgpool", 3, 2), ("conv", 136, 5, 1, 2)), 3, 2),
+    "wide_rows": (net(3, 9, 41, ("conv", 72, 3, 1, 1), ("conv", 96, 3, 1, 0), ("avgpool", 3, 2)), 2, 2),
+    "stride_2": (net(3, 29, 27, ("conv", 80, 7, 2, 0), ("conv", 72, 3, 1, 0), ("avgpool", 3, 2)), 2, 2),
+    "many_learners": (net(3, 8, 8, ("conv", 128, 3, 1, 1), ("conv", 256, 3, 1, 1), ("avgpool", 3, 2)), 4, 12),
+    # up to 64 output channels
+    "narrow_one_step": (net(3, 5, 5, ("conv", 8, 3, 1, 0), ("conv", 64, 2, 1, 0)), 1, 1),
+    "narrow_ragged": (net(3, 12, 11, ("conv", 32, 3, 1, 1), ("conv", 64, 5, 1, 2), ("avgpool", 3, 2), ("conv", 24, 3, 1, 1)), 5, 3),
+    "narrow_wide_rows": (net(3, 9, 70, ("conv", 40, 3, 1, 1), ("conv", 32, 3, 1, 0), ("avgpool", 3, 2)), 2, 2),
+    "narrow_full_tiles": (net(3, 16, 16, ("conv", 64, 3, 1, 1), ("conv", 32, 2, 1, 0), ("conv", 16, 4, 1, 1), ("avgpool", 3, 2)), 4, 12),
+    "written_out_fc": ({"name": "tiles", "input": (3, 16, 16), "classes": 8,
+                        "layers": [("conv", 72, 3, 1, 1), ("conv", 72, 3, 1, 1), ("avgpool", 3, 2), ("fc", 136), ("fc", 8)]}, 40, 1),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_weight_gradient(name):
+    nt, mu, lam = CASES[name]
+    for (g, rg, loss, rl) in one_gradient(nt, mu, "bf16", seed=sum(map(ord, name)), scale=0.1, lam=lam):
+        check_gradient(nt, "bf16", g, rg, loss, rl, name)
