@@ -8,9 +8,10 @@ at the start).  This realises the server-view update of the paper's Section 3 fo
 from __future__ import annotations
 
 
-def _rows(schedule):
-    """The schedule as lists of Python integers (an array element costs several times as much to fetch)."""
-    return schedule.tolist() if hasattr(schedule, "tolist") else [[int(t) for t in row] for row in schedule]
+def _rows(schedule, c):
+    """The first c entries of every row as Python integers (an array element costs several times as much to fetch)."""
+    rows = schedule.tolist() if hasattr(schedule, "tolist") else schedule
+    return [[int(t) for t in row[:c]] for row in rows]
 
 
 def run_softsync(ctx, schedule, batch_of, lam, loss_out=None, on_gradient=None, first_update=0, base_rates=None):
@@ -27,7 +28,7 @@ def run_softsync(ctx, schedule, batch_of, lam, loss_out=None, on_gradient=None, 
     """
     c = ctx.c
     log = []
-    schedule = _rows(schedule)
+    schedule = _rows(schedule, c)
     for k in range(len(schedule)):
         i = first_update + k
         assert ctx.timestamp() == i
@@ -64,7 +65,7 @@ def run_softsync_batched(ctx, schedule, batch_of, lam, loss_out=None, first_upda
     """
     c = ctx.c
     K = len(schedule)
-    stale = [t for row in _rows(schedule) for t in row]      # gradient id -> requested staleness
+    stale = _rows(schedule, c)                  # requested staleness
     done = {}                                   # gradient id -> (learner, timestamp j)
     log = []
     calls = 0
@@ -79,7 +80,7 @@ def run_softsync_batched(ctx, schedule, batch_of, lam, loss_out=None, first_upda
                 if g in done:
                     continue
                 i2, l2 = first_update + g // c, g % c
-                j = i2 - min(stale[g], i2)
+                j = i2 - min(stale[g // c][l2], i2)
                 if j > i:
                     continue                    # its weights do not exist yet
                 learner = (i2 * c + l2) % lam

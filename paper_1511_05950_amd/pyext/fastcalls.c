@@ -53,14 +53,14 @@ static int address(PyObject* o, void** out) {
   return PyErr_Occurred() ? -1 : 0;
 }
 
-/* Python and numpy integers, and whatever else int() takes. */
+/* Python and numpy integers; a float is refused, as ctypes refuses it. */
 static int integer(PyObject* o, long long* out) {
   PyObject* v;
   if (PyLong_Check(o)) {
     *out = PyLong_AsLongLong(o);
     return *out == -1 && PyErr_Occurred() ? -1 : 0;
   }
-  v = PyNumber_Long(o);
+  v = PyNumber_Index(o);
   if (!v) return -1;
   *out = PyLong_AsLongLong(v);
   Py_DECREF(v);
@@ -75,6 +75,18 @@ static int integer32(PyObject* o, int32_t* out) {
   }
   *out = (int32_t)v;
   return 0;
+}
+
+/* The same with int() applied first: staleness values of any numeric type. */
+static int as_integer32(PyObject* o, int32_t* out) {
+  PyObject* v;
+  int bad;
+  if (PyLong_Check(o)) return integer32(o, out);
+  v = PyNumber_Long(o);
+  if (!v) return -1;
+  bad = integer32(v, out);
+  Py_DECREF(v);
+  return bad;
 }
 
 #define NARGS(n) \
@@ -219,14 +231,14 @@ static PyObject* apply_update_no_alloc(PyObject* self, PyObject* const* a, Py_ss
   }
   c = PySequence_Fast_GET_SIZE(gs);
   nst = PySequence_Fast_GET_SIZE(ss);
-  if (nst > c) {                    /* one staleness per gradient; missing ones read as 0, as an array of c zeros does */
+  if (nst > (c ? c : 1)) {                  /* one staleness per gradient; missing ones read as 0, as an array of c zeros does */
     PyErr_SetString(PyExc_IndexError, "more staleness values than gradients");
     bad = 1;
   }
   for (k = 0; !bad && k < c && k < SASGD_NOALLOC_MAX_GRADIENTS; k++) {
     void* g;
     stale[k] = 0;
-    bad = address(PySequence_Fast_GET_ITEM(gs, k), &g) || (k < nst && integer32(PySequence_Fast_GET_ITEM(ss, k), &stale[k]));
+    bad = address(PySequence_Fast_GET_ITEM(gs, k), &g) || (k < nst && as_integer32(PySequence_Fast_GET_ITEM(ss, k), &stale[k]));
     grads[k] = (const float*)g;
   }
   Py_DECREF(gs);
