@@ -29,6 +29,9 @@ CASES = {
     "narrow_ragged": (net(3, 12, 11, ("conv", 32, 3, 1, 1), ("conv", 64, 5, 1, 2), ("avgpool", 3, 2), ("conv", 24, 3, 1, 1)), 5, 3),
     "narrow_wide_rows": (net(3, 9, 70, ("conv", 40, 3, 1, 1), ("conv", 32, 3, 1, 0), ("avgpool", 3, 2)), 2, 2),
     "narrow_full_tiles": (net(3, 16, 16, ("conv", 64, 3, 1, 1), ("conv", 32, 2, 1, 0), ("conv", 16, 4, 1, 1), ("avgpool", 3, 2)), 4, 12),
+    # many taps per channel, input channels in groups of which the last is shorter
+    "many_taps": (net(3, 20, 20, ("conv", 40, 3, 1, 1), ("conv", 24, 11, 1, 5), ("avgpool", 3, 2)), 3, 2),
+    "uneven_groups": (net(3, 12, 12, ("conv", 136, 3, 1, 1), ("conv", 72, 3, 1, 1), ("avgpool", 3, 2)), 4, 2),
     "written_out_fc": ({"name": "tiles", "input": (3, 16, 16), "classes": 8,
                         "layers": [("conv", 72, 3, 1, 1), ("conv", 72, 3, 1, 1), ("avgpool", 3, 2), ("fc", 136), ("fc", 8)]}, 40, 1),
 }
