@@ -799,7 +799,8 @@ template <typename T, bool DGRAD>
 __device__ __forceinline__ void fc_store(char* wsb, const T* wts, const CompactFc& f, int n, int c, float s) {
   if (DGRAD) {
     if (f.use_mask && !(ldf((const T*)wsb + f.x_off + (uint32_t)n * f.in + c) > 0.f)) s = 0.f;
-    const int ch = f.by_hw(c), hw = c - ch * f.HW;            // behind a flattening: channels innermost
+    // behind a flattening: channels innermost.  A plain division: c goes up to channels x pixels, beyond what FastDiv divides
+    const int ch = c / f.HW, hw = c - ch * f.HW;
     stf((T*)wsb + f.dx_off + (uint32_t)n * f.in + hw * (f.in / f.HW) + ch, s);
   } else {
     s += ldf(wts + f.b_off + c);
@@ -987,10 +988,18 @@ bool compact_conv_ok(const CompactConv& v, bool need_dx) {
   if (!(k == 1 || k == 2 || k == 3 || k == 4 || k == 5 || k == 7 || k == 11)) return false;
   if (need_dx && v.stride != 1) return false;
   if ((v.w_off + (int64_t)v.K * v.C * k * k) * 4 >= ((int64_t)1 << 31)) return false;
+  // every division of the kernels: positions by row lengths, filter columns and patch elements (of which LDS holds at most
+  // kLdsMost / 4) by channels and patch columns
+  const int64_t patch = (int64_t)kLdsMost / 4, filter = (int64_t)k * k * v.C;
+  if (!FastDiv::exact(v.OW, (int64_t)v.OH * v.OW - 1) || !FastDiv::exact(v.W, (int64_t)v.H * v.W - 1) ||
+      !FastDiv::exact(v.C, std::max(patch, filter)) || !FastDiv::exact(v.K, patch) || !FastDiv::exact((v.OW - 1) * v.stride + k, patch) ||
+      !FastDiv::exact(v.W - 1 + k, patch))
+    return false;
   return fwd_lds(v, kSmall) <= kLdsMost && wgrad_lds(v, kSmall.NW, 32) <= kLdsMost &&
          (!need_dx || dgrad_lds(v, kSmall) <= kLdsMost);
 }
 size_t compact_head_lds(int in, int K) { return ((((size_t)in + 3) & ~(size_t)3) + K) * 4; }
+// (its divisions stay below 2^14 x 2^14: the inputs lie in LDS)
 bool compact_head_ok(int in, int K) { return (int64_t)in * K <= (int64_t)1 << 18 && compact_head_lds(in, K) <= 48 * 1024; }
 bool compact_fc_ok(int in, int out) { return (int64_t)in * out < ((int64_t)1 << 29); }
 

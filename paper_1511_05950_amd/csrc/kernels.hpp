@@ -5,6 +5,7 @@
 // order of the C ABI.
 #pragma once
 #include "ctx.hpp"
+#include "fastdiv.hpp"
 
 namespace sasgd {
 
@@ -196,14 +197,6 @@ hipError_t launch_fc_save_factors(const PtrTab& ws, const PtrTab& grads, size_t 
 hipError_t launch_fc_expand_factors(const void* fx, const void* fdy, float* dw, int N, int in, int out, int NP, hipStream_t s);
 
 // ---- small networks and mini-batches in few launches (compact.hip)
-// Division by a number known at launch: floor(n / d) for n d < 2^32.
-struct FastDiv {
-  uint32_t d, m;
-  __host__ void set(int div) { d = (uint32_t)div; m = magic_u32(div); }
-#ifdef __HIPCC__
-  __device__ __forceinline__ int operator()(int n) const { return d <= 1u ? n : (int)__umulhi((uint32_t)n, m); }
-#endif
-};
 // Where a layer's input comes from.
 enum { CSRC_TENSOR = 0, CSRC_IMAGES = 1, CSRC_MAXPOOL = 2, CSRC_AVGPOOL = 3, CSRC_FLAT = 4 };
 struct CompactSrc {
@@ -247,7 +240,6 @@ struct CompactHead {
 struct CompactFc {
   int N, in, out, relu, use_mask;
   int HW;                      // pixels of the input in front of a flattening (1: none)
-  FastDiv by_hw;
   int64_t w_off, b_off;
   size_t x_off, y_off, dy_off, dx_off;
   int splits, aligned;         // set by the launcher

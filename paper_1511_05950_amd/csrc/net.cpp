@@ -116,7 +116,9 @@ static CompactPlan compact_plan(const Net* net) {
     if (!compact_conv_ok(st.v, !cp.stages.empty())) return cp;
     i++;
     if (i < n && (ops[(size_t)i].kind == OP_POOL_MAX || ops[(size_t)i].kind == OP_POOL_AVG)) {
-      if (ops[(size_t)i].ps.ks > 2 * ops[(size_t)i].ps.stride) return cp;      // more than two windows per direction reach a position
+      const PoolShape& ps = ops[(size_t)i].ps;
+      if (ps.ks > 2 * ps.stride) return cp;                          // more than two windows per direction reach a position
+      if (!FastDiv::exact(ps.stride, std::max(ps.H, ps.W))) return cp;
       st.pool = i++;
     }
     cp.stages.push_back(st);
@@ -592,7 +594,6 @@ static hipError_t compact_gradient(Net* net, const PtrTab& ws, const CPtrTab& wt
     f.dx_off = k ? cp.fc_dy[(size_t)k - 1] : net->grad_a;
     f.use_mask = (k ? T[(size_t)op.in_t].relu : pooled_relu) ? 1 : 0;
     f.HW = k ? 1 : flat_hw;
-    f.by_hw.set(f.HW);
     f.part_off = net->scratch_off;
     return f;
   };
@@ -617,7 +618,7 @@ static hipError_t compact_gradient(Net* net, const PtrTab& ws, const CPtrTab& wt
     hd.use_mask = f.use_mask;
     hd.need_dx = 1;
     hd.HW = f.HW; hd.C = f.in / f.HW;
-    hd.by_hw = f.by_hw;
+    hd.by_hw.set(f.HW);
     TRY(launch_compact_head(bf, ws, wts, labs, s, hd, out_rank_dev, count, stream));
   }
   CompactFinish fin;

@@ -26,6 +26,9 @@ NETS = {
     "hidden_split": (net(3, 22, 22, 5, ("conv", 21, 3, 1, 1), R, ("maxpool", 3, 2), ("fc", 37), R, ("fc", 18), R), 17, 2),
     "no_pooling": (net(4, 6, 7, 6, ("conv", 9, 3, 1, 1), R, ("conv", 12, 3, 1, 1), R), 5, 2),
     "large_tiles": (net(3, 17, 16, 5, ("conv", 36, 5, 1, 2), R, ("maxpool", 3, 2), ("conv", 34, 3, 1, 1), R), 15, 16),
+    # flattened inputs of many pixels per channel (no ReLU: every sum is decided): index times pixels is beyond 2^32
+    "flat_160x160": (net(3, 160, 160, 10, ("conv", 8, 3, 1, 1), ("fc", 64)), 2, 1),
+    "flat_112x112": (net(2, 112, 112, 5, ("conv", 64, 3, 1, 1), ("fc", 4)), 2, 2),
     "wide_tiles": (net(3, 26, 24, 5, ("conv", 33, 3, 1, 1), R, ("conv", 30, 3, 1, 1), R, ("avgpool", 3, 2)), 32, 2),
 }
 
@@ -35,9 +38,10 @@ NETS = {
 def test_gradient(name, compute):
     nt, mu, lam = NETS[name]
     seed = sum(map(ord, name))
+    scale = 0.02 if name.startswith("flat") else 0.3     # sums of 10^5 terms: scores stay around one
     if compute == "fp32":
-        seed = decided_seed(nt, lam, mu, seed, 0.3)
-    for (g, rg, loss, rl) in one_gradient(nt, mu, compute, seed=seed, lam=lam):
+        seed = decided_seed(nt, lam, mu, seed, scale)
+    for (g, rg, loss, rl) in one_gradient(nt, mu, compute, seed=seed, lam=lam, scale=scale):
         check_gradient(nt, compute, g, rg, loss, rl, name)
 
 
