@@ -84,7 +84,9 @@ typedef struct {
                            (mu x out and mu x in values) and applyUpdate forms the product on the fly in the
                            same fp32 arithmetic.  The 4 bytes per weight of gradient written by the learner
                            and read by the server disappear; copyGradient / gradientPtr expand the product on
-                           demand.  The flag forces the written-out gradient instead.
+                           demand.  The flag forces the written-out gradient instead.  (Calls of few images on small
+                           networks with a layer of an odd size write it out as well; both kinds may meet in
+                           one update.)
                            SASGD_FLAG_EAGER_UPDATES: applyUpdate enqueues its kernels before it returns.  By default
                            the kernels of an update whose gradients all come from the library's learners wait until
                            something needs their result (see sasgd_applyUpdate).                              */
@@ -222,7 +224,7 @@ int sasgd_setPixelMean(sasgd_ctx* ctx, const float* mean_dev);
 int sasgd_timestamp(sasgd_ctx* ctx, int64_t* out);
 int sasgd_numParams(sasgd_ctx* ctx, int64_t* out);
 int sasgd_gradientsPerUpdate(sasgd_ctx* ctx, int32_t* out_c);
-/* Number of parameters (fully connected weights) whose gradients are kept as factors (see flags); 0 if none. */
+/* Number of parameters (fully connected weights) whose gradients can be kept as factors (see flags); 0 if none. */
 int sasgd_factoredParams(sasgd_ctx* ctx, int64_t* out);
 /* Timestamp of the learner's last computed gradient (-1 if none). */
 int sasgd_gradientTimestamp(sasgd_ctx* ctx, int32_t learner, int64_t* out);

@@ -162,7 +162,9 @@ hipError_t enqueue_updates(sasgd_ctx* ctx, int n) {
   // Layers whose gradients are kept as factors get their own launch; the stretches of the flat vector between them
   // go through the streaming kernel.
   FactoredLayer fl[kMaxFactoredLayers];
-  const int nfl = ctx->net ? net_factored_layers(ctx->net, fl, kMaxFactoredLayers) : 0;
+  bool factors = false;                // gradients that are all written out take the streaming kernel alone
+  for (int l = 0; l < total; l++) factors = factors || src[l]->factors_ws;
+  const int nfl = factors ? net_factored_layers(ctx->net, fl, kMaxFactoredLayers) : 0;
   prof_begin(ctx, 1, n);
   hipError_t e = hipSuccess;
   auto flat_range = [&](int64_t begin, int64_t end) {
@@ -433,13 +435,15 @@ int sasgd_calcGradient(sasgd_ctx* ctx, const int32_t* learners, int32_t count, f
     binds[k].grad = L.grad;
   }
   prof_begin(ctx, 0);
-  hipError_t e = net_calc_gradient(ctx->net, ids, binds, count, out_loss_dev, nullptr, ctx->stream);
+  bool factors = false;
+  hipError_t e = net_calc_gradient(ctx->net, ids, binds, count, out_loss_dev, nullptr, &factors, ctx->stream);
   prof_end(ctx);
   if (e != hipSuccess) return fail_hip(ctx, e, "calcGradient");
   for (int k = 0; k < count; k++) {
     Learner& L = ctx->learners[(size_t)ids[k]];
     L.grad_timestamp = L.pulled_version;   // gradient timestamp = timestamp of the weights used (Section 2.1)
     L.grad_state = GRAD_COMPUTED;
+    L.has_factors = factors;
     L.fc_expanded = false;
     L.has_weights = false;                 // one mini-batch per push: nothing is accrued at the learner
     L.images = nullptr;
@@ -474,7 +478,7 @@ int sasgd_evaluate(sasgd_ctx* ctx, const int32_t* learners, int32_t count, float
     binds[k].version = L.pulled_version;
     binds[k].grad = nullptr;             // the evaluation pass writes no gradient
   }
-  hipError_t e = net_calc_gradient(ctx->net, ids, binds, count, out_loss_dev, out_rank_dev, ctx->stream);
+  hipError_t e = net_calc_gradient(ctx->net, ids, binds, count, out_loss_dev, out_rank_dev, nullptr, ctx->stream);
   if (e != hipSuccess) return fail_hip(ctx, e, "evaluate");
   // The bindings stay, but a binding that an evaluation has used no longer keeps its version in the ring: a training
   // loop evaluates and moves on, and must not be stopped by applyUpdate's eviction check many updates later.
@@ -505,7 +509,7 @@ int sasgd_pushGradient(sasgd_ctx* ctx, int32_t learner, int32_t* out_staleness) 
   if (L.grad_state != GRAD_COMPUTED) return fail(ctx, SASGD_ESTATE, "pushGradient: no freshly computed gradient");
   if ((int)ctx->pending.size() >= kMaxLearners) return fail(ctx, SASGD_ESTATE, "pushGradient: pending queue full");
   Pending p;
-  p.factors_ws = L.workspace;   // fully connected factors, if the network keeps any, live in the learner's workspace
+  p.factors_ws = L.has_factors ? L.workspace : nullptr;
   p.grad = L.grad;
   p.timestamp = L.grad_timestamp;
   p.staleness = (int32_t)(ctx->timestamp - L.grad_timestamp);   // tau = i - j
@@ -712,7 +716,7 @@ int sasgd_copyWeights(sasgd_ctx* ctx, int64_t version, float* host_out) {
 
 // Writes the fully connected weight gradients that the learner holds as factors into its flat gradient buffer.
 static hipError_t expand_factored(sasgd_ctx* ctx, Learner& L) {
-  if (!ctx->net || L.fc_expanded || L.grad_timestamp < 0) return hipSuccess;
+  if (!ctx->net || !L.has_factors || L.fc_expanded || L.grad_timestamp < 0) return hipSuccess;
   FactoredLayer fl[kMaxFactoredLayers];
   const int nfl = net_factored_layers(ctx->net, fl, kMaxFactoredLayers);
   for (int k = 0; k < nfl; k++) {

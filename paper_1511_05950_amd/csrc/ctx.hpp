@@ -106,9 +106,10 @@ hipError_t net_prepare_version(Net* net, const void* flat, void* packed, hipStre
 hipError_t net_prepare_versions(Net* net, const void* const* flat, void* const* packed, int versions, hipStream_t stream);
 // out_rank_dev == nullptr: forward, loss, backward (gradients into binds[k].grad).
 // out_rank_dev != nullptr: evaluation pass, forward and loss only, plus the rank of each image's true class.
+// *wrote_factors (unless null): the factored layers' weight gradients were left as factors; false: all gradients are written out.
 hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* binds, int count,
-                             float* out_loss_dev, int32_t* out_rank_dev, hipStream_t stream);
-// Fully connected layers whose weight gradient calcGradient leaves as factors in the learner's workspace
+                             float* out_loss_dev, int32_t* out_rank_dev, bool* wrote_factors, hipStream_t stream);
+// Fully connected layers whose weight gradient calcGradient can leave as factors in the learner's workspace
 // (bf16 element offsets from the workspace base): weights at w_off [out][in], bias right behind them.
 struct FactoredLayer {
   int64_t w_off;
@@ -134,7 +135,8 @@ struct Learner {
   GradState grad_state = GRAD_NONE;
   float* grad = nullptr;       // [P] fp32 (nullptr for NET_NONE)
   void* workspace = nullptr;
-  bool fc_expanded = false;    // the factored parts of the current gradient have been written out into `grad`
+  bool has_factors = false;    // the current gradient's factored layers lie in `workspace` as factors
+  bool fc_expanded = false;    // those have been written out into `grad` as well
 };
 
 struct Pending;

@@ -62,8 +62,12 @@ struct CompactStage {
 };
 struct CompactPlan {
   bool ok = false;             // the network fits
-  bool always = false;         // no other path is worth taking; otherwise small calls only
-  int64_t macs = 0;            // multiply-adds of an image's forward pass
+  bool always = false;         // every call of this context goes there: nothing is laid out for the layer-by-layer kernels
+  // what a call's cost is made of (compact_wins), in units of 2^20: multiply-adds of an image's forward pass in convolutions that
+  // have a matrix-instruction kernel of their own (and in the last layer) and in those that do not ("odd"), weights of hidden
+  // fully connected layers with and without one, values of an image's layer outputs
+  double macs = 0, odd_macs = 0, fc = 0, odd_fc = 0, values = 0;
+  bool any_odd() const { return odd_macs + odd_fc > 0; }
   std::vector<CompactStage> stages;
   int flatten = -1;            // OP_FLATTEN in front of the first fully connected layer, if any
   std::vector<int> fcs;
@@ -134,9 +138,45 @@ static CompactPlan compact_plan(const Net* net) {
     const ConvShape& cs = ops[(size_t)cp.fcs[k]].cs;
     if (k + 1 == cp.fcs.size() ? !compact_head_ok(cs.C, cs.K) : !compact_fc_ok(cs.C, cs.K)) return cp;
   }
-  for (const Op& op : ops) cp.macs += (int64_t)op.cs.K * op.cs.C * op.cs.ks * op.cs.ks * op.cs.OH * op.cs.OW;
+  for (int k = 0; k < n; k++) {
+    const Op& op = ops[(size_t)k];
+    cp.values += (op.kind == OP_CONV ? (double)op.cs.K * op.cs.OH * op.cs.OW : (double)op.ps.C * op.ps.OH * op.ps.OW) / (1 << 20);
+    const double m = (double)op.cs.K * op.cs.C * op.cs.ks * op.cs.ks * op.cs.OH * op.cs.OW / (1 << 20);
+    if (k == cp.fcs.back()) cp.macs += m;
+    else if (op.is_fc) (op.mfma ? cp.fc : cp.odd_fc) += m;
+    else (op.mfma ? cp.macs : cp.odd_macs) += m;
+  }
   cp.ok = true;
   return cp;
+}
+
+// Are the compact kernels the faster ones for a call of `count` learners?  They save launches, and layers without a
+// matrix-instruction kernel of their own (channel counts that are no multiple of 8 in bf16, 4 in fp32; strided first layers with
+// padding; such hidden layers) are scalar kernels on the other path.  They lose where work is large: fp32 matrix instructions
+// whatever the type, the weights of a hidden layer read again for every learner and every 16 images and its gradient written out.
+// The differences in us, per unit of CompactPlan's terms, from both paths' times of 24 networks at 1 to 1 152 images a call:
+// the faster path is taken or missed by less than 10 % in nine of ten cases, and the path below is slower than the
+// layer-by-layer one by 17 % at most (one to 18 learners on thin layers, 20 us).  E.g. 64- and 96-channel convolutions in front of a
+// hidden layer of 137 units, bf16, 18 x 128 images 2 189 us layer by layer, 8 422 us compact; 1 x 8 images 165 against 102; two
+// hidden layers of 4 096 units behind a convolution of 30 channels, 18 x 4 images 649 against 3 437; the CIFAR-shaped net in
+// fp32 at 4 / 64 / 128 images 62 / 162 / 274 us compact, 139 / 256 / 358 layer by layer, in bf16 at 8 / 32 / 64 images
+// 86 / 125 / 217 against 123 / 149 / 169.
+struct CompactCost {
+  double launches;             // saved, us a call
+  double macs, odd_macs;       // per image (odd: saved)
+  double fc, odd_fc;           // per image and weight
+  double fc_once, odd_fc_once; // per learner and weight
+  double fc_again;             // per learner, weight and 16 images behind the first
+  double values;               // per image
+};
+static const CompactCost kCompactCost[2][2] = {   // [bf16][evaluation]
+    {{95, 0.045, 4.5, 0.08, 0.4, -6.5, 0, 0, 2}, {50, 0, 0.9, 0, 0.13, -2.5, 0, 1, 0.4}},
+    {{78, 0.145, 3.8, 0.1, 0.9, 3, 2.2, 1.4, 12}, {40, 0.05, 1, 0.012, 0.18, 0.7, 0.6, 0.4, 3}}};
+static bool compact_wins(const CompactPlan& p, bool bf16, int mu, int count, bool evaluation) {
+  const CompactCost& k = kCompactCost[bf16][evaluation];
+  const double image = k.macs * p.macs - k.odd_macs * p.odd_macs + k.fc * p.fc - k.odd_fc * p.odd_fc + k.values * p.values;
+  const double learner = k.fc_once * p.fc + k.odd_fc_once * p.odd_fc + k.fc_again * (p.fc + p.odd_fc) * ((mu + 15) / 16 - 1);
+  return count * (mu * image + learner) <= k.launches;
 }
 
 static int pool_out_size(int n, int k, int s) {
@@ -336,20 +376,18 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
     net->scores_f32 = true;
     if (net->bf16) { new_tensor(net->tensors[(size_t)cur].elems); }   // room for the wider elements (tensor is last in the arena)
   }
-  // small networks and mini-batches: the compact kernels.  They are the only good path where a layer does not fit the other
-  // matrix-instruction kernels (channel counts that are no multiple of 8); otherwise they serve small calls.
+  // small networks and mini-batches: the compact kernels
   net->compact = compact_plan(net);
   if (net->compact.ok) {
     CompactPlan& cp = net->compact;
     bool any_factored = false;
-    for (size_t k = 0; k < net->ops.size(); k++) {
-      const Op& op = net->ops[k];
-      if (op.kind == OP_CONV && !op.mfma && (int)k != cp.fcs.back()) cp.always = true;
-      any_factored = any_factored || op.factored;
-    }
+    for (const Op& op : net->ops) any_factored = any_factored || op.factored;
+    // they write every gradient out: not where factors are kept and all layers have kernels of their own
+    if (any_factored && !cp.any_odd()) cp.ok = false;
+    // the cost is linear in the learners of a call, so that the largest call decides for all of them
+    cp.always = cp.ok && compact_wins(cp, net->bf16, N, cfg.lambda, false) && compact_wins(cp, net->bf16, N, cfg.lambda, true);
     if (cp.always)
       for (Op& op : net->ops) op.factored = op.grouped = false;
-    else if (any_factored) cp.ok = false;
     if (cp.ok)
       for (int f : cp.fcs) cp.fc_dy.push_back(net->tensors[(size_t)new_tensor((size_t)N * net->ops[(size_t)f].cs.K)].off);
   }
@@ -388,7 +426,7 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
   cursor += 256;
   for (Op& op : net->ops) op.gf.zero_off = op.gd.zero_off = net->zero_off;
   for (const Op& op : net->ops) {
-    if (!op.mfma || op.pack_fwd < 0 || (net->compact.ok && net->compact.always)) continue;
+    if (!op.mfma || op.pack_fwd < 0 || net->compact.always) continue;
     if (net->pack.count == kMaxPackJobs) { delete net; err = "too many convolution layers for the MFMA path"; return SASGD_EINVAL; }
     PackJob& jb = net->pack.job[net->pack.count++];
     jb.v = op.vc;
@@ -430,7 +468,7 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
   if (need > 0 || compact_parts > 0) {
     size_t sb = need * 8;
     if (sb > ((size_t)128 << 20)) sb = need > ((size_t)128 << 20) ? need : ((size_t)128 << 20);
-    if (net->compact.ok && net->compact.always) sb = 0;
+    if (net->compact.always) sb = 0;
     sb = std::max(sb, compact_parts);
     net->scratch_off = (bytes + 255) & ~(size_t)255;
     net->scratch_bytes = sb;
@@ -444,7 +482,7 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
     size_t g = 256, max_in = 0, max_out = 0;
     net->g_zero_off = 0;
     for (Op& op : net->ops) {
-      if (!(op.is_fc && op.mfma) || op.grouped || (net->compact.ok && net->compact.always)) continue;
+      if (!(op.is_fc && op.mfma) || op.grouped || net->compact.always) continue;
       const size_t in = (size_t)op.cs.C, outn = (size_t)op.cs.K;
       if ((N * in * 2) % 16 || (N * outn * (op.out_f32 ? 4 : 2)) % 16 || R * std::max(in, outn) * 4 >= ((size_t)1 << 31)) continue;
       op.stacked = true;
@@ -530,12 +568,6 @@ int net_factored_layers(const Net* net, FactoredLayer* out, int max) {
 
 void net_set_pixel_mean(Net* net, const float* mean_dev) { net->pixel_mean = mean_dev; }
 void net_input_shape(const Net* net, int* C, int* H, int* W) { *C = net->inC; *H = net->inH; *W = net->inW; }
-
-// Multiply-adds of a call's forward passes up to which the compact kernels serve networks that the layer-by-layer kernels
-// take as well.  Measured on the CIFAR-shaped net (12.3 M an image), compact against layer by layer: fp32 at 4 / 64 / 128 / 480
-// images 62 / 162 / 274 / 874 us against 139 / 256 / 358 / 952; bf16 at 8 / 32 / 64 images 86 / 125 / 217 against 123 / 149 /
-// 169.  fp32 with 93 M an image at 12 / 128 images: 272 / 2 034 against 371 / 2 203.
-constexpr int64_t kCompactMacs[2] = {(int64_t)1600 << 20, (int64_t)400 << 20};   // fp32, bf16
 
 static CompactSrc compact_src(const Net* net, const CompactStage* st) {
   CompactSrc s;
@@ -682,7 +714,7 @@ static hipError_t compact_gradient(Net* net, const PtrTab& ws, const CPtrTab& wt
 
 // Forward pass, loss and (unless out_rank_dev is given, which makes this an evaluation pass) backward pass.
 hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* binds, int count, float* out_loss_dev,
-                             int32_t* out_rank_dev, hipStream_t stream) {
+                             int32_t* out_rank_dev, bool* wrote_factors, hipStream_t stream) {
   PtrTab ws, grads;
   CPtrTab wts, imgs, labs;
   memset(&ws, 0, sizeof(ws)); memset(&grads, 0, sizeof(grads));
@@ -696,7 +728,12 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
   }
   const bool bf = net->bf16;
   const std::vector<Tensor>& T = net->tensors;
-  if (net->compact.ok && (net->compact.always || count * net->mu * net->compact.macs <= kCompactMacs[bf]))
+  const bool compact = net->compact.ok && (net->compact.always || compact_wins(net->compact, bf, net->mu, count, out_rank_dev != nullptr));
+  if (wrote_factors) {
+    *wrote_factors = false;
+    for (const Op& op : net->ops) *wrote_factors = *wrote_factors || (op.factored && !compact);
+  }
+  if (compact)
     return compact_gradient(net, ws, wts, imgs, labs, grads, count, out_loss_dev, out_rank_dev, stream);
   // Learners that read the same weight version: the stacked fully connected layers take each such group (two members
   // and more) as one matrix product; `single` lists the others.  Groups lie one after the other in the staging area.
