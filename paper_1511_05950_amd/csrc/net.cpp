@@ -455,21 +455,32 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
     need = wg > need ? wg : need;
     need = dg > need ? dg : need;
   }
-  size_t compact_parts = 0;                        // partial weight gradients of all convolutions side by side
-  if (net->compact.ok)
-    for (CompactStage& st : net->compact.stages) {
-      // one tile of 32 positions per workgroup where that costs little memory
-      const int64_t elems = (int64_t)st.v.K * st.v.C * st.v.ks * st.v.ks + st.v.K;
-      st.most_splits = (int)std::min<int64_t>(std::min<int64_t>(256, std::max<int64_t>(32, ((int64_t)1 << 20) / elems)),
+  size_t sb = net->compact.always ? 0 : std::min(need * 8, std::max(need, (size_t)128 << 20));
+  if (net->compact.ok) {
+    // partial weight gradients of all convolutions side by side: one tile of 32 positions per workgroup where that costs
+    // little memory, and fewer partial copies of the largest where all together would take more than 128 MiB a learner
+    // (eight 512 x 512 x 3 x 3 convolutions at 32 images: 2.4 GiB uncapped)
+    std::vector<CompactStage>& stages = net->compact.stages;
+    auto elems = [](const CompactStage& st) { return (int64_t)st.v.K * st.v.C * st.v.ks * st.v.ks + st.v.K; };
+    for (CompactStage& st : stages)
+      st.most_splits = (int)std::min<int64_t>(std::min<int64_t>(256, std::max<int64_t>(32, ((int64_t)1 << 20) / elems(st))),
                                               (int64_t)st.v.N * ((st.v.OH * st.v.OW + 31) / 32));
-      st.part_off = compact_parts;
-      compact_parts += ((size_t)st.most_splits * ((size_t)st.v.K * st.v.C * st.v.ks * st.v.ks + st.v.K) * 4 + 255) & ~(size_t)255;
+    const size_t most = std::max(sb, (size_t)128 << 20);
+    size_t parts;
+    for (;;) {
+      parts = 0;
+      CompactStage* largest = nullptr;
+      for (CompactStage& st : stages) {
+        st.part_off = parts;
+        parts += ((size_t)st.most_splits * elems(st) * 4 + 255) & ~(size_t)255;
+        if (st.most_splits > 1 && (!largest || st.most_splits * elems(st) > largest->most_splits * elems(*largest))) largest = &st;
+      }
+      if (parts <= most || !largest) break;
+      largest->most_splits = (largest->most_splits + 1) / 2;
     }
-  if (need > 0 || compact_parts > 0) {
-    size_t sb = need * 8;
-    if (sb > ((size_t)128 << 20)) sb = need > ((size_t)128 << 20) ? need : ((size_t)128 << 20);
-    if (net->compact.always) sb = 0;
-    sb = std::max(sb, compact_parts);
+    sb = std::max(sb, parts);
+  }
+  if (sb > 0) {
     net->scratch_off = (bytes + 255) & ~(size_t)255;
     net->scratch_bytes = sb;
     bytes = net->scratch_off + sb;

@@ -6,7 +6,7 @@ import pytest
 
 import workloads as wl
 from oracle import cnn, protocol
-from test_gpu_net import check_gradient, draw_case, rel
+from test_gpu_net import check_gradient, draw_case, one_gradient, rel
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -84,3 +84,38 @@ def test_window_of_both_kinds():
     th, v = protocol.server_update(th, v, late, (0, 0), 0.01, 0.9, 1e-3)
     assert rel(r.ctx.copyWeights() - r.theta, th - r.theta) < 1e-4 and rel(r.ctx.copyMomentum(), v) < 1e-5
     r.ctx.destroy()
+
+
+DEEP = {"name": "deep", "input": (8, 3, 3), "classes": 10, "layers": [("conv", 512, 3, 1, 1)] * 9 + [("fc", 10)]}
+
+
+def test_partial_gradients_are_bounded():
+    """Split weight gradients of nine 512-channel convolutions: 20 M parameters, so 32 partial copies of each would take 2.4 GB a
+    learner.  With fewer copies (two images and fewer splits than tiles) the gradients are the oracle's."""
+    from paper_1511_05950_amd import binding
+    lib = binding.load()
+    sizes, held = [], {}
+
+    def alloc(size, _):
+        sizes.append(size)
+        t = torch.empty(size, dtype=torch.uint8, device="cuda")
+        held[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def release(address, _):
+        del held[address]
+
+    hooks = binding.ALLOC_FN(alloc), binding.RELEASE_FN(release)
+    cfg = binding.SasgdConfig()
+    cfg.lambda_, cfg.mu, cfg.n, cfg.ring_depth, cfg.net, cfg.num_layers = 1, 32, 1, 1, binding.NET_CUSTOM, 10
+    layers = (binding.SasgdLayer * 10)(*[(0, 512, 3, 1, 1)] * 9, (4, 10, 0, 0, 0))
+    cfg.layers, cfg.in_channels, cfg.in_height, cfg.in_width = layers, 8, 3, 3
+    cfg.alloc, cfg.release = hooks
+    w0 = torch.zeros(wl.num_params(DEEP), device="cuda")
+    h = binding.ctypes.c_void_p()
+    assert lib.sasgd_create(binding.ctypes.byref(cfg), w0.data_ptr(), binding.ctypes.byref(h)) == binding.OK
+    lib.sasgd_destroy(h)
+    assert not held and max(sizes) < 160 << 20          # the workspace: 128 MiB of partial sums and a few MiB of activations
+
+    for (g, rg, loss, rl) in one_gradient(DEEP, 2, "fp32", seed=3, scale=0.015, lam=1):
+        check_gradient(DEEP, "fp32", g, rg, loss, rl, "deep")
