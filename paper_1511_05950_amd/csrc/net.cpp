@@ -65,8 +65,9 @@ struct CompactPlan {
   bool always = false;         // every call of this context goes there: nothing is laid out for the layer-by-layer kernels
   // what a call's cost is made of (compact_wins), in units of 2^20: multiply-adds of an image's forward pass in convolutions that
   // have a matrix-instruction kernel of their own (and in the last layer) and in those that do not ("odd"), weights of hidden
-  // fully connected layers with and without one, values of an image's layer outputs
+  // fully connected layers with and without one, values of an image's layer outputs; output units of the odd hidden layers
   double macs = 0, odd_macs = 0, fc = 0, odd_fc = 0, values = 0;
+  int odd_units = 0;
   bool any_odd() const { return odd_macs + odd_fc > 0; }
   std::vector<CompactStage> stages;
   int flatten = -1;            // OP_FLATTEN in front of the first fully connected layer, if any
@@ -145,6 +146,7 @@ static CompactPlan compact_plan(const Net* net) {
     if (k == cp.fcs.back()) cp.macs += m;
     else if (op.is_fc) (op.mfma ? cp.fc : cp.odd_fc) += m;
     else (op.mfma ? cp.macs : cp.odd_macs) += m;
+    if (op.is_fc && !op.mfma && k != cp.fcs.back()) cp.odd_units += op.cs.K;
   }
   cp.ok = true;
   return cp;
@@ -154,29 +156,31 @@ static CompactPlan compact_plan(const Net* net) {
 // matrix-instruction kernel of their own (channel counts that are no multiple of 8 in bf16, 4 in fp32; strided first layers with
 // padding; such hidden layers) are scalar kernels on the other path.  They lose where work is large: fp32 matrix instructions
 // whatever the type, the weights of a hidden layer read again for every learner and every 16 images and its gradient written out.
-// The differences in us, per unit of CompactPlan's terms, from both paths' times of 24 networks at 1 to 1 152 images a call:
-// the faster path is taken or missed by less than 10 % in nine of ten cases, and the path below is slower than the
-// layer-by-layer one by 17 % at most (one to 18 learners on thin layers, 20 us).  E.g. 64- and 96-channel convolutions in front of a
+// The differences in us, per unit of CompactPlan's terms, from both paths' times of 24 networks at 1 to 2 304 images a call:
+// what this takes is the faster path or within 10 % of it in all but a few cases, and behind the layer-by-layer path by 13 % at
+// most (20 us of a call on 1 x 1 convolutions).  E.g. 64- and 96-channel convolutions in front of a
 // hidden layer of 137 units, bf16, 18 x 128 images 2 189 us layer by layer, 8 422 us compact; 1 x 8 images 165 against 102; two
 // hidden layers of 4 096 units behind a convolution of 30 channels, 18 x 4 images 649 against 3 437; the CIFAR-shaped net in
 // fp32 at 4 / 64 / 128 images 62 / 162 / 274 us compact, 139 / 256 / 358 layer by layer, in bf16 at 8 / 32 / 64 images
 // 86 / 125 / 217 against 123 / 149 / 169.
 struct CompactCost {
-  double launches;             // saved, us a call
+  double launches, hidden;     // saved, us a call and us per hidden layer
+  double odd_units;            // saved: the scalar input gradient walks a layer's units one after the other
   double macs, odd_macs;       // per image (odd: saved)
   double fc, odd_fc;           // per image and weight
+  double learner;              // per learner
   double fc_once, odd_fc_once; // per learner and weight
   double fc_again;             // per learner, weight and 16 images behind the first
   double values;               // per image
 };
 static const CompactCost kCompactCost[2][2] = {   // [bf16][evaluation]
-    {{95, 0.045, 4.5, 0.08, 0.4, -6.5, 0, 0, 2}, {50, 0, 0.9, 0, 0.13, -2.5, 0, 1, 0.4}},
-    {{78, 0.145, 3.8, 0.1, 0.9, 3, 2.2, 1.4, 12}, {40, 0.05, 1, 0.012, 0.18, 0.7, 0.6, 0.4, 3}}};
+    {{72, 0, 0.08, 0.045, 4.5, 0.08, 0.45, 0, -6.5, 0, 0, 0}, {50, 0, 0, 0, 0.9, 0, 0.13, 0, -2.5, 0, 1, 0.4}},
+    {{84, 12, 0.08, 0.145, 3.8, 0.1, 0.9, 2, 3, 3.5, 1.2, 12}, {40, 8, 0, 0.05, 1, 0.012, 0.18, 0, 0.7, 0.8, 0.4, 5}}};
 static bool compact_wins(const CompactPlan& p, bool bf16, int mu, int count, bool evaluation) {
   const CompactCost& k = kCompactCost[bf16][evaluation];
   const double image = k.macs * p.macs - k.odd_macs * p.odd_macs + k.fc * p.fc - k.odd_fc * p.odd_fc + k.values * p.values;
-  const double learner = k.fc_once * p.fc + k.odd_fc_once * p.odd_fc + k.fc_again * (p.fc + p.odd_fc) * ((mu + 15) / 16 - 1);
-  return count * (mu * image + learner) <= k.launches;
+  const double learner = k.learner + k.fc_once * p.fc + k.odd_fc_once * p.odd_fc + k.fc_again * (p.fc + p.odd_fc) * ((mu + 15) / 16 - 1);
+  return count * (mu * image + learner) <= k.launches + k.hidden * ((double)p.fcs.size() - 1) + k.odd_units * p.odd_units;
 }
 
 static int pool_out_size(int n, int k, int s) {
