@@ -19,6 +19,9 @@
 // buffer is 8 MiB and is read back right after it was written (it passes the L2s' memory interface both ways, 8 bytes
 // per parameter of counted traffic, and fits the memory-side cache many times over).  P = 62 M with a bf16 copy: c = 54
 // 2.27 ms against 2.42 ms in one pass; the two forms cross at c of about 30 (1.41 against 1.40 ms).
+// The second pass keeps the shape of the first, blocks of 256 lanes with four pieces each, and reads the sums with ordinary loads:
+// c = 54 behind c = 1 updates of 60 M parameters 2 175 us, against 2 228 with one-wavefront workgroups of two pieces, 2 226 with
+// four pieces, 2 224 with two pieces a lane in blocks of 256, and 2 265 with ordinary loads of theta and v.
 #include "ctx.hpp"
 #include "dev_common.hpp"
 
@@ -126,11 +129,12 @@ __device__ __forceinline__ float sum_element(const GradTable& t, int begin, int 
 // lane of the last whole workgroup, their loads come after that wavefront's own: 11.3 instead of 6 us at P = 89 578, c = 30).
 enum { kCached = 0, kReuse = 1, kStream = 2 };
 constexpr int kUpdThreads = 64;
-template <int ILP, int U, bool SHADOW, int MODE>
-__global__ __launch_bounds__(kUpdThreads) void apply_update_kernel(const float* theta_in, float* theta_out, float* v,
+// TH: lanes of a workgroup.  GPLAIN: the gradients are read with ordinary loads (the second pass of a long window).
+template <int ILP, int U, bool SHADOW, int MODE, int TH = kUpdThreads, bool GPLAIN = false>
+__global__ __launch_bounds__(TH) void apply_update_kernel(const float* theta_in, float* theta_out, float* v,
                                                                    bf16_t* __restrict__ shadow, int64_t P, int c, GradTable t, float m,
                                                                    float decay, int reverse) {
-  const int64_t n4 = P >> 2, whole = (n4 + kUpdThreads * ILP - 1) / (kUpdThreads * ILP);
+  const int64_t n4 = P >> 2, whole = (n4 + TH * ILP - 1) / (TH * ILP);
   if (blockIdx.x >= whole) {
     const int64_t k = n4 * 4 + threadIdx.x;
     if (k >= P) return;
@@ -142,14 +146,14 @@ __global__ __launch_bounds__(kUpdThreads) void apply_update_kernel(const float* 
     return;
   }
   const int64_t blk = reverse ? whole - 1 - blockIdx.x : blockIdx.x;
-  const int64_t base = blk * (kUpdThreads * ILP) + threadIdx.x;
+  const int64_t base = blk * (TH * ILP) + threadIdx.x;
   const float4* th4 = reinterpret_cast<const float4*>(theta_in);
   float4* v4 = reinterpret_cast<float4*>(v);
   float4 s[ILP], th[ILP], vv[ILP];
   bool in[ILP];
 #pragma unroll
   for (int e = 0; e < ILP; e++) {
-    const int64_t i = base + e * kUpdThreads;
+    const int64_t i = base + e * TH;
     in[e] = i < n4;
     s[e] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (in[e]) {
@@ -164,7 +168,7 @@ __global__ __launch_bounds__(kUpdThreads) void apply_update_kernel(const float* 
     for (int u = 0; u < U; u++)
 #pragma unroll
       for (int e = 0; e < ILP; e++)
-        if (in[e]) g[u][e] = ldg_nt(reinterpret_cast<const float4*>(t.g[l + u]) + base + e * kUpdThreads);
+        if (in[e]) g[u][e] = GPLAIN ? reinterpret_cast<const float4*>(t.g[l + u])[base + e * TH] : ldg_nt(reinterpret_cast<const float4*>(t.g[l + u]) + base + e * TH);
 #pragma unroll
     for (int u = 0; u < U; u++)             // arrival order l, l+1, ... within every element
 #pragma unroll
@@ -176,7 +180,7 @@ __global__ __launch_bounds__(kUpdThreads) void apply_update_kernel(const float* 
     for (int u = 0; u < U; u++)
 #pragma unroll
       for (int e = 0; e < ILP; e++)
-        if (in[e] && l + u < c) g[u][e] = ldg_nt(reinterpret_cast<const float4*>(t.g[l + u]) + base + e * kUpdThreads);
+        if (in[e] && l + u < c) g[u][e] = GPLAIN ? reinterpret_cast<const float4*>(t.g[l + u])[base + e * TH] : ldg_nt(reinterpret_cast<const float4*>(t.g[l + u]) + base + e * TH);
 #pragma unroll
     for (int u = 0; u < U; u++)
       if (l + u < c) {
@@ -186,7 +190,7 @@ __global__ __launch_bounds__(kUpdThreads) void apply_update_kernel(const float* 
   }
 #pragma unroll
   for (int e = 0; e < ILP; e++) {
-    const int64_t i = base + e * kUpdThreads;
+    const int64_t i = base + e * TH;
     if (in[e]) {
       update4(th[e], vv[e], s[e], m, decay);
       float4* to = reinterpret_cast<float4*>(theta_out) + i;
@@ -315,14 +319,14 @@ __global__ __launch_bounds__(kUpdThreads) void apply_updates_fused_kernel(const 
 // Workgroups for n4 pieces, `per` each, plus the one of the remaining elements.
 static unsigned update_grid(int64_t P, int64_t per) { return (unsigned)((P / 4 + per - 1) / per + (P % 4 ? 1 : 0)); }
 
-template <int ILP, int U, int MODE>
+template <int ILP, int U, int MODE, int TH = kUpdThreads, bool GPLAIN = false>
 static void launch_update(const UpdateLaunch& u, const GradTable& t, int residency_lds, hipStream_t stream) {
-  const dim3 grid(update_grid(u.P, kUpdThreads * ILP));
+  const dim3 grid(update_grid(u.P, TH * ILP));
   if (u.shadow_out)
-    hipLaunchKernelGGL((apply_update_kernel<ILP, U, true, MODE>), grid, dim3(kUpdThreads), residency_lds, stream, u.theta_in, u.theta_out, u.v,
+    hipLaunchKernelGGL((apply_update_kernel<ILP, U, true, MODE, TH, GPLAIN>), grid, dim3(TH), residency_lds, stream, u.theta_in, u.theta_out, u.v,
                        u.shadow_out, u.P, u.c, t, u.momentum, u.decay, u.reverse);
   else
-    hipLaunchKernelGGL((apply_update_kernel<ILP, U, false, MODE>), grid, dim3(kUpdThreads), residency_lds, stream, u.theta_in, u.theta_out, u.v,
+    hipLaunchKernelGGL((apply_update_kernel<ILP, U, false, MODE, TH, GPLAIN>), grid, dim3(TH), residency_lds, stream, u.theta_in, u.theta_out, u.v,
                        u.shadow_out, u.P, u.c, t, u.momentum, u.decay, u.reverse);
 }
 
@@ -356,7 +360,7 @@ hipError_t launch_apply_update(const UpdateLaunch& u, hipStream_t stream) {
       r.v = u.v + off;
       r.shadow_out = u.shadow_out ? u.shadow_out + off : nullptr;
       r.P = len;
-      launch_update<2, 8, kStream>(r, tb, 0, stream);
+      launch_update<4, 1, kStream, 256, true>(r, tb, 0, stream);
     }
     return hipGetLastError();
   }
