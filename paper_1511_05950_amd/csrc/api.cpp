@@ -231,10 +231,10 @@ int flush_updates(sasgd_ctx* ctx) {
       total += (int)ctx->deferred[(size_t)n].grads.size();
       n++;
     }
-    if ((int)ctx->deferred[0].grads.size() >= kTwoPassMinC) n = 1;   // long windows go alone (two-pass form)
+    if ((int)ctx->deferred[0].grads.size() >= kAloneMinC) n = 1;   // long windows go alone
     else
       for (int t = 1; t < n; t++)
-        if ((int)ctx->deferred[(size_t)t].grads.size() >= kTwoPassMinC) { n = t; break; }
+        if ((int)ctx->deferred[(size_t)t].grads.size() >= kAloneMinC) { n = t; break; }
     if (n < 1) n = 1;
     hipError_t e = enqueue_updates(ctx, n);
     ctx->deferred.erase(ctx->deferred.begin(), ctx->deferred.begin() + n);
@@ -313,7 +313,7 @@ int sasgd_create(const sasgd_config* cfg, const float* init_weights, sasgd_ctx**
     }
     ctx->v = (float*)ctx_alloc(ctx, P * sizeof(float));
     if (!ctx->ring_f32 || !ctx->v) { rc = fail(ctx, SASGD_ENOMEM, "weight ring / momentum"); break; }
-    if (cfg->lambda / cfg->n >= kTwoPassMinC) {
+    if (two_pass_update(ctx->P, ctx->c)) {
       ctx->sum_buf = (float*)ctx_alloc(ctx, (size_t)kSumStretch * sizeof(float));
       if (!ctx->sum_buf) { rc = fail(ctx, SASGD_ENOMEM, "buffer of the two-pass update"); break; }
     }
@@ -574,8 +574,8 @@ int sasgd_applyUpdate(sasgd_ctx* ctx, int64_t* out_new_timestamp) {
   d.decay = abar * ctx->cfg.weight_decay;
   // Deferral: the kernels of consecutive updates are launched together, as one pass over the vector (fused steps),
   // once something needs their result.  Only windows whose gradients the library owns wait (a caller's buffer may
-  // change as soon as this call returns), and long windows keep their two-pass form.
-  const bool defer = !(ctx->cfg.flags & SASGD_FLAG_EAGER_UPDATES) && own && ctx->window_count < kTwoPassMinC;
+  // change as soon as this call returns), and long windows go alone.
+  const bool defer = !(ctx->cfg.flags & SASGD_FLAG_EAGER_UPDATES) && own && ctx->window_count < kAloneMinC;
   int queued = 0;
   for (const DeferredUpdate& q : ctx->deferred) queued += (int)q.grads.size();
   if (!defer || (int)ctx->deferred.size() == kMaxFusedSteps || queued + ctx->window_count > kMaxLearners) {

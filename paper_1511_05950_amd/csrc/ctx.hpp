@@ -42,9 +42,11 @@ struct StepTable {
   float* theta_out[kMaxFusedSteps];     // fp32 weights after step t (ring slot), or nullptr: not kept (fp32 master in place)
   bf16_t* shadow_out[kMaxFusedSteps];   // bf16 copy of the weights after step t, or nullptr
 };
-// Windows of at least kTwoPassMinC gradients go alone (never fused with other steps) and may be applied in two passes per
-// stretch of kSumStretch parameters.
-constexpr int kTwoPassMinC = 25;
+// Windows of at least this many gradients are applied at once and alone, never deferred and fused with other steps (two of them
+// would fill the gradient table).
+constexpr int kAloneMinC = 25;
+// Is a window of c gradients over P parameters applied in two passes per stretch of kSumStretch parameters?  See update.hip.
+inline bool two_pass_update(int64_t P, int c) { return P >= (int64_t)1 << 22 && (c >= 45 || (c >= 36 && P > (int64_t)1 << 25)); }
 constexpr int64_t kSumStretch = (int64_t)1 << 21;   // 8 MiB of sums: 512 workgroups of 4 096 parameters
 hipError_t launch_apply_update(const UpdateLaunch& u, hipStream_t stream);
 // Fused steps over a flat stretch: u supplies theta_in, v, P, momentum, the gradient table (u.c entries in all, at most
@@ -173,7 +175,7 @@ struct sasgd_ctx {
   size_t slot_elems_b16 = 0;         // elements per bf16 slot (P rounded up + packed filters)
   size_t slot_elems_f32 = 0;         // FP32 compute: elements per ring slot (P rounded up to 64)
   float* v = nullptr;                // momentum [P]
-  float* sum_buf = nullptr;          // [kSumStretch] partial result of long windows (c >= kTwoPassMinC), else nullptr
+  float* sum_buf = nullptr;          // [kSumStretch] partial result of windows that take two passes (two_pass_update), else nullptr
   std::vector<sasgd::Learner> learners;
   std::vector<sasgd::Pending> pending;
   std::vector<sasgd::DeferredUpdate> deferred;   // updates applied on the host whose kernels are not launched yet

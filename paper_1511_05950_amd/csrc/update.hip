@@ -10,15 +10,17 @@
 // bandwidth bound (latency bound below a million parameters); each lane moves 16-byte vectors,
 // gradients are read with non-temporal loads because they are never read again.
 //
-// Long windows over long vectors (c >= kTwoPassLaunchC, P >= kTwoPassLaunchP) take the same arithmetic in two launches per
-// stretch of kSumStretch parameters:
+// Long windows over long vectors (two_pass_update) take the same arithmetic in two launches per stretch of kSumStretch parameters:
 // sum_gradients_kernel writes s for the stretch to a small buffer, apply_update_kernel then runs on the stretch with
 // that buffer as its one "gradient" of coefficient 1 (fma(1, s, 0) = s: the result is bit-identical).  A pass that
 // only reads streams c gradients at the rate of a pure read (7.07 TB/s measured); in the single pass the two written
-// streams are interleaved with the 54 read ones all the time.  The
+// streams are interleaved with the c read ones all the time.  The
 // buffer is 8 MiB and is read back right after it was written (it passes the L2s' memory interface both ways, 8 bytes
-// per parameter of counted traffic, and fits the memory-side cache many times over).  P = 62 M with a bf16 copy: c = 54
-// 2.27 ms against 2.42 ms in one pass; the two forms cross at c of about 30 (1.41 against 1.40 ms).
+// per parameter of counted traffic, and fits the memory-side cache many times over).  The line, from one pass against two over
+// P = 4 M .. 62 M: from 48 gradients on two passes are the faster form everywhere (P = 62 M with a bf16 copy c = 48 2 055 against
+// 2 212 us, c = 54 2 266 against 2 431; P = 10 M c = 54 365 against 380; P = 4 M c = 48 133 against 134), up to 32 one pass is
+// (P = 17 M, c = 32: 399 against 433), and between them they differ by up to 4 % either way: two passes win beyond 32 M
+// parameters (P = 62 M, c = 40: 1 804 against 1 859), one pass below (17 M: by 3 %).
 // The second pass keeps the shape of the first, blocks of 256 lanes with four pieces each, and reads the sums with ordinary loads:
 // c = 54 behind c = 1 updates of 60 M parameters 2 175 us, against 2 228 with one-wavefront workgroups of two pieces, 2 226 with
 // four pieces, 2 224 with two pieces a lane in blocks of 256, and 2 265 with ordinary loads of theta and v.
@@ -330,9 +332,6 @@ static void launch_update(const UpdateLaunch& u, const GradTable& t, int residen
                        u.shadow_out, u.P, u.c, t, u.momentum, u.decay, u.reverse);
 }
 
-constexpr int kTwoPassLaunchC = 32;                       // see the head of this file
-constexpr int64_t kTwoPassLaunchP = (int64_t)1 << 24;     // shorter vectors: one pass (P = 10 M, c = 54: 380 against 390 us)
-
 hipError_t launch_apply_update(const UpdateLaunch& u, hipStream_t stream) {
   if (u.P <= 0) return hipSuccess;
   if (u.P / 4 > (int64_t)0x7fffff00 * kUpdThreads) return hipErrorInvalidValue;
@@ -341,7 +340,7 @@ hipError_t launch_apply_update(const UpdateLaunch& u, hipStream_t stream) {
     t.g[l] = l < u.c ? u.grads[l] : nullptr;
     t.coef[l] = l < u.c ? u.coef[l] : 0.f;
   }
-  if (u.P >= kTwoPassLaunchP && u.c >= kTwoPassLaunchC && u.sum_buf) {
+  if (two_pass_update(u.P, u.c) && u.sum_buf) {
     // stretches of 512 summing workgroups (two per compute unit; 256-1024 measured within 4 %, other counts slower)
     UpdateLaunch r = u;
     r.c = 1;

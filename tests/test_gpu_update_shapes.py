@@ -8,7 +8,9 @@ pytestmark = pytest.mark.gpu
 
 M2 = 1 << 20
 CASES = [(1, 1), (3, 5), (4, 16), (255, 17), (257, 2), (600_000, 33), (600_003, 7), (1_500_001, 9), (1_500_005, 4), (6_000_002, 5), (6_000_007, 25),
-         (16 * M2 - 1, 32), (16 * M2 + 3, 32), (32 * M2 + 2, 1), (32 * M2 + 6, 5)]
+         (16 * M2 - 1, 32), (16 * M2 + 3, 32), (32 * M2 + 2, 1), (32 * M2 + 6, 5),
+         # around the lines of the two-pass form, with stretches that end in part of a block and part of a piece
+         (4 * M2 - 1, 45), (4 * M2 + 3, 45), (4 * M2 + 3, 44), (6 * M2 + 4101, 46), (32 * M2, 36), (32 * M2 + 5, 36)]
 
 
 @pytest.mark.parametrize("P,c", CASES)
