@@ -8,10 +8,16 @@ at the start).  This realises the server-view update of the paper's Section 3 fo
 from __future__ import annotations
 
 
-def _rows(schedule, c):
-    """The first c entries of every row as Python integers (an array element costs several times as much to fetch)."""
-    rows = schedule.tolist() if hasattr(schedule, "tolist") else schedule
-    return [[int(t) for t in row[:c]] for row in rows]
+def _plain(schedule):
+    """An array as nested lists (an array element costs several times as much to fetch); anything else as it is."""
+    return schedule.tolist() if hasattr(schedule, "tolist") else schedule
+
+
+def _row(schedule, k, c):
+    """The first c entries of row k as Python integers, fetched by index only: a schedule may be any object with a length whose
+    rows come to be while the run goes on."""
+    row = schedule[k]
+    return [int(row[l]) for l in range(c)]
 
 
 def run_softsync(ctx, schedule, batch_of, lam, loss_out=None, on_gradient=None, first_update=0, base_rates=None):
@@ -28,17 +34,18 @@ def run_softsync(ctx, schedule, batch_of, lam, loss_out=None, on_gradient=None, 
     """
     c = ctx.c
     log = []
-    schedule = _rows(schedule, c)
+    schedule = _plain(schedule)
     for k in range(len(schedule)):
         i = first_update + k
         assert ctx.timestamp() == i
+        stale = _row(schedule, k, c)
         learners = []
         stamps = []
         for l in range(c):
             learner = (i * c + l) % lam
             x, y = batch_of(i, l)
             ctx.getMinibatch(learner, x, y)
-            stamps.append(ctx.pullWeights(learner, schedule[k][l]))
+            stamps.append(ctx.pullWeights(learner, stale[l]))
             learners.append(learner)
         ctx.calcGradient(learners, loss_out)
         for l in range(c):
@@ -65,7 +72,8 @@ def run_softsync_batched(ctx, schedule, batch_of, lam, loss_out=None, first_upda
     """
     c = ctx.c
     K = len(schedule)
-    stale = _rows(schedule, c)                  # requested staleness
+    schedule = _plain(schedule)
+    stale = []                                  # requested staleness, row by row as updates come within reach
     done = {}                                   # gradient id -> (learner, timestamp j)
     log = []
     calls = 0
@@ -76,7 +84,10 @@ def run_softsync_batched(ctx, schedule, batch_of, lam, loss_out=None, first_upda
         first = k * c
         if any(g not in done for g in range(first, first + c)):
             learners = []
-            for g in range(first, min(K * c, first + lam)):
+            end = min(K * c, first + lam)
+            while len(stale) * c < end:
+                stale.append(_row(schedule, len(stale), c))
+            for g in range(first, end):
                 if g in done:
                     continue
                 i2, l2 = first_update + g // c, g % c

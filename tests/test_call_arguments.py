@@ -77,3 +77,32 @@ def test_schedule_forms(form):
             run(ctx, schedule, lambda i, l: (None, None), 4)
             log.append((run.__name__, ctx.asked))
     assert log[0] == log[2] and log[1] == log[3]
+
+
+class _AsItGoes:
+    """A schedule that is made while the run goes on: length and rows by index only, rows that know nothing but their entries, none
+    of them further ahead of the server than the learners can be."""
+
+    def __init__(self, ctx, rows, ahead):
+        self.ctx, self.rows, self.ahead = ctx, rows, ahead
+
+    def __len__(self):
+        return len(self.rows)
+
+    def __iter__(self):
+        raise TypeError("rows are fetched by index")
+
+    def __getitem__(self, k):
+        assert k <= self.ctx.ts + self.ahead
+        return dict(enumerate(self.rows[k]))
+
+
+@pytest.mark.parametrize("run, ahead", [(driver.run_softsync, 0), (driver.run_softsync_batched, 2)])
+def test_schedule_made_while_the_run_goes_on(run, ahead):
+    c, lam, rows = 2, 4, [[0, 0], [1, 0], [0, 1], [2, 1], [1, 0], [0, 0], [3, 2]]
+    asked = []
+    for schedule in (lambda ctx: _AsItGoes(ctx, rows, ahead), lambda ctx: np.asarray(rows)):
+        ctx = _Context(c)
+        run(ctx, schedule(ctx), lambda i, l: (None, None), lam)
+        asked.append(ctx.asked)
+    assert asked[0] == asked[1] and len(asked[0]) == c * len(rows)
