@@ -25,6 +25,16 @@ NETS = {
     "window_11": (net(3, 31, 35, 4, ("conv", 33, 11, 4, 0), R, ("conv", 13, 3, 1, 1), ("avgpool", 3, 2), R, ("fc", 19), R), 2, 2),
     "hidden_split": (net(3, 22, 22, 5, ("conv", 21, 3, 1, 1), R, ("maxpool", 3, 2), ("fc", 37), R, ("fc", 18), R), 17, 2),
     "no_pooling": (net(4, 6, 7, 6, ("conv", 9, 3, 1, 1), R, ("conv", 12, 3, 1, 1), R), 5, 2),
+    # pooling windows other than 3 x 3 / 2, four channels at a time and one, clipped at the border, and of stride 1
+    "max_4_3": (net(3, 20, 17, 5, ("conv", 12, 3, 1, 1), R, ("maxpool", 4, 3), ("conv", 9, 3, 1, 1), R, ("maxpool", 4, 2)), 3, 2),
+    "max_2_2": (net(3, 15, 18, 5, ("conv", 9, 3, 1, 1), R, ("maxpool", 2, 2), ("conv", 12, 3, 1, 1), R, ("maxpool", 5, 3)), 3, 2),
+    "stride_1": (net(3, 10, 9, 5, ("conv", 12, 3, 1, 1), R, ("maxpool", 2, 1), ("conv", 9, 3, 1, 1), R, ("avgpool", 2, 1)), 2, 2),
+    "max_1_1": (net(3, 9, 9, 5, ("conv", 8, 3, 1, 1), ("maxpool", 1, 2), R, ("conv", 5, 3, 1, 1), R, ("maxpool", 2, 1)), 2, 2),
+    # hidden layers whose products are split over workgroups: both directions, rows of 16 bytes, one image and more than 16;
+    # the input gradient alone with weights that start between 16-byte pieces
+    "fc_split_1": (net(2, 12, 12, 6, ("conv", 16, 3, 1, 1), R, ("fc", 2052), R), 1, 1),
+    "fc_split_17": (net(2, 12, 12, 6, ("conv", 16, 3, 1, 1), R, ("fc", 2052), R), 17, 1),
+    "fc_split_unaligned": (net(2, 8, 12, 6, ("conv", 6, 3, 1, 1), R, ("maxpool", 2, 2), ("fc", 2052), R), 17, 1),
     "large_tiles": (net(3, 17, 16, 5, ("conv", 36, 5, 1, 2), R, ("maxpool", 3, 2), ("conv", 34, 3, 1, 1), R), 15, 16),
     # flattened inputs of many pixels per channel (no ReLU: every sum is decided): index times pixels is beyond 2^32
     "flat_160x160": (net(3, 160, 160, 10, ("conv", 8, 3, 1, 1), ("fc", 64)), 2, 1),
