@@ -17,7 +17,7 @@
 // What bounds such a launch is latency: a memory round trip is 2 000 cycles when another chiplet wrote the data, and code that
 // runs once is fetched as it goes (unrolling the contraction into 13 KiB of straight-line code made the CIFAR-shaped conv2 take
 // 14 us with 2.7 us of matrix instructions).  So loops stay rolled, independent requests are issued together in front of them,
-// and small calls use workgroups of 16 wavefronts on 16 x 16 tiles: many small pieces, each loaded in one round.
+// and small calls use workgroups of 16 wavefronts on 32 x 16 tiles: many small pieces, each loaded in one round.
 //
 // Arithmetic: fp32 matrix instructions on fp32 operands whatever the storage type T is (bf16 values are exact in fp32), fp32
 // accumulation.  Tensors are rounded to T at the same points as in the other paths (layer outputs, pooled values, activation
@@ -754,7 +754,6 @@ __global__ __launch_bounds__(kHeadTh) void compact_head_kernel(PtrTab ws, CPtrTa
     zs[j] = d;                                    // each score is read and replaced by its own thread
   }
   __syncthreads();
-  if (!hd.need_dx) return;
   T* dx = (T*)wsb + hd.dx_off + (uint32_t)n * in;
   for (int i = tid * V; i < in; i += kHeadTh * V) {
     float acc[V];
@@ -868,9 +867,9 @@ __global__ __launch_bounds__(64) void compact_fc_sum_kernel(PtrTab ws, CPtrTab w
 }
 
 // ---------------------------------------------------------------- everything that is left at the end
-// Jobs one after the other in the launch index: sums of split weight gradients (a split's partial lies in flat parameter
-// order, weights then biases, so input and output are contiguous), fully connected weight gradients (kFinU output units per
-// thread, their dy of up to kFinN images in LDS), mean losses.
+// Jobs one after the other in the launch index: sums of split weight gradients (a split's partial lies as wgrad_part left it, a
+// channel's columns by tap and then its bias: read in that order, each sum written to its place in the flat order), fully
+// connected weight gradients (kFinU output units per thread, their dy of up to kFinN images in LDS), mean losses.
 constexpr int kFinU = 8, kFinN = 32;
 template <typename T>
 __global__ __launch_bounds__(256) void compact_finish_kernel(PtrTab ws, PtrTab grads, CompactFinish fin, size_t loss_off, int N, float* loss_out) {
@@ -881,7 +880,7 @@ __global__ __launch_bounds__(256) void compact_finish_kernel(PtrTab ws, PtrTab g
   const CompactJob& jb = fin.job[j];
   const int b = blockIdx.x - jb.first_block;
   if (jb.kind == CJOB_SUM) {                       // element (channel n, column j = tap C + c, or the bias behind the columns)
-    // many splits: dealt out to jb.groups groups of lanes, so that an element's partials arrive in one or two rounds
+    // many splits: dealt out to jb.groups groups of lanes, which take four each a round (two rounds for 64 splits, eight for 256)
     __shared__ float red[256];
     const int per = 256 / jb.groups, g = threadIdx.x / per, e = threadIdx.x - g * per, i = b * per + e;
     const float* part = reinterpret_cast<const float*>(wsb + jb.part_off) + min(i, (int)jb.elems - 1);

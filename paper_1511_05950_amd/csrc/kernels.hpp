@@ -233,7 +233,7 @@ struct CompactHead {
   int N, in, K;
   int64_t w_off, b_off;
   size_t flat_off, dz_off, dx_off, loss_off;   // elements; loss_off bytes
-  int use_mask, need_dx;
+  int use_mask;
   int C, HW;                   // the input in front of a flattening: channels, pixels (HW = 1, C = in: none)
   FastDiv by_hw;
 };
@@ -260,7 +260,7 @@ struct CompactFinish {
   int count;
 };
 // Floats per pixel of an LDS patch: room for C rounded up to a multiple of four, and 4 (mod 8).
-__host__ __device__ inline int compact_pixel_stride(int C) { return (((C + 3) & ~3) & ~7) + ((((C + 3) & ~3) & 7) > 4 ? 12 : 4); }
+__host__ __device__ inline int compact_pixel_stride(int C) { return ((C + 3) & ~7) + 4; }
 // Wavefronts of a weight-gradient workgroup side by side across its column blocks (a power of two).
 __host__ __device__ inline int wgrad_waves_across(int blocks, int waves) {
   int w = 1;

@@ -70,7 +70,6 @@ struct CompactPlan {
   int odd_units = 0;
   bool any_odd() const { return odd_macs + odd_fc > 0; }
   std::vector<CompactStage> stages;
-  int flatten = -1;            // OP_FLATTEN in front of the first fully connected layer, if any
   std::vector<int> fcs;
   std::vector<size_t> fc_dy;   // element offset of every fully connected layer's output gradient
 };
@@ -129,7 +128,7 @@ static CompactPlan compact_plan(const Net* net) {
     cp.stages.push_back(st);
   }
   if (cp.stages.empty()) return cp;
-  if (i < n && ops[(size_t)i].kind == OP_FLATTEN) cp.flatten = i++;
+  if (i < n && ops[(size_t)i].kind == OP_FLATTEN) i++;
   for (; i < n; i++) {
     if (!ops[(size_t)i].is_fc) return cp;
     cp.fcs.push_back(i);
@@ -663,7 +662,6 @@ static hipError_t compact_gradient(Net* net, const PtrTab& ws, const CPtrTab& wt
     hd.w_off = f.w_off; hd.b_off = f.b_off;
     hd.flat_off = flat_off; hd.dz_off = f.dy_off; hd.dx_off = f.dx_off; hd.loss_off = net->loss_off;
     hd.use_mask = f.use_mask;
-    hd.need_dx = 1;
     hd.HW = f.HW; hd.C = f.in / f.HW;
     hd.by_hw.set(f.HW);
     TRY(launch_compact_head(bf, ws, wts, labs, s, hd, out_rank_dev, count, stream));
