@@ -85,8 +85,18 @@ struct IGemm {
   uint32_t a_bytes, b_bytes;
 };
 
-// floor(n / d) == (n * magic(d)) >> 32 for all 0 <= n with n * d < 2^32 (d >= 2); d == 1 is handled apart.
-inline uint32_t magic_u32(int d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1) << 32) / (uint32_t)d + 1u); }
+// The multipliers are FastDiv's, with its limits; d == 1 is handled apart.
+inline uint32_t magic_u32(int d) {
+  FastDiv f;
+  f.set(d);
+  return f.m;
+}
+// Are all of an implicit GEMM's divisions exact?  Rows go up to M, contraction chunks up to Kchunks.  Not so e.g. for 33 images of
+// 512 x 512, or a fully connected layer of 307 200 inputs in fp32: such layers stay on the direct kernels.
+inline bool igemm_divides(const IGemm& g) {
+  return FastDiv::exact(g.OW, g.M - 1) && FastDiv::exact(g.OH, g.M / g.OW - 1) && FastDiv::exact(g.CPT, g.Kchunks - 1) &&
+         FastDiv::exact(g.ks, g.ks * g.ks - 1);
+}
 inline void igemm_set_magics(IGemm& g, int elem_bytes) {
   if (g.OH > 0 && g.OW > 0) g.a_bytes = (uint32_t)((int64_t)(g.M / (g.OH * g.OW)) * g.H * g.W * g.C * elem_bytes);
   g.b_bytes = (uint32_t)((int64_t)((g.Ncols + 31) & ~31) * g.ldb * 2);

@@ -243,7 +243,10 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
   bool first_mfma = false;
   if (layers[0].kind == SASGD_CONV && layers[0].units % chunk == 0 && layers[0].window >= 1 && layers[0].stride >= 1) {
     const sasgd_layer& L0 = layers[0];
-    if (L0.stride == 1) {
+    const int oh = (H + 2 * L0.pad - L0.window) / L0.stride + 1, ow = (W + 2 * L0.pad - L0.window) / L0.stride + 1;
+    if (oh < 1 || ow < 1 || !FastDiv::exact(ow, (int64_t)N * oh * ow - 1) || !FastDiv::exact(oh, (int64_t)N * oh - 1)) {
+      // refused below, or more positions than the matrix kernels can divide (igemm_divides)
+    } else if (L0.stride == 1) {
       net->inpack.Cp = round_chunk(C);
       first_mfma = true;
     } else if (L0.pad == 0 && L0.window <= H && L0.window <= W) {
@@ -291,13 +294,13 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
           pack_cursor += (size_t)round32(L.units) * op.Kp;
         }
       } else if (cur != 0 && L.stride == 1 && C % chunk == 0 && L.units % chunk == 0) {
-        op.mfma = true;
         op.vc = VConv{C, L.window, L.units, 1, C, L.window};
         op.gf = IGemm{0, 0, N * op.cs.OH * op.cs.OW, L.units, H, W, C, op.cs.OH, op.cs.OW, L.window, L.pad,
                       L.window * L.window * C / chunk, C / chunk, 0};
         op.gd = IGemm{0, 0, N * H * W, C, op.cs.OH, op.cs.OW, L.units, H, W, L.window, L.window - 1 - L.pad,
                       L.window * L.window * L.units / chunk, L.units / chunk, 0};
-        if (net->bf16) {
+        op.mfma = igemm_divides(op.gf) && igemm_divides(op.gd);
+        if (net->bf16 && op.mfma) {
           op.Kp = round32(L.window * L.window * C);
           op.Kpt = round32(L.window * L.window * L.units);
           op.pack_fwd = (int64_t)pack_cursor;
@@ -338,16 +341,16 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
       if (cur != 0 && in % chunk == 0 && L.units % chunk == 0 && (!net->bf16 || op.w_off % 8 == 0)) {
         // fully connected: the flat weight matrix [out][in] is the B operand as it lies (forward), and is read
         // transposed for the input gradient; no packed copy
-        op.mfma = true;
         op.dgrad_bt = true;
         op.vc = VConv{in, 1, L.units, 1, in, 1};
         op.gf = IGemm{0, op.w_off, N, L.units, 1, 1, in, 1, 1, 1, 0, in / chunk, in / chunk, in};
         op.gd = IGemm{0, op.w_off, N, in, 1, 1, L.units, 1, 1, 1, 0, L.units / chunk, L.units / chunk, in};
-        op.grouped = net->bf16 && fc_group_layer_ok(N, in, L.units);
+        op.mfma = igemm_divides(op.gf) && igemm_divides(op.gd);
+        op.grouped = op.mfma && net->bf16 && fc_group_layer_ok(N, in, L.units);
         // rank-N weight gradient kept as factors: worth it while the N FMAs per weight and pending gradient stay far
         // below what the update's streaming rate leaves room for
         const int c_upd = cfg.lambda / cfg.n;
-        if (net->bf16 && !(cfg.flags & SASGD_FLAG_FLAT_FC_GRADIENT) && N <= 32 && (int64_t)c_upd * N <= 1024 && op.w_off % 4 == 0 &&
+        if (op.mfma && net->bf16 && !(cfg.flags & SASGD_FLAG_FLAT_FC_GRADIENT) && N <= 32 && (int64_t)c_upd * N <= 1024 && op.w_off % 4 == 0 &&
             L.units % 4 == 0 && in % 8 == 0 && n_factored < kMaxFactoredLayers) {
           op.factored = true;
           op.NP = (N + 7) & ~7;
