@@ -34,12 +34,12 @@ HBM_PEAK_GBS = 8000.0
 # FETCH_SIZE / WRITE_SIZE runs of this script scaled by a plain 240 MB copy in the same run (summary:
 # profiles/apply_update_config1.txt); the line says so in "traffic_source".
 TRAFFIC_C1 = 1.2000e9
-TRAFFIC_C54 = 14.402e9      # the two-pass form writes and re-reads its sums: + 2 x 240 MB
+TRAFFIC_C54 = 14.401e9      # the two-pass form writes and re-reads its sums: + 2 x 240 MB
 TRAFFIC_SOURCE = "rocprofv3 --pmc FETCH_SIZE/WRITE_SIZE, profiles/apply_update_config1.txt (not measured by this run)"
 # Counted / algorithmic HBM bytes of an update pass of BASELINE config 4 (fused steps, factored fully connected layers),
 # from the same two counters over `--workload alex` (summary: profiles/apply_update_config4_fused.txt).
-TRAFFIC_RATIO_CFG4 = 1.011
-TRAFFIC_SOURCE_CFG4 = ("bytes_per_launch x 1.011 = counted / algorithmic bytes of rocprofv3 --pmc FETCH_SIZE/WRITE_SIZE runs, "
+TRAFFIC_RATIO_CFG4 = 1.014
+TRAFFIC_SOURCE_CFG4 = ("bytes_per_launch x 1.014 = counted / algorithmic bytes of rocprofv3 --pmc FETCH_SIZE/WRITE_SIZE runs, "
                        "profiles/apply_update_config4_fused.txt (not measured by this run)")
 PREWARM_CFG4 = 36           # updates that fill the ring of BASELINE config 4 before anything is timed
 
