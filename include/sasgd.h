@@ -15,8 +15,8 @@
  *  - All device work is enqueued on the hipStream_t given at creation (passed as void*).
  *    Calls return without waiting for the device, except the copy* getters, which block.
  *  - The context owns the weight ring, momentum, per-learner gradient buffers and
- *    workspaces (and, when floor(lambda / n) >= 25, an 8 MiB buffer of partial sums for the
- *    update of long windows); all are allocated in sasgd_create and freed in sasgd_destroy; no other
+ *    workspaces (and, where floor(lambda / n) gradients take the two-launch form of applyUpdateNoAlloc's
+ *    description, its 8 MiB of partial sums); all are allocated in sasgd_create and freed in sasgd_destroy; no other
  *    call allocates device memory.  The caller owns mini-batch buffers and externally
  *    pushed gradients and keeps them alive until the work that reads them has completed
  *    on the stream.
@@ -174,9 +174,9 @@ int sasgd_flush(sasgd_ctx* ctx);
  * sumGradients + applyUpdate on caller-owned vectors, without a context:
  *     coef_l = alpha(tau_l) / c   (lr_mode, alpha0 and the staleness tau_l = staleness[l] as in sumGradients)
  *     v <- momentum v + sum_l coef_l g_l + (sum_l coef_l) weight_decay theta_in;   theta_out = theta_in - v
- * run by the kernels of sasgd_applyUpdate: same arithmetic, same order, bit-identical results.  Windows of 25 and
- * more gradients over at least 2 Mi parameters take the two-launch form, whose 8 MiB of partial sums live in an array
- * compiled into the library (one copy per GPU, held until the process ends) instead of in a context's allocation.
+ * run by the kernels of sasgd_applyUpdate: same arithmetic, same order, bit-identical results.  Long windows over
+ * long vectors (45 gradients and 4 Mi parameters; 36 gradients beyond 32 Mi parameters) take a two-launch form, whose 8 MiB
+ * of partial sums live in an array compiled into the library (one copy per GPU, held until the process ends) instead of in a context's allocation.
  *   theta_in_dev, theta_out_dev, v_dev: device float32 [num_params], 16-byte aligned; theta_out may be theta_in.
  *   shadow_out_dev: optional device bf16 [num_params] (8-byte aligned) receiving theta_out rounded to nearest even.
  *   grads_dev: HOST array of c device pointers (float32 [num_params] each, 16-byte aligned); staleness: HOST int32 [c].
