@@ -19,12 +19,13 @@ ODD_CONV = {"name": "odd_conv", "input": (3, 20, 20), "classes": 10,
 
 
 class Run:
-    def __init__(self, net, compute, lam, mu, n, seed):
+    def __init__(self, net, compute, lam, mu, n, seed, flags=0):
         from paper_1511_05950_amd import binding
         self.net, self.compute, self.lam, self.mu = net, compute, lam, mu
         self.theta, self.X, self.Y = draw_case(net, lam, mu, seed, 0.1)
         self.Xd, self.Yd = torch.from_numpy(self.X).cuda(), torch.from_numpy(self.Y).cuda()
-        self.ctx = binding.Sasgd(lam, mu, n, 4, net=net, compute=compute, alpha0=0.01, momentum=0.9, weight_decay=1e-3, init_weights=self.theta)
+        self.ctx = binding.Sasgd(lam, mu, n, 4, net=net, compute=compute, alpha0=0.01, momentum=0.9, weight_decay=1e-3, init_weights=self.theta,
+                                 flags=flags)
         self.loss = torch.zeros(lam, device="cuda")
 
     def calc(self, learners):
@@ -84,6 +85,26 @@ def test_window_of_both_kinds():
     th, v = protocol.server_update(th, v, late, (0, 0), 0.01, 0.9, 1e-3)
     assert rel(r.ctx.copyWeights() - r.theta, th - r.theta) < 1e-4 and rel(r.ctx.copyMomentum(), v) < 1e-5
     r.ctx.destroy()
+
+
+def test_one_pass_over_both_kinds_has_the_bits_of_separate_launches():
+    """Windows of factors, of both kinds and of written-out gradients (which take another kernel when they are alone)."""
+    from paper_1511_05950_amd import binding
+    out = []
+    for flags in (0, binding.FLAG_EAGER_UPDATES):
+        r = Run(ODD_HIDDEN, "bf16", 8, 32, 4, seed=9, flags=flags)
+        r.calc(list(range(8)))
+        for k in (1, 4, 5):
+            r.calc([k])
+        for window in ((0, 1), (2, 3), (4, 5), (6, 7)):
+            for k in window:
+                r.ctx.pushGradient(k)
+            r.ctx.sumGradients()
+            r.ctx.applyUpdate()
+        out.append((r.ctx.copyWeights(), r.ctx.copyMomentum(), r.ctx.copyWeights(2)))
+        r.ctx.destroy()
+    for a, b in zip(*out):
+        assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
 
 
 DEEP = {"name": "deep", "input": (8, 3, 3), "classes": 10, "layers": [("conv", 512, 3, 1, 1)] * 9 + [("fc", 10)]}
