@@ -1688,7 +1688,8 @@ __global__ __launch_bounds__(256) void igemm_wgrad_kernel(PtrTab ws, PtrTab grad
 // compiler know that an LDS read of one does not wait for the loads into another.
 // What bounds it: the transposing LDS reads (32 KiB a step at 82 B/clk per compute unit) and the arriving tiles.  AlexNet-shaped
 // net, 288 images, average of its five layers: 147 us against 173 us with staging registers and two buffers.  128 x 256 tiles
-// (64 x 128 per wavefront) read a quarter less but leave two wavefronts a SIMD and too few tiles: 152 us.
+// (64 x 128 per wavefront) read a quarter less but leave two wavefronts a SIMD and too few tiles: 152 us.  Where there is enough
+// work for a round of its larger tiles, wgrad_wide_kernel below is the faster one (wgrad_tiles).
 template <bool INCR>
 __global__ __launch_bounds__(256, 3) void wgrad_panel_kernel(PtrTab ws, PtrTab grads, IGemm g, VConv v, size_t dy_off, int64_t w_off,
                                                              int64_t b_off, int partial) {
@@ -1831,6 +1832,187 @@ __global__ __launch_bounds__(256, 3) void wgrad_panel_kernel(PtrTab ws, PtrTab g
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no load is left on its way to this workgroup's LDS
   wgrad_write<TM, TN>(acc, ws, grads, g, v, w_off, b_off, partial, z, sp, n0 + wm0, k0 + wn0, lane);
 }
+// All but the youngest N loads of this wavefront have landed, its LDS reads are done, and so for every wavefront.
+template <int N>
+__device__ __forceinline__ void landed_and_read() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+}
+
+// Large products: tiles of 32 TM WM output channels x 128 (4 / WM) im2col columns, one wavefront a SIMD with 32 TM x 128 of them
+// in its accumulators.  What bounds wgrad_panel_kernel is the rate at which a compute unit issues transposing LDS reads (6.2 cycles
+// each, four a product of 64 x 64 wavefront tiles' 32 cycles): a 128 x 128 wavefront tile needs half as many for the same
+// products.  With one wavefront a SIMD nothing else covers a latency, so every read is issued a k-block ahead, between the
+// products of the one before, and four stages are in LDS, two of them on their way.  Panels, addresses and the bias column are
+// wgrad_panel_kernel's.  AlexNet-shaped net, 256 images of one learner, its five layers from the input on: 159 / 229 / 99 / 122 / 100 us
+// there, 90 / 182 / 76 / 105 / 72 us here (1.26 PFLOP/s in the second).
+template <int TM, int WM>
+__global__ __launch_bounds__(256, 1) void wgrad_wide_kernel(PtrTab ws, PtrTab grads, IGemm g, VConv v, size_t dy_off, int64_t w_off, int64_t b_off) {
+  constexpr int TN = 4, BMG = 32 * TM * WM, BNG = 128 * (4 / WM);
+  constexpr int PA = BMG / 32, PB = BNG / 32, PANEL = BK * 32;
+  constexpr int LA = (PA * 2 + 3) / 4, LB = PB * 2 / 4;    // half panels a wavefront loads per stage (dy: the last one perhaps none)
+  static_assert(LB % 2 == 0 && (PA * 2 % 4 == 0 || PA * 2 == LA * 3), "shares");
+  __shared__ __attribute__((aligned(16))) bf16_t buf0[(PA + PB) * PANEL], buf1[(PA + PB) * PANEL], buf2[(PA + PB) * PANEL], buf3[(PA + PB) * PANEL];
+
+  const TileIdx tile = xcd_tile(1);
+  const int z = tile.z / g.splits, sp = tile.z % g.splits;
+  const bf16_t* x = (const bf16_t*)ws.p[z] + g.a_off;
+  const bf16_t* dy = (const bf16_t*)ws.p[z] + dy_off;
+  const int n0 = tile.x * BMG, k0 = tile.y * BNG;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = (wave % WM) * (32 * TM), wn0 = (wave / WM) * 128;
+
+  const int all_steps = (g.M + BK - 1) / BK;
+  const int per = (all_steps + g.splits - 1) / g.splits;
+  const int ms_begin = __builtin_amdgcn_readfirstlane(sp * per);
+  const int ms_end = __builtin_amdgcn_readfirstlane(min(all_steps, ms_begin + per));
+  const int m_end = min(g.M, ms_end * BK);
+
+  const int one_off = (int)((g.zero_off + 128 - g.a_off) * 2);
+  const bool has_bias = g.Kchunks * 8 >= k0 && g.Kchunks * 8 < k0 + BNG;
+  const __amdgpu_buffer_rsrc_t rsrc_dy = __builtin_amdgcn_make_buffer_rsrc((void*)dy, 0, (int)((int64_t)m_end * g.Ncols * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc((void*)x, 0, has_bias ? one_off + 16 : (int)g.a_bytes, 0x00020000);
+  const int row = lane >> 2, ch = lane & 3;
+  // dy: half panel a = LA * wave + l is panel a / 2, rows 16 (a % 2) .. + 15
+  int a_off[LA];
+  const int a_step = BK * g.Ncols * 2;
+#pragma unroll
+  for (int l = 0; l < LA; l++) {
+    const int a = LA * wave + l, n = n0 + (a >> 1) * 32 + ch * 8;
+    a_off[l] = n < g.Ncols ? (int)((((int64_t)ms_begin * BK + 16 * (a & 1) + row) * g.Ncols + n) * 2) : (int)kOutOfRange;
+  }
+  // x: panels (LB / 2) * wave + p, both halves; a lane's chunk of a panel is one tap, 8 channels
+  int b_dkh[LB / 2], b_dkw[LB / 2], b_koff[LB / 2], b_else[LB / 2];
+#pragma unroll
+  for (int p = 0; p < LB / 2; p++) {
+    const int q = k0 / 8 + (LB / 2 * wave + p) * 4 + ch;
+    const uint32_t tap = fastdiv((uint32_t)q, g.CPT, g.mg_cpt);
+    const int c8 = q - (int)tap * g.CPT;
+    const int kh = (int)fastdiv(tap, g.ks, g.mg_ks), kw = (int)tap - kh * g.ks;
+    b_dkh[p] = q < g.Kchunks ? kh - g.pad : (int)kOutOfRange;      // a row that no input has
+    b_dkw[p] = kw - g.pad;
+    b_koff[p] = ((kh - g.pad) * g.W * g.C + (kw - g.pad) * g.C + c8 * 8) * 2;
+    b_else[p] = q == g.Kchunks ? one_off : (int)kOutOfRange;
+  }
+  int r_m[2], r_oh[2], r_ow[2], r_off[2];
+#pragma unroll
+  for (int h = 0; h < 2; h++) {
+    r_m[h] = ms_begin * BK + 16 * h + row;
+    const uint32_t mm = r_m[h] < g.M ? (uint32_t)r_m[h] : 0u;
+    const uint32_t rest = fastdiv(mm, g.OW, g.mg_ow);
+    const uint32_t n = fastdiv(rest, g.OH, g.mg_oh);
+    r_ow[h] = (int)(mm - rest * (uint32_t)g.OW);
+    r_oh[h] = (int)(rest - n * (uint32_t)g.OH);
+    r_off[h] = (int)(((n * (uint32_t)g.H + (uint32_t)r_oh[h]) * (uint32_t)g.W + (uint32_t)r_ow[h]) * (uint32_t)g.C * 2u);
+  }
+  const int d_ow = BK / g.OW, m_ow = BK - d_ow * g.OW;
+  const int inc0 = (d_ow * g.W + m_ow) * g.C * 2;
+  const int inc_w = (g.W - g.OW) * g.C * 2;
+  const int inc_h = (g.H - g.OH) * g.W * g.C * 2;
+
+  auto issue = [&](bf16_t* S) {
+    if (PA * 2 % 4 == 0 || wave < 3)
+#pragma unroll
+    for (int l = 0; l < LA; l++) {
+      const int off = a_off[l];
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_dy, (__attribute__((address_space(3))) void*)(S + (LA * wave + l) * (PANEL / 2)), 16, off, 0, 0, 0);
+      a_off[l] += a_step;
+    }
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      const bool in = r_m[h] < m_end;
+#pragma unroll
+      for (int p = 0; p < LB / 2; p++) {
+        const bool ok = in & ((unsigned)(r_oh[h] + b_dkh[p]) < (unsigned)g.H) & ((unsigned)(r_ow[h] + b_dkw[p]) < (unsigned)g.W);
+        const int off = ok ? r_off[h] + b_koff[p] : b_else[p];
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_x, (__attribute__((address_space(3))) void*)(S + (PA + LB / 2 * wave + p) * PANEL + h * (PANEL / 2)), 16,
+                                                 off, 0, 0, 0);
+      }
+      r_m[h] += BK;
+      r_ow[h] += m_ow;
+      const bool c1 = r_ow[h] >= g.OW;
+      r_ow[h] -= c1 ? g.OW : 0;
+      r_oh[h] += d_ow + (c1 ? 1 : 0);
+      const bool c2 = r_oh[h] >= g.OH;
+      r_oh[h] -= c2 ? g.OH : 0;
+      r_off[h] += inc0 + (c1 ? inc_w : 0) + (c2 ? inc_h : 0);
+    }
+  };
+
+  floatx16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
+
+  const int j16 = lane & 15;
+  const int lane_off = (8 * (lane >> 5) + (j16 >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (j16 & 3);
+  const int pa_off = (wm0 / 32) * PANEL + lane_off, pb_off = (PA + wn0 / 32) * PANEL + lane_off;
+  auto read_frag = [&](const bf16_t* p) {
+    union { bf16x8 v; shortx4 h[2]; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((shortx4 __attribute__((address_space(3)))*)(p));
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((shortx4 __attribute__((address_space(3)))*)(p + 4 * 32));
+    return u.v;
+  };
+  auto read = [&](bf16x8 (&a)[TM], bf16x8 (&b)[TN], const bf16_t* S, int kk) {
+#pragma unroll
+    for (int i = 0; i < TM; i++) a[i] = read_frag(S + pa_off + i * PANEL + kk * 16 * 32);
+#pragma unroll
+    for (int j = 0; j < TN; j++) b[j] = read_frag(S + pb_off + j * PANEL + kk * 16 * 32);
+  };
+  auto multiply = [&](const bf16x8 (&a)[TM], const bf16x8 (&b)[TN]) {
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+  };
+  // Step s on stage buffer `cur`: the second k-block is read while the first one's products run.  Then the next stage has landed
+  // (one more is on its way), every wavefront's reads of `cur` are done, and the stage after those is requested into the buffer
+  // that was left a step ago; the next stage's first k-block is read while the second one's products run.
+  bf16x8 a0[TM], b0[TN], a1[TM], b1[TN];
+  auto step = [&](bf16_t* cur, bf16_t* next, bf16_t* free_) {
+    read(a1, b1, cur, 1);
+    multiply(a0, b0);
+#pragma unroll
+    for (int k = 0; k < TM * TN; k++) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // a product ...
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);       // ... and a read behind it
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (PA * 2 % 4 == 0 || wave < 3) landed_and_read<LA + LB>();
+    else landed_and_read<LB>();
+    read(a0, b0, next, 0);
+    multiply(a1, b1);
+    issue(free_);
+#pragma unroll
+    for (int k = 0; k < TM * TN; k++) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);       // addresses of the loads
+      if (k & 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int steps = ms_end - ms_begin;
+  issue(buf0);
+  issue(buf1);
+  issue(buf2);
+  if (PA * 2 % 4 == 0 || wave < 3) landed_and_read<2 * (LA + LB)>();
+  else landed_and_read<2 * LB>();
+  read(a0, b0, buf0, 0);
+  // stages 0, 1, 2 are requested; step s requests stage s + 3
+#pragma unroll 1
+  for (int s = 0; s < steps; s += 4) {           // stages behind the last one are zeros
+    step(buf0, buf1, buf3);
+    step(buf1, buf2, buf0);
+    step(buf2, buf3, buf1);
+    step(buf3, buf0, buf2);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no load is left on its way to this workgroup's LDS
+  wgrad_write<TM, TN>(acc, ws, grads, g, v, w_off, b_off, 1, z, sp, n0 + wm0, k0 + wn0, lane);
+}
 // Row length of a second pass's sums in LDS, per tap: whole float4s and an odd number of them, so that the taps of a channel,
 // which the write to the flat gradient takes one after the other, lie in different banks.
 __host__ __device__ inline int wgrad_finish_ld(int cw) { return 4 * (((cw + 3) >> 2) | 1); }
@@ -1905,27 +2087,65 @@ __global__ __launch_bounds__(256) void wgrad_finish_kernel(PtrTab ws, PtrTab gra
     }
     return;
   }
-  if (blockIdx.y == 0 && threadIdx.x == 0) {     // bias gradient: the extra im2col column
-    float acc = 0.f;
-    for (int sp = 0; sp < g.splits; sp++) acc += part[sp * split_stride + kcols];
-    ((float*)grads.p[z] + b_off)[n] = acc;
-  }
-  // first layer seen through a space-to-depth input (a small filter), or a window too large for the sums in LDS: one thread
-  // per im2col column, blockIdx.y selects a run of 256 columns; the column's place in the flat filter is looked up and written on its own
-  const int k = blockIdx.y * 256 + threadIdx.x;
-  if (k >= kcols) return;
-  const int tap = k / g.C, cp = k - tap * g.C;
-  const int64_t dst = filter_src(v, 0, tap, cp);          // position inside one filter, or -1 for padding
-  if (dst < 0) return;
-  float acc = 0.f;
+  // first layer seen through a space-to-depth input (a small filter, hundreds of splits), or a window too large for the sums in
+  // LDS: a lane adds four im2col columns of every fourth split, the wavefronts' four sums are added through LDS, and each
+  // column's place in the flat filter is looked up and written on its own.  blockIdx.y selects a run of 256 columns.
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, k = blockIdx.y * 256 + 4 * lane;
+  __shared__ float4 sums[4][64];
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (k < ldk) {                                          // column kcols is the bias gradient, the row's rest padding
 #pragma unroll 8
-  for (int sp = 0; sp < g.splits; sp++) acc += part[sp * split_stride + k];
-  dw[dst] = acc;
+    for (int sp = wave; sp < g.splits; sp += 4) {
+      const float4 p = *reinterpret_cast<const float4*>(part + sp * split_stride + k);
+      acc.x += p.x; acc.y += p.y; acc.z += p.z; acc.w += p.w;
+    }
+  }
+  sums[wave][lane] = acc;
+  __syncthreads();
+  const int col = blockIdx.y * 256 + threadIdx.x;
+  const float* f = reinterpret_cast<const float*>(sums) + threadIdx.x;
+  const float total = ((f[0] + f[256]) + f[512]) + f[768];
+  if (col == kcols) ((float*)grads.p[z] + b_off)[n] = total;
+  if (col >= kcols) return;
+  const int tap = col / g.C, cp = col - tap * g.C;
+  const int64_t dst = filter_src(v, 0, tap, cp);          // position inside one filter, or -1 for padding
+  if (dst >= 0) dw[dst] = total;
 }
 
-hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm& g, const VConv& v, size_t dy_off, int64_t w_off,
-                              int64_t b_off, int count, hipStream_t s) {
-  if (g.C % 8 || g.Ncols % 8 || g.splits < 1) return hipErrorInvalidValue;
+// Tiles and splits of a convolution's weight gradient with more than 64 output channels: the cheapest of the three tile shapes
+// of wgrad_wide_kernel and the 128 x 128 tiles of wgrad_panel_kernel, each at splits that fill one to six rounds of the chip,
+// by their times in us, fitted to the AlexNet-shaped layers at 16 to 288 images:
+//   wide: rounds of 256 workgroups x (14 + 0.58 .. 0.82 a step), nothing overlaps the start and end of a workgroup;
+//   panel: three workgroups share a compute unit and its LDS, 0.42 a step for one, 0.23 a step and workgroup for several.
+// Partial sums cost the second pass their reading.
+struct WgradTiles { int shape, splits; };
+static WgradTiles wgrad_tiles(const IGemm& g, int count, bool wide_ok, size_t scratch_bytes) {
+  static const struct { int rows, cols; double step; } kShape[4] = {{128, 128, 0}, {96, 512, 0.82}, {256, 256, 0.7}, {384, 128, 0.58}};
+  const int cols = g.Kchunks * 8 + 1, steps = (g.M + 31) / 32;
+  const size_t part = (size_t)g.Ncols * (g.Kchunks * 8 + 8) * 4;
+  const int most = (int)std::min<size_t>(std::max<size_t>(1, part ? scratch_bytes / part : 1), std::max(1, steps / 4));
+  WgradTiles best{0, 1};
+  double best_cost = 1e30;
+  for (int k = 0; k < (wide_ok ? 4 : 1); k++) {
+    const int64_t tiles = (int64_t)((g.Ncols + kShape[k].rows - 1) / kShape[k].rows) * ((cols + kShape[k].cols - 1) / kShape[k].cols) * count;
+    for (int round = 0; round <= 6; round++) {
+      int sp = (int)std::min<int64_t>(most, round ? round * 256 / tiles : 1);
+      if (sp < 1) continue;
+      const int each = (steps + sp - 1) / sp;
+      sp = (steps + each - 1) / each;                  // no workgroup without a step
+      const double n = each, units = (double)((tiles * sp + 255) / 256);
+      const double cost = (k ? units * (14 + n * kShape[k].step) : 14 + n * (units > 1 ? 0.23 * units : 0.42)) +
+                          (double)sp * count * part / 4.5e6;
+      if (cost < best_cost) { best_cost = cost; best = WgradTiles{k, sp}; }
+    }
+  }
+  return best;
+}
+
+hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm& g_in, const VConv& v, size_t dy_off, int64_t w_off,
+                              int64_t b_off, size_t scratch_bytes, int count, hipStream_t s) {
+  IGemm g = g_in;
+  if (g.C % 8 || g.Ncols % 8) return hipErrorInvalidValue;
   const int cols = g.Kchunks * 8 + 1;          // im2col columns plus the bias column
   const bool incr = BK / g.OW + 1 <= g.OH;      // one wrap of oh per step at most
   // A convolution's tile holds one tap of many channels, the flat gradient wants all taps of one channel together:
@@ -1933,22 +2153,45 @@ hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm
   // workgroups as the window has taps (measured: 65-125 us per AlexNet layer at 18 learners).  So convolutions
   // always go through the partial buffer and the second pass, which reads and writes whole lines (28-51 us).
   const bool conv = v.ks > 1 || v.s2d > 1;
+  // the constant block has to lie within a 31-bit byte offset from the layer's input
+  const bool near = g.zero_off >= g.a_off && (g.zero_off - g.a_off + 256) * 2 < ((size_t)1 << 31);
+  int shape = 0;
+  if (conv && g.Ncols > 64 && near) {
+    const WgradTiles t = wgrad_tiles(g, count, incr, scratch_bytes);
+    shape = t.shape;
+    g.splits = t.splits;
+  } else {
+    // narrow layers run small tiles (24-32 KiB of LDS, few registers): six and more workgroups fit a compute
+    // unit and each one alone is latency-bound, so they want more of them
+    // (CIFAR-shaped layers, 18 learners x 128 images: 1200 workgroups against 600 take conv1 from 148 to 97 us and
+    // conv2 from 112 to 80 us; 900 and 1500 are slower again)
+    const int64_t tiles = (int64_t)((g.Ncols + 127) / 128) * ((cols + 127) / 128);
+    g.splits = choose_splits(tiles, count, (g.M + 31) / 32, (size_t)g.Ncols * (g.Kchunks * 8 + 8) * 4, scratch_bytes, g.Ncols <= 64 ? 1200 : 600);
+  }
   const int partial = (g.splits > 1 || conv) ? 1 : 0;
 #define SASGD_WGRAD(BMG, BNG, WMG, WNG)                                                                                          \
   do {                                                                                                                           \
     if (incr) hipLaunchKernelGGL((igemm_wgrad_kernel<BMG, BNG, WMG, WNG, true>), grid, dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off, partial); \
     else hipLaunchKernelGGL((igemm_wgrad_kernel<BMG, BNG, WMG, WNG, false>), grid, dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off, partial);    \
   } while (0)
+  auto grid_of = [&](int rows, int columns) {
+    return dim3((unsigned)((g.Ncols + rows - 1) / rows), (unsigned)((cols + columns - 1) / columns), (unsigned)(count * g.splits));
+  };
   if (g.Ncols <= 32) {
-    dim3 grid(1, (unsigned)((cols + 127) / 128), (unsigned)(count * g.splits));
+    const dim3 grid = grid_of(32, 128);
     SASGD_WGRAD(32, 128, 32, 32);
   } else if (g.Ncols <= 64) {
-    dim3 grid(1, (unsigned)((cols + 127) / 128), (unsigned)(count * g.splits));
+    const dim3 grid = grid_of(64, 128);
     SASGD_WGRAD(64, 128, 32, 64);
+  } else if (shape == 1) {
+    hipLaunchKernelGGL((wgrad_wide_kernel<3, 1>), grid_of(96, 512), dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off);
+  } else if (shape == 2) {
+    hipLaunchKernelGGL((wgrad_wide_kernel<4, 2>), grid_of(256, 256), dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off);
+  } else if (shape == 3) {
+    hipLaunchKernelGGL((wgrad_wide_kernel<3, 4>), grid_of(384, 128), dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off);
   } else {
-    dim3 grid((unsigned)((g.Ncols + 127) / 128), (unsigned)((cols + 127) / 128), (unsigned)(count * g.splits));
-    // the constant block has to lie within a 31-bit byte offset from the layer's input
-    if (g.zero_off >= g.a_off && (g.zero_off - g.a_off + 256) * 2 < ((size_t)1 << 31)) {
+    const dim3 grid = grid_of(128, 128);
+    if (near) {
       if (incr) hipLaunchKernelGGL((wgrad_panel_kernel<true>), grid, dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off, partial);
       else hipLaunchKernelGGL((wgrad_panel_kernel<false>), grid, dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off, partial);
     } else {
@@ -1958,7 +2201,7 @@ hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm
 #undef SASGD_WGRAD
   if (partial) {
     // enough workgroups to keep the chip busy: the channels of a filter are divided among several of them
-    int groups = (cols + 254) / 256, cgroup = 0;         // runs of 256 columns, no LDS
+    int groups = (cols + 255) / 256, cgroup = 0;         // runs of 256 columns
     size_t lds = 0;
     const int cap = (15360 / (v.ks * v.ks) - 4) & ~3;    // input channels whose sums fit 60 KiB of LDS
     if (v.s2d == 1 && cap >= 4) {

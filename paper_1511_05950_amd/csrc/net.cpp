@@ -946,17 +946,8 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
           if (need_dx) TRY(fc_dgrad(op, tin, dy, dx));
         } else if (op.mfma) {
           IGemm gw = op.gf;
-          {
-            const int64_t tiles = (int64_t)((gw.Ncols + 127) / 128) * ((gw.Kchunks * 8 + 1 + 127) / 128);
-            gw.scratch_off = net->scratch_off;
-            // narrow layers run small tiles (24-32 KiB of LDS, few registers): six and more workgroups fit a compute
-            // unit and each one alone is latency-bound, so they want more of them
-            // (CIFAR-shaped layers, 18 learners x 128 images: 1200 workgroups against 600 take conv1 from 148 to 97 us and
-            // conv2 from 112 to 80 us; 900 and 1500 are slower again)
-            const int64_t target = gw.Ncols <= 64 ? 1200 : 600;
-            gw.splits = choose_splits(tiles, count, (gw.M + 31) / 32, (size_t)gw.Ncols * (gw.Kchunks * 8 + 8) * 4, net->scratch_bytes, target);
-          }
-          TRY(launch_igemm_wgrad(ws, grads, gw, op.vc, dy, op.w_off, op.b_off, count, stream));
+          gw.scratch_off = net->scratch_off;
+          TRY(launch_igemm_wgrad(ws, grads, gw, op.vc, dy, op.w_off, op.b_off, net->scratch_bytes, count, stream));
           if (need_dx && op.is_fc) {
             TRY(fc_dgrad(op, tin, dy, dx));
           } else if (need_dx) {

@@ -24,6 +24,13 @@ CASES = {
     "wide_rows": (net(3, 9, 41, ("conv", 72, 3, 1, 1), ("conv", 96, 3, 1, 0), ("avgpool", 3, 2)), 2, 2),
     "stride_2": (net(3, 29, 27, ("conv", 80, 7, 2, 0), ("conv", 72, 3, 1, 0), ("avgpool", 3, 2)), 2, 2),
     "many_learners": (net(3, 8, 8, ("conv", 128, 3, 1, 1), ("conv", 256, 3, 1, 1), ("avgpool", 3, 2)), 4, 12),
+    # the wide tiles (96 x 512, 256 x 256, 384 x 128), full and partly filled: many learners make them the cheapest at a few steps each
+    "wide_96": (net(3, 9, 9, ("conv", 224, 3, 1, 1), ("conv", 96, 3, 1, 1), ("avgpool", 3, 2)), 2, 64),
+    "wide_88": (net(3, 7, 7, ("conv", 224, 3, 1, 1), ("conv", 88, 3, 1, 1), ("avgpool", 3, 2)), 3, 64),
+    "wide_256": (net(3, 9, 9, ("conv", 112, 3, 1, 1), ("conv", 256, 3, 1, 1), ("avgpool", 3, 2)), 2, 64),
+    "wide_200": (net(3, 9, 7, ("conv", 112, 3, 1, 1), ("conv", 200, 3, 1, 1), ("avgpool", 3, 2)), 2, 64),
+    "wide_384": (net(3, 9, 9, ("conv", 56, 3, 1, 1), ("conv", 384, 3, 1, 1), ("avgpool", 3, 2)), 2, 64),
+    "wide_360_one_step": (net(3, 5, 5, ("conv", 56, 3, 1, 1), ("conv", 360, 3, 1, 1), ("avgpool", 3, 2)), 1, 64),
     # up to 64 output channels
     "narrow_one_step": (net(3, 5, 5, ("conv", 8, 3, 1, 0), ("conv", 64, 2, 1, 0)), 1, 1),
     "narrow_ragged": (net(3, 12, 11, ("conv", 32, 3, 1, 1), ("conv", 64, 5, 1, 2), ("avgpool", 3, 2), ("conv", 24, 3, 1, 1)), 5, 3),
