@@ -1378,15 +1378,21 @@ hipError_t launch_igemm_frag(const PtrTab& ws, const CPtrTab& wts, const IGemm& 
     if (launch_halo_t<128, 64, 64, 32>(ws, wts, g, ep, count, own, s)) return hipGetLastError();
   }
   if (g.Ncols > 64) {
-    // (measured slower for the 128-wide layers: 128 x 64 wave tiles in blocks of two wavefronts, and 256 x 128 blocks)
-    // Learners on one weight version share their filter fragments in every L2 and 128-row tiles spread over all XCDs
-    // are fastest (conv3 forward, 18 learners: 89 us; 101 us with the XCD-contiguous order, 105 us with 256 rows).  With
-    // a version per learner the fragments are the larger part of a workgroup's traffic: 256-row tiles read them half as
-    // often and the XCD-contiguous order keeps a learner's tiles on one L2 (101 us against 120 us).  Also measured
-    // slower in both cases: 128 x 64 wave tiles in two-wavefront blocks, eight-wavefront 256 x 128 blocks, 256 x 256.
+    // Layers of whole 256-column tiles: 128 x 256, every filter fragment serves four products.  Others take 128-row tiles, three
+    // workgroups on a compute unit, or 256-row ones, two, which read the fragments half as often: whichever fills its places
+    // better (halo_time, in us of a step of 32 channels of one tap).  3 x 3 over 384 channels, 384 columns, 256 images of one
+    // learner: 1 014 tiles in 122 us against 507, a whole round, in 98; twelve learners of 16 on one version: 792 tiles in 114 us
+    // against 396 in 89; 18 of them, 1 188 and 594 tiles: 135 and 138.  With a version per learner the fragments are the larger
+    // part of a workgroup's traffic (18 learners: 120 us against 101).  Also measured slower: 128 x 64 wave tiles in two-wavefront blocks, eight-wavefront 256 x 128 blocks, 256 x 256.
+    const auto halo_time = [&](int rows, int places, double full, double two, double one) {
+      const int64_t tiles = (int64_t)((g.M + rows - 1) / rows) * ((g.Ncols + 127) / 128) * count, each = (tiles + 255) / 256;
+      const int left = (int)(each % places);
+      return (double)(each / places) * full + (left == 2 ? two : left == 1 ? one : 0.);
+    };
+    const bool tall = g.Ncols > 128 && halo_time(256, 2, 0.90, 0., 0.47) < (own ? 1.18 : 1.) * halo_time(128, 3, 0.72, 0.58, 0.45);
     const bool done = g.Ncols % 256 == 0 ? launch_halo_t<128, 256, 128, 64>(ws, wts, g, ep, count, own, s)
-                      : own && g.Ncols > 128 ? launch_halo_t<256, 128, 128, 64>(ws, wts, g, ep, count, own, s)
-                                             : launch_halo_t<128, 128, 64, 64>(ws, wts, g, ep, count, own, s);
+                      : tall             ? launch_halo_t<256, 128, 128, 64>(ws, wts, g, ep, count, own, s)
+                                         : launch_halo_t<128, 128, 64, 64>(ws, wts, g, ep, count, own, s);
     if (done) return hipGetLastError();
   }
   // Wave tile 128 x 64 (two wavefronts per SIMD, accumulators in ordinary registers) wins where the columns fill
