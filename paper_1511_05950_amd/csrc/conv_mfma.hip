@@ -2019,6 +2019,202 @@ __global__ __launch_bounds__(256, 1) void wgrad_wide_kernel(PtrTab ws, PtrTab gr
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no load is left on its way to this workgroup's LDS
   wgrad_write<TM, TN>(acc, ws, grads, g, v, w_off, b_off, 1, z, sp, n0 + wm0, k0 + wn0, lane);
 }
+// Up to 64 output channels.  Gathered tap by tap, a narrow tile's im2col columns pass the vector L1 once per tap and 128 columns,
+// which took longer than anything else (32 channels of 16 x 16 images, 5 x 5 over 32: 1.3 GB for 37 MB of input).  Here
+// the input patch under a tile of MT output positions is in LDS, all channels of a pixel, and the transposing reads pick every
+// tap's columns out of it: a lane's address is its position's place in the patch plus an offset that depends on its column only.
+// A workgroup of eight wavefronts holds 32 WN TN columns (the last place of the last group is the bias: a fragment of ones),
+// its 8 / WN position groups take a tile's 16-position steps in turn and are added through LDS at the end.  Patch, dy and the
+// positions' places are double-buffered: the next tile's are requested before this one is multiplied, one barrier a tile.
+// Bound by the transposing LDS reads.  CIFAR-shaped net, 18 learners x 128 images: its three layers 96 / 79 / 36 us gathered,
+// 51 / 45 / 31 here.
+struct StripArgs {
+  int PW;                    // patch width in pixels
+  int tiles, per;            // tiles of MT positions, and how many a workgroup takes
+  int patch, buf;            // bytes of a patch and of a whole buffer (dy, patch, places) in LDS
+  FastDiv by_pw, by_cpt, by_band;   // divisions by PW, by 8-channel chunks of a pixel and by OH + ks - 1 (rows of a whole image in the patch)
+};
+
+template <int TM, int WN, int TN, int MT>
+__global__ __launch_bounds__(512, 2) void wgrad_strip_kernel(PtrTab ws, IGemm g, size_t dy_off, StripArgs h) {
+  constexpr int WK = 8 / WN, NT = 512, DY = TM * MT * 64;
+  extern __shared__ __attribute__((aligned(16))) char strip_lds[];
+  char* lds = strip_lds;
+  const int z = blockIdx.z / g.splits, sp = blockIdx.z % g.splits, cg = blockIdx.y;
+  const bf16_t* x = (const bf16_t*)ws.p[z] + g.a_off;
+  const bf16_t* dy = (const bf16_t*)ws.p[z] + dy_off;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = wave % WN, wk = wave / WN;
+  const int ks = g.ks, PW = h.PW;
+  const int kcols = g.Kchunks * 8;
+  const int j16 = lane & 15;
+  // this lane's columns of each block: the offset of their tap and channels in the patch
+  int off[TN];
+#pragma unroll
+  for (int p = 0; p < TN; p++) {
+    const int panel = (cg * WN + wn) * TN + p, col = panel * 32 + 16 * ((lane >> 4) & 1) + 4 * (j16 & 3);
+    const uint32_t tap = fastdiv((uint32_t)col >> 3, g.CPT, g.mg_cpt);
+    const int kh = (int)fastdiv(tap, ks, g.mg_ks), kw = (int)tap - kh * ks;
+    off[p] = col < kcols ? ((kh * PW + kw) * g.C + col - (int)tap * g.C) * 2 : 0;
+  }
+  const bool last_group = cg == (int)gridDim.y - 1, bias = last_group && wn == WN - 1;   // (its block TN - 1)
+  bf16x8 ones;
+  {
+    union { bf16x8 v; bf16_t e[8]; } u;
+#pragma unroll
+    for (int e = 0; e < 8; e++) u.e[e] = lane % 32 == 0 ? (bf16_t)0x3F80 : (bf16_t)0;
+    ones = u.v;
+  }
+
+  v4i_t rsrc_dy, rsrc_x;
+  rsrc_dy.x = __builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)dy);
+  rsrc_dy.y = __builtin_amdgcn_readfirstlane((int)((uintptr_t)dy >> 32) & 0xffff);
+  rsrc_dy.z = (int)((int64_t)g.M * g.Ncols * 2);
+  rsrc_dy.w = 0x00020000;
+  rsrc_x.x = __builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)x);
+  rsrc_x.y = __builtin_amdgcn_readfirstlane((int)((uintptr_t)x >> 32) & 0xffff);
+  rsrc_x.z = (int)g.a_bytes;
+  rsrc_x.w = 0x00020000;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  // Written out because the compiler, which cannot tell the buffers apart, would wait for all of them in front of every LDS read.
+  auto dma = [&](const v4i_t& rsrc, uint32_t dst, int voff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds0 + dst), "v"(voff), "s"(rsrc) : "memory");
+  };
+  auto request = [&](int t, int buf) {
+    const int m0 = t * MT, m_last = min(m0 + MT, g.M) - 1;
+#pragma unroll
+    for (int i = 0; i < TM * MT / 128; i++) {      // dy: [32-channel panel][position][64 bytes]
+      const int s = i * NT + tid, panel = s / (MT * 4), row = (s / 4) % MT, n = panel * 32 + (s & 3) * 8;
+      dma(rsrc_dy, (uint32_t)(buf + (i * NT + wave * 64) * 16), n < g.Ncols ? ((m0 + row) * g.Ncols + n) * 2 : (int)kOutOfRange);
+    }
+    // patch rows: the first image's output rows of the tile and their halo, then whole images
+    const int gr_lo = (int)fastdiv((uint32_t)m0, g.OW, g.mg_ow), gr_hi = (int)fastdiv((uint32_t)m_last, g.OW, g.mg_ow);
+    const int n_lo = (int)fastdiv((uint32_t)gr_lo, g.OH, g.mg_oh), n_hi = (int)fastdiv((uint32_t)gr_hi, g.OH, g.mg_oh);
+    const int oh_lo = gr_lo - n_lo * g.OH, first = min(g.OH - oh_lo, gr_hi - gr_lo + 1) + ks - 1;
+    const int n_slots = (gr_hi - gr_lo + 1 + (ks - 1) * (n_hi - n_lo + 1)) * PW * g.CPT;
+#pragma unroll 1
+    for (int s0 = wave * 64; s0 < n_slots; s0 += NT) {
+      const int s = s0 + lane, px = h.by_cpt(s), sub = s - px * g.CPT, pr = h.by_pw(px), pc = px - pr * PW;
+      const int q = pr - first, nb = q < 0 ? 0 : h.by_band(q);
+      const int n = q < 0 ? n_lo : n_lo + 1 + nb, ih = (q < 0 ? oh_lo + pr : q - nb * (g.OH + ks - 1)) - g.pad, iw = pc - g.pad;
+      const bool ok = s < n_slots && (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
+      dma(rsrc_x, (uint32_t)(buf + DY + s0 * 16), ok ? (((n * g.H + ih) * g.W + iw) * g.C + sub * 8) * 2 : (int)kOutOfRange);
+    }
+    // each position's place in the patch; positions behind M repeat the last one, their dy is zero
+    static_assert(MT <= NT, "a position a thread");
+    if (tid < MT) {
+      const uint32_t m = (uint32_t)min(m0 + tid, m_last);
+      const uint32_t gr = fastdiv(m, g.OW, g.mg_ow), ow = m - gr * (uint32_t)g.OW, n = fastdiv(gr, g.OH, g.mg_oh);
+      const int pr = ((int)gr - gr_lo) + (ks - 1) * ((int)n - n_lo);
+      reinterpret_cast<int*>(lds + buf + DY + h.patch)[tid] = (pr * PW + (int)ow) * g.C * 2;
+    }
+  };
+
+  floatx16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
+
+  auto read_tr = [&](const char* p0, const char* p1) {
+    union { bf16x8 v; shortx4 q[2]; } u;
+    u.q[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((shortx4 __attribute__((address_space(3)))*)(p0));
+    u.q[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((shortx4 __attribute__((address_space(3)))*)(p1));
+    return u.v;
+  };
+  const int row = 8 * (lane >> 5) + (j16 >> 2), dy_lane = row * 64 + 32 * ((lane >> 4) & 1) + 8 * (j16 & 3);
+  const int t_begin = sp * h.per, t_end = min(h.tiles, t_begin + h.per);
+  int buf = 0;
+  if (t_begin < t_end) request(t_begin, 0);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll 1
+  for (int t = t_begin; t < t_end; t++) {
+    if (t + 1 < t_end) request(t + 1, h.buf - buf);
+    const char* D = lds + buf;
+    const char* X = D + DY;
+    const int* place = reinterpret_cast<const int*>(X + h.patch);
+    // a step's operands are read between the products of the step before, its positions' places a step earlier still
+    bf16x8 a0[TM], b0[TN], a1[TM], b1[TN];
+    int at0[2], at1[2];
+    auto places = [&](int (&at)[2], int st) {
+      const int k = min(wk + WK * st, MT / 16 - 1);        // behind the last step: read, not used
+      at[0] = place[16 * k + row];
+      at[1] = place[16 * k + row + 4];
+    };
+    auto operands = [&](bf16x8 (&a)[TM], bf16x8 (&b)[TN], const int (&at)[2], int st) {
+      const int k = min(wk + WK * st, MT / 16 - 1);
+#pragma unroll
+      for (int i = 0; i < TM; i++) a[i] = read_tr(D + (i * MT + 16 * k) * 64 + dy_lane, D + (i * MT + 16 * k + 4) * 64 + dy_lane);
+#pragma unroll
+      for (int j = 0; j < TN; j++) b[j] = read_tr(X + at[0] + off[j], X + at[1] + off[j]);
+    };
+    auto multiply = [&](const bf16x8 (&a)[TM], const bf16x8 (&b)[TN]) {
+#pragma unroll
+      for (int j = 0; j < TN; j++) {
+        bf16x8 bj = b[j];
+        if (j == TN - 1 && bias) bj = ones;
+#pragma unroll
+        for (int i = 0; i < TM; i++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], bj, acc[i][j], 0, 0, 0);
+      }
+    };
+    auto interleave = [&]() {
+#pragma unroll
+      for (int q = 0; q < TM * TN; q++) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, TM == 1 ? 3 : 2, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int kSteps = MT / 16 / WK;
+    static_assert(kSteps % 2 == 0, "two steps a turn");
+    places(at0, 0);
+    places(at1, 1);
+    operands(a0, b0, at0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll 1
+    for (int st = 0; st < kSteps; st += 2) {
+      operands(a1, b1, at1, st + 1);
+      places(at0, st + 2);
+      multiply(a0, b0);
+      interleave();
+      operands(a0, b0, at0, st + 2);
+      places(at1, st + 3);
+      multiply(a1, b1);
+      interleave();
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the next tile is there, this one read
+    buf = h.buf - buf;
+  }
+
+  // the position groups' sums, block by block, in group order
+  const int ldk = kcols + 8;
+  float* part = reinterpret_cast<float*>((char*)ws.p[z] + g.scratch_off) + (int64_t)sp * g.Ncols * ldk;
+  float* red = reinterpret_cast<float*>(lds);                // [wavefront][1024]
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++) {
+#pragma unroll
+      for (int r = 0; r < 16; r++) red[wave * 1024 + r * 64 + lane] = acc[i][j][r];
+      __syncthreads();
+#pragma unroll
+      for (int e = tid; e < WN * 1024; e += NT) {
+        float v = red[e];
+#pragma unroll
+        for (int w = 1; w < WK; w++) v += red[w * WN * 1024 + e];
+        const int c = e / 1024, r = (e / 64) % 16, l = e % 64;
+        const int n = 32 * i + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
+        int kc = ((cg * WN + c) * TN + j) * 32 + (l & 31);
+        const bool last = last_group && c == WN - 1 && j == TN - 1;
+        if (last) kc = (l & 31) == 0 ? kcols : kcols + 1;
+        if (n < g.Ncols && (last ? kc == kcols : kc < kcols)) part[(int64_t)n * ldk + kc] = v;
+      }
+      __syncthreads();
+    }
+}
+
 // Row length of a second pass's sums in LDS, per tap: whole float4s and an odd number of them, so that the taps of a channel,
 // which the write to the flat gradient takes one after the other, lie in different banks.
 __host__ __device__ inline int wgrad_finish_ld(int cw) { return 4 * (((cw + 3) >> 2) | 1); }
@@ -2037,71 +2233,76 @@ __global__ __launch_bounds__(256) void wgrad_finish_kernel(PtrTab ws, PtrTab gra
   const float* part = reinterpret_cast<const float*>((const char*)ws.p[z] + g.scratch_off) + (int64_t)n * ldk;
   const int64_t split_stride = (int64_t)g.Ncols * ldk;
   float* dw = (float*)grads.p[z] + w_off + (int64_t)n * v.Creal * v.ksr * v.ksr;
-  if (cgroup > 0) {
-    // channels [c_lo, c_hi) of this filter, all taps: columns tap * C + c are read tap by tap (contiguous runs), the
-    // run [c_lo * T, c_hi * T) of the flat gradient is written in its own order.  The bias gradient, the extra im2col
-    // column, is one more read of the first group.
-    const int T = v.ks * v.ks;
-    const int c_lo = blockIdx.y * cgroup, c_hi = min(v.Creal, c_lo + cgroup), cw = c_hi - c_lo;
-    if (cw <= 0) return;
-    const int cw4 = (cw + 3) >> 2, ld = wgrad_finish_ld(cw);
-    const int units = T * cw4, all = units + (blockIdx.y == 0 ? 1 : 0);
-    for (int u0 = threadIdx.x; u0 < all; u0 += 2 * 256) {
-      const float* src[2];
-      int dst[2];
-      float4 acc[2];
+  // channels [c_lo, c_hi) of this filter, all taps: columns tap * C + c are read tap by tap (contiguous runs), the
+  // run [c_lo * T, c_hi * T) of the flat gradient is written in its own order.  The bias gradient, the extra im2col
+  // column, is one more read of the first group.
+  const int T = v.ks * v.ks;
+  const int c_lo = blockIdx.y * cgroup, c_hi = min(v.Creal, c_lo + cgroup), cw = c_hi - c_lo;
+  if (cw <= 0) return;
+  const int cw4 = (cw + 3) >> 2, ld = wgrad_finish_ld(cw);
+  const int units = T * cw4, all = units + (blockIdx.y == 0 ? 1 : 0);
+  for (int u0 = threadIdx.x; u0 < all; u0 += 2 * 256) {
+    const float* src[2];
+    int dst[2];
+    float4 acc[2];
 #pragma unroll
-      for (int q = 0; q < 2; q++) {
-        const int u = min(u0 + 256 * q, all - 1);
-        const int tap = u / cw4, cc = 4 * (u - tap * cw4);
-        dst[q] = u0 + 256 * q >= all ? -2 : u == units ? -1 : tap * ld + cc;
-        src[q] = part + (u == units ? kcols : tap * g.C + c_lo + cc);
-        acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-      for (int sp = 0; sp < g.splits; sp += 4) {
-        float4 p[4][2];
-#pragma unroll
-        for (int t = 0; t < 4; t++)
-#pragma unroll
-          for (int q = 0; q < 2; q++)
-            if (sp + t < g.splits) p[t][q] = *reinterpret_cast<const float4*>(src[q] + (sp + t) * split_stride);
-#pragma unroll
-        for (int t = 0; t < 4; t++)
-          if (sp + t < g.splits)
-#pragma unroll
-            for (int q = 0; q < 2; q++) {
-              acc[q].x += p[t][q].x;
-              acc[q].y += p[t][q].y;
-              acc[q].z += p[t][q].z;
-              acc[q].w += p[t][q].w;
-            }
-      }
-#pragma unroll
-      for (int q = 0; q < 2; q++) {
-        if (dst[q] >= 0) *reinterpret_cast<float4*>(row + dst[q]) = acc[q];
-        else if (dst[q] == -1) ((float*)grads.p[z] + b_off)[n] = acc[q].x;
-      }
+    for (int q = 0; q < 2; q++) {
+      const int u = min(u0 + 256 * q, all - 1);
+      const int tap = u / cw4, cc = 4 * (u - tap * cw4);
+      dst[q] = u0 + 256 * q >= all ? -2 : u == units ? -1 : tap * ld + cc;
+      src[q] = part + (u == units ? kcols : tap * g.C + c_lo + cc);
+      acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    __syncthreads();
-    int cc = threadIdx.x / T, tap = threadIdx.x - cc * T;
-    const int dc = 256 / T, dt = 256 - dc * T;
-    for (int j = threadIdx.x; j < T * cw; j += 256) {
-      dw[(int64_t)c_lo * T + j] = row[tap * ld + cc];
-      cc += dc;
-      tap += dt;
-      if (tap >= T) { tap -= T; cc++; }
+    for (int sp = 0; sp < g.splits; sp += 4) {
+      float4 p[4][2];
+#pragma unroll
+      for (int t = 0; t < 4; t++)
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+          if (sp + t < g.splits) p[t][q] = *reinterpret_cast<const float4*>(src[q] + (sp + t) * split_stride);
+#pragma unroll
+      for (int t = 0; t < 4; t++)
+        if (sp + t < g.splits)
+#pragma unroll
+          for (int q = 0; q < 2; q++) {
+            acc[q].x += p[t][q].x;
+            acc[q].y += p[t][q].y;
+            acc[q].z += p[t][q].z;
+            acc[q].w += p[t][q].w;
+          }
     }
-    return;
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      if (dst[q] >= 0) *reinterpret_cast<float4*>(row + dst[q]) = acc[q];
+      else if (dst[q] == -1) ((float*)grads.p[z] + b_off)[n] = acc[q].x;
+    }
   }
-  // first layer seen through a space-to-depth input (a small filter, hundreds of splits), or a window too large for the sums in
-  // LDS: a lane adds four im2col columns of every fourth split, the wavefronts' four sums are added through LDS, and each
-  // column's place in the flat filter is looked up and written on its own.  blockIdx.y selects a run of 256 columns.
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, k = blockIdx.y * 256 + 4 * lane;
-  __shared__ float4 sums[4][64];
+  __syncthreads();
+  int cc = threadIdx.x / T, tap = threadIdx.x - cc * T;
+  const int dc = 256 / T, dt = 256 - dc * T;
+  for (int j = threadIdx.x; j < T * cw; j += 256) {
+    dw[(int64_t)c_lo * T + j] = row[tap * ld + cc];
+    cc += dc;
+    tap += dt;
+    if (tap >= T) { tap -= T; cc++; }
+  }
+}
+
+// The same where there are many splits and few columns, for a first layer seen through a space-to-depth input, and for a window
+// too large for the sums in LDS: a lane adds four im2col columns of every sixteenth split, the sixteen wavefronts' sums are added
+// through LDS, and each column's place in the flat filter is looked up and written on its own.  blockIdx.y selects a run of 256
+// columns.  11 x 11 / 4 first layer of the AlexNet shape, 256 images, 254 splits: 8 us; a lane per column that adds all splits
+// one after the other took 80.
+__global__ __launch_bounds__(1024) void wgrad_columns_kernel(PtrTab ws, PtrTab grads, IGemm g, VConv v, int64_t w_off, int64_t b_off) {
+  __shared__ float4 sums[16][64];
+  const int z = blockIdx.z, n = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kcols = g.Kchunks * 8, ldk = kcols + 8, k = blockIdx.y * 256 + 4 * lane;
+  const float* part = reinterpret_cast<const float*>((const char*)ws.p[z] + g.scratch_off) + (int64_t)n * ldk;
+  const int64_t split_stride = (int64_t)g.Ncols * ldk;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   if (k < ldk) {                                          // column kcols is the bias gradient, the row's rest padding
 #pragma unroll 8
-    for (int sp = wave; sp < g.splits; sp += 4) {
+    for (int sp = wave; sp < g.splits; sp += 16) {
       const float4 p = *reinterpret_cast<const float4*>(part + sp * split_stride + k);
       acc.x += p.x; acc.y += p.y; acc.z += p.z; acc.w += p.w;
     }
@@ -2109,13 +2310,50 @@ __global__ __launch_bounds__(256) void wgrad_finish_kernel(PtrTab ws, PtrTab gra
   sums[wave][lane] = acc;
   __syncthreads();
   const int col = blockIdx.y * 256 + threadIdx.x;
+  if (threadIdx.x >= 256 || col > kcols) return;
   const float* f = reinterpret_cast<const float*>(sums) + threadIdx.x;
-  const float total = ((f[0] + f[256]) + f[512]) + f[768];
-  if (col == kcols) ((float*)grads.p[z] + b_off)[n] = total;
-  if (col >= kcols) return;
+  float total = f[0];
+#pragma unroll
+  for (int w = 1; w < 16; w++) total += f[w * 256];
+  if (col == kcols) {
+    ((float*)grads.p[z] + b_off)[n] = total;
+    return;
+  }
   const int tap = col / g.C, cp = col - tap * g.C;
   const int64_t dst = filter_src(v, 0, tap, cp);          // position inside one filter, or -1 for padding
-  if (dst >= 0) dw[dst] = total;
+  if (dst >= 0) ((float*)grads.p[z] + w_off + (int64_t)n * v.Creal * v.ksr * v.ksr)[dst] = total;
+}
+
+template <int TM, int WN, int TN, int MT>
+static bool launch_strip_t(const PtrTab& ws, const IGemm& g_in, size_t dy_off, size_t scratch_bytes, int count, int* splits, hipStream_t s) {
+  IGemm g = g_in;
+  StripArgs h;
+  h.PW = g.OW + g.ks - 1;
+  const int rows = (MT + g.OW - 2) / g.OW + 1;          // output rows a tile can touch
+  const int images = (rows + g.OH - 2) / g.OH + 1;           // and images those rows can belong to
+  const int64_t patch = ((int64_t)(rows + (g.ks - 1) * images) * h.PW * g.C * 2 + 1023) / 1024 * 1024;
+  if (patch > 64 * 1024) return false;
+  h.patch = (int)patch;
+  h.buf = TM * MT * 64 + h.patch + MT * 4;
+  const size_t bytes = std::max((size_t)2 * h.buf, (size_t)8 * 4096);
+  if (bytes > 160 * 1024) return false;
+  h.by_pw.set(h.PW);
+  h.by_cpt.set(g.CPT);
+  h.by_band.set(g.OH + g.ks - 1);
+  const int panels = (g.Kchunks * 8 + 31) / 32, groups = (panels + WN * TN) / (WN * TN);   // and the bias's place
+  // Below this the tiles a workgroup has to itself are too few to pay for its start and its sum over the position groups
+  // (CIFAR-shaped conv2, 64 images of one learner: 11 us with the gathering kernel, 14 here; 8 x 64 images: 25 and 19).
+  if ((int64_t)g.M * groups * count < 65536) return false;
+  h.tiles = (g.M + MT - 1) / MT;
+  // one workgroup a compute unit: whole rounds of 256 of them
+  const size_t part = (size_t)g.Ncols * (g.Kchunks * 8 + 8) * 4;
+  const int most = (int)std::min<int64_t>(h.tiles, std::max<int64_t>(1, (int64_t)(scratch_bytes / part)));
+  const int want = std::max(1, std::min(most, 256 / (groups * count)));
+  h.per = (h.tiles + want - 1) / want;
+  g.splits = (h.tiles + h.per - 1) / h.per;
+  *splits = g.splits;
+  hipLaunchKernelGGL((wgrad_strip_kernel<TM, WN, TN, MT>), dim3(1, (unsigned)groups, (unsigned)(count * g.splits)), dim3(512), bytes, s, ws, g, dy_off, h);
+  return true;
 }
 
 // Tiles and splits of a convolution's weight gradient with more than 64 output channels: the cheapest of the three tile shapes
@@ -2175,6 +2413,15 @@ hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm
     g.splits = choose_splits(tiles, count, (g.M + 31) / 32, (size_t)g.Ncols * (g.Kchunks * 8 + 8) * 4, scratch_bytes, g.Ncols <= 64 ? 1200 : 600);
   }
   const int partial = (g.splits > 1 || conv) ? 1 : 0;
+  bool done = false;
+  if (conv && g.Ncols <= 64 && g.OW + g.ks - 1 == g.W + 2 * g.pad) {
+    const int panels = (g.Kchunks * 8 + 31) / 32;
+    if (g.Ncols > 32) done = panels < 8 ? launch_strip_t<2, 2, 4, 256>(ws, g, dy_off, scratch_bytes, count, &g.splits, s)
+                                        : launch_strip_t<2, 4, 4, 256>(ws, g, dy_off, scratch_bytes, count, &g.splits, s);
+    else if (panels < 8) done = launch_strip_t<1, 1, 8, 512>(ws, g, dy_off, scratch_bytes, count, &g.splits, s);
+    else if (panels < 16) done = launch_strip_t<1, 2, 8, 256>(ws, g, dy_off, scratch_bytes, count, &g.splits, s);
+    else done = launch_strip_t<1, 4, 7, 256>(ws, g, dy_off, scratch_bytes, count, &g.splits, s);
+  }
 #define SASGD_WGRAD(BMG, BNG, WMG, WNG)                                                                                          \
   do {                                                                                                                           \
     if (incr) hipLaunchKernelGGL((igemm_wgrad_kernel<BMG, BNG, WMG, WNG, true>), grid, dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off, partial); \
@@ -2183,7 +2430,8 @@ hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm
   auto grid_of = [&](int rows, int columns) {
     return dim3((unsigned)((g.Ncols + rows - 1) / rows), (unsigned)((cols + columns - 1) / columns), (unsigned)(count * g.splits));
   };
-  if (g.Ncols <= 32) {
+  if (done) {
+  } else if (g.Ncols <= 32) {
     const dim3 grid = grid_of(32, 128);
     SASGD_WGRAD(32, 128, 32, 32);
   } else if (g.Ncols <= 64) {
@@ -2206,19 +2454,21 @@ hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm
   }
 #undef SASGD_WGRAD
   if (partial) {
-    // enough workgroups to keep the chip busy: the channels of a filter are divided among several of them
-    int groups = (cols + 255) / 256, cgroup = 0;         // runs of 256 columns
-    size_t lds = 0;
     const int cap = (15360 / (v.ks * v.ks) - 4) & ~3;    // input channels whose sums fit 60 KiB of LDS
-    if (v.s2d == 1 && cap >= 4) {
-      groups = (int)((1536 + (int64_t)g.Ncols * count - 1) / ((int64_t)g.Ncols * count));
-      if (groups > v.Creal / 8) groups = v.Creal / 8;
-      if (groups < 1) groups = 1;
-      cgroup = ((v.Creal + groups - 1) / groups + 3) & ~3;              // channels are read four at a time
-      if (cgroup > cap) cgroup = cap;
-      groups = (v.Creal + cgroup - 1) / cgroup;
-      lds = (size_t)wgrad_finish_ld(cgroup) * v.ks * v.ks * sizeof(float);
+    // (few columns: CIFAR-shaped layers, 128 images of one learner, 256 / 128 / 32 splits: 34 / 19 / 6 us there, 5 / 4 / 4 here)
+    if (v.s2d > 1 || cap < 4 || (g.splits >= 16 && (int64_t)g.Ncols * count * cols <= 256 * 1024)) {
+      hipLaunchKernelGGL(wgrad_columns_kernel, dim3((unsigned)g.Ncols, (unsigned)((cols + 255) / 256), (unsigned)count), dim3(1024), 0, s, ws, grads, g, v,
+                         w_off, b_off);
+      return hipGetLastError();
     }
+    // enough workgroups to keep the chip busy: the channels of a filter are divided among several of them
+    int groups = (int)((1536 + (int64_t)g.Ncols * count - 1) / ((int64_t)g.Ncols * count));
+    if (groups > v.Creal / 8) groups = v.Creal / 8;
+    if (groups < 1) groups = 1;
+    int cgroup = ((v.Creal + groups - 1) / groups + 3) & ~3;            // channels are read four at a time
+    if (cgroup > cap) cgroup = cap;
+    groups = (v.Creal + cgroup - 1) / cgroup;
+    const size_t lds = (size_t)wgrad_finish_ld(cgroup) * v.ks * v.ks * sizeof(float);
     hipLaunchKernelGGL(wgrad_finish_kernel, dim3((unsigned)g.Ncols, (unsigned)groups, (unsigned)count), dim3(256), lds, s, ws, grads, g, v,
                        w_off, b_off, cgroup);
   }

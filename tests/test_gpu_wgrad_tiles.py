@@ -36,6 +36,12 @@ CASES = {
     "narrow_ragged": (net(3, 12, 11, ("conv", 32, 3, 1, 1), ("conv", 64, 5, 1, 2), ("avgpool", 3, 2), ("conv", 24, 3, 1, 1)), 5, 3),
     "narrow_wide_rows": (net(3, 9, 70, ("conv", 40, 3, 1, 1), ("conv", 32, 3, 1, 0), ("avgpool", 3, 2)), 2, 2),
     "narrow_full_tiles": (net(3, 16, 16, ("conv", 64, 3, 1, 1), ("conv", 32, 2, 1, 0), ("conv", 16, 4, 1, 1), ("avgpool", 3, 2)), 4, 12),
+    # narrow layers of many positions: tiles inside an image, across lines, across many small images; one and several column groups
+    "strip_first": (net(3, 32, 32, ("conv", 24, 5, 1, 2), ("avgpool", 3, 2)), 1, 64),
+    "strip_ragged": (net(3, 31, 37, ("conv", 8, 4, 1, 0), ("conv", 32, 5, 1, 2), ("conv", 16, 3, 1, 1), ("avgpool", 3, 2)), 1, 64),
+    "strip_small_images": (net(3, 9, 7, ("conv", 16, 3, 1, 1), ("conv", 24, 5, 1, 2), ("conv", 40, 3, 1, 1), ("avgpool", 3, 2)), 18, 64),
+    "strip_two_rows": (net(3, 33, 32, ("conv", 64, 3, 1, 1), ("conv", 48, 3, 1, 0), ("avgpool", 3, 2)), 1, 64),
+    "strip_groups": (net(3, 16, 16, ("conv", 32, 3, 1, 1), ("conv", 64, 5, 1, 2), ("conv", 32, 5, 1, 2), ("avgpool", 3, 2)), 4, 64),
     # many taps per channel, input channels in groups of which the last is shorter
     "many_taps": (net(3, 20, 20, ("conv", 40, 3, 1, 1), ("conv", 24, 11, 1, 5), ("avgpool", 3, 2)), 3, 2),
     "uneven_groups": (net(3, 12, 12, ("conv", 136, 3, 1, 1), ("conv", 72, 3, 1, 1), ("avgpool", 3, 2)), 4, 2),
