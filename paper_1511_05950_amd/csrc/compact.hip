@@ -67,8 +67,8 @@ __device__ __forceinline__ void stv(T* p, const float (&f)[V]) {
     *reinterpret_cast<float4*>(p) = make_float4(f[0], f[1], f[2], f[3]);
   } else {
     uint2 q;
-    q.x = (uint32_t)f2bf(f[0]) | ((uint32_t)f2bf(f[1]) << 16);
-    q.y = (uint32_t)f2bf(f[2]) | ((uint32_t)f2bf(f[3]) << 16);
+    q.x = pack2bf(f[0], f[1]);
+    q.y = pack2bf(f[2], f[3]);
     *reinterpret_cast<uint2*>(p) = q;
   }
 }

@@ -1213,8 +1213,8 @@ __global__ __launch_bounds__(256) void igemm_finish_kernel(PtrTab ws, CPtrTab wt
       reinterpret_cast<float4*>(out)[o4] = make_float4(f[0], f[1], f[2], f[3]);
     } else {
       uint2 w;
-      w.x = (uint32_t)f2bf(f[0]) | ((uint32_t)f2bf(f[1]) << 16);
-      w.y = (uint32_t)f2bf(f[2]) | ((uint32_t)f2bf(f[3]) << 16);
+      w.x = pack2bf(f[0], f[1]);
+      w.y = pack2bf(f[2], f[3]);
       *reinterpret_cast<uint2*>(out + o) = w;
     }
   }

@@ -174,8 +174,8 @@ __global__ __launch_bounds__(256) void fc_group_fwd_kernel(PtrTab ws, CPtrTab wt
       *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + o) = make_float4(f[0], f[1], f[2], f[3]);
     } else {
       uint2 w2;
-      w2.x = (uint32_t)f2bf(f[0]) | ((uint32_t)f2bf(f[1]) << 16);
-      w2.y = (uint32_t)f2bf(f[2]) | ((uint32_t)f2bf(f[3]) << 16);
+      w2.x = pack2bf(f[0], f[1]);
+      w2.y = pack2bf(f[2], f[3]);
       *reinterpret_cast<uint2*>(out + o) = w2;
     }
   }
@@ -373,8 +373,8 @@ __global__ __launch_bounds__(256) void fc_group_finish_kernel(PtrTab ws, CPtrTab
       reinterpret_cast<float4*>(out)[l4] = make_float4(f[0], f[1], f[2], f[3]);
     } else {
       uint2 w;
-      w.x = (uint32_t)f2bf(f[0]) | ((uint32_t)f2bf(f[1]) << 16);
-      w.y = (uint32_t)f2bf(f[2]) | ((uint32_t)f2bf(f[3]) << 16);
+      w.x = pack2bf(f[0], f[1]);
+      w.y = pack2bf(f[2], f[3]);
       *reinterpret_cast<uint2*>(out + o) = w;
     }
   }

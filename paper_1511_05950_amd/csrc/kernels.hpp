@@ -162,8 +162,10 @@ hipError_t launch_conv_dgrad_simple(bool is_bf16, const PtrTab& ws, const CPtrTa
 hipError_t launch_conv_wgrad_simple(bool is_bf16, const PtrTab& ws, const PtrTab& grads, size_t x_off, size_t dy_off, int64_t w_off,
                                     int64_t b_off, const ConvShape& sh, int count, hipStream_t s);
 
+// input_relu: the input holds ReLU outputs (max: the winners then keep which windows no gradient passes, and the backward
+// pass of a max pooling ignores use_mask).
 hipError_t launch_pool_fwd(bool is_bf16, bool is_max, const PtrTab& ws, size_t x_off, size_t y_off, size_t arg_byte_off,
-                           const PoolShape& sh, bool relu, int count, hipStream_t s);
+                           const PoolShape& sh, bool relu, bool input_relu, int count, hipStream_t s);
 hipError_t launch_pool_bwd(bool is_bf16, bool is_max, const PtrTab& ws, size_t dy_off, size_t dx_off, size_t arg_byte_off,
                            const PoolShape& sh, bool use_mask, size_t mask_off, int count, hipStream_t s);
 

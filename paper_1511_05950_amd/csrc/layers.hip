@@ -23,10 +23,10 @@ struct bf8 {
 };
 __device__ __forceinline__ uint4 pack8(const float* f) {
   uint4 o;
-  o.x = (uint32_t)f2bf(f[0]) | ((uint32_t)f2bf(f[1]) << 16);
-  o.y = (uint32_t)f2bf(f[2]) | ((uint32_t)f2bf(f[3]) << 16);
-  o.z = (uint32_t)f2bf(f[4]) | ((uint32_t)f2bf(f[5]) << 16);
-  o.w = (uint32_t)f2bf(f[6]) | ((uint32_t)f2bf(f[7]) << 16);
+  o.x = pack2bf(f[0], f[1]);
+  o.y = pack2bf(f[2], f[3]);
+  o.z = pack2bf(f[4], f[5]);
+  o.w = pack2bf(f[6], f[7]);
   return o;
 }
 
@@ -62,19 +62,18 @@ __global__ __launch_bounds__(256) void pack_input_kernel(CPtrTab images, PtrTab 
   }
 }
 
-// One lane per destination pixel (bf16, Cp % 8 == 0): the Cp channels are assembled in registers and written as
-// 16-byte chunks; neighbouring lanes read neighbouring source columns.
+// One lane per destination pixel of image blockIdx.y (bf16, Cp % 8 == 0): the Cp channels are assembled in registers and written
+// as 16-byte chunks; neighbouring lanes read neighbouring source columns.
 __global__ __launch_bounds__(256) void pack_input_pixel_kernel(CPtrTab images, PtrTab ws, size_t out_off, int N, InPack ip,
                                                                const float* __restrict__ mean) {
   const float* in = (const float*)images.p[blockIdx.z];
   bf16_t* out = (bf16_t*)ws.p[blockIdx.z] + out_off;
-  const int64_t total = (int64_t)N * ip.Hp * ip.Wp;
+  const uint32_t pixels = (uint32_t)ip.Hp * (uint32_t)ip.Wp;
   const int64_t plane = (int64_t)ip.H * ip.W;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    int X = (int)(i % ip.Wp);
-    int64_t r = i / ip.Wp;
-    int Y = (int)(r % ip.Hp);
-    int n = (int)(r / ip.Hp);
+  const int n = blockIdx.y;
+  for (uint32_t q = blockIdx.x * 256 + threadIdx.x; q < pixels; q += gridDim.x * 256) {
+    const int Y = (int)(q / (uint32_t)ip.Wp), X = (int)(q - (uint32_t)Y * (uint32_t)ip.Wp);
+    const int64_t i = (int64_t)n * pixels + q;
     const float* src = in + (int64_t)n * ip.C * plane;
     for (int c0 = 0; c0 < ip.Cp; c0 += 8) {
       float f[8];
@@ -102,61 +101,52 @@ __global__ __launch_bounds__(256) void pack_input_pixel_kernel(CPtrTab images, P
   }
 }
 
-// Space-to-depth by 4 of a 3-channel image (the 11 x 11 / 4 first layer): one lane per destination pixel reads twelve
-// aligned float4 (channel c, row 4Y + dh, columns 4X .. 4X+3) and writes its 48 channels (dh * 4 + dw) * 3 + c as six
-// 16-byte chunks.  Needs W % 4 == 0 and 16-byte aligned images (and mean).
-__global__ __launch_bounds__(256) void pack_input_s2d4_kernel(CPtrTab images, PtrTab ws, size_t out_off, int N, InPack ip,
-                                                              const float* __restrict__ mean) {
-  const float* in = (const float*)images.p[blockIdx.z];
-  bf16_t* out = (bf16_t*)ws.p[blockIdx.z] + out_off;
-  const int64_t total = (int64_t)N * ip.Hp * ip.Wp;
-  const int64_t plane = (int64_t)ip.H * ip.W;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    uint32_t r = (uint32_t)i;
-    const int X = (int)(r % (uint32_t)ip.Wp);
-    r /= (uint32_t)ip.Wp;
-    const int Y = (int)(r % (uint32_t)ip.Hp);
-    const int n = (int)(r / (uint32_t)ip.Hp);
-    const float* src = in + (int64_t)n * 3 * plane;
-    float f[48];
+// Space-to-depth by 4 of a 3-channel image (the 11 x 11 / 4 first layer): a workgroup makes one row of destination pixels.  A
+// thread reads the three channels' aligned float4 (row 4Y + dh, columns 4X .. 4X + 3) and puts their twelve values, channels
+// (dh * 4 + dw) * 3 + c, into LDS; the row leaves as it lies there.  Needs W % 4 == 0 and 16-byte aligned images (and mean).
+// Bound by HBM: 18 learners x 16 images 3 x 224 x 224, 260 MB, in 48 us; a lane per pixel, which writes its 96 bytes on its own,
+// took 78.
+__global__ __launch_bounds__(256) void pack_input_s2d4_kernel(CPtrTab images, PtrTab ws, size_t out_off, InPack ip, const float* __restrict__ mean) {
+  extern __shared__ __attribute__((aligned(16))) uint2 s2d_row[];       // [Wp][96 bytes]
+  const int Y = blockIdx.x, n = blockIdx.y;
+  const uint32_t plane = (uint32_t)ip.H * (uint32_t)ip.W;
+  const float* src = (const float*)images.p[blockIdx.z] + (int64_t)n * 3 * plane;
+  for (int t = threadIdx.x; t < 4 * ip.Wp; t += 256) {
+    const int dh = t / ip.Wp, X = t - dh * ip.Wp, h = 4 * Y + dh;
+    float f[12];
 #pragma unroll
-    for (int dh = 0; dh < 4; dh++) {
-      const int h = 4 * Y + dh;
-#pragma unroll
-      for (int c = 0; c < 3; c++) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (h < ip.H && 4 * X < ip.W) {
-          const int64_t pix = c * plane + (int64_t)h * ip.W + 4 * X;
-          v = *reinterpret_cast<const float4*>(src + pix);
-          if (mean) {
-            const float4 mv = *reinterpret_cast<const float4*>(mean + pix);
-            v.x -= mv.x; v.y -= mv.y; v.z -= mv.z; v.w -= mv.w;
-          }
+    for (int c = 0; c < 3; c++) {
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (h < ip.H) {
+        const uint32_t pix = c * plane + (uint32_t)h * (uint32_t)ip.W + 4 * X;
+        v = *reinterpret_cast<const float4*>(src + pix);
+        if (mean) {
+          const float4 mv = *reinterpret_cast<const float4*>(mean + pix);
+          v.x -= mv.x; v.y -= mv.y; v.z -= mv.z; v.w -= mv.w;
         }
-        f[(dh * 4 + 0) * 3 + c] = v.x;
-        f[(dh * 4 + 1) * 3 + c] = v.y;
-        f[(dh * 4 + 2) * 3 + c] = v.z;
-        f[(dh * 4 + 3) * 3 + c] = v.w;
       }
+      f[c] = v.x; f[3 + c] = v.y; f[6 + c] = v.z; f[9 + c] = v.w;
     }
 #pragma unroll
-    for (int c0 = 0; c0 < 48; c0 += 8) *reinterpret_cast<uint4*>(out + i * 48 + c0) = pack8(f + c0);
+    for (int q = 0; q < 3; q++) s2d_row[X * 12 + dh * 3 + q] = make_uint2(pack2bf(f[4 * q], f[4 * q + 1]), pack2bf(f[4 * q + 2], f[4 * q + 3]));
   }
+  __syncthreads();
+  uint4* out = reinterpret_cast<uint4*>((bf16_t*)ws.p[blockIdx.z] + out_off) + ((int64_t)n * ip.Hp + Y) * ip.Wp * 6;
+  for (int t = threadIdx.x; t < ip.Wp * 6; t += 256) out[t] = reinterpret_cast<const uint4*>(s2d_row)[t];
 }
 
 hipError_t launch_pack_input(bool is_bf16, const CPtrTab& images, const PtrTab& ws, size_t out_off, int count, int N,
                              const InPack& ip, const float* mean, hipStream_t s) {
-  if (is_bf16 && ip.s2d == 4 && ip.C == 3 && ip.Cp == 48 && ip.W % 4 == 0 && out_off % 8 == 0 && ((uintptr_t)mean & 15) == 0) {
-    bool aligned = true;
-    for (int k = 0; k < count; k++) aligned = aligned && ((uintptr_t)images.p[k] & 15) == 0;
-    if (aligned) {
-      dim3 gv = grid_for((int64_t)N * ip.Hp * ip.Wp, count, 16384);
-      hipLaunchKernelGGL(pack_input_s2d4_kernel, gv, dim3(256), 0, s, images, ws, out_off, N, ip, mean);
-      return hipGetLastError();
-    }
+  bool aligned = is_bf16 && ip.W % 4 == 0 && out_off % 8 == 0 && ((uintptr_t)mean & 15) == 0;
+  for (int k = 0; k < count; k++) aligned = aligned && ((uintptr_t)images.p[k] & 15) == 0;
+  if (aligned && ip.s2d == 4 && ip.C == 3 && ip.Cp == 48 && ip.Wp <= 640) {
+    hipLaunchKernelGGL(pack_input_s2d4_kernel, dim3((unsigned)ip.Hp, (unsigned)N, (unsigned)count), dim3(256), (size_t)ip.Wp * 96, s, images, ws,
+                       out_off, ip, mean);
+    return hipGetLastError();
   }
   if (is_bf16 && ip.Cp % 8 == 0 && out_off % 8 == 0) {
-    dim3 gv = grid_for((int64_t)N * ip.Hp * ip.Wp, count, 16384);
+    dim3 gv = grid_for((int64_t)ip.Hp * ip.Wp, count, 16384);
+    gv.y = (unsigned)N;
     hipLaunchKernelGGL(pack_input_pixel_kernel, gv, dim3(256), 0, s, images, ws, out_off, N, ip, mean);
     return hipGetLastError();
   }
@@ -169,10 +159,12 @@ hipError_t launch_pack_input(bool is_bf16, const CPtrTab& images, const PtrTab& 
 // ------------------------------------------------------------------ pooling
 // Windows start at (oh*stride, ow*stride) and are clipped at the border.  Max: the first maximum in
 // row-major window order wins and its position inside the window is kept (one byte) for the backward
-// pass.  Average: the divisor is the number of in-bounds elements.
+// pass.  Where the input is a ReLU's output (`marks`), a window whose maximum is not positive keeps 255 instead, a position it
+// does not have: no gradient passes that ReLU, and the backward pass need not read the input again to know it.
+// Average: the divisor is the number of in-bounds elements.
 template <typename T, bool MAX>
 __global__ __launch_bounds__(256) void pool_fwd_kernel(PtrTab ws, size_t x_off, size_t y_off, size_t arg_byte_off, PoolShape sh,
-                                                       int relu) {
+                                                       int relu, int marks) {
   const T* x = (const T*)ws.p[blockIdx.z] + x_off;
   T* y = (T*)ws.p[blockIdx.z] + y_off;
   uint8_t* arg = (uint8_t*)ws.p[blockIdx.z] + arg_byte_off;
@@ -198,6 +190,7 @@ __global__ __launch_bounds__(256) void pool_fwd_kernel(PtrTab ws, size_t x_off, 
         cnt++;
       }
     if (!MAX) acc /= (float)cnt;
+    if (MAX && marks && !(acc > 0.f)) best = 255;
     if (relu) acc = fmaxf(acc, 0.f);
     stf(y + i, acc);
     if (MAX) arg[i] = (uint8_t)best;
@@ -247,7 +240,7 @@ __global__ __launch_bounds__(256) void pool_bwd_kernel(PtrTab ws, size_t dy_off,
 // writes 1 KiB contiguous runs.
 template <bool MAX>
 __global__ __launch_bounds__(256) void pool_fwd_vec8_kernel(PtrTab ws, size_t x_off, size_t y_off, size_t arg_byte_off, PoolShape sh,
-                                                            int relu) {
+                                                            int relu, int marks) {
   const bf16_t* x = (const bf16_t*)ws.p[blockIdx.z] + x_off;
   bf16_t* y = (bf16_t*)ws.p[blockIdx.z] + y_off;
   uint8_t* arg = (uint8_t*)ws.p[blockIdx.z] + arg_byte_off;
@@ -286,6 +279,7 @@ __global__ __launch_bounds__(256) void pool_fwd_vec8_kernel(PtrTab ws, size_t x_
 #pragma unroll
     for (int e = 0; e < 8; e++) {
       if (!MAX) acc[e] /= (float)cnt;
+      if (MAX && marks && !(acc[e] > 0.f)) best[e] = 255;
       if (relu) acc[e] = fmaxf(acc[e], 0.f);
     }
     *reinterpret_cast<uint4*>(y + i * 8) = pack8(acc);
@@ -301,21 +295,26 @@ __global__ __launch_bounds__(256) void pool_fwd_vec8_kernel(PtrTab ws, size_t x_
 // 3 x 3 windows (every pooling layer of the two reference networks): the nine 16-byte reads of a window are all
 // requested before the first is used (the general kernel above walks the window in a loop whose trip count the
 // compiler does not know, one dependent read after the other).  Same arithmetic and the same winner on ties.
+// Divisions of a flat index by the 8-channel chunks of a pixel, then by the columns and the rows it runs over.
+struct PoolDiv {
+  FastDiv c8, w, h;
+};
+static bool pool_divides(PoolDiv* d, int64_t total, int C8, int W, int H) {
+  d->c8.set(C8);
+  d->w.set(W);
+  d->h.set(H);
+  return FastDiv::exact(C8, total) && FastDiv::exact(W, total / C8) && FastDiv::exact(H, total / C8 / W);
+}
+
 template <bool MAX>
-__global__ __launch_bounds__(256) void pool_fwd_3x3_kernel(PtrTab ws, size_t x_off, size_t y_off, size_t arg_byte_off, PoolShape sh, int relu) {
+__global__ __launch_bounds__(256) void pool_fwd_3x3_kernel(PtrTab ws, size_t x_off, size_t y_off, size_t arg_byte_off, PoolShape sh, PoolDiv dv, int relu, int marks) {
   const bf16_t* x = (const bf16_t*)ws.p[blockIdx.z] + x_off;
   bf16_t* y = (bf16_t*)ws.p[blockIdx.z] + y_off;
   uint8_t* arg = (uint8_t*)ws.p[blockIdx.z] + arg_byte_off;
   const int C8 = sh.C / 8;
   const uint32_t total = (uint32_t)sh.N * sh.OH * sh.OW * C8;
   for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
-    uint32_t r = i;
-    const int c8 = (int)(r % (uint32_t)C8);
-    r /= (uint32_t)C8;
-    const int ow = (int)(r % (uint32_t)sh.OW);
-    r /= (uint32_t)sh.OW;
-    const int oh = (int)(r % (uint32_t)sh.OH);
-    const int n = (int)(r / (uint32_t)sh.OH);
+    const int r1 = dv.c8((int)i), c8 = (int)i - r1 * C8, r2 = dv.w(r1), ow = r1 - r2 * sh.OW, n = dv.h(r2), oh = r2 - n * sh.OH;
     const int h0 = oh * sh.stride, w0 = ow * sh.stride;
     const int nh = min(3, sh.H - h0), nw = min(3, sh.W - w0);          // rows and columns of the window inside the image
     const bf16_t* base = x + (((int64_t)n * sh.H + h0) * sh.W + w0) * sh.C + c8 * 8;
@@ -348,6 +347,7 @@ __global__ __launch_bounds__(256) void pool_fwd_3x3_kernel(PtrTab ws, size_t x_o
 #pragma unroll
     for (int e = 0; e < 8; e++) {
       if (!MAX) acc[e] /= cnt;
+      if (MAX && marks && !(acc[e] > 0.f)) best[e] = 255;
       if (relu) acc[e] = fmaxf(acc[e], 0.f);
     }
     *reinterpret_cast<uint4*>(y + (size_t)i * 8) = pack8(acc);
@@ -419,8 +419,10 @@ __global__ __launch_bounds__(256) void pool_bwd_vec8_kernel(PtrTab ws, size_t dy
 // 3 x 3 windows at stride 2 (every pooling layer of the two reference networks): one lane owns 8 channels of a 2 x 2
 // block of the input, rows 2a, 2a+1 and columns 2b, 2b+1.  Only the four windows (a-1 | a, b-1 | b) reach into the
 // block, so they are read once for the four results instead of once per covered element (nine reads per block).
+// Max: neither the mask nor the input is read (the winners know both); AlexNet-shaped net, 256 images, its three layers from the input on
+// 61 / 43 / 16 -> 45 / 31 / 11 us.
 template <bool MAX>
-__global__ __launch_bounds__(256) void pool_bwd_3x3s2_kernel(PtrTab ws, size_t dy_off, size_t dx_off, size_t arg_byte_off, PoolShape sh,
+__global__ __launch_bounds__(256) void pool_bwd_3x3s2_kernel(PtrTab ws, size_t dy_off, size_t dx_off, size_t arg_byte_off, PoolShape sh, PoolDiv dv,
                                                              int use_mask, size_t mask_off) {
   const bf16_t* dy = (const bf16_t*)ws.p[blockIdx.z] + dy_off;
   bf16_t* dx = (bf16_t*)ws.p[blockIdx.z] + dx_off;
@@ -429,13 +431,7 @@ __global__ __launch_bounds__(256) void pool_bwd_3x3s2_kernel(PtrTab ws, size_t d
   const int C8 = sh.C / 8, HB = (sh.H + 1) / 2, WB = (sh.W + 1) / 2;
   const uint32_t total = (uint32_t)sh.N * HB * WB * C8;
   for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
-    uint32_t r = i;
-    const int c8 = (int)(r % (uint32_t)C8);
-    r /= (uint32_t)C8;
-    const int b = (int)(r % (uint32_t)WB);
-    r /= (uint32_t)WB;
-    const int a = (int)(r % (uint32_t)HB);
-    const int n = (int)(r / (uint32_t)HB);
+    const int r1 = dv.c8((int)i), c8 = (int)i - r1 * C8, r2 = dv.w(r1), b = r1 - r2 * WB, n = dv.h(r2), a = r2 - n * HB;
     // All reads are requested before the first is used: windows outside the output and block elements outside the
     // input read a clamped (valid) address and are discarded by a predicate instead of a branch around the load.
     bool w_ok[4];
@@ -472,7 +468,7 @@ __global__ __launch_bounds__(256) void pool_bwd_3x3s2_kernel(PtrTab ws, size_t d
         x_ok[q] = ih < sh.H && iw < sh.W;
         xo[q] = ((((int64_t)n * sh.H + min(ih, sh.H - 1)) * sh.W + min(iw, sh.W - 1)) * C8 + c8) * 8;
         mv[q] = make_uint4(0u, 0u, 0u, 0u);
-        if (use_mask) mv[q] = *reinterpret_cast<const uint4*>(mask + xo[q]);
+        if (!MAX && use_mask) mv[q] = *reinterpret_cast<const uint4*>(mask + xo[q]);
       }
     float acc[4][8];                                    // [2 * dh + dw][channel]
 #pragma unroll
@@ -513,7 +509,7 @@ __global__ __launch_bounds__(256) void pool_bwd_3x3s2_kernel(PtrTab ws, size_t d
 #pragma unroll
     for (int q = 0; q < 4; q++) {
       if (!x_ok[q]) continue;
-      if (use_mask) {
+      if (!MAX && use_mask) {
         bf8 mk;
         mk.v = mv[q];
 #pragma unroll
@@ -526,26 +522,28 @@ __global__ __launch_bounds__(256) void pool_bwd_3x3s2_kernel(PtrTab ws, size_t d
 }
 
 hipError_t launch_pool_fwd(bool is_bf16, bool is_max, const PtrTab& ws, size_t x_off, size_t y_off, size_t arg_byte_off,
-                           const PoolShape& sh, bool relu, int count, hipStream_t s) {
+                           const PoolShape& sh, bool relu, bool input_relu, int count, hipStream_t s) {
   dim3 g = grid_for((int64_t)sh.N * sh.OH * sh.OW * sh.C, count);
-  int r = relu ? 1 : 0;
+  const int r = relu ? 1 : 0, m = is_max && input_relu ? 1 : 0;
   if (is_bf16 && sh.C % 8 == 0 && x_off % 8 == 0 && y_off % 8 == 0 && arg_byte_off % 8 == 0) {
     dim3 gv = grid_for((int64_t)sh.N * sh.OH * sh.OW * (sh.C / 8), count, 16384);
-    if (sh.ks == 3 && (int64_t)sh.N * sh.H * sh.W * sh.C < ((int64_t)1 << 31)) {
-      if (is_max) hipLaunchKernelGGL((pool_fwd_3x3_kernel<true>), gv, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r);
-      else hipLaunchKernelGGL((pool_fwd_3x3_kernel<false>), gv, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r);
+    PoolDiv dv;
+    if (sh.ks == 3 && (int64_t)sh.N * sh.H * sh.W * sh.C < ((int64_t)1 << 31) &&
+        pool_divides(&dv, (int64_t)sh.N * sh.OH * sh.OW * (sh.C / 8), sh.C / 8, sh.OW, sh.OH)) {
+      if (is_max) hipLaunchKernelGGL((pool_fwd_3x3_kernel<true>), gv, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, dv, r, m);
+      else hipLaunchKernelGGL((pool_fwd_3x3_kernel<false>), gv, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, dv, r, m);
       return hipGetLastError();
     }
-    if (is_max) hipLaunchKernelGGL((pool_fwd_vec8_kernel<true>), gv, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r);
-    else hipLaunchKernelGGL((pool_fwd_vec8_kernel<false>), gv, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r);
+    if (is_max) hipLaunchKernelGGL((pool_fwd_vec8_kernel<true>), gv, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r, m);
+    else hipLaunchKernelGGL((pool_fwd_vec8_kernel<false>), gv, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r, m);
     return hipGetLastError();
   }
   if (is_bf16) {
-    if (is_max) hipLaunchKernelGGL((pool_fwd_kernel<bf16_t, true>), g, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r);
-    else hipLaunchKernelGGL((pool_fwd_kernel<bf16_t, false>), g, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r);
+    if (is_max) hipLaunchKernelGGL((pool_fwd_kernel<bf16_t, true>), g, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r, m);
+    else hipLaunchKernelGGL((pool_fwd_kernel<bf16_t, false>), g, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r, m);
   } else {
-    if (is_max) hipLaunchKernelGGL((pool_fwd_kernel<float, true>), g, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r);
-    else hipLaunchKernelGGL((pool_fwd_kernel<float, false>), g, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r);
+    if (is_max) hipLaunchKernelGGL((pool_fwd_kernel<float, true>), g, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r, m);
+    else hipLaunchKernelGGL((pool_fwd_kernel<float, false>), g, dim3(256), 0, s, ws, x_off, y_off, arg_byte_off, sh, r, m);
   }
   return hipGetLastError();
 }
@@ -553,12 +551,14 @@ hipError_t launch_pool_fwd(bool is_bf16, bool is_max, const PtrTab& ws, size_t x
 hipError_t launch_pool_bwd(bool is_bf16, bool is_max, const PtrTab& ws, size_t dy_off, size_t dx_off, size_t arg_byte_off,
                            const PoolShape& sh, bool use_mask, size_t mask_off, int count, hipStream_t s) {
   dim3 g = grid_for((int64_t)sh.N * sh.H * sh.W * sh.C, count);
-  int um = use_mask ? 1 : 0;
+  const int um = use_mask && !is_max ? 1 : 0;      // max: the winners know (launch_pool_fwd's input_relu)
   if (is_bf16 && sh.C % 8 == 0 && dy_off % 8 == 0 && dx_off % 8 == 0 && arg_byte_off % 8 == 0 && mask_off % 8 == 0) {
-    if (sh.ks == 3 && sh.stride == 2) {
+    PoolDiv dv;
+    if (sh.ks == 3 && sh.stride == 2 &&
+        pool_divides(&dv, (int64_t)sh.N * ((sh.H + 1) / 2) * ((sh.W + 1) / 2) * (sh.C / 8), sh.C / 8, (sh.W + 1) / 2, (sh.H + 1) / 2)) {
       dim3 gb = grid_for((int64_t)sh.N * ((sh.H + 1) / 2) * ((sh.W + 1) / 2) * (sh.C / 8), count, 16384);
-      if (is_max) hipLaunchKernelGGL((pool_bwd_3x3s2_kernel<true>), gb, dim3(256), 0, s, ws, dy_off, dx_off, arg_byte_off, sh, um, mask_off);
-      else hipLaunchKernelGGL((pool_bwd_3x3s2_kernel<false>), gb, dim3(256), 0, s, ws, dy_off, dx_off, arg_byte_off, sh, um, mask_off);
+      if (is_max) hipLaunchKernelGGL((pool_bwd_3x3s2_kernel<true>), gb, dim3(256), 0, s, ws, dy_off, dx_off, arg_byte_off, sh, dv, um, mask_off);
+      else hipLaunchKernelGGL((pool_bwd_3x3s2_kernel<false>), gb, dim3(256), 0, s, ws, dy_off, dx_off, arg_byte_off, sh, dv, um, mask_off);
       return hipGetLastError();
     }
     dim3 gv = grid_for((int64_t)sh.N * sh.H * sh.W * (sh.C / 8), count, 16384);

@@ -875,7 +875,7 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
         break;
       case OP_POOL_MAX:
       case OP_POOL_AVG:
-        TRY(launch_pool_fwd(bf, op.kind == OP_POOL_MAX, ws, xi, yo, op.arg_off, op.ps, op.relu, count, stream));
+        TRY(launch_pool_fwd(bf, op.kind == OP_POOL_MAX, ws, xi, yo, op.arg_off, op.ps, op.relu, T[(size_t)op.in_t].relu, count, stream));
         break;
       case OP_FLATTEN:
         TRY(launch_flatten_fwd(bf, ws, xi, yo, op.ps.N, op.ps.C, op.ps.H, op.ps.W, count, stream));

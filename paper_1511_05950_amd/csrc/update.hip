@@ -76,8 +76,8 @@ __device__ __forceinline__ void stg_nt(float4* p, float4 v) {
 }
 __device__ __forceinline__ uint2 pack_bf4(float4 a) {
   uint2 o;
-  o.x = (uint32_t)f2bf(a.x) | ((uint32_t)f2bf(a.y) << 16);
-  o.y = (uint32_t)f2bf(a.z) | ((uint32_t)f2bf(a.w) << 16);
+  o.x = pack2bf(a.x, a.y);
+  o.y = pack2bf(a.z, a.w);
   return o;
 }
 __device__ __forceinline__ void fma4(float4& s, float cf, const float4& g) {
@@ -465,8 +465,8 @@ __global__ __launch_bounds__(256) void apply_update_fc_kernel(const float* theta
       a.x -= b.x; a.y -= b.y; a.z -= b.z; a.w -= b.w;
       if (SHADOW) {
         uint2 o;
-        o.x = (uint32_t)f2bf(a.x) | ((uint32_t)f2bf(a.y) << 16);
-        o.y = (uint32_t)f2bf(a.z) | ((uint32_t)f2bf(a.w) << 16);
+        o.x = pack2bf(a.x, a.y);
+        o.y = pack2bf(a.z, a.w);
         *reinterpret_cast<uint2*>(st.shadow_out[step] + woff + e) = o;
       }
     }
@@ -562,8 +562,8 @@ __global__ __launch_bounds__(256) void apply_update_fc_kernel(const float* theta
       vv[q] = b;
       if (SHADOW) {
         uint2 w2;
-        w2.x = (uint32_t)f2bf(a.x) | ((uint32_t)f2bf(a.y) << 16);
-        w2.y = (uint32_t)f2bf(a.z) | ((uint32_t)f2bf(a.w) << 16);
+        w2.x = pack2bf(a.x, a.y);
+        w2.y = pack2bf(a.z, a.w);
         *reinterpret_cast<uint2*>(st.shadow_out[step] + woff + (int64_t)o * in + w0 + cc) = w2;
       }
     }
