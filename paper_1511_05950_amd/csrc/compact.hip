@@ -222,6 +222,8 @@ __device__ __forceinline__ void load_patch(float* lds, const CompactSrc& s, char
 // put other loads between the requests and their use.
 template <typename T, int V>
 struct GradAt {
+  // mk: the ReLU's output, or the gradient itself where it is read as stored (in one place: two, read in two branches, were
+  // merged into one read with a selected destination, and both arrays went to scratch memory)
   float d[4][V], mk[V];
   uint32_t won[4];
 
@@ -229,7 +231,7 @@ struct GradAt {
     const T* dp = (const T*)wsb + g.off;
     const uint32_t e = ((uint32_t)(n * g.OH + oh) * g.OW + ow) * g.K + c;
     if (g.kind == CGRAD_PLAIN) {
-      ldv<T, V>(dp + e, d[0]);
+      ldv<T, V>(dp + e, mk);
       return;
     }
     const uint8_t* arg = (const uint8_t*)wsb + g.arg_off;
@@ -250,7 +252,7 @@ struct GradAt {
   __device__ __forceinline__ void value(const CompactGrad& g, int oh, int ow, float (&val)[V]) const {
     if (g.kind == CGRAD_PLAIN) {
 #pragma unroll
-      for (int v = 0; v < V; v++) val[v] = d[0][v];
+      for (int v = 0; v < V; v++) val[v] = mk[v];
       return;
     }
     const int ph_hi = g.by_pst(oh), pw_hi = g.by_pst(ow);
