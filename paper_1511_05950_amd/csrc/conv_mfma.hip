@@ -411,8 +411,7 @@ __device__ __forceinline__ void frag_epilogue(floatx16 (&acc)[WM / 32][WN / 32],
     __syncthreads();                                     // every wavefront has finished reading the last tile
     bf16_t* stage = lds + wave * (32 * LDE);
     constexpr int CPRW = WN / 8;                         // 16-byte chunks per row of the wavefront's tile
-    constexpr int RPI = 64 / CPRW;                       // rows covered by one 64-lane pass
-    const int rrow = lane / CPRW, rchunk = lane % CPRW;
+    static_assert(32 * CPRW % 64 == 0, "a block leaves in whole passes of 64 chunks");
 #pragma unroll
     for (int i = 0; i < TM; i++) {
 #pragma unroll
@@ -431,8 +430,8 @@ __device__ __forceinline__ void frag_epilogue(floatx16 (&acc)[WM / 32][WN / 32],
       __builtin_amdgcn_wave_barrier();
       asm volatile("" ::: "memory");
 #pragma unroll
-      for (int it = 0; it < 32 / RPI; it++) {
-        const int row = rrow + RPI * it;
+      for (int it = 0; it < 32 * CPRW / 64; it++) {
+        const int row = (lane + 64 * it) / CPRW, rchunk = (lane + 64 * it) % CPRW;
         const int m = mw + 32 * i + row, n = nw + rchunk * 8;
         uint4 q = *reinterpret_cast<const uint4*>(stage + row * LDE + rchunk * 8);
         if (m < g.M && n < g.Ncols) {
@@ -1363,6 +1362,11 @@ hipError_t launch_igemm_frag(const PtrTab& ws, const CPtrTab& wts, const IGemm& 
     }
     if (done) return hipGetLastError();
   }
+  // Columns that whole 96s cover with fewer to spare than whole 128s (96, 192, 272 .. 288, ...): 256 x 96 tiles, 64 x 96 a
+  // wavefront, three quarters of the products of a 128-column tile for the same filter reads per product.  5 x 5 over 256
+  // channels, 96 columns, 27 x 27 outputs: 256 images of one learner 212 -> 169 us, 2 / 6 / 15 learners of 16 on versions of
+  // their own 54 / 123 / 205 -> 46 (split, with its second pass) / 122 / 171.
+  const bool c96 = g.Ncols > 64 && (g.Ncols + 95) / 96 * 96 < (g.Ncols + 127) / 128 * 128;
   // own: most learners of this call read a weight version of their own (lambda-softsync) rather than a shared one
   int same = 0;
   for (int k = 1; k < count; k++) same += wts.p[k] == wts.p[0] ? 1 : 0;
@@ -1390,18 +1394,23 @@ hipError_t launch_igemm_frag(const PtrTab& ws, const CPtrTab& wts, const IGemm& 
       return (double)(each / places) * full + (left == 2 ? two : left == 1 ? one : 0.);
     };
     const bool tall = g.Ncols > 128 && halo_time(256, 2, 0.90, 0., 0.47) < (own ? 1.18 : 1.) * halo_time(128, 3, 0.72, 0.58, 0.45);
-    const bool done = g.Ncols % 256 == 0 ? launch_halo_t<128, 256, 128, 64>(ws, wts, g, ep, count, own, s)
-                      : tall             ? launch_halo_t<256, 128, 128, 64>(ws, wts, g, ep, count, own, s)
-                                         : launch_halo_t<128, 128, 64, 64>(ws, wts, g, ep, count, own, s);
+    // (a 256-row tile whose patch does not fit is no reason against 128 rows)
+    const bool done = (c96 && launch_halo_t<256, 96, 64, 96>(ws, wts, g, ep, count, own, s)) ||
+                      (g.Ncols % 256 == 0 ? launch_halo_t<128, 256, 128, 64>(ws, wts, g, ep, count, own, s)
+                                          : (tall && launch_halo_t<256, 128, 128, 64>(ws, wts, g, ep, count, own, s)) ||
+                                                launch_halo_t<128, 128, 64, 64>(ws, wts, g, ep, count, own, s));
     if (done) return hipGetLastError();
   }
   // Wave tile 128 x 64 (two wavefronts per SIMD, accumulators in ordinary registers) wins where the columns fill
   // whole 256-wide tiles: each B fragment then serves four MFMAs instead of two.  Measured slower: 256 x 128 blocks,
-  // 192-wide tiles of three wavefronts for 384 columns, 96-wide tiles for 96 columns, and taking the filters
+  // 192-wide tiles of three wavefronts for 384 columns, and taking the filters
   // through LDS as well (tiles 128 x 128 to 256 x 256, staging registers two steps deep): with both operands in
   // LDS its bandwidth becomes the limit instead of the vector L1's.
   if (g.Ncols <= 32) launch_frag_t<128, 32, 32, 32>(ws, wts, g, ep, count, s);
   else if (g.Ncols <= 64) launch_frag_t<128, 64, 64, 32>(ws, wts, g, ep, count, s);
+  // (the tap-by-tap kernel: only where the 256-row tiles fill the chip; 3 x 3 over 48 channels, 54 x 54 outputs, 1 / 2 / 6 / 15
+  // learners of 16 images: 15 / 20 / 60 / 123 us with 128 x 128 tiles, 18 / 21 / 63 / 117 with these)
+  else if (c96 && (int64_t)((g.M + 255) / 256) * ((g.Ncols + 95) / 96) * count >= 256) launch_frag_t<256, 96, 64, 96>(ws, wts, g, ep, count, s);
   else if (g.Ncols % 256 == 0) launch_frag_t<128, 256, 128, 64>(ws, wts, g, ep, count, s);
   else launch_frag_t<128, 128, 64, 64>(ws, wts, g, ep, count, s);
   return hipGetLastError();
