@@ -292,9 +292,6 @@ __global__ __launch_bounds__(256) void pool_fwd_vec8_kernel(PtrTab ws, size_t x_
   }
 }
 
-// 3 x 3 windows (every pooling layer of the two reference networks): the nine 16-byte reads of a window are all
-// requested before the first is used (the general kernel above walks the window in a loop whose trip count the
-// compiler does not know, one dependent read after the other).  Same arithmetic and the same winner on ties.
 // Divisions of a flat index by the 8-channel chunks of a pixel, then by the columns and the rows it runs over.
 struct PoolDiv {
   FastDiv c8, w, h;
@@ -306,6 +303,9 @@ static bool pool_divides(PoolDiv* d, int64_t total, int C8, int W, int H) {
   return FastDiv::exact(C8, total) && FastDiv::exact(W, total / C8) && FastDiv::exact(H, total / C8 / W);
 }
 
+// 3 x 3 windows (every pooling layer of the two reference networks): the nine 16-byte reads of a window are all
+// requested before the first is used (the general kernel above walks the window in a loop whose trip count the
+// compiler does not know, one dependent read after the other).  Same arithmetic and the same winner on ties.
 template <bool MAX>
 __global__ __launch_bounds__(256) void pool_fwd_3x3_kernel(PtrTab ws, size_t x_off, size_t y_off, size_t arg_byte_off, PoolShape sh, PoolDiv dv, int relu, int marks) {
   const bf16_t* x = (const bf16_t*)ws.p[blockIdx.z] + x_off;
