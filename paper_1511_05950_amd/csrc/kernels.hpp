@@ -6,6 +6,7 @@
 #pragma once
 #include "ctx.hpp"
 #include "fastdiv.hpp"
+#include "tile_rules.hpp"
 
 namespace sasgd {
 

@@ -101,24 +101,26 @@ __global__ __launch_bounds__(256) void pack_input_pixel_kernel(CPtrTab images, P
   }
 }
 
-// Space-to-depth by 4 of a 3-channel image (the 11 x 11 / 4 first layer): a workgroup makes one row of destination pixels.  A
-// thread reads the three channels' aligned float4 (row 4Y + dh, columns 4X .. 4X + 3) and puts their twelve values, channels
-// (dh * 4 + dw) * 3 + c, into LDS; the row leaves as it lies there.  Needs W % 4 == 0 and 16-byte aligned images (and mean).
-// Bound by HBM: 18 learners x 16 images 3 x 224 x 224, 260 MB, in 48 us; a lane per pixel, which writes its 96 bytes on its own,
-// took 78.
-__global__ __launch_bounds__(256) void pack_input_s2d4_kernel(CPtrTab images, PtrTab ws, size_t out_off, InPack ip, const float* __restrict__ mean) {
-  extern __shared__ __attribute__((aligned(16))) uint2 s2d_row[];       // [Wp][96 bytes]
-  const int Y = blockIdx.x, n = blockIdx.y;
+// Space-to-depth by 4 of a 3-channel image (the 11 x 11 / 4 first layer): a workgroup makes `width` pixels of one row of destination
+// pixels (input_row_piece).  A thread reads the three channels' aligned float4 (row 4Y + dh, columns 4X .. 4X + 3) and puts
+// their twelve values, channels (dh * 4 + dw) * 3 + c, into LDS; the pixels leave as they lie there.  Needs W % 4 == 0 and 16-byte
+// aligned images (and mean).  Bound by HBM: 18 learners x 16 images 3 x 224 x 224, 260 MB, in 48 us; a lane per pixel, which writes
+// its 96 bytes on its own, took 78.
+__global__ __launch_bounds__(256) void pack_input_s2d4_kernel(CPtrTab images, PtrTab ws, size_t out_off, InPack ip, int width,
+                                                              int pieces, const float* __restrict__ mean) {
+  extern __shared__ __attribute__((aligned(16))) uint2 s2d_row[];       // [width][96 bytes]
+  const int Y = blockIdx.x / pieces, x0 = (blockIdx.x - Y * pieces) * width;
+  const int n = blockIdx.y, pixels = min(width, ip.Wp - x0);
   const uint32_t plane = (uint32_t)ip.H * (uint32_t)ip.W;
   const float* src = (const float*)images.p[blockIdx.z] + (int64_t)n * 3 * plane;
-  for (int t = threadIdx.x; t < 4 * ip.Wp; t += 256) {
-    const int dh = t / ip.Wp, X = t - dh * ip.Wp, h = 4 * Y + dh;
+  for (int t = threadIdx.x; t < 4 * pixels; t += 256) {
+    const int dh = t / pixels, X = t - dh * pixels, h = 4 * Y + dh;
     float f[12];
 #pragma unroll
     for (int c = 0; c < 3; c++) {
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
       if (h < ip.H) {
-        const uint32_t pix = c * plane + (uint32_t)h * (uint32_t)ip.W + 4 * X;
+        const uint32_t pix = c * plane + (uint32_t)h * (uint32_t)ip.W + 4 * (x0 + X);
         v = *reinterpret_cast<const float4*>(src + pix);
         if (mean) {
           const float4 mv = *reinterpret_cast<const float4*>(mean + pix);
@@ -131,20 +133,22 @@ __global__ __launch_bounds__(256) void pack_input_s2d4_kernel(CPtrTab images, Pt
     for (int q = 0; q < 3; q++) s2d_row[X * 12 + dh * 3 + q] = make_uint2(pack2bf(f[4 * q], f[4 * q + 1]), pack2bf(f[4 * q + 2], f[4 * q + 3]));
   }
   __syncthreads();
-  uint4* out = reinterpret_cast<uint4*>((bf16_t*)ws.p[blockIdx.z] + out_off) + ((int64_t)n * ip.Hp + Y) * ip.Wp * 6;
-  for (int t = threadIdx.x; t < ip.Wp * 6; t += 256) out[t] = reinterpret_cast<const uint4*>(s2d_row)[t];
+  uint4* out = reinterpret_cast<uint4*>((bf16_t*)ws.p[blockIdx.z] + out_off) + (((int64_t)n * ip.Hp + Y) * ip.Wp + x0) * 6;
+  for (int t = threadIdx.x; t < pixels * 6; t += 256) out[t] = reinterpret_cast<const uint4*>(s2d_row)[t];
 }
 
 hipError_t launch_pack_input(bool is_bf16, const CPtrTab& images, const PtrTab& ws, size_t out_off, int count, int N,
                              const InPack& ip, const float* mean, hipStream_t s) {
-  bool aligned = is_bf16 && ip.W % 4 == 0 && out_off % 8 == 0 && ((uintptr_t)mean & 15) == 0;
+  bool aligned = ip.W % 4 == 0 && ((uintptr_t)mean & 15) == 0;
   for (int k = 0; k < count; k++) aligned = aligned && ((uintptr_t)images.p[k] & 15) == 0;
-  if (aligned && ip.s2d == 4 && ip.C == 3 && ip.Cp == 48 && ip.Wp <= 640) {
-    hipLaunchKernelGGL(pack_input_s2d4_kernel, dim3((unsigned)ip.Hp, (unsigned)N, (unsigned)count), dim3(256), (size_t)ip.Wp * 96, s, images, ws,
-                       out_off, ip, mean);
+  const InputLayout layout = out_off % 8 == 0 ? input_layout(is_bf16, ip.s2d, ip.C, ip.Cp, aligned) : InputLayout::kValues;
+  if (layout == InputLayout::kRows) {
+    const int width = input_row_piece(ip.Wp), pieces = (ip.Wp + width - 1) / width;
+    hipLaunchKernelGGL(pack_input_s2d4_kernel, dim3((unsigned)(ip.Hp * pieces), (unsigned)N, (unsigned)count), dim3(256), (size_t)width * 96, s, images,
+                       ws, out_off, ip, width, pieces, mean);
     return hipGetLastError();
   }
-  if (is_bf16 && ip.Cp % 8 == 0 && out_off % 8 == 0) {
+  if (layout == InputLayout::kPixels) {
     dim3 gv = grid_for((int64_t)ip.Hp * ip.Wp, count, 16384);
     gv.y = (unsigned)N;
     hipLaunchKernelGGL(pack_input_pixel_kernel, gv, dim3(256), 0, s, images, ws, out_off, N, ip, mean);
