@@ -17,5 +17,10 @@ inline int input_row_piece(int Wp) {
   const int pieces = (Wp + 639) / 640;
   return (Wp + pieces - 1) / pieces;
 }
+// Workgroups of the kPixels kernel a learner: 256 pixels each, counted through all images.
+inline int64_t input_pixel_groups(int N, int Hp, int Wp) {
+  const int64_t groups = ((int64_t)N * Hp * Wp + 255) / 256;
+  return groups < 16384 ? groups : 16384;
+}
 
 }  // namespace sasgd

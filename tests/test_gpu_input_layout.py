@@ -1,5 +1,6 @@
-"""Re-layout of a mini-batch's images, bf16: long rows of a space-to-depth first layer, in pieces; the row kernel against the kernel with a
-lane per pixel, which takes over where images lie at an address that is no multiple of 16, to the bit; with a pixel mean and without."""
+"""Re-layout of a mini-batch's images, bf16: long rows of a space-to-depth first layer, in pieces; the row kernel against the kernel
+with a lane per pixel, which takes over where images lie at an address that is no multiple of 16, to the bit; with a pixel mean and
+without; images of a few pixels, several in a workgroup."""
 import numpy as np
 import pytest
 
@@ -53,3 +54,10 @@ def test_rows_and_pixels_have_the_same_bits(nt, mu, lam):
             assert np.array_equal(a.view(np.uint32), b.view(np.uint32)) and np.abs(a).max() > 0
     # the mean is subtracted before anything is rounded
     assert np.array_equal(gradients(nt, mu, theta, X - mean, Y, 0, None)[0], gradients(nt, mu, theta, X, Y, 0, mean)[0])
+
+
+@pytest.mark.parametrize("h, w, mu, lam", [(5, 3, 70, 6), (3, 3, 300, 2), (4, 9, 64, 8)])
+def test_images_of_a_few_pixels(h, w, mu, lam):
+    nt = net(h, w, ("conv", 72, 3, 1, 1))
+    for (g, rg, loss, rl) in one_gradient(nt, mu, "bf16", seed=h * w, scale=0.1, lam=lam):
+        check_gradient(nt, "bf16", g, rg, loss, rl, (h, w))

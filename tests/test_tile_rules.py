@@ -19,6 +19,10 @@ int main() {
       int bf16, s2d, C, Cp, Wp, aligned;
       if (scanf("%d %d %d %d %d %d", &bf16, &s2d, &C, &Cp, &Wp, &aligned) != 6) return 1;
       printf("%d %d\n", (int)input_layout(bf16, s2d, C, Cp, aligned), input_row_piece(Wp));
+    } else if (!strcmp(rule, "pixels")) {
+      int N, Hp, Wp;
+      if (scanf("%d %d %d", &N, &Hp, &Wp) != 3) return 1;
+      printf("%d\n", (int)input_pixel_groups(N, Hp, Wp));
     } else {
       return 1;
     }
@@ -50,3 +54,7 @@ def test_input_layout(ask):
         assert -(-wp // piece) == -(-wp // 640)
     assert [r[0] for r in ask([("input", 1, 4, 3, 48, 56, 0), ("input", 1, 2, 3, 16, 56, 1), ("input", 1, 1, 3, 8, 56, 1),
                                ("input", 0, 4, 3, 48, 56, 1), ("input", 1, 1, 13, 13, 56, 1)])] == [1, 1, 1, 2, 2]
+
+
+def test_small_images_share_workgroups(ask):
+    assert ask([("pixels", *q) for q in ((2048, 4, 4), (1, 3, 5), (4096, 3, 9), (128, 32, 32), (16, 512, 512))]) == [(128,), (1,), (432,), (512,), (16384,)]
