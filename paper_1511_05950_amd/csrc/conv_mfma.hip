@@ -1242,12 +1242,7 @@ static void launch_igemm_t(const PtrTab& ws, const CPtrTab& wts, const IGemm& g,
 template <int BM, int BN, int WM, int WN>
 static void launch_frag_t(const PtrTab& ws, const CPtrTab& wts, const IGemm& g_in, const Epilogue& ep, int count, hipStream_t s) {
   IGemm g = g_in;
-  {
-    // a split of up to six ways is not worth its second pass once the tiles alone take a fifth of the resident places
-    const int64_t tiles = (int64_t)((g.M + BM - 1) / BM) * ((g.Ncols + BN - 1) / BN) * count;
-    const int64_t places = 256 * (WM * WN > 64 * 64 ? 2 : 3);
-    if (g.splits <= 6 && tiles * 5 >= places) g.splits = 1;
-  }
+  g.splits = worthwhile_splits(g.splits, (int64_t)((g.M + BM - 1) / BM) * ((g.Ncols + BN - 1) / BN) * count, 256 * (WM * WN > 64 * 64 ? 2 : 3));
   dim3 grid((unsigned)((g.M + BM - 1) / BM), (unsigned)((g.Ncols + BN - 1) / BN), (unsigned)(count * g.splits));
   constexpr int NT = 64 * (BM / WM) * (BN / WN);
   const bool uni = g.CPT % 4 == 0 && g.ks * g.ks <= 32 && g.Kchunks % 4 == 0;
@@ -1263,21 +1258,14 @@ static void launch_frag_t(const PtrTab& ws, const CPtrTab& wts, const IGemm& g_i
 // Convolution forward / input gradient with fragment-packed filters (g.b_off points at the fragment copy).
 // The patch-in-LDS kernel applies to windows larger than 1 x 1 over a multiple of 32 channels whose patch (plus the
 // pixel table, 84 bytes per pixel) fits 64 KiB of LDS; the contraction is split at most once per channel chunk.
+// decided: g.splits is the split to take, not the most.
 template <int BM, int BN, int WM, int WN>
-static bool launch_halo_t(const PtrTab& ws, const CPtrTab& wts, const IGemm& g_in, const Epilogue& ep, int count, bool xcd_order, hipStream_t s) {
+static bool launch_halo_t(const PtrTab& ws, const CPtrTab& wts, const IGemm& g_in, const Epilogue& ep, int count, bool xcd_order, hipStream_t s,
+                          bool decided = false) {
   if (g_in.ks < 2 || g_in.C % 32 || g_in.OW + g_in.ks - 1 != g_in.W + 2 * g_in.pad) return false;
   IGemm g = g_in;
   g.splits = std::min(g.splits, g.C / 32);
-  {
-    // A split of up to six ways is not worth its partials and second pass once the tiles alone take a fifth of the
-    // resident places (conv5 forward of the AlexNet shape at 18 learners, 396 tiles on 512 places: 92 us unsplit against
-    // 104 + 25 us; conv3 forward at 8 learners, 264 tiles: two-way split 60 + 18 us for the second pass; over a run of
-    // config 4 the calcGradient phase takes 0.230 ms per update with this rule against 0.237 ms when only two-way
-    // splits of tiles filling 60 % of the places were dropped, and 0.233 ms when nothing is split)
-    const int64_t tiles = (int64_t)((g.M + BM - 1) / BM) * ((g.Ncols + BN - 1) / BN) * count;
-    const int64_t places = 256 * (WM * WN > 64 * 64 ? 2 : 3);
-    if (g.splits <= 6 && tiles * 5 >= places) g.splits = 1;
-  }
+  if (!decided) g.splits = worthwhile_splits(g.splits, (int64_t)((g.M + BM - 1) / BM) * ((g.Ncols + BN - 1) / BN) * count, 256 * (WM * WN > 64 * 64 ? 2 : 3));
   HaloArgs h;
   h.PW = g.OW + g.ks - 1;
   h.xcd = xcd_order ? 1 : 0;
@@ -1315,11 +1303,7 @@ static bool launch_halo_seq_t(const PtrTab& ws, const CPtrTab& wts, const IGemm&
   IGemm g = g_in;
   const int all_steps = (g.ldb / 16 + 1) / 2;
   g.splits = std::min(g.splits, std::max(1, all_steps / 2));
-  {
-    const int64_t tiles = (int64_t)((g.M + BM - 1) / BM) * ((g.Ncols + BN - 1) / BN) * count;
-    const int64_t places = 256 * (WM * WN > 64 * 64 ? 2 : 3);
-    if (g.splits <= 6 && tiles * 5 >= places) g.splits = 1;
-  }
+  g.splits = worthwhile_splits(g.splits, (int64_t)((g.M + BM - 1) / BM) * ((g.Ncols + BN - 1) / BN) * count, 256 * (WM * WN > 64 * 64 ? 2 : 3));
   HaloSeqArgs h;
   h.PW = g.OW + g.ks - 1;
   h.mg_pw = magic_u32(h.PW);
@@ -1362,15 +1346,11 @@ hipError_t launch_igemm_frag(const PtrTab& ws, const CPtrTab& wts, const IGemm& 
     }
     if (done) return hipGetLastError();
   }
-  // Columns that whole 96s cover with fewer to spare than whole 128s (96, 192, 272 .. 288, ...): 256 x 96 tiles, 64 x 96 a
-  // wavefront, three quarters of the products of a 128-column tile for the same filter reads per product.  5 x 5 over 256
-  // channels, 96 columns, 27 x 27 outputs: 256 images of one learner 212 -> 169 us, 2 / 6 / 15 learners of 16 on versions of
-  // their own 54 / 123 / 205 -> 46 (split, with its second pass) / 122 / 171.
-  const bool c96 = g.Ncols > 64 && (g.Ncols + 95) / 96 * 96 < (g.Ncols + 127) / 128 * 128;
   // own: most learners of this call read a weight version of their own (lambda-softsync) rather than a shared one
   int same = 0;
   for (int k = 1; k < count; k++) same += wts.p[k] == wts.p[0] ? 1 : 0;
   const bool own = count > 1 && 2 * same < count;
+  const ConvProduct product{g.M, g.Ncols, g.C, g.ks, count, own, g.splits};
   // Narrow layers: 256-row tiles (64 x 32 per wavefront) once there are enough of them to fill the chip, else 128 rows.
   // Measured on the CIFAR-shaped layers (18 learners x 128 images): 5x5 over 32 channels, 16x16 images, 39 us against
   // 46 us with 128-row tiles and 68 us for the tap-by-tap gather; 8x8 images 27 us against 33 us and 43 us.
@@ -1381,25 +1361,20 @@ hipError_t launch_igemm_frag(const PtrTab& ws, const CPtrTab& wts, const IGemm& 
   } else if (g.Ncols <= 64) {
     if (launch_halo_t<128, 64, 64, 32>(ws, wts, g, ep, count, own, s)) return hipGetLastError();
   }
-  if (g.Ncols > 64) {
-    // Layers of whole 256-column tiles: 128 x 256, every filter fragment serves four products.  Others take 128-row tiles, three
-    // workgroups on a compute unit, or 256-row ones, two, which read the fragments half as often: whichever fills its places
-    // better (halo_time, in us of a step of 32 channels of one tap).  3 x 3 over 384 channels, 384 columns, 256 images of one
-    // learner: 1 014 tiles in 122 us against 507, a whole round, in 98; twelve learners of 16 on one version: 792 tiles in 114 us
-    // against 396 in 89; 18 of them, 1 188 and 594 tiles: 135 and 138.  With a version per learner the fragments are the larger
-    // part of a workgroup's traffic (18 learners: 120 us against 101).  Also measured slower: 128 x 64 wave tiles in two-wavefront blocks, eight-wavefront 256 x 128 blocks, 256 x 256.
-    const auto halo_time = [&](int rows, int places, double full, double two, double one) {
-      const int64_t tiles = (int64_t)((g.M + rows - 1) / rows) * ((g.Ncols + 127) / 128) * count, each = (tiles + 255) / 256;
-      const int left = (int)(each % places);
-      return (double)(each / places) * full + (left == 2 ? two : left == 1 ? one : 0.);
-    };
-    const bool tall = g.Ncols > 128 && halo_time(256, 2, 0.90, 0., 0.47) < (own ? 1.18 : 1.) * halo_time(128, 3, 0.72, 0.58, 0.45);
-    // (a 256-row tile whose patch does not fit is no reason against 128 rows)
-    const bool done = (c96 && launch_halo_t<256, 96, 64, 96>(ws, wts, g, ep, count, own, s)) ||
-                      (g.Ncols % 256 == 0 ? launch_halo_t<128, 256, 128, 64>(ws, wts, g, ep, count, own, s)
-                                          : (tall && launch_halo_t<256, 128, 128, 64>(ws, wts, g, ep, count, own, s)) ||
-                                                launch_halo_t<128, 128, 64, 64>(ws, wts, g, ep, count, own, s));
-    if (done) return hipGetLastError();
+  if (g.Ncols > 64 && g.Ncols % 256 == 0) {     // whole 256-column tiles: every filter fragment serves four products
+    if (launch_halo_t<128, 256, 128, 64>(ws, wts, g, ep, count, own, s)) return hipGetLastError();
+  } else if (g.Ncols > 64) {
+    // (also measured slower: 128 x 64 wave tiles in two-wavefront blocks, eight-wavefront 256 x 128 blocks, 256 x 256)
+    ConvChoice choice[3];
+    const int n = conv_choices(product, choice);
+    for (int k = 0; k < n; k++) {                // the next one where a patch does not fit
+      IGemm gs = g;
+      gs.splits = choice[k].splits;
+      const bool done = choice[k].tile == ConvTile::k256x96   ? launch_halo_t<256, 96, 64, 96>(ws, wts, gs, ep, count, own, s, true)
+                        : choice[k].tile == ConvTile::k256x128 ? launch_halo_t<256, 128, 128, 64>(ws, wts, gs, ep, count, own, s, true)
+                                                               : launch_halo_t<128, 128, 64, 64>(ws, wts, gs, ep, count, own, s, true);
+      if (done) return hipGetLastError();
+    }
   }
   // Wave tile 128 x 64 (two wavefronts per SIMD, accumulators in ordinary registers) wins where the columns fill
   // whole 256-wide tiles: each B fragment then serves four MFMAs instead of two.  Measured slower: 256 x 128 blocks,
@@ -1408,10 +1383,11 @@ hipError_t launch_igemm_frag(const PtrTab& ws, const CPtrTab& wts, const IGemm& 
   // LDS its bandwidth becomes the limit instead of the vector L1's.
   if (g.Ncols <= 32) launch_frag_t<128, 32, 32, 32>(ws, wts, g, ep, count, s);
   else if (g.Ncols <= 64) launch_frag_t<128, 64, 64, 32>(ws, wts, g, ep, count, s);
-  // (the tap-by-tap kernel: only where the 256-row tiles fill the chip; 3 x 3 over 48 channels, 54 x 54 outputs, 1 / 2 / 6 / 15
-  // learners of 16 images: 15 / 20 / 60 / 123 us with 128 x 128 tiles, 18 / 21 / 63 / 117 with these)
-  else if (c96 && (int64_t)((g.M + 255) / 256) * ((g.Ncols + 95) / 96) * count >= 256) launch_frag_t<256, 96, 64, 96>(ws, wts, g, ep, count, s);
-  else if (g.Ncols % 256 == 0) launch_frag_t<128, 256, 128, 64>(ws, wts, g, ep, count, s);
+  else if (frag_takes_96(product, (g.Kchunks + 3) / 4)) {
+    IGemm gs = g;
+    gs.splits = 1;
+    launch_frag_t<256, 96, 64, 96>(ws, wts, gs, ep, count, s);
+  } else if (g.Ncols % 256 == 0) launch_frag_t<128, 256, 128, 64>(ws, wts, g, ep, count, s);
   else launch_frag_t<128, 128, 64, 64>(ws, wts, g, ep, count, s);
   return hipGetLastError();
 }

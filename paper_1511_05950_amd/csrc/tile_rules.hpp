@@ -23,4 +23,97 @@ inline int64_t input_pixel_groups(int N, int Hp, int Wp) {
   return groups < 16384 ? groups : 16384;
 }
 
+// ---- forward pass and input gradient of a convolution, bf16
+
+// A split of up to six ways is not worth its partials and second pass once the tiles alone take a fifth of the resident
+// places (conv5 forward of the AlexNet shape at 18 learners, 396 tiles on 512 places: 92 us unsplit against
+// 104 + 25 us; conv3 forward at 8 learners, 264 tiles: two-way split 60 + 18 us for the second pass; over a run of
+// the 18-softsync benchmark the calcGradient phase takes 0.230 ms per update with this rule against 0.237 ms when only two-way
+// splits of tiles filling 60 % of the places were dropped, and 0.233 ms when nothing is split).
+inline int worthwhile_splits(int splits, int64_t tiles, int places) { return splits <= 6 && tiles * 5 >= places ? 1 : splits; }
+
+// A product: M positions, Ncols columns, ks x ks windows over C channels, `count` learners.  own: most of
+// them read a weight version of their own.  splits: what the contraction may be split into (never more than that: it is what
+// the scratch memory holds).
+struct ConvProduct {
+  int64_t M;
+  int Ncols, C, ks, count;
+  bool own;
+  int splits;
+};
+enum class ConvTile { k128x128, k256x128, k256x96 };
+struct ConvChoice {
+  ConvTile tile;
+  int splits;
+  double us;
+};
+// Times in us: start of a launch, filling a patch with 32 channels (tap by tap: start of a workgroup), a step of 32 values of the
+// contraction with one, two, three workgroups on a compute unit (the last the places it has); a chip whose places are partly empty
+// is faster by `spare` of the empty part.  Fitted to 1 243 products of 200 random networks and the AlexNet-shaped one (72 to 512
+// columns, windows of 2 to 7, 30 to 500 000 positions, 1 to 30 learners), each in every form, split and not: off by 7 to 10 %.
+struct ConvTileTimes {
+  int rows, cols, places;
+  double start, fill, step[3], spare;
+  int64_t tiles(const ConvProduct& p) const { return (p.M + rows - 1) / rows * ((p.Ncols + cols - 1) / cols) * p.count; }
+};
+inline double conv_time(const ConvTileTimes& t, const ConvProduct& p, int splits, int fills, int steps) {
+  const int64_t groups = t.tiles(p) * splits, each = (groups + 255) / 256;
+  const int left = (int)(each % t.places);
+  const double full = t.step[t.places - 1], rounds = (double)(each / t.places) + (left ? t.step[left - 1] / full : 0.);
+  const double empty = 1. - (double)groups / (256. * each);
+  const double second_pass = splits > 1 ? 3.5 + 4e-6 / 4.5 * splits * (double)p.M * p.Ncols * p.count : 0.;
+  return t.start + rounds * (full * (1. - t.spare * empty) * steps + t.fill * fills) + second_pass;
+}
+// The form in question has to be better than the plain one by more than the times are off.
+constexpr double kConvMargin = 1.02;
+// Columns that whole 96s cover with fewer to spare than whole 128s: 72 .. 96, 136 .. 192, 264 .. 288, 392 .. 480, ...
+inline bool spares_columns_96(int Ncols) { return (Ncols + 95) / 96 * 96 < (Ncols + 127) / 128 * 128; }
+
+// Tiles of a product of the patch-in-LDS kernel with more than 64 columns, no multiple of 256, the cheapest first; returns how many.
+//   128 x 128: three workgroups on a compute unit.
+//   256 x 128, more than 128 columns: two, which read the filter fragments half as often.
+//   256 x 96, where that spares columns: two, and up to a quarter fewer products, in larger steps.  272 columns, 3 x 3 over 128, 15 learners of 2 704
+//     positions: 51 us with 128 x 128, 35 here; 448 columns, 5 x 5 over 448, 29 learners of 1 300: 375 and 416; 96 columns, 3 x 3
+//     over 96, 4 learners of 5 832: 16, and 25 split three ways.  Taken wherever it spares columns, it was the slower one by
+//     more than 3 % in 145 of 544 products, by up to 60 %; by these times in 5, by up to 11 %.
+// With a weight version per learner the fragments are the larger part of the traffic, and 128 x 128 has to be better by more than
+// that (3 x 3 over 384, 384 columns, 18 learners: 120 us against 101 with 256 x 128).
+inline int conv_choices(const ConvProduct& p, ConvChoice (&out)[3]) {
+  static const ConvTileTimes k128 = {128, 128, 3, 7.6, 2.7, {0.21, 0.32, 0.47}, 0.36}, k256 = {256, 128, 2, 9.5, 2.0, {0.40, 0.645, 0}, 0.34},
+                             k96 = {256, 96, 2, 8.7, 2.0, {0.31, 0.52, 0}, 0.39};
+  const int chunks = (p.C + 31) / 32, most = p.splits < chunks ? p.splits : chunks;
+  auto time = [&](const ConvTileTimes& t, int splits) {
+    const int fills = (chunks + splits - 1) / splits;
+    return conv_time(t, p, splits, fills, fills * p.ks * p.ks);
+  };
+  int n = 0;
+  auto add = [&](ConvTile tile, int splits, double us) {
+    int at = n++;
+    for (; at > 0 && out[at - 1].us > us; at--) out[at] = out[at - 1];
+    out[at] = ConvChoice{tile, splits, us};
+  };
+  const bool wide = p.Ncols > 128;
+  const int s128 = worthwhile_splits(most, k128.tiles(p), 256 * 3);
+  add(ConvTile::k128x128, s128, time(k128, s128) * (p.own && wide ? 1.18 : 1.));
+  if (wide) {
+    const int s256 = worthwhile_splits(most, k256.tiles(p), 256 * 2);
+    add(ConvTile::k256x128, s256, time(k256, s256) * (p.own ? 1. : kConvMargin));
+  }
+  if (spares_columns_96(p.Ncols)) {
+    const double whole = time(k96, 1) * kConvMargin, split = time(k96, most) * kConvMargin * kConvMargin;
+    const bool splits = most > 1 && split < whole;
+    add(ConvTile::k256x96, splits ? most : 1, splits ? split : whole);
+  }
+  return n;
+}
+// The kernel that gathers tap by tap, `steps` of 32 values: 256 x 96 tiles, never split, instead of 128 x 128?  72 columns, 7 x 7 over 328
+// channels, 17 learners of 7 320 positions: 659 us with 128 x 128, 547 with 256 x 96; 448 columns, 3 x 3 over 232, 5 learners of
+// 2 772: 132 and 213.
+inline bool frag_takes_96(const ConvProduct& p, int steps) {
+  static const ConvTileTimes k128 = {128, 128, 3, 4.8, 2.3, {0.43, 0.57, 0.92}, 0.13}, k96 = {256, 96, 2, 5.4, 3.5, {0.68, 1.13, 0}, 0.19};
+  if (p.Ncols <= 64 || !spares_columns_96(p.Ncols)) return false;
+  const int s128 = worthwhile_splits(p.splits, k128.tiles(p), 256 * 3);
+  return conv_time(k96, p, 1, 1, steps) * kConvMargin < conv_time(k128, p, s128, 1, (steps + s128 - 1) / s128);
+}
+
 }  // namespace sasgd

@@ -23,6 +23,17 @@ int main() {
       int N, Hp, Wp;
       if (scanf("%d %d %d", &N, &Hp, &Wp) != 3) return 1;
       printf("%d\n", (int)input_pixel_groups(N, Hp, Wp));
+    } else if (!strcmp(rule, "conv") || !strcmp(rule, "taps")) {
+      ConvProduct p;
+      int own, steps;
+      if (scanf("%ld %d %d %d %d %d %d %d", &p.M, &p.Ncols, &p.C, &p.ks, &p.count, &own, &p.splits, &steps) != 8) return 1;
+      p.own = own != 0;
+      ConvChoice c[3];
+      const int n = conv_choices(p, c);
+      for (int k = 1; k < n; k++)
+        if (c[k].us < c[k - 1].us) return 1;
+      if (rule[0] == 'c') printf("%d %d %d\n", (int)c[0].tile, c[0].splits, n);
+      else printf("%d\n", (int)frag_takes_96(p, steps));
     } else {
       return 1;
     }
@@ -30,6 +41,89 @@ int main() {
   return 0;
 }
 """
+
+# Measured on one card, us with the second pass: products whose forms differ most, either way, and a draw of others.
+# positions, columns, channels, window, learners, versions of their own, most splits; 128 x 128 and 256 x 128 tiles (split by
+# the plain rule), 256 x 96 whole and split
+PATCH = [
+    (252, 424, 352, 5, 1, 0, 11, 16.6, 22.4, 83, 19.4),
+    (392, 96, 320, 3, 13, 0, 10, 21.8, None, 43.3, 21.6),
+    (392, 160, 224, 7, 2, 0, 7, 21.2, 30.2, 91.3, 25.7),
+    (400, 192, 128, 5, 22, 0, 4, 28.4, 36.3, 35.6, 31.9),
+    (432, 160, 224, 5, 2, 0, 7, 17.3, 22.5, 54.8, 19.6),
+    (441, 72, 288, 3, 6, 0, 9, 16.2, None, 36.5, 17.3),
+    (450, 288, 384, 7, 4, 0, 12, 39.8, 46.6, 149.5, 40.7),
+    (500, 80, 192, 5, 3, 0, 6, 16.6, None, 46.1, 19),
+    (800, 192, 352, 7, 1, 0, 11, 20.8, 30.4, 137.9, 26.6),
+    (1152, 160, 192, 5, 1, 0, 6, 16.4, 21.8, 46.4, 19.4),
+    (1500, 80, 96, 3, 10, 0, 3, 17.6, None, 17.2, 18.6),
+    (1519, 88, 480, 3, 2, 0, 15, 19.8, None, 60.3, 21),
+    (1568, 192, 64, 5, 6, 0, 2, 17.9, 28.4, 22.5, 25.2),
+    (1575, 168, 416, 3, 1, 0, 13, 18.3, 19.2, 52, 19),
+    (1575, 264, 96, 3, 20, 0, 1, 35.9, 32.1, 27.6, 27.5),
+    (1701, 160, 224, 3, 16, 0, 2, 37.5, 40.2, 35.2, 43.3),
+    (2048, 144, 160, 3, 4, 1, 5, 21.8, 24.4, 24.4, 23.6),
+    (2704, 272, 128, 3, 15, 0, 1, 49.9, 40, 34.4, 34.6),
+    (2704, 272, 128, 3, 15, 1, 1, 47.2, 39.4, 34.4, 34.3),
+    (3136, 96, 64, 3, 6, 0, 2, 20.7, None, 15, 21.5),
+    (3136, 96, 64, 3, 6, 1, 2, 21.4, None, 15, 20.8),
+    (3136, 96, 64, 3, 8, 0, 2, 13.8, None, 15, 23.2),
+    (3136, 192, 128, 5, 12, 0, 1, 60.2, 75.4, 60.7, 60.2),
+    (5832, 96, 96, 3, 3, 1, 3, 21.8, None, 16.9, 22.2),
+    (5832, 96, 96, 3, 5, 1, 3, 16, None, 17.7, 26),
+    (6272, 80, 64, 3, 15, 1, 1, 22.2, None, 21.4, 21),
+    (6936, 160, 96, 3, 1, 0, 3, 21.3, 22.2, 17.7, 21.8),
+    (11520, 440, 256, 3, 18, 0, 1, 479.8, 407.7, 412.7, 418.7),
+    (11664, 96, 256, 5, 9, 1, 1, 140.8, None, 111, 111.6),
+    (11664, 96, 256, 5, 12, 0, 1, 173.7, None, 163.8, 164.3),
+    (40848, 288, 256, 3, 2, 0, 1, 153.9, 129.7, 114.5, 116.8),
+    (45864, 192, 192, 2, 5, 0, 1, 117.1, 115.7, 103.9, 107.7),
+    (116272, 160, 160, 3, 2, 0, 1, 200.2, 169, 148.3, 142.5),
+    (212868, 184, 256, 3, 5, 0, 1, 1305.5, 1070.6, 931.7, 947.8),
+    (357216, 96, 160, 3, 3, 0, 1, 447.4, None, 313.8, 316.6),
+    (357216, 160, 96, 3, 3, 0, 1, 544, 468.8, 398.6, 402.7),
+    (450, 384, 288, 7, 4, 0, 9, 43, 33.6, None, None),
+    (672, 320, 256, 5, 2, 0, 8, 22.1, 26.8, None, None),
+    (2080, 224, 160, 3, 5, 0, 4, 20.3, 32.2, None, None),
+    (2080, 312, 224, 7, 5, 0, 3, 82.6, 128.5, None, None),
+    (2704, 384, 256, 3, 4, 1, 3, 39.4, 43.4, None, None),
+    (2704, 384, 256, 3, 12, 1, 1, 80.7, 66.1, None, None),
+    (2704, 384, 256, 3, 18, 1, 1, 104.4, 99.6, None, None),
+    (2704, 384, 384, 3, 18, 1, 1, 145.3, 138.5, None, None),
+    (2772, 232, 448, 5, 5, 0, 3, 92.3, 139.4, None, None),
+    (4988, 352, 192, 3, 7, 0, 1, 66, 52, None, None),
+    (8100, 384, 160, 2, 1, 0, 4, 15, 28.4, None, None),
+    (12470, 504, 320, 3, 2, 0, 1, 104.2, 80, None, None),
+    (17595, 320, 96, 2, 28, 0, 1, 217.2, 222.3, None, None),
+    (124384, 488, 160, 3, 1, 0, 1, 215.5, 185.1, None, None),
+]
+# positions, columns, channels, window, learners, most splits; 128 x 128 tiles, 256 x 96 whole
+TAP_BY_TAP = [
+    (18, 448, 304, 7, 4, 38, 22.3, 300.2),
+    (18, 448, 448, 7, 4, 38, 26.6, 438.2),
+    (28, 72, 344, 7, 13, 47, 20.7, 309.9),
+    (50, 136, 344, 5, 9, 34, 17.9, 171.7),
+    (63, 192, 368, 5, 13, 24, 21, 172),
+    (84, 72, 368, 5, 23, 27, 21.8, 172),
+    (704, 424, 456, 5, 4, 7, 61.8, 214.8),
+    (704, 440, 440, 3, 2, 13, 27.1, 83.3),
+    (800, 96, 72, 2, 18, 2, 16.3, 12.9),
+    (1280, 96, 248, 3, 5, 12, 21.3, 48),
+    (1380, 392, 112, 3, 22, 1, 50.4, 64),
+    (2048, 160, 144, 3, 4, 5, 23.9, 30.6),
+    (2048, 160, 144, 3, 6, 4, 22.8, 30.4),
+    (5984, 88, 48, 2, 21, 1, 18.8, 15.6),
+    (6050, 160, 272, 3, 9, 1, 105.2, 93.5),
+    (6208, 184, 280, 3, 9, 1, 94.7, 83.3),
+    (6270, 96, 72, 5, 1, 13, 21.5, 39),
+    (7440, 288, 280, 3, 2, 2, 50.4, 57.9),
+    (7986, 168, 104, 3, 2, 3, 19.2, 25.7),
+    (8008, 160, 504, 2, 4, 2, 49.2, 49.9),
+    (24300, 192, 72, 7, 22, 1, 872.6, 778.8),
+    (26364, 192, 112, 3, 2, 1, 46.6, 40.2),
+    (46656, 96, 48, 3, 4, 1, 34.8, 39.2),
+    (97440, 192, 160, 5, 1, 1, 217.7, 222.1),
+]
 
 
 @pytest.fixture(scope="module")
@@ -58,3 +152,34 @@ def test_input_layout(ask):
 
 def test_small_images_share_workgroups(ask):
     assert ask([("pixels", *q) for q in ((2048, 4, 4), (1, 3, 5), (4096, 3, 9), (128, 32, 32), (16, 512, 512))]) == [(128,), (1,), (432,), (512,), (16384,)]
+
+
+def test_convolution_tiles_are_the_faster_ones(ask):
+    """The form that is chosen against the plain one (128 x 128; 256 x 128 for more than 128 columns on versions of their own) and the
+    best: by column count alone 256 x 96 is up to 60 % slower than the plain one."""
+    behind, chosen, best = [], 0, 0
+    for row, (tile, splits, n) in zip(PATCH, ask([("conv", *row[:7], 0) for row in PATCH])):
+        (m, cols, c, ks, learners, own, most), times = row[:7], row[7:]
+        assert n == sum(t is not None for t in times[:3]) and 1 <= splits <= most
+        t = times[tile + (tile == 2 and splits > 1)]
+        plain = times[1 if own and cols > 128 else 0]
+        assert t <= 1.12 * plain, row
+        behind += [row] if t > 1.03 * plain else []
+        chosen, best = chosen + t, best + min(x for x in times if x is not None)
+    assert len(behind) <= 2, behind
+    assert chosen <= 1.02 * best
+
+
+def test_tap_by_tap_tiles_are_the_faster_ones(ask):
+    steps = [-(-(row[2] // 8 * row[3] ** 2) // 4) for row in TAP_BY_TAP]
+    behind, chosen, best = [], 0, 0
+    for row, (takes,) in zip(TAP_BY_TAP, ask([("taps", *row[:5], 0, row[5], n) for row, n in zip(TAP_BY_TAP, steps)])):
+        plain, t96 = row[6:]
+        t = t96 if takes else plain
+        assert t <= 1.12 * plain, row
+        behind += [row] if t > 1.03 * plain else []
+        chosen, best = chosen + t, best + min(plain, t96)
+    assert len(behind) <= 1, behind
+    assert chosen <= 1.03 * best
+    # 64 columns and fewer, and columns that whole 96s do not spare
+    assert ask([("taps", 10**6, n, 128, 3, 18, 0, 1, 36) for n in (64, 128, 256, 200, 384)]) == [(0,)] * 5
