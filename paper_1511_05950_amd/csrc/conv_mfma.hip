@@ -2274,12 +2274,15 @@ __global__ __launch_bounds__(256) void wgrad_finish_kernel(PtrTab ws, PtrTab gra
 }
 
 // The same where there are many splits and few columns, for a first layer seen through a space-to-depth input, and for a window
-// too large for the sums in LDS: a lane adds four im2col columns of every sixteenth split, the sixteen wavefronts' sums are added
-// through LDS, and each column's place in the flat filter is looked up and written on its own.  blockIdx.y selects a run of 256
-// columns.  11 x 11 / 4 first layer of the AlexNet shape, 256 images, 254 splits: 8 us; a lane per column that adds all splits
-// one after the other took 80.
-__global__ __launch_bounds__(1024) void wgrad_columns_kernel(PtrTab ws, PtrTab grads, IGemm g, VConv v, int64_t w_off, int64_t b_off) {
-  __shared__ float4 sums[16][64];
+// too large for the sums in LDS: a lane adds four im2col columns of every W-th split, the W wavefronts' sums are added through
+// LDS, and each column's place in the flat filter is looked up and written on its own.  blockIdx.y selects a run of 256
+// columns.  Of 818 layers of random networks and the AlexNet-shaped one with 1 to 256 splits, sixteen wavefronts were the faster ones
+// nowhere, at 64 and more splits level (5 us), and below 16 splits up to three times as slow, most of them with nothing to add
+// (344 filters of 576 columns, 29 learners, 3 splits: 92 us, 33 with four); at 503 splits 7 us, 11 with four.
+template <int W>
+__global__ __launch_bounds__(64 * W) void wgrad_columns_kernel(PtrTab ws, PtrTab grads, IGemm g, VConv v, int64_t w_off, int64_t b_off) {
+  static_assert(W >= 4, "a thread a column");
+  __shared__ float4 sums[W][64];
   const int z = blockIdx.z, n = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int kcols = g.Kchunks * 8, ldk = kcols + 8, k = blockIdx.y * 256 + 4 * lane;
   const float* part = reinterpret_cast<const float*>((const char*)ws.p[z] + g.scratch_off) + (int64_t)n * ldk;
@@ -2287,7 +2290,7 @@ __global__ __launch_bounds__(1024) void wgrad_columns_kernel(PtrTab ws, PtrTab g
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   if (k < ldk) {                                          // column kcols is the bias gradient, the row's rest padding
 #pragma unroll 8
-    for (int sp = wave; sp < g.splits; sp += 16) {
+    for (int sp = wave; sp < g.splits; sp += W) {
       const float4 p = *reinterpret_cast<const float4*>(part + sp * split_stride + k);
       acc.x += p.x; acc.y += p.y; acc.z += p.z; acc.w += p.w;
     }
@@ -2299,7 +2302,7 @@ __global__ __launch_bounds__(1024) void wgrad_columns_kernel(PtrTab ws, PtrTab g
   const float* f = reinterpret_cast<const float*>(sums) + threadIdx.x;
   float total = f[0];
 #pragma unroll
-  for (int w = 1; w < 16; w++) total += f[w * 256];
+  for (int w = 1; w < W; w++) total += f[w * 256];
   if (col == kcols) {
     ((float*)grads.p[z] + b_off)[n] = total;
     return;
@@ -2440,10 +2443,11 @@ hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm
 #undef SASGD_WGRAD
   if (partial) {
     const int cap = (15360 / (v.ks * v.ks) - 4) & ~3;    // input channels whose sums fit 60 KiB of LDS
-    // (few columns: CIFAR-shaped layers, 128 images of one learner, 256 / 128 / 32 splits: 34 / 19 / 6 us there, 5 / 4 / 4 here)
+    // (few columns, at most 256 K values over all learners: the kernel below 7 / 10 / 14 us at 16 / 32 / 64 and more splits, this one 5 / 5 / 5)
     if (v.s2d > 1 || cap < 4 || (g.splits >= 16 && (int64_t)g.Ncols * count * cols <= 256 * 1024)) {
-      hipLaunchKernelGGL(wgrad_columns_kernel, dim3((unsigned)g.Ncols, (unsigned)((cols + 255) / 256), (unsigned)count), dim3(1024), 0, s, ws, grads, g, v,
-                         w_off, b_off);
+      const dim3 grid((unsigned)g.Ncols, (unsigned)((cols + 255) / 256), (unsigned)count);
+      if (g.splits > 256) hipLaunchKernelGGL(wgrad_columns_kernel<16>, grid, dim3(1024), 0, s, ws, grads, g, v, w_off, b_off);
+      else hipLaunchKernelGGL(wgrad_columns_kernel<4>, grid, dim3(256), 0, s, ws, grads, g, v, w_off, b_off);
       return hipGetLastError();
     }
     // enough workgroups to keep the chip busy: the channels of a filter are divided among several of them

@@ -42,6 +42,11 @@ CASES = {
     "strip_small_images": (net(3, 9, 7, ("conv", 16, 3, 1, 1), ("conv", 24, 5, 1, 2), ("conv", 40, 3, 1, 1), ("avgpool", 3, 2)), 18, 64),
     "strip_two_rows": (net(3, 33, 32, ("conv", 64, 3, 1, 1), ("conv", 48, 3, 1, 0), ("avgpool", 3, 2)), 1, 64),
     "strip_groups": (net(3, 16, 16, ("conv", 32, 3, 1, 1), ("conv", 64, 5, 1, 2), ("conv", 32, 5, 1, 2), ("avgpool", 3, 2)), 4, 64),
+    # space-to-depth first layers, whose second pass adds column by column: one split and a few, columns of one run of 256 and of several
+    "strided_one_split": (net(3, 33, 35, ("conv", 40, 9, 2, 0), ("avgpool", 3, 2)), 1, 40),
+    "strided_few_splits": (net(3, 47, 45, ("conv", 104, 11, 2, 0), ("avgpool", 3, 2)), 3, 12),
+    "strided_many_splits": (net(3, 47, 45, ("conv", 24, 11, 4, 0), ("avgpool", 3, 2)), 48, 3),
+    "most_splits": (net(3, 93, 91, ("conv", 72, 3, 1, 1), ("avgpool", 3, 2)), 8, 1),
     # many taps per channel, input channels in groups of which the last is shorter
     "many_taps": (net(3, 20, 20, ("conv", 40, 3, 1, 1), ("conv", 24, 11, 1, 5), ("avgpool", 3, 2)), 3, 2),
     "uneven_groups": (net(3, 12, 12, ("conv", 136, 3, 1, 1), ("conv", 72, 3, 1, 1), ("avgpool", 3, 2)), 4, 2),
