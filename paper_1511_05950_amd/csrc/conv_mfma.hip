@@ -1219,15 +1219,6 @@ __global__ __launch_bounds__(256) void igemm_finish_kernel(PtrTab ws, CPtrTab wt
   }
 }
 
-int choose_splits(int64_t tiles, int count, int steps, size_t bytes_per_split, size_t scratch_bytes, int64_t target) {
-  // target = workgroups wanted per launch; 600 by default (256..1024 measured, flat between 400 and 768 at 6 and 18 learners)
-  int64_t sp = (target + tiles * count - 1) / (tiles * count);
-  if (sp > steps / 4) sp = steps / 4;                // keep at least four contraction steps per workgroup
-  if (bytes_per_split > 0 && (int64_t)(scratch_bytes / bytes_per_split) < sp) sp = (int64_t)(scratch_bytes / bytes_per_split);
-  if (sp > 64) sp = 64;
-  return sp < 2 ? 1 : (int)sp;
-}
-
 template <int BM, int BN, int WM, int WN, bool BT>
 static void launch_igemm_t(const PtrTab& ws, const CPtrTab& wts, const IGemm& g, const Epilogue& ep, int count, hipStream_t s) {
   dim3 grid((unsigned)((g.M + BM - 1) / BM), (unsigned)((g.Ncols + BN - 1) / BN), (unsigned)(count * g.splits));
@@ -2344,36 +2335,6 @@ static bool launch_strip_t(const PtrTab& ws, const IGemm& g_in, size_t dy_off, s
   return true;
 }
 
-// Tiles and splits of a convolution's weight gradient with more than 64 output channels: the cheapest of the three tile shapes
-// of wgrad_wide_kernel and the 128 x 128 tiles of wgrad_panel_kernel, each at splits that fill one to six rounds of the chip,
-// by their times in us, fitted to the AlexNet-shaped layers at 16 to 288 images:
-//   wide: rounds of 256 workgroups x (14 + 0.58 .. 0.82 a step), nothing overlaps the start and end of a workgroup;
-//   panel: three workgroups share a compute unit and its LDS, 0.42 a step for one, 0.23 a step and workgroup for several.
-// Partial sums cost the second pass their reading.
-struct WgradTiles { int shape, splits; };
-static WgradTiles wgrad_tiles(const IGemm& g, int count, bool wide_ok, size_t scratch_bytes) {
-  static const struct { int rows, cols; double step; } kShape[4] = {{128, 128, 0}, {96, 512, 0.82}, {256, 256, 0.7}, {384, 128, 0.58}};
-  const int cols = g.Kchunks * 8 + 1, steps = (g.M + 31) / 32;
-  const size_t part = (size_t)g.Ncols * (g.Kchunks * 8 + 8) * 4;
-  const int most = (int)std::min<size_t>(std::max<size_t>(1, part ? scratch_bytes / part : 1), std::max(1, steps / 4));
-  WgradTiles best{0, 1};
-  double best_cost = 1e30;
-  for (int k = 0; k < (wide_ok ? 4 : 1); k++) {
-    const int64_t tiles = (int64_t)((g.Ncols + kShape[k].rows - 1) / kShape[k].rows) * ((cols + kShape[k].cols - 1) / kShape[k].cols) * count;
-    for (int round = 0; round <= 6; round++) {
-      int sp = (int)std::min<int64_t>(most, round ? round * 256 / tiles : 1);
-      if (sp < 1) continue;
-      const int each = (steps + sp - 1) / sp;
-      sp = (steps + each - 1) / each;                  // no workgroup without a step
-      const double n = each, units = (double)((tiles * sp + 255) / 256);
-      const double cost = (k ? units * (14 + n * kShape[k].step) : 14 + n * (units > 1 ? 0.23 * units : 0.42)) +
-                          (double)sp * count * part / 4.5e6;
-      if (cost < best_cost) { best_cost = cost; best = WgradTiles{k, sp}; }
-    }
-  }
-  return best;
-}
-
 hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm& g_in, const VConv& v, size_t dy_off, int64_t w_off,
                               int64_t b_off, size_t scratch_bytes, int count, hipStream_t s) {
   IGemm g = g_in;
@@ -2387,10 +2348,10 @@ hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm
   const bool conv = v.ks > 1 || v.s2d > 1;
   // the constant block has to lie within a 31-bit byte offset from the layer's input
   const bool near = g.zero_off >= g.a_off && (g.zero_off - g.a_off + 256) * 2 < ((size_t)1 << 31);
-  int shape = 0;
+  WgradTile shape = WgradTile::k128x128;
   if (conv && g.Ncols > 64 && near) {
-    const WgradTiles t = wgrad_tiles(g, count, incr, scratch_bytes);
-    shape = t.shape;
+    const WgradTiles t = wgrad_tiles(WgradProduct{g.M, g.Ncols, cols, count, scratch_bytes}, incr);
+    shape = t.tile;
     g.splits = t.splits;
   } else {
     // narrow layers run small tiles (24-32 KiB of LDS, few registers): six and more workgroups fit a compute
@@ -2425,11 +2386,11 @@ hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm
   } else if (g.Ncols <= 64) {
     const dim3 grid = grid_of(64, 128);
     SASGD_WGRAD(64, 128, 32, 64);
-  } else if (shape == 1) {
+  } else if (shape == WgradTile::k96x512) {
     hipLaunchKernelGGL((wgrad_wide_kernel<3, 1>), grid_of(96, 512), dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off);
-  } else if (shape == 2) {
+  } else if (shape == WgradTile::k256x256) {
     hipLaunchKernelGGL((wgrad_wide_kernel<4, 2>), grid_of(256, 256), dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off);
-  } else if (shape == 3) {
+  } else if (shape == WgradTile::k384x128) {
     hipLaunchKernelGGL((wgrad_wide_kernel<3, 4>), grid_of(384, 128), dim3(256), 0, s, ws, grads, g, v, dy_off, w_off, b_off);
   } else {
     const dim3 grid = grid_of(128, 128);

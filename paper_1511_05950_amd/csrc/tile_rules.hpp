@@ -1,5 +1,6 @@
 // Which kernel and which tiles serve a layer, from its sizes.  No HIP types: host code and host tests include it alone.
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 namespace sasgd {
@@ -21,6 +22,17 @@ inline int input_row_piece(int Wp) {
 inline int64_t input_pixel_groups(int N, int Hp, int Wp) {
   const int64_t groups = ((int64_t)N * Hp * Wp + 255) / 256;
   return groups < 16384 ? groups : 16384;
+}
+
+// ---- matrix products
+// Splits of a contraction: enough workgroups for the chip, bounded by the contraction's length and the scratch size.
+// target = workgroups wanted per launch; 600 by default (256..1024 measured, flat between 400 and 768 at 6 and 18 learners).
+inline int choose_splits(int64_t tiles, int count, int steps, size_t bytes_per_split, size_t scratch_bytes, int64_t target = 600) {
+  int64_t sp = (target + tiles * count - 1) / (tiles * count);
+  if (sp > steps / 4) sp = steps / 4;                // keep at least four contraction steps per workgroup
+  if (bytes_per_split > 0 && (int64_t)(scratch_bytes / bytes_per_split) < sp) sp = (int64_t)(scratch_bytes / bytes_per_split);
+  if (sp > 64) sp = 64;
+  return sp < 2 ? 1 : (int)sp;
 }
 
 // ---- forward pass and input gradient of a convolution, bf16
@@ -114,6 +126,78 @@ inline bool frag_takes_96(const ConvProduct& p, int steps) {
   if (p.Ncols <= 64 || !spares_columns_96(p.Ncols)) return false;
   const int s128 = worthwhile_splits(p.splits, k128.tiles(p), 256 * 3);
   return conv_time(k96, p, 1, 1, steps) * kConvMargin < conv_time(k128, p, s128, 1, (steps + s128 - 1) / s128);
+}
+
+// ---- weight gradient of a convolution with more than 64 output channels, bf16
+// M positions, Ncols output channels, cols im2col columns with the bias's, `count` learners.
+struct WgradProduct {
+  int64_t M;
+  int Ncols, cols, count;
+  size_t scratch_bytes;
+};
+// The 128 x 128 tiles of wgrad_panel_kernel, three workgroups on a compute unit, and the three shapes of wgrad_wide_kernel, one.
+enum class WgradTile { k128x128, k96x512, k256x256, k384x128 };
+struct WgradTiles {
+  WgradTile tile;
+  int splits;
+};
+// Times in us: start of a launch, start and end of a workgroup (128 x 128: of three), a step of 32 positions with one (two, three)
+// workgroups on a compute unit; steps are faster by `spare` of the part of their loads that brings nothing (output channels and columns
+// behind the last, an empty part of the chip).  Fitted to 686 layers of 200 random networks and the AlexNet-shaped one (72 to 512 output
+// channels, windows of 2 to 7, 30 to 500 000 positions, 1 to 30 learners), each with every shape at several splits: off by 8
+// (the wide shapes) to 13 %.
+struct WgradTimes {
+  int rows, cols;
+  double start, group, step[3], spare;
+};
+constexpr WgradTimes kWgradTimes[4] = {{128, 128, 2.6, 4.9, {0.37, 0.52, 0.745}, 0.18},
+                                       {96, 512, 3.2, 10.0, {0.80, 0, 0}, 0.21},
+                                       {256, 256, 2.8, 11.4, {0.78, 0, 0}, 0.31},
+                                       {384, 128, 2.9, 9.3, {0.67, 0, 0}, 0.33}};
+inline double wgrad_time(WgradTile tile, const WgradProduct& p, int splits) {
+  const WgradTimes& t = kWgradTimes[(int)tile];
+  const int64_t down = (p.Ncols + t.rows - 1) / t.rows, across = (p.cols + t.cols - 1) / t.cols;
+  const int64_t groups = down * across * p.count * splits, each = (groups + 255) / 256, steps = ((p.M + 31) / 32 + splits - 1) / splits;
+  const double load = ((double)p.Ncols / down + (double)p.cols / across) / (t.rows + t.cols);
+  const double faster = 1. - t.spare * (1. - load * groups / (256. * each));
+  double us = t.start + 4.5 + 4e-6 / 6. * splits * p.count * p.Ncols * (p.cols + 7);        // and the second pass
+  if (tile == WgradTile::k128x128) {
+    const int left = (int)(each % 3);
+    us += (each / 3 * t.step[2] + (left ? t.step[left - 1] : 0.)) * steps * faster + (double)((each + 2) / 3) * t.group;
+  } else {
+    us += each * (t.group + t.step[0] * steps * faster);
+  }
+  return us;
+}
+// The cheapest of 128 x 128 tiles at 600 workgroups (choose_splits) and every shape at splits that fill one to six rounds of the chip.
+// wide_ok: wgrad_wide_kernel takes the layer.
+// Against the first alone: of those layers 16 more than 3 % behind (7 more than 6 %, 10 at most), all together 86 % of its time.  With times
+// that were fitted to the AlexNet-shaped layers alone: 99 (46), by up to 29 % (3 x 3 over 160 channels, 144 output channels, 8 learners of
+// 2 048 positions: 28 and 36 us), 88 %.
+inline WgradTiles wgrad_tiles(const WgradProduct& p, bool wide_ok) {
+  const int64_t steps = (p.M + 31) / 32;
+  const size_t part = (size_t)p.Ncols * (p.cols + 7) * 4;
+  const int64_t held = (int64_t)(p.scratch_bytes / part), most = held < 1 || steps < 8 ? 1 : held < steps / 4 ? held : steps / 4;
+  const int64_t plain = (int64_t)((p.Ncols + 127) / 128) * ((p.cols + 127) / 128);
+  WgradTiles best{WgradTile::k128x128, choose_splits(plain, p.count, (int)steps, part, p.scratch_bytes)};
+  double least = wgrad_time(best.tile, p, best.splits);
+  for (int k = 0; k < (wide_ok ? 4 : 1); k++) {
+    const WgradTimes& t = kWgradTimes[k];
+    const int64_t tiles = (int64_t)((p.Ncols + t.rows - 1) / t.rows) * ((p.cols + t.cols - 1) / t.cols) * p.count;
+    for (int round = 0; round <= 6; round++) {
+      int64_t sp = round ? round * 256 / tiles : 1;
+      if (sp > most) sp = most;
+      if (sp < 1) continue;
+      const int64_t each = (steps + sp - 1) / sp;
+      sp = (steps + each - 1) / each;                  // no workgroup without a step
+      const double us = wgrad_time((WgradTile)k, p, (int)sp) * (k ? 1. : 1.01);
+      if (us < least) {
+        least = us;
+        best = WgradTiles{(WgradTile)k, (int)sp};
+      }
+    }
+  }
+  return best;
 }
 
 }  // namespace sasgd
