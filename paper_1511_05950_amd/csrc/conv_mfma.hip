@@ -2053,9 +2053,13 @@ __global__ __launch_bounds__(512, 2) void wgrad_strip_kernel(PtrTab ws, IGemm g,
   rsrc_x.w = 0x00020000;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   // Written out because the compiler, which cannot tell the buffers apart, would wait for all of them in front of every LDS read.
+  // m0 is a register that it never allocates (hence its warning) but whose values it shares between neighbouring uses of its own.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
   auto dma = [&](const v4i_t& rsrc, uint32_t dst, int voff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds0 + dst), "v"(voff), "s"(rsrc) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds0 + dst), "v"(voff), "s"(rsrc) : "memory", "m0");
   };
+#pragma clang diagnostic pop
   auto request = [&](int t, int buf) {
     const int m0 = t * MT, m_last = min(m0 + MT, g.M) - 1;
 #pragma unroll
