@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256) void pool_bwd_kernel(PtrTab ws, size_t dy_off,
     int ih = (int)(r % sh.H);
     int n = (int)(r / sh.H);
     float acc = 0.f;
-    if (!use_mask || ldf(mask + i) > 0.f) {
+    if (MAX || !use_mask || ldf(mask + i) > 0.f) {          // (max: the winners know)
       // windows that contain (ih, iw): oh*stride <= ih < oh*stride + ks
       int oh_lo = ih - sh.ks + 1 > 0 ? (ih - sh.ks + sh.stride) / sh.stride : 0;
       int oh_hi = min(sh.OH - 1, ih / sh.stride);
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(256) void pool_bwd_vec8_kernel(PtrTab ws, size_t dy
           for (int e = 0; e < 8; e++) acc[e] += d.get(e) / inv;
         }
       }
-    if (use_mask) {
+    if (!MAX && use_mask) {
       bf8 mk;
       mk.v = *reinterpret_cast<const uint4*>(mask + i * 8);
 #pragma unroll
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(256) void pool_bwd_3x3s2_kernel(PtrTab ws, size_t d
     // All reads are requested before the first is used: windows outside the output and block elements outside the
     // input read a clamped (valid) address and are discarded by a predicate instead of a branch around the load.
     bool w_ok[4];
-    uint4 dv[4];
+    uint4 dw[4];
     uint2 av[4];
     float inv[4];
 #pragma unroll
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(256) void pool_bwd_3x3s2_kernel(PtrTab ws, size_t d
         w_ok[q] = oh >= 0 && oh < sh.OH && ow >= 0 && ow < sh.OW;
         const int ohc = min(max(oh, 0), sh.OH - 1), owc = min(max(ow, 0), sh.OW - 1);
         const int64_t o = ((((int64_t)n * sh.OH + ohc) * sh.OW + owc) * C8 + c8) * 8;
-        dv[q] = *reinterpret_cast<const uint4*>(dy + o);
+        dw[q] = *reinterpret_cast<const uint4*>(dy + o);
         av[q] = make_uint2(0u, 0u);
         if (MAX) av[q] = *reinterpret_cast<const uint2*>(arg + o);
         inv[q] = 1.f;
@@ -484,7 +484,7 @@ __global__ __launch_bounds__(256) void pool_bwd_3x3s2_kernel(PtrTab ws, size_t d
       for (int ww = 0; ww < 2; ww++) {
         const int wq = 2 * wh + ww;
         bf8 d;
-        d.v = w_ok[wq] ? dv[wq] : make_uint4(0u, 0u, 0u, 0u);
+        d.v = w_ok[wq] ? dw[wq] : make_uint4(0u, 0u, 0u, 0u);
         const uint2 ar = av[wq];
         // window (oh, ow) = (a - 1 + wh, b - 1 + ww) starts at row 2 oh, column 2 ow: block row dh sits at window row
         // 2 (a - oh) + dh, i.e. 2, 3 for the window above (only 2 is inside), 0, 1 for the own one
