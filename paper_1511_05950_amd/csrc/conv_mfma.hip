@@ -2307,36 +2307,20 @@ __global__ __launch_bounds__(64 * W) void wgrad_columns_kernel(PtrTab ws, PtrTab
   if (dst >= 0) ((float*)grads.p[z] + w_off + (int64_t)n * v.Creal * v.ksr * v.ksr)[dst] = total;
 }
 
-template <int TM, int WN, int TN, int MT>
-static bool launch_strip_t(const PtrTab& ws, const IGemm& g_in, size_t dy_off, size_t scratch_bytes, int count, int* splits, hipStream_t s) {
-  IGemm g = g_in;
+template <int F>
+static void launch_strip_t(const PtrTab& ws, const IGemm& g, size_t dy_off, const StripPlan& p, int count, hipStream_t s) {
+  constexpr StripForm f = kStripForms[F];
   StripArgs h;
-  h.PW = g.OW + g.ks - 1;
-  const int rows = (MT + g.OW - 2) / g.OW + 1;          // output rows a tile can touch
-  const int images = (rows + g.OH - 2) / g.OH + 1;           // and images those rows can belong to
-  const int64_t patch = ((int64_t)(rows + (g.ks - 1) * images) * h.PW * g.C * 2 + 1023) / 1024 * 1024;
-  if (patch > 64 * 1024) return false;
-  h.patch = (int)patch;
-  h.buf = TM * MT * 64 + h.patch + MT * 4;
-  const size_t bytes = std::max((size_t)2 * h.buf, (size_t)8 * 4096);
-  if (bytes > 160 * 1024) return false;
-  h.by_pw.set(h.PW);
+  h.PW = p.PW;
+  h.tiles = p.tiles;
+  h.per = p.per;
+  h.patch = p.patch;
+  h.buf = p.buf;
+  h.by_pw.set(p.PW);
   h.by_cpt.set(g.CPT);
   h.by_band.set(g.OH + g.ks - 1);
-  const int panels = (g.Kchunks * 8 + 31) / 32, groups = (panels + WN * TN) / (WN * TN);   // and the bias's place
-  // Below this the tiles a workgroup has to itself are too few to pay for its start and its sum over the position groups
-  // (CIFAR-shaped conv2, 64 images of one learner: 11 us with the gathering kernel, 14 here; 8 x 64 images: 25 and 19).
-  if ((int64_t)g.M * groups * count < 65536) return false;
-  h.tiles = (g.M + MT - 1) / MT;
-  // one workgroup a compute unit: whole rounds of 256 of them
-  const size_t part = (size_t)g.Ncols * (g.Kchunks * 8 + 8) * 4;
-  const int most = (int)std::min<int64_t>(h.tiles, std::max<int64_t>(1, (int64_t)(scratch_bytes / part)));
-  const int want = std::max(1, std::min(most, 256 / (groups * count)));
-  h.per = (h.tiles + want - 1) / want;
-  g.splits = (h.tiles + h.per - 1) / h.per;
-  *splits = g.splits;
-  hipLaunchKernelGGL((wgrad_strip_kernel<TM, WN, TN, MT>), dim3(1, (unsigned)groups, (unsigned)(count * g.splits)), dim3(512), bytes, s, ws, g, dy_off, h);
-  return true;
+  hipLaunchKernelGGL((wgrad_strip_kernel<f.TM, f.WN, f.TN, f.MT>), dim3(1, (unsigned)p.groups, (unsigned)(count * p.splits)), dim3(512), p.lds, s, ws, g,
+                     dy_off, h);
 }
 
 hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm& g_in, const VConv& v, size_t dy_off, int64_t w_off,
@@ -2366,14 +2350,17 @@ hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm
     g.splits = choose_splits(tiles, count, (g.M + 31) / 32, (size_t)g.Ncols * (g.Kchunks * 8 + 8) * 4, scratch_bytes, g.Ncols <= 64 ? 1200 : 600);
   }
   const int partial = (g.splits > 1 || conv) ? 1 : 0;
-  bool done = false;
-  if (conv && g.Ncols <= 64 && g.OW + g.ks - 1 == g.W + 2 * g.pad) {
-    const int panels = (g.Kchunks * 8 + 31) / 32;
-    if (g.Ncols > 32) done = panels < 8 ? launch_strip_t<2, 2, 4, 256>(ws, g, dy_off, scratch_bytes, count, &g.splits, s)
-                                        : launch_strip_t<2, 4, 4, 256>(ws, g, dy_off, scratch_bytes, count, &g.splits, s);
-    else if (panels < 8) done = launch_strip_t<1, 1, 8, 512>(ws, g, dy_off, scratch_bytes, count, &g.splits, s);
-    else if (panels < 16) done = launch_strip_t<1, 2, 8, 256>(ws, g, dy_off, scratch_bytes, count, &g.splits, s);
-    else done = launch_strip_t<1, 4, 7, 256>(ws, g, dy_off, scratch_bytes, count, &g.splits, s);
+  StripPlan strip;
+  const bool done = conv && strip_plan(StripLayer{g.M, g.Ncols, g.C, g.ks, g.OH, g.OW, g.W, g.pad, count, scratch_bytes}, &strip);
+  if (done) {
+    g.splits = strip.splits;
+    switch (strip.form) {
+      case 0: launch_strip_t<0>(ws, g, dy_off, strip, count, s); break;
+      case 1: launch_strip_t<1>(ws, g, dy_off, strip, count, s); break;
+      case 2: launch_strip_t<2>(ws, g, dy_off, strip, count, s); break;
+      case 3: launch_strip_t<3>(ws, g, dy_off, strip, count, s); break;
+      default: launch_strip_t<4>(ws, g, dy_off, strip, count, s); break;
+    }
   }
 #define SASGD_WGRAD(BMG, BNG, WMG, WNG)                                                                                          \
   do {                                                                                                                           \

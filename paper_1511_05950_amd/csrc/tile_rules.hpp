@@ -200,4 +200,49 @@ inline WgradTiles wgrad_tiles(const WgradProduct& p, bool wide_ok) {
   return best;
 }
 
+// ---- weight gradient of a stride-1 convolution with up to 64 output channels, bf16
+// Forms of wgrad_strip_kernel: 32 TM output channels, WN TN blocks of 32 im2col columns a workgroup, MT positions a tile.
+struct StripForm {
+  int TM, WN, TN, MT;
+};
+constexpr StripForm kStripForms[5] = {{2, 2, 4, 256}, {2, 4, 4, 256}, {1, 1, 8, 512}, {1, 2, 8, 256}, {1, 4, 7, 256}};
+struct StripLayer {
+  int M, Ncols, C, ks, OH, OW, W, pad, count;
+  size_t scratch_bytes;
+};
+struct StripPlan {
+  int form, PW;              // kStripForms, patch width in pixels
+  int groups, tiles, per, splits;   // column groups; tiles of positions, how many a workgroup takes, workgroups along them
+  int patch, buf;            // bytes of a patch and of a whole buffer (dy, patch, places) in LDS
+  size_t lds;
+};
+// Does the kernel take the layer, and how?
+inline bool strip_plan(const StripLayer& g, StripPlan* p) {
+  if (g.Ncols > 64 || g.OW + g.ks - 1 != g.W + 2 * g.pad) return false;
+  const int kcols = g.ks * g.ks * g.C, panels = (kcols + 31) / 32;
+  p->form = g.Ncols > 32 ? (panels < 8 ? 0 : 1) : panels < 8 ? 2 : panels < 16 ? 3 : 4;
+  const StripForm& f = kStripForms[p->form];
+  p->PW = g.OW + g.ks - 1;
+  const int rows = (f.MT + g.OW - 2) / g.OW + 1;             // output rows a tile can touch
+  const int images = (rows + g.OH - 2) / g.OH + 1;           // and images those rows can belong to
+  const int64_t patch = ((int64_t)(rows + (g.ks - 1) * images) * p->PW * g.C * 2 + 1023) / 1024 * 1024;
+  if (patch > 64 * 1024) return false;
+  p->patch = (int)patch;
+  p->buf = f.TM * f.MT * 64 + p->patch + f.MT * 4;
+  p->lds = 2 * (size_t)p->buf > 8 * 4096 ? 2 * (size_t)p->buf : 8 * 4096;
+  if (p->lds > 160 * 1024) return false;
+  p->groups = (panels + f.WN * f.TN) / (f.WN * f.TN);        // with the bias's place
+  // Below this the tiles a workgroup has to itself are too few to pay for its start and its sum over the position groups
+  // (CIFAR-shaped conv2, 64 images of one learner: 11 us with the gathering kernel, 14 here; 8 x 64 images: 25 and 19).
+  if ((int64_t)g.M * p->groups * g.count < 65536) return false;
+  p->tiles = (g.M + f.MT - 1) / f.MT;
+  // one workgroup a compute unit: whole rounds of 256 of them
+  const int64_t held = (int64_t)(g.scratch_bytes / ((size_t)g.Ncols * (kcols + 8) * 4));
+  const int most = held < 1 ? 1 : held < p->tiles ? (int)held : p->tiles, fill = 256 / (p->groups * g.count);
+  const int want = fill < 1 ? 1 : fill < most ? fill : most;
+  p->per = (p->tiles + want - 1) / want;
+  p->splits = (p->tiles + p->per - 1) / p->per;
+  return true;
+}
+
 }  // namespace sasgd

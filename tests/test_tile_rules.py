@@ -4,6 +4,12 @@ import subprocess
 
 import pytest
 
+import workloads as wl
+
+pytest.importorskip("torch")
+import test_gpu_conv_tiles as conv_tiles            # noqa: E402
+import test_gpu_wgrad_tiles as wgrad_tiles          # noqa: E402  (the networks; nothing runs on a GPU here)
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PROGRAM = r"""
@@ -40,6 +46,12 @@ int main() {
       if (scanf("%ld %d %d %d %zu %d", &p.M, &p.Ncols, &p.cols, &p.count, &p.scratch_bytes, &wide_ok) != 6) return 1;
       const WgradTiles t = wgrad_tiles(p, wide_ok != 0);
       printf("%d %d\n", (int)t.tile, t.splits);
+    } else if (!strcmp(rule, "strip")) {
+      StripLayer g;
+      if (scanf("%d %d %d %d %d %d %d %d %d %zu", &g.M, &g.Ncols, &g.C, &g.ks, &g.OH, &g.OW, &g.W, &g.pad, &g.count, &g.scratch_bytes) != 10) return 1;
+      StripPlan p;
+      if (strip_plan(g, &p)) printf("%d %d %d %d\n", p.form, p.splits, p.groups, (int)p.lds);
+      else printf("-1 0 0 0\n");
     } else {
       return 1;
     }
@@ -217,6 +229,68 @@ WEIGHTS = [
 ]
 
 
+
+def weight_gradient_kernels(ask, net, mu, learners):
+    """The kernel and the splits that every convolution of a network takes its weight gradient with, first to last, and the steps."""
+    c, h, w = net["input"]
+    products, need = [], 0
+    for layer in net["layers"]:
+        if layer[0] == "conv":
+            _, k, ks, stride, pad = layer
+            oh, ow = (h + 2 * pad - ks) // stride + 1, (w + 2 * pad - ks) // stride + 1
+            if stride > 1:                                    # space to depth
+                seen, window, width, margin = -(-stride * stride * c // 8) * 8, -(-ks // stride), -(-w // stride), 0
+            else:
+                seen, window, width, margin = -(-c // 8) * 8, ks, w, pad
+            products.append((mu * oh * ow, k, seen, window, oh, ow, width, margin))
+            need = max([need, 4 * mu * oh * ow * k, 4 * k * (seen * window ** 2 + 8)] + ([4 * mu * h * w * c] if len(products) > 1 else []))
+            c, h, w = k, oh, ow
+        elif layer[0] in ("maxpool", "avgpool"):
+            h, w = wl._pool_out(h, layer[1], layer[2]), wl._pool_out(w, layer[1], layer[2])
+        elif layer[0] == "fc":
+            need = max(need, 4 * mu * max(c * h * w, layer[1]), 4 * layer[1] * (c * h * w + 8))
+            c, h, w = layer[1], 1, 1
+    scratch = min(8 * need, max(need, 128 << 20))
+    out = []
+    for m, k, seen, window, oh, ow, width, margin in products:
+        steps = -(-m // 32)
+        if k <= 64:
+            form, splits, groups, _ = ask([("strip", m, k, seen, window, oh, ow, width, margin, learners, scratch)])[0]
+            out.append(("gather" if form < 0 else "strip%d" % form, splits, groups))
+        else:
+            tile, splits = ask([("weights", m, k, seen * window ** 2 + 1, learners, scratch, int(32 // ow + 1 <= oh))])[0]
+            out.append((("128x128", "96x512", "256x256", "384x128")[tile], splits, steps))
+    return out
+
+
+def convolution_tiles(ask, net, mu, learners, own=False):
+    """The tiles and splits of every convolution's product with more than 64 columns, no multiple of 256: forward passes first to last, then
+    input gradients, patch in LDS (32-channel layers) or tap by tap."""
+    c, h, w = net["input"]
+    products = []
+    for layer in net["layers"]:
+        if layer[0] == "conv":
+            _, k, ks, stride, pad = layer
+            oh, ow = (h + 2 * pad - ks) // stride + 1, (w + 2 * pad - ks) // stride + 1
+            seen, window = (-(-stride * stride * c // 8) * 8, -(-ks // stride)) if stride > 1 else (-(-c // 8) * 8 if not products else c, ks)
+            products.append(((mu * oh * ow, k, seen, window), (mu * h * w, c, k, ks)))
+            c, h, w = k, oh, ow
+        elif layer[0] in ("maxpool", "avgpool"):
+            h, w = wl._pool_out(h, layer[1], layer[2]), wl._pool_out(w, layer[1], layer[2])
+    out = []
+    for m, cols, ch, ks in [f for f, _ in products] + [d for _, d in products[:0:-1]]:
+        if cols <= 64 or cols % 256 == 0 or ch == 8:
+            continue
+        steps = -(-ks * ks * ch // 32)
+        most = max(1, min(-(-600 // (-(-m // 128) * -(-cols // 128) * learners)), steps // 4, 64))
+        if ch % 32:
+            out.append(("taps 256x96" if ask([("taps", m, cols, ch, ks, learners, int(own), most, steps)])[0][0] else "taps 128x128", 1))
+        else:
+            tile, splits, _ = ask([("conv", m, cols, ch, ks, learners, int(own), most, 0)])[0]
+            out.append((("128x128", "256x128", "256x96")[tile], splits))
+    return out
+
+
 @pytest.fixture(scope="module")
 def ask(tmp_path_factory):
     where = tmp_path_factory.mktemp("rules")
@@ -298,3 +372,31 @@ def test_splits_stay_within_steps_and_scratch(ask):
         steps, part = -(-m // 32), n * (cols + 7) * 4
         assert 1 <= splits <= max(1, steps // 4) and (splits == 1 or splits * part <= scratch)
         assert -(-steps // -(-steps // splits)) == splits or tile == 0       # no workgroup without a step
+
+
+def test_gpu_convolution_cases_reach_the_tiles_they_name(ask):
+    for name, expected in conv_tiles.REACHES.items():
+        got = convolution_tiles(ask, *conv_tiles.CASES[name])
+        assert tuple(tile + (" split" if splits > 1 else "") for tile, splits in got) == expected, (name, got)
+
+
+def test_gpu_weight_gradient_cases_reach_the_kernels_they_name(ask):
+    """The weight-gradient cases that run on a GPU, layer by layer."""
+    tiles = {"96x512", "256x256", "384x128"}
+    split, whole, forms = set(), set(), set()
+    for name, expected in wgrad_tiles.REACHES.items():
+        net, mu, learners = wgrad_tiles.CASES[name]
+        got = weight_gradient_kernels(ask, net, mu, learners)
+        assert tuple(k for k, _, _ in got) == expected, (name, got)
+        kernel, splits, steps = got[-1]
+        if kernel in tiles:
+            (split if splits > 1 else whole).add((kernel, net["layers"][[k for k, l in enumerate(net["layers"]) if l[0] == "conv"][-1]][1]))
+        if name.endswith("_splits") and kernel in tiles:
+            each = -(-steps // splits)
+            assert splits > 1 and each > 4 and steps % each, (name, got)     # the last split is shorter
+        forms |= {k for k, _, _ in got if k.startswith("strip")}
+    # every wide shape, full and partly filled, with and without splits, and every form of the strip kernel
+    shapes = {("96x512", 96), ("96x512", 88), ("256x256", 256), ("256x256", 200), ("384x128", 384), ("384x128", 360)}
+    assert shapes <= split and shapes <= whole and forms == {"strip%d" % k for k in range(5)}
+    assert weight_gradient_kernels(ask, *wgrad_tiles.CASES["most_splits"])[0][1] > 256
+    assert weight_gradient_kernels(ask, *wgrad_tiles.CASES["strided_few_splits"])[0][1] in (2, 3, 4)
