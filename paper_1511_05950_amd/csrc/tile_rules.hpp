@@ -13,7 +13,7 @@ inline InputLayout input_layout(bool is_bf16, int s2d, int C, int Cp, bool align
   return is_bf16 && Cp % 8 == 0 ? InputLayout::kPixels : InputLayout::kValues;
 }
 // Pixels of a row that one workgroup of the kRows kernel makes: the row in even pieces of up to 640, 60 KiB of LDS
-// (3072 x 256 pixels, 4 learners x 2 images: 21 us; a lane per pixel takes 50).
+// (3072 x 256 pixels, 4 learners x 2 images: 17 us; a lane per pixel takes 50).
 inline int input_row_piece(int Wp) {
   const int pieces = (Wp + 639) / 640;
   return (Wp + pieces - 1) / pieces;
