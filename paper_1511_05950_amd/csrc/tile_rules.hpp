@@ -87,7 +87,7 @@ inline bool spares_columns_96(int Ncols) { return (Ncols + 95) / 96 * 96 < (Ncol
 //   256 x 96, where that spares columns: two, and up to a quarter fewer products, in larger steps.  272 columns, 3 x 3 over 128, 15 learners of 2 704
 //     positions: 51 us with 128 x 128, 35 here; 448 columns, 5 x 5 over 448, 29 learners of 1 300: 375 and 416; 96 columns, 3 x 3
 //     over 96, 4 learners of 5 832: 16, and 25 split three ways.  Taken wherever it spares columns, it was the slower one by
-//     more than 3 % in 145 of 544 products, by up to 60 %; by these times in 5, by up to 11 %.
+//     more than 3 % in 145 of 544 products, by up to 60 %; by these times in 4, by up to 11 %.
 // With a weight version per learner the fragments are the larger part of the traffic, and 128 x 128 has to be better by more than
 // that (3 x 3 over 384, 384 columns, 18 learners: 120 us against 101 with 256 x 128).
 inline int conv_choices(const ConvProduct& p, ConvChoice (&out)[3]) {
