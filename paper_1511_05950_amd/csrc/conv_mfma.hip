@@ -1,12 +1,11 @@
-// bf16 MFMA implicit-GEMM kernels for calcGradient's convolutions and fully connected layers
+// bf16 MFMA implicit-GEMM kernels for calcGradient's convolutions, and the weight gradients of fully connected layers
 // (Section 2.1 learner step; layer shapes of Section 4.1), written for gfx950 (CDNA4):
 // v_mfma_f32_32x32x16_bf16 tiles, fp32 accumulation, LDS-staged im2col tiles, 64-wide wavefronts.
 //
 // GEMM views (activations NHWC bf16, "chunk" = 8 consecutive channels = 16 bytes):
 //   forward  y[m][n]  = sum_k im2col(x)[m][k] * Wp[n][k]      m = (image, oh, ow), k = (kh, kw, c)
 //   dgrad    dx[m][c] = sum_k im2col(dy)[m][k] * Wt[c][k]     the same kernel on dy with flipped, transposed
-//                                                             filters (stride 1), or, for fully connected
-//                                                             layers, with the B operand read transposed
+//                                                             filters (stride 1)
 //   wgrad    dW[n][k] = sum_m dy[m][n] * im2col(x)[m][k]      both operands are contraction-major in memory;
 //                                                             they are staged as they lie and read with the
 //                                                             LDS transpose load (ds_read_b64_tr_b16)
@@ -25,7 +24,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(short)))) short shortx4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 
 constexpr int BK = 32;           // contraction elements per step (4 chunks)
-constexpr int LDA = BK + 8;      // row stride (elements) of k-contiguous LDS tiles: 80 B, conflict-free 16 B reads
 
 // ------------------------------------------------------------------ filter packing (once per weight version)
 // Filters are stored in MFMA operand ("fragment") order so that a wavefront fetches the B operand of one
@@ -183,17 +181,8 @@ hipError_t launch_pack_filters(const PackVersions& pv, int versions, const PackT
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ im2col chunk gather
-// Row m of the virtual im2col matrix, chunk q (8 channels of one tap): 16 bytes from the NHWC tensor or zeros.
-// All loads are unconditional (an out-of-range chunk is read from a block of zeros kept in the workspace) and all
-// index arithmetic is branch-free, so the loops below are straight-line code: nothing touches a loaded value
-// before the MFMAs of the current step have been issued, and the compiler can wait on exactly the loads it needs
-// instead of draining the whole queue.
+// ------------------------------------------------------------------ im2col rows
 __device__ __forceinline__ uint32_t fastdiv(uint32_t n, int d, uint32_t magic) { return d == 1 ? n : __umulhi(n, magic); }
-
-__device__ __forceinline__ uint4 ld16_or_zero(const bf16_t* p, bool ok, const bf16_t* zeros) {
-  return *reinterpret_cast<const uint4*>(ok ? p : zeros);
-}
 
 struct RowPos {
   const bf16_t* base;   // &t[n][oh - pad][ow - pad][0]  (may point outside; only dereferenced when in range)
@@ -213,184 +202,6 @@ __device__ __forceinline__ RowPos row_pos(const bf16_t* t, const IGemm& g, int m
   r.ow = ow - g.pad;
   r.base = t + (((int64_t)n * g.H + r.oh) * g.W + r.ow) * g.C;
   return r;
-}
-
-__device__ __forceinline__ uint4 gather_chunk(const RowPos& r, const IGemm& g, int q, const bf16_t* zeros) {
-  const uint32_t tap = fastdiv((uint32_t)q, g.CPT, g.mg_cpt);
-  const int c8 = q - (int)tap * g.CPT;
-  const int kh = (int)fastdiv(tap, g.ks, g.mg_ks), kw = (int)tap - kh * g.ks;
-  const int ih = r.oh + kh, iw = r.ow + kw;
-  const bool ok = r.valid && q < g.Kchunks && (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
-  return ld16_or_zero(r.base + ((int64_t)kh * g.W + kw) * g.C + c8 * 8, ok, zeros);
-}
-
-// ------------------------------------------------------------------ forward / dgrad kernel
-// Block tile BM x BN, four wavefronts each owning a WM x WN sub-tile of 32x32 MFMA blocks.
-// BT = false: B rows are output columns, k-contiguous (packed filters): B[n][k], row length ldb.
-// BT = true : B is stored contraction-major, B[k][n] with row length ldb (flat fully connected weights
-//             used for dgrad); its tile is staged as it lies and read with the transpose load.
-template <int BM, int BN, int WM, int WN, bool BT>
-__global__ __launch_bounds__(256) void igemm_kernel(PtrTab ws, CPtrTab wts, IGemm g, Epilogue ep) {
-  constexpr int WAVES_N = BN / WN;
-  constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int LDBT = BN + (BN == 128 ? 32 : (BN == 64 ? 32 : 0));   // transposed tile: row stride = 16 (mod 64) words
-  constexpr int A_ELEMS = BM * LDA;
-  constexpr int B_ELEMS = BT ? BK * LDBT : BN * LDA;
-  __shared__ __attribute__((aligned(16))) bf16_t lds[2 * (A_ELEMS + B_ELEMS)];
-
-  const int z = blockIdx.z / g.splits, sp = blockIdx.z % g.splits;
-  const bf16_t* act = (const bf16_t*)ws.p[z] + g.a_off;
-  const bf16_t* zeros = (const bf16_t*)ws.p[z] + g.zero_off;
-  const bf16_t* Bm = (const bf16_t*)wts.p[z] + g.b_off;
-  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
-
-  // loader assignment: chunk column cc (0..3) is fixed per thread, rows stride 64
-  constexpr int A_LOADS = (BM * 4 + 255) / 256;
-  constexpr int B_LOADS = BT ? (BK * (BN / 8) + 255) / 256 : (BN * 4 + 255) / 256;
-  const int cc = tid & 3, lrow = tid >> 2;
-  RowPos rp[A_LOADS];
-#pragma unroll
-  for (int i = 0; i < A_LOADS; i++) rp[i] = row_pos(act, g, m0 + lrow + 64 * i);
-
-  uint4 ra[A_LOADS], rb[B_LOADS];
-  auto load_regs = [&](int ks) {
-#pragma unroll
-    for (int i = 0; i < A_LOADS; i++) ra[i] = gather_chunk(rp[i], g, ks * 4 + cc, zeros);
-    if (!BT) {
-#pragma unroll
-      for (int i = 0; i < B_LOADS; i++) {
-        const int r = lrow + 64 * i;
-        const int n = n0 + r;
-        const int q = ks * 4 + cc;
-        rb[i] = ld16_or_zero(Bm + (int64_t)n * g.ldb + q * 8, r < BN && n < g.Ncols && q * 8 < g.ldb, zeros);
-      }
-    } else {
-      constexpr int CPR = BN / 8;   // chunks per tile row
-#pragma unroll
-      for (int i = 0; i < B_LOADS; i++) {
-        const int idx = tid + 256 * i;
-        const int r = idx / CPR, ch = idx % CPR;
-        const int k = ks * BK + r, n = n0 + ch * 8;
-        rb[i] = ld16_or_zero(Bm + (int64_t)k * g.ldb + n, r < BK && k < g.Kchunks * 8 && n < g.Ncols, zeros);
-      }
-    }
-  };
-  auto store_lds = [&](int buf) {
-    bf16_t* A = lds + buf * (A_ELEMS + B_ELEMS);
-    bf16_t* B = A + A_ELEMS;
-#pragma unroll
-    for (int i = 0; i < A_LOADS; i++)
-      if (lrow + 64 * i < BM) *reinterpret_cast<uint4*>(A + (lrow + 64 * i) * LDA + cc * 8) = ra[i];
-    if (!BT) {
-#pragma unroll
-      for (int i = 0; i < B_LOADS; i++)
-        if (lrow + 64 * i < BN) *reinterpret_cast<uint4*>(B + (lrow + 64 * i) * LDA + cc * 8) = rb[i];
-    } else {
-      constexpr int CPR = BN / 8;
-#pragma unroll
-      for (int i = 0; i < B_LOADS; i++) {
-        int idx = tid + 256 * i;
-        int r = idx / CPR, ch = idx % CPR;
-        if (r < BK) *reinterpret_cast<uint4*>(B + r * LDBT + ch * 8) = rb[i];
-      }
-    }
-  };
-
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; i++)
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
-
-  const int all_steps = (g.Kchunks + 3) / 4;
-  const int per = (all_steps + g.splits - 1) / g.splits;
-  const int ks_begin = sp * per;
-  const int ksteps = min(all_steps, ks_begin + per);
-  if (ks_begin < ksteps) {
-    load_regs(ks_begin);
-    store_lds(ks_begin & 1);
-  }
-  __syncthreads();
-  for (int ks = ks_begin; ks < ksteps; ks++) {
-    const int buf = ks & 1;
-    if (ks + 1 < ksteps) load_regs(ks + 1);
-    const bf16_t* A = lds + buf * (A_ELEMS + B_ELEMS);
-    const bf16_t* B = A + A_ELEMS;
-#pragma unroll
-    for (int kk = 0; kk < 2; kk++) {
-      bf16x8 a[TM], b[TN];
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-        a[i] = *reinterpret_cast<const bf16x8*>(A + (wm0 + 32 * i + (lane & 31)) * LDA + 16 * kk + 8 * (lane >> 5));
-      if (!BT) {
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-          b[j] = *reinterpret_cast<const bf16x8*>(B + (wn0 + 32 * j + (lane & 31)) * LDA + 16 * kk + 8 * (lane >> 5));
-      } else {
-        // transpose load: lane j16 of a 16-lane group supplies the row k0 + j16/4, columns 4*(j16%4)..+3 and
-        // receives the four k values of column (lane%16) of the group's 16 columns
-        const int j16 = lane & 15, half = (lane >> 4) & 1, kb = 16 * kk + 8 * (lane >> 5);
-#pragma unroll
-        for (int j = 0; j < TN; j++) {
-          const bf16_t* p = B + (kb + (j16 >> 2)) * LDBT + wn0 + 32 * j + 16 * half + 4 * (j16 & 3);
-          union { bf16x8 v; shortx4 h[2]; } u;
-          u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((shortx4 __attribute__((address_space(3)))*)(p));
-          u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((shortx4 __attribute__((address_space(3)))*)(p + 4 * LDBT));
-          b[j] = u.v;
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    if (ks + 1 < ksteps) store_lds(buf ^ 1);
-    __syncthreads();
-  }
-
-  // epilogue: lane holds column n = l%32 and rows 8*(r/4) + 4*(l/32) + r%4 of every 32x32 block
-  if (g.splits > 1) {   // raw fp32 partial tile; igemm_finish_kernel adds the splits and applies the epilogue
-    float* part = reinterpret_cast<float*>((char*)ws.p[z] + g.scratch_off) + (int64_t)sp * g.M * g.Ncols;
-#pragma unroll
-    for (int j = 0; j < TN; j++) {
-      const int n = n0 + wn0 + 32 * j + (lane & 31);
-      if (n >= g.Ncols) continue;
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int r = 0; r < 16; r++) {
-          const int m = m0 + wm0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (m < g.M) part[(int64_t)m * g.Ncols + n] = acc[i][j][r];
-        }
-    }
-    return;
-  }
-  bf16_t* out = (bf16_t*)ws.p[z] + ep.out_off;
-  const bf16_t* mask = (const bf16_t*)ws.p[z] + ep.mask_off;
-  const bf16_t* bias = (const bf16_t*)wts.p[z] + ep.bias_off;
-#pragma unroll
-  for (int j = 0; j < TN; j++) {
-    const int n = n0 + wn0 + 32 * j + (lane & 31);
-    if (n >= g.Ncols) continue;
-    const float bv = ep.has_bias ? bf2f(bias[n]) : 0.f;
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const int m = m0 + wm0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (m >= g.M) continue;
-        float v = acc[i][j][r] + bv;
-        if (ep.relu) v = fmaxf(v, 0.f);
-        const int64_t o = (int64_t)m * g.Ncols + n;
-        if (ep.use_mask && !(bf2f(mask[o]) > 0.f)) v = 0.f;
-        if (ep.out_f32) reinterpret_cast<float*>(out)[o] = v;
-        else out[o] = f2bf(v);
-      }
-  }
 }
 
 typedef int v4i_t __attribute__((ext_vector_type(4)));
@@ -1219,17 +1030,6 @@ __global__ __launch_bounds__(256) void igemm_finish_kernel(PtrTab ws, CPtrTab wt
   }
 }
 
-template <int BM, int BN, int WM, int WN, bool BT>
-static void launch_igemm_t(const PtrTab& ws, const CPtrTab& wts, const IGemm& g, const Epilogue& ep, int count, hipStream_t s) {
-  dim3 grid((unsigned)((g.M + BM - 1) / BM), (unsigned)((g.Ncols + BN - 1) / BN), (unsigned)(count * g.splits));
-  hipLaunchKernelGGL((igemm_kernel<BM, BN, WM, WN, BT>), grid, dim3(256), 0, s, ws, wts, g, ep);
-  if (g.splits > 1) {
-    int64_t total = ((int64_t)g.M * g.Ncols) >> 2;
-    unsigned blocks = (unsigned)((total + 255) / 256 < 2048 ? (total + 255) / 256 : 2048);
-    hipLaunchKernelGGL(igemm_finish_kernel, dim3(blocks, 1, (unsigned)count), dim3(256), 0, s, ws, wts, g, ep);
-  }
-}
-
 template <int BM, int BN, int WM, int WN>
 static void launch_frag_t(const PtrTab& ws, const CPtrTab& wts, const IGemm& g_in, const Epilogue& ep, int count, hipStream_t s) {
   IGemm g = g_in;
@@ -1380,28 +1180,6 @@ hipError_t launch_igemm_frag(const PtrTab& ws, const CPtrTab& wts, const IGemm& 
     launch_frag_t<256, 96, 64, 96>(ws, wts, gs, ep, count, s);
   } else if (g.Ncols % 256 == 0) launch_frag_t<128, 256, 128, 64>(ws, wts, g, ep, count, s);
   else launch_frag_t<128, 128, 64, 64>(ws, wts, g, ep, count, s);
-  return hipGetLastError();
-}
-
-hipError_t launch_igemm(const PtrTab& ws, const CPtrTab& wts, const IGemm& g_in, const Epilogue& ep, bool b_transposed, int count,
-                        hipStream_t s) {
-  const IGemm& g = g_in;
-  if (g.C % 8 || g.ldb % 8 || (b_transposed && g.Ncols % 8) || g.splits < 1) return hipErrorInvalidValue;
-  if (g.M <= 32) {
-    // input gradient of a wide fully connected layer: 512-byte pieces of the weight rows (236 us against 252 us)
-    if (b_transposed && g.Ncols >= 1024) launch_igemm_t<32, 256, 32, 64, true>(ws, wts, g, ep, count, s);
-    else if (b_transposed) launch_igemm_t<32, 128, 32, 32, true>(ws, wts, g, ep, count, s);
-    else launch_igemm_t<32, 128, 32, 32, false>(ws, wts, g, ep, count, s);
-  } else if (g.Ncols <= 32) {
-    if (b_transposed) launch_igemm_t<128, 32, 32, 32, true>(ws, wts, g, ep, count, s);
-    else launch_igemm_t<128, 32, 32, 32, false>(ws, wts, g, ep, count, s);
-  } else if (g.Ncols <= 64) {
-    if (b_transposed) launch_igemm_t<128, 64, 64, 32, true>(ws, wts, g, ep, count, s);
-    else launch_igemm_t<128, 64, 64, 32, false>(ws, wts, g, ep, count, s);
-  } else {
-    if (b_transposed) launch_igemm_t<128, 128, 64, 64, true>(ws, wts, g, ep, count, s);
-    else launch_igemm_t<128, 128, 64, 64, false>(ws, wts, g, ep, count, s);
-  }
   return hipGetLastError();
 }
 

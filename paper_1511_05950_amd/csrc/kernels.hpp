@@ -144,8 +144,6 @@ hipError_t launch_igemm_f32(const PtrTab& ws, const CPtrTab& wts, const IGemm& g
 hipError_t launch_igemm_wgrad_f32(const PtrTab& ws, const PtrTab& grads, const IGemm& g, const VConv& v, size_t dy_off, int64_t w_off,
                                   int64_t b_off, int count, hipStream_t s);
 hipError_t launch_igemm_frag(const PtrTab& ws, const CPtrTab& wts, const IGemm& g, const Epilogue& ep, int count, hipStream_t s);
-hipError_t launch_igemm(const PtrTab& ws, const CPtrTab& wts, const IGemm& g, const Epilogue& ep, bool b_transposed, int count,
-                        hipStream_t s);
 // dW and db of one layer (the bias gradient rides along as one extra im2col column of ones).
 hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm& g, const VConv& v, size_t dy_off, int64_t w_off,
                               int64_t b_off, size_t scratch_bytes, int count, hipStream_t s);
@@ -181,28 +179,20 @@ hipError_t launch_softmax_ce(bool is_bf16, bool z_f32, const PtrTab& ws, const C
                              size_t loss_byte_off, int N, int K, float* loss_out, int count, hipStream_t s);
 hipError_t launch_label_rank(bool is_bf16, bool z_f32, const PtrTab& ws, const CPtrTab& labels, size_t z_off, int N, int K,
                              int32_t* rank_out, int count, hipStream_t s);
-// ---- fully connected layers grouped by weight version (fc_group.hip)
-// Group k = members first[k] .. first[k] + members[k] - 1 of the pointer tables handed to the launch (learners that read
-// one weight version, listed next to each other); at most kMaxGroupRows image rows per group.
-constexpr int kMaxGroupRows = 128;
-struct GroupTab {
+// ---- fully connected layers over all rows of a weight version (fc_rows.hip)
+// Version k = members first[k] .. first[k] + members[k] - 1 of the pointer tables handed to the launch.
+struct alignas(4) GroupTab {
   uint8_t first[kMaxLearners];
   uint8_t members[kMaxLearners];
 };
-// A layer of `in` inputs and `out` units on mini-batches of mu images that the grouped kernels take.
-bool fc_group_layer_ok(int mu, int in, int out);
-// y = x W^T + b (optional ReLU, optional fp32 output) for every group; g = the layer's forward GEMM of ONE learner
-// (M = mu).  scratch_off / scratch_bytes: the split-partial area of a workspace (the first member's is used).
-hipError_t launch_fc_group_fwd(const PtrTab& ws, const CPtrTab& wts, const GroupTab& gt, int groups, const IGemm& g, const Epilogue& ep,
-                               size_t scratch_off, size_t scratch_bytes, hipStream_t s);
-// dx = dy W (optionally zeroed where the forward tensor at ep.mask_off is <= 0); g = the layer's input-gradient GEMM of
-// one learner with a_off = offset of dy.
-hipError_t launch_fc_group_dgrad(const PtrTab& ws, const CPtrTab& wts, const GroupTab& gt, int groups, const IGemm& g, const Epilogue& ep,
-                                 size_t scratch_off, size_t scratch_bytes, hipStream_t s);
+// A layer of `in` inputs is within reach of the kernels' 32-bit offsets.
+inline bool fc_rows_layer_ok(int in) { return in < 1 << 23; }
+// y = x W^T + b (optional ReLU, optional fp32 output), or dx = dy W (optionally zeroed where the forward tensor at ep.mask_off is
+// <= 0), for every version of the table; g = the layer's product for ONE learner (M = mu).  scratch_off / scratch_bytes: the
+// split-partial area of a workspace (a version's first member's is used).
+hipError_t launch_fc_rows(const PtrTab& ws, const CPtrTab& wts, const GroupTab& gt, int groups, const IGemm& g, const Epilogue& ep, bool dgrad,
+                          size_t scratch_off, size_t scratch_bytes, hipStream_t s);
 
-// Copies [bytes_per_member] between every member's workspace (at member_off_bytes) and consecutive pieces of `stage`.
-hipError_t launch_stack_rows(const PtrTab& members, int count, size_t member_off_bytes, void* stage, int64_t bytes_per_member,
-                             bool to_stage, hipStream_t s);
 hipError_t launch_fc_save_factors(const PtrTab& ws, const PtrTab& grads, size_t x_off, size_t dy_off, size_t fx_off, size_t fdy_off,
                                   int64_t b_off, int N, int in, int out, int NP, int count, hipStream_t s);
 hipError_t launch_fc_expand_factors(const void* fx, const void* fdy, float* dw, int N, int in, int out, int NP, hipStream_t s);
