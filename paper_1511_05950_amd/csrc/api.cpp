@@ -716,7 +716,7 @@ static hipError_t expand_factored(sasgd_ctx* ctx, Learner& L) {
   for (int k = 0; k < nfl; k++) {
     const FactoredLayer& F = fl[k];
     hipError_t e = launch_fc_expand_factors((const bf16_t*)L.workspace + F.fx_off, (const bf16_t*)L.workspace + F.fdy_off,
-                                            L.grad + F.w_off, F.N, F.in, F.out, F.NP, ctx->stream);
+                                            L.grad + F.w_off, F.in, F.out, F.NP, ctx->stream);
     if (e != hipSuccess) return e;
   }
   L.fc_expanded = true;

@@ -58,6 +58,7 @@ hipError_t launch_apply_updates_fused(const UpdateLaunch& u, const StepTable& st
 hipError_t static_sum_buffer(float** out);
 // Update of the fully connected layers (each: weights [out][in] followed by the bias [out]) whose gradients are kept as
 // factors, all layers in ONE launch.  theta_in / theta_out / v / shadow_out / grads address element 0 of the flat vector.
+constexpr int kMaxFactorRows = 256;      // images of a mini-batch whose weight gradients are kept as factors
 constexpr int kMaxFactoredLayers = 16;   // further fully connected layers write their gradient out
 struct FcUpdateLaunch {
   const float* theta_in;
@@ -80,6 +81,8 @@ struct FcUpdateLaunch {
 // st == nullptr: one step (u.shadow_out, u.decay).  Otherwise fused steps: st's first / decay / shadow_out are used (its
 // theta_out is ignored: the weights are written once, to u.theta_out).
 hipError_t launch_apply_update_fc(const FcUpdateLaunch& u, hipStream_t stream, const StepTable* st = nullptr);
+// dW [out][in] fp32 from the factors; used by the getters that hand out a written-out gradient
+hipError_t launch_fc_expand_factors(const void* fx, const void* fdy, float* dw, int in, int out, int NP, hipStream_t stream);
 hipError_t launch_fp32_to_bf16(const float* src, bf16_t* dst, int64_t n, hipStream_t stream);
 hipError_t launch_bf16_to_fp32(const bf16_t* src, float* dst, int64_t n, hipStream_t stream);
 
@@ -115,8 +118,6 @@ struct FactoredLayer {
   size_t fx_off, fdy_off;
 };
 int net_factored_layers(const Net* net, FactoredLayer* out, int max);
-// dW [out][in] fp32 from the factors (layers.hip); used by the getters that hand out a written-out gradient
-hipError_t launch_fc_expand_factors(const void* fx, const void* fdy, float* dw, int N, int in, int out, int NP, hipStream_t s);
 void net_set_pixel_mean(Net* net, const float* mean_dev);
 void net_input_shape(const Net* net, int* C, int* H, int* W);
 

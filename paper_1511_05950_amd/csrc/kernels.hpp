@@ -195,7 +195,6 @@ hipError_t launch_fc_rows(const PtrTab& ws, const CPtrTab& wts, const GroupTab& 
 
 hipError_t launch_fc_save_factors(const PtrTab& ws, const PtrTab& grads, size_t x_off, size_t dy_off, size_t fx_off, size_t fdy_off,
                                   int64_t b_off, int N, int in, int out, int NP, int count, hipStream_t s);
-hipError_t launch_fc_expand_factors(const void* fx, const void* fdy, float* dw, int N, int in, int out, int NP, hipStream_t s);
 
 // ---- small networks and mini-batches in few launches (compact.hip)
 // Where a layer's input comes from.

@@ -335,11 +335,11 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
         op.gd = IGemm{0, op.w_off, N, in, 1, 1, L.units, 1, 1, 1, 0, L.units / chunk, L.units / chunk, in};
         op.mfma = igemm_divides(op.gf) && igemm_divides(op.gd);
         if (net->bf16) op.mfma = op.mfma && fc_rows_layer_ok(in);
-        // rank-N weight gradient kept as factors: worth it while the N FMAs per weight and pending gradient stay far
-        // below what the update's streaming rate leaves room for
+        // rank-N weight gradient kept as factors: worth it while the products per weight and pending gradient stay far
+        // below what the update's streaming rate leaves room for; with more than 32 images where every update is a pass of its own
         const int c_upd = cfg.lambda / cfg.n;
-        if (op.mfma && net->bf16 && !(cfg.flags & SASGD_FLAG_FLAT_FC_GRADIENT) && N <= 32 && (int64_t)c_upd * N <= 1024 && op.w_off % 4 == 0 &&
-            L.units % 4 == 0 && in % 8 == 0 && n_factored < kMaxFactoredLayers) {
+        if (op.mfma && net->bf16 && !(cfg.flags & SASGD_FLAG_FLAT_FC_GRADIENT) && N <= (cfg.n == 1 ? kMaxFactorRows : 32) && (int64_t)c_upd * N <= 1024 &&
+            op.w_off % 4 == 0 && L.units % 4 == 0 && in % 8 == 0 && n_factored < kMaxFactoredLayers) {
           op.factored = true;
           op.NP = (N + 7) & ~7;
           n_factored++;
@@ -376,8 +376,8 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
     CompactPlan& cp = net->compact;
     bool any_factored = false;
     for (const Op& op : net->ops) any_factored = any_factored || op.factored;
-    // they write every gradient out: not where factors are kept and all layers have kernels of their own
-    if (any_factored && !cp.any_odd()) cp.ok = false;
+    // they write every gradient out: not where the factors of few images are kept and all layers have kernels of their own
+    if (any_factored && N <= 32 && !cp.any_odd()) cp.ok = false;
     // the cost is linear in the learners of a call, so that the largest call decides for all of them
     cp.always = cp.ok && compact_wins(cp, net->bf16, N, cfg.lambda, false) && compact_wins(cp, net->bf16, N, cfg.lambda, true);
     if (cp.always)

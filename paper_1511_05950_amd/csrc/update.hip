@@ -578,9 +578,275 @@ __global__ __launch_bounds__(256) void apply_update_fc_kernel(const float* theta
   }
 }
 
+// The same for one step of long sums (many gradients, or many images in one): what counts there are the factors' reads and the sums, so
+// a wavefront owns 64 x 64 weights, each operand serves two products, the running sum stays in MFMA order and is turned around once,
+// at its end.  theta and v come half a tile at a time, the first half on its way during the sums.
+// Lone steps of the AlexNet-shaped net's 58.6 M weights, all layers, whose theta, v and bf16 copy alone take 175 us at the copy rate: 18
+// gradients of 16 images 335 us with 32 x 32 weights a wavefront, 219 here; 8 of 32 267 and 204; one of 256 images 341 and 195 (written out
+// by the weight-gradient kernel, 118 us, and read again, it took 200); 4 of 256 961 and 304.
+typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
+typedef unsigned v2u_t __attribute__((ext_vector_type(2)));
+constexpr int kDeepTile = 128;                        // weights of a workgroup in each direction: 2 x 2 wavefronts
+constexpr int kDeepStage = 2 * kDeepTile * 128;       // bytes of a stage: 64 images of both operands
+constexpr int kDeepLds = 64 + 4;                      // LDS row stride in floats
+
+// Weight elements e .. e + 3 of the flat vector from the sum of their gradients.
+template <bool SHADOW>
+__device__ __forceinline__ void update4(float4& a, float4& b, const float4& s, float m, float decay, uint2* shadow) {
+  b.x = fmaf(m, b.x, s.x) + decay * a.x; b.y = fmaf(m, b.y, s.y) + decay * a.y;
+  b.z = fmaf(m, b.z, s.z) + decay * a.z; b.w = fmaf(m, b.w, s.w) + decay * a.w;
+  a.x -= b.x; a.y -= b.y; a.z -= b.z; a.w -= b.w;
+  if (SHADOW) {
+    uint2 o;
+    o.x = pack2bf(a.x, a.y);
+    o.y = pack2bf(a.z, a.w);
+    *shadow = o;
+  }
+}
+
+// Mini-batches of up to 16 images are one k-block, whose operands come straight from memory; larger ones pass through LDS in stages
+// of 64 images, two in turn, which the four wavefronts share (laid out like fc_rows_kernel's stages).
+// EXPAND: the product of one gradient's factors is written out at theta_out instead.
+template <bool SHADOW, bool STAGED, bool EXPAND>
+__global__ __launch_bounds__(256, 2) void apply_update_fc_deep_kernel(const float* theta_in, float* theta_out, float* v, bf16_t* shadow, int NP, int c,
+                                                                      GradTable t, FcFactors f, FcLayerTab lt, float m, float decay) {
+  __shared__ __attribute__((aligned(16))) float lds[STAGED ? 2 * kDeepStage / 4 : 4 * 32 * kDeepLds];
+  int layer = 0;
+  for (int k = 1; k < lt.count; k++) layer = (int)blockIdx.x >= lt.tile0[k] ? k : layer;
+  const int in = lt.in[layer], out = lt.out[layer];
+  const int64_t woff = lt.w_off[layer];
+  theta_in += woff; theta_out += woff; v += woff;
+  if (SHADOW) shadow += woff;
+  const int rows = (out + kDeepTile - 1) / kDeepTile, cols = lt.cols[layer], tiles = rows * cols;
+  int local = (int)blockIdx.x - lt.tile0[layer];
+  const int tid = threadIdx.x;
+  if (local >= tiles) {       // bias: elements out * in + col .. col + 3 (written out already)
+    if (EXPAND) return;
+    const int col = ((local - tiles) * 256 + tid) * 4;
+    if (col >= out) return;
+    const int64_t e = (int64_t)out * in + col;
+    float4 a = *reinterpret_cast<const float4*>(theta_in + e), b = *reinterpret_cast<const float4*>(v + e);
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int l = 0; l < c; l++) {
+      const float4 g = *reinterpret_cast<const float4*>(t.g[l] + woff + e);
+      s.x = fmaf(t.coef[l], g.x, s.x); s.y = fmaf(t.coef[l], g.y, s.y);
+      s.z = fmaf(t.coef[l], g.z, s.z); s.w = fmaf(t.coef[l], g.w, s.w);
+    }
+    update4<SHADOW>(a, b, s, m, decay, SHADOW ? reinterpret_cast<uint2*>(shadow + e) : nullptr);
+    *reinterpret_cast<float4*>(v + e) = b;
+    *reinterpret_cast<float4*>(theta_out + e) = a;
+    return;
+  }
+  // launch order is dealt round-robin to the eight XCDs (a layer's first workgroup is a multiple of eight): each takes a contiguous
+  // eighth of the tiles column by column, whose input factors stay in its L2
+  const int eighth = tiles >> 3;
+  if (local < eighth * 8) local = (local & 7) * eighth + (local >> 3);
+  const int bx = local / rows, by = local - bx * rows;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int o0 = by * kDeepTile + 64 * (wave >> 1), w0 = bx * kDeepTile + 64 * (wave & 1);
+  if (!STAGED && (o0 >= out || w0 >= in)) return;   // whole wavefronts: no workgroup barrier below
+  float* tile = lds + wave * (32 * kDeepLds);
+  // row-major registers: piece q of a half is row 4 q + lane / 16, columns 4 (lane % 16) .. + 3
+  const int rr = lane >> 4, cc = 4 * (lane & 15);
+  // offsets from the tile's first weight; out of range where the layer ends: loads give zeros, stores do nothing
+  const int64_t e0 = (int64_t)o0 * in + w0;
+  auto offset = [&](int half, int q) {
+    const int o = 32 * half + 4 * q + rr;
+    return o0 + o < out && w0 + cc < in ? (o * in + cc) * 4 : (int)0x80000000u;      // in is a multiple of 4, and below 2^23
+  };
+  const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc((void*)(theta_in + e0), 0, 0x7fffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)(v + e0), 0, 0x7fffffff, 0x00020000);
+  constexpr int kNt = 2;                              // streamed: nobody reads these lines again soon
+  float4 th[2][8], vv[2][8];
+  auto fetch = [&](int half) {
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+      th[half][q] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rt, offset(half, q), 0, kNt));
+      vv[half][q] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rv, offset(half, q), 0, kNt));
+    }
+  };
+  if (!EXPAND && !STAGED) fetch(0);
+  // MFMA operands: lane (j = lane % 32, h = lane / 32) holds k = 8 h .. 8 h + 7 of row / column j.  Units behind the layer's last
+  // one repeat it: their products are not stored.
+  const int j = lane & 31, h = lane >> 5;
+  floatx16_t sm[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; i++)
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) sm[i][b][r] = 0.f;
+  if constexpr (!STAGED) {
+    // three gradients' operands are on their way
+    int ao[2], bo[2];                                 // bytes; the half behind the factors' rows is out of range and comes as zeros
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      ao[i] = 8 * h < NP ? (min(o0 + 32 * i + j, out - 1) * NP + 8 * h) * 2 : (int)0x80000000u;
+      bo[i] = 8 * h < NP ? (min(w0 + 32 * i + j, in - 1) * NP + 8 * h) * 2 : (int)0x80000000u;
+    }
+    int fl = 0;                                       // the next one to be requested; behind the last one that one again, for nobody
+    const bf16_t* fbase = f.base[0];
+    auto request = [&](uint4 (&a)[2], uint4 (&b)[2]) {
+      const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc((void*)(fbase + lt.fdy_off[layer]), 0, 0x7fffffff, 0x00020000);
+      const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)(fbase + lt.fx_off[layer]), 0, 0x7fffffff, 0x00020000);
+#pragma unroll
+      for (int i = 0; i < 2; i++) {
+        a[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rd, ao[i], 0, 0));
+        b[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rx, bo[i], 0, 0));
+      }
+      fl = min(fl + 1, c - 1);
+      fbase = f.base[fl];
+    };
+    int l = 0;
+    auto multiply = [&](uint4 (&fa)[2], uint4 (&fb)[2]) {
+      const floatx16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      floatx16_t p[2][2];
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+          p[i][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fa[i]), __builtin_bit_cast(bf16x8_t, fb[q]), zero, 0, 0, 0);
+      request(fa, fb);
+      const float cf = t.coef[l++];
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+#pragma unroll
+          for (int r = 0; r < 16; r++) sm[i][q][r] = fmaf(cf, p[i][q][r], sm[i][q][r]);
+    };
+    uint4 a0[2], b0[2], a1[2], b1[2], a2[2], b2[2];
+    request(a0, b0);
+    request(a1, b1);
+    request(a2, b2);
+#pragma unroll 1
+    for (int it = 0; it < c; it += 3) {
+      multiply(a0, b0);
+      if (it + 1 < c) multiply(a1, b1);
+      if (it + 2 < c) multiply(a2, b2);
+    }
+  } else {
+    // a row of a stage is the 64 images (128 bytes) of a unit, its 16-byte pieces exchanged: piece p of row r at place p ^ (r % 8)
+    const int per = (NP + 63) >> 6, total = c * per;
+    const int pc = (lane & 7) ^ (lane >> 3);
+    int ro[4], rx[4];                                 // load q of a wavefront fetches rows 8 (4 wave + q) .. + 7 of either operand
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int r = 8 * (4 * wave + q) + (lane >> 3);
+      ro[q] = (min(by * kDeepTile + r, out - 1) * NP + 8 * pc) * 2;
+      rx[q] = (min(bx * kDeepTile + r, in - 1) * NP + 8 * pc) * 2;
+    }
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)lds);
+    int fl = 0, fst = 0;                              // the next stage to be requested
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"       // the host pass knows no m0
+    auto request = [&](uint32_t at) {                 // behind the last gradient: the last one's once more, for nobody
+      const bf16_t* base = f.base[min(fl, c - 1)];
+      const bool ok = 64 * fst + 8 * pc < NP;
+      const uintptr_t pd = (uintptr_t)(base + lt.fdy_off[layer] + 64 * fst), px = (uintptr_t)(base + lt.fx_off[layer] + 64 * fst);
+      const v4u_t rd = {(uint32_t)pd, (uint32_t)(pd >> 32) & 0xffffu, 0x7fffffffu, 0x00020000u};
+      const v4u_t rxs = {(uint32_t)px, (uint32_t)(px >> 32) & 0xffffu, 0x7fffffffu, 0x00020000u};
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const uint32_t dst = lds0 + at + (4 * wave + q) * 1024;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst), "v"(ok ? ro[q] : (int)0x80000000u), "s"(rd) : "m0");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst + kDeepTile * 128), "v"(ok ? rx[q] : (int)0x80000000u), "s"(rxs) : "m0");
+      }
+      if (++fst == per) { fst = 0; fl++; }
+    };
+#pragma clang diagnostic pop
+    request(0);
+    request(kDeepStage);
+    if (!EXPAND) fetch(0);
+    const char* L = reinterpret_cast<const char*>(lds);
+    const int arow = (64 * (wave >> 1) + j) * 128, brow = kDeepTile * 128 + (64 * (wave & 1) + j) * 128;
+    floatx16_t p[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int q = 0; q < 2; q++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) p[i][q][r] = 0.f;
+    int l = 0, stg = 0;
+    uint32_t at = 0;
+#pragma unroll 1
+    for (int s = 0; s < total; s++) {
+      // this stage has landed (behind the first two: theta's and momentum's pieces, requested between them and the third)
+      if (!EXPAND && s < 2) asm volatile("s_waitcnt vmcnt(24)\n\ts_barrier" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+      const int kks = min(4, (NP - 64 * stg + 15) >> 4);
+      auto read = [&](bf16x8_t (&a)[2], bf16x8_t (&b)[2], int kk) {
+        const int place = ((2 * kk + h) ^ (j & 7)) * 16;
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+          a[i] = *reinterpret_cast<const bf16x8_t*>(L + at + arow + 32 * 128 * i + place);
+          b[i] = *reinterpret_cast<const bf16x8_t*>(L + at + brow + 32 * 128 * i + place);
+        }
+      };
+#pragma unroll
+      for (int kk = 0; kk < 4; kk++) {
+        if (kk >= kks) break;                         // the pieces behind are zeros
+        bf16x8_t a[2], b[2];
+        read(a, b, kk);
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+          for (int q = 0; q < 2; q++) p[i][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[q], p[i][q], 0, 0, 0);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // every wavefront has read it
+      request(at);
+      at ^= kDeepStage;
+      if (++stg == per) {
+        const float cf = t.coef[l];
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+          for (int q = 0; q < 2; q++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+              sm[i][q][r] = fmaf(cf, p[i][q][r], sm[i][q][r]);
+              p[i][q][r] = 0.f;
+            }
+        stg = 0;
+        l++;
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");        // no load is on its way to LDS, which takes the sums now
+  }
+  if (!EXPAND) fetch(1);
+  const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void*)(theta_out + e0), 0, 0x7fffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)(shadow + e0), 0, 0x7fffffff, 0x00020000);
+#pragma unroll
+  for (int half = 0; half < 2; half++) {
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) tile[(8 * (r >> 2) + 4 * h + (r & 3)) * kDeepLds + 32 * b + j] = sm[half][b][r];
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+      const int at = offset(half, q);
+      const float4 s = *reinterpret_cast<const float4*>(tile + (4 * q + rr) * kDeepLds + cc);
+      if (EXPAND) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u_t, s), ro, at, 0, kNt);
+        continue;
+      }
+      float4 a = th[half][q], b = vv[half][q];
+      uint2 sh;
+      update4<SHADOW>(a, b, s, m, decay, &sh);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u_t, b), rv, at, 0, kNt);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u_t, a), ro, at, 0, kNt);
+      if (SHADOW) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u_t, sh), rs, at < 0 ? at : at >> 1, 0, 0);
+    }
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+  }
+}
+
 hipError_t launch_apply_update_fc(const FcUpdateLaunch& u, hipStream_t stream, const StepTable* steps) {
   if (u.layers < 1 || u.layers > kMaxFactoredLayers || u.c < 1 || u.c > kMaxLearners) return hipErrorInvalidValue;
-  if (u.NP < 8 || u.NP > 32 || (u.NP & 7)) return hipErrorInvalidValue;
+  if (u.NP < 8 || u.NP > kMaxFactorRows || (u.NP & 7)) return hipErrorInvalidValue;
   GradTable t;
   FcFactors f;
   for (int l = 0; l < kMaxLearners; l++) {
@@ -591,6 +857,11 @@ hipError_t launch_apply_update_fc(const FcUpdateLaunch& u, hipStream_t stream, c
   FcLayerTab lt;
   memset(&lt, 0, sizeof(lt));
   lt.count = u.layers;
+  // where the two kernels' times cross (one step, us, small tiles / large ones): 16 images, 6 gradients 186 / 194, 9 222 / 202; 8 images, 8
+  // gradients 201 / 198; one gradient of 64 images 196 / 196, of 96 204 / 192; 4 of 32 199 / 195, 2 of 32 175 / 200.  Large tiles read no written-out gradients.
+  bool deep = (steps ? steps->steps : 1) == 1 && (u.NP <= 16 ? u.c >= 8 : u.c * ((u.NP + 15) / 16) >= 5);
+  for (int l = 0; l < u.c; l++) deep = deep && u.factors[l];
+  for (int k = 0; k < u.layers; k++) deep = deep && u.in[k] < 1 << 23;
   int64_t tiles = 0;
   for (int k = 0; k < u.layers; k++) {
     if (u.in[k] < 4 || u.out[k] < 4 || (u.in[k] & 3) || (u.out[k] & 3)) return hipErrorInvalidValue;
@@ -599,6 +870,14 @@ hipError_t launch_apply_update_fc(const FcUpdateLaunch& u, hipStream_t stream, c
     lt.w_off[k] = u.w_off[k];
     lt.fx_off[k] = (int64_t)u.fx_off[k];
     lt.fdy_off[k] = (int64_t)u.fdy_off[k];
+    if (deep) {
+      tiles = (tiles + 7) & ~(int64_t)7;
+      lt.cols[k] = (u.in[k] + kDeepTile - 1) / kDeepTile;
+      lt.tile0[k] = (int)tiles;
+      tiles += (int64_t)lt.cols[k] * ((u.out[k] + kDeepTile - 1) / kDeepTile) + (u.out[k] + 1023) / 1024;
+      if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+      continue;
+    }
     // 4 kFcTileCols input units per workgroup (four wavefronts side by side), or 1024 bias elements in the extra row
     lt.cols[k] = std::max((u.in[k] + 4 * kFcTileCols - 1) / (4 * kFcTileCols), (u.out[k] + 1023) / 1024);
     lt.tile0[k] = (int)tiles;
@@ -621,10 +900,38 @@ hipError_t launch_apply_update_fc(const FcUpdateLaunch& u, hipStream_t stream, c
   for (int k = 0; k < st.steps; k++)
     if ((st.shadow_out[k] != nullptr) != shadow) return hipErrorInvalidValue;
   const dim3 grid((unsigned)tiles);
-  if (shadow)
+  auto launch_deep = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, u.theta_in, u.theta_out, u.v, st.shadow_out[0], u.NP, u.c, t, f, lt, u.momentum, st.decay[0]);
+  };
+  if (deep && u.NP <= 16) shadow ? launch_deep(apply_update_fc_deep_kernel<true, false, false>) : launch_deep(apply_update_fc_deep_kernel<false, false, false>);
+  else if (deep) shadow ? launch_deep(apply_update_fc_deep_kernel<true, true, false>) : launch_deep(apply_update_fc_deep_kernel<false, true, false>);
+  else if (shadow)
     hipLaunchKernelGGL((apply_update_fc_kernel<true>), grid, dim3(256), 0, stream, u.theta_in, u.theta_out, u.v, u.NP, t, f, lt, st, u.momentum);
   else
     hipLaunchKernelGGL((apply_update_fc_kernel<false>), grid, dim3(256), 0, stream, u.theta_in, u.theta_out, u.v, u.NP, t, f, lt, st, u.momentum);
+  return hipGetLastError();
+}
+
+hipError_t launch_fc_expand_factors(const void* fx, const void* fdy, float* dw, int in, int out, int NP, hipStream_t stream) {
+  if (in < 4 || out < 4 || (in & 3) || (out & 3) || in >= 1 << 23 || NP < 8 || NP > kMaxFactorRows || (NP & 7)) return hipErrorInvalidValue;
+  GradTable t;
+  FcFactors f;
+  FcLayerTab lt;
+  memset(&t, 0, sizeof(t)); memset(&f, 0, sizeof(f)); memset(&lt, 0, sizeof(lt));
+  t.coef[0] = 1.f;
+  f.base[0] = (const bf16_t*)fx;
+  lt.count = 1;
+  lt.in[0] = in;
+  lt.out[0] = out;
+  lt.fdy_off[0] = (const bf16_t*)fdy - (const bf16_t*)fx;
+  lt.cols[0] = (in + kDeepTile - 1) / kDeepTile;
+  const int64_t tiles = (int64_t)lt.cols[0] * ((out + kDeepTile - 1) / kDeepTile);
+  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(256), 0, stream, dw, dw, dw, (bf16_t*)nullptr, NP, 1, t, f, lt, 0.f, 0.f);
+  };
+  if (NP <= 16) launch(apply_update_fc_deep_kernel<false, false, true>);
+  else launch(apply_update_fc_deep_kernel<false, true, true>);
   return hipGetLastError();
 }
 

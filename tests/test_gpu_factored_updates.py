@@ -1,0 +1,61 @@
+"""One-pass updates from the factors of fully connected gradients (bf16): written-out products and updates against runs whose gradients are
+written out by the weight-gradient kernels, which test_gpu_net.py compares with the oracle.  Many gradients of up to 16 images (operands
+straight from memory, half a k-block and a whole one), mini-batches that pass through LDS in one to four stages with remainders
+of 8 to 56 images, layers that end inside a tile, few and many tiles."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from test_gpu_net import rel
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+NET = {"name": "factors", "input": (3, 12, 12), "classes": 8,                       # 1 152 -> 4 104 -> 264 -> 8: large enough for the layer-by-layer
+      # kernels, which keep factors, at every size below
+       "layers": [("conv", 32, 3, 1, 1), ("avgpool", 3, 2), ("fc", 4104), ("relu",), ("fc", 264), ("relu",), ("fc", 8)]}
+
+
+def one_update(lam, mu, flags):
+    from paper_1511_05950_amd import binding
+    w0 = wl.init_weights(NET, 5, std=0.05)
+    X, Y = torch.from_numpy(wl.images(NET, lam * mu, 6)).cuda(), torch.from_numpy(wl.labels(NET, lam * mu, 7)).cuda()
+    ctx = binding.Sasgd(lam, mu, 1, 2, net=NET, compute="bf16", alpha0=0.05, momentum=0.5, weight_decay=1e-2, init_weights=w0, flags=flags)
+    assert (ctx.factoredParams() > 0) == (flags == 0)
+    for update in range(2):
+        for k in range(lam):
+            ctx.getMinibatch(k, X[k * mu:(k + 1) * mu], Y[k * mu:(k + 1) * mu])
+            ctx.pullWeights(k, 0)
+        ctx.calcGradient(list(range(lam)))
+        if update == 0:
+            grads = [ctx.copyGradient(k) for k in sorted({0, lam - 1})]
+        for k in range(lam):
+            ctx.pushGradient(k)
+        ctx.sumGradients()
+        ctx.applyUpdate()
+        if update == 0:
+            w, v = ctx.copyWeights(), ctx.copyMomentum()
+    out = grads, w, v, ctx.copyWeights(), w0
+    ctx.destroy()
+    return out
+
+
+@pytest.mark.parametrize("lam, mu", [(8, 8), (12, 16), (20, 13), (64, 4), (12, 20), (5, 32), (1, 100), (1, 136), (1, 200), (1, 256), (3, 190), (4, 256)])
+def test_update_from_factors(lam, mu):
+    from paper_1511_05950_amd import binding
+    fa, fl = one_update(lam, mu, 0), one_update(lam, mu, binding.FLAG_FLAT_FC_GRADIENT)
+    # the same operands and 32-bit sums in another order: n products of magnitude a sum to within n eps a of each other at most, and to
+    # within a few eps of the norm on average
+    for a, b in zip(fa[0], fl[0]):
+        assert rel(a, b) < 1e-5
+    w0 = fa[4].astype(np.float64)
+    assert rel(fa[1] - w0, fl[1] - w0) < 1e-5
+    assert rel(fa[2], fl[2]) < 1e-5
+    # element by element, over every tensor's own size
+    pos = 0
+    for shape, nb in wl.param_shapes(NET):
+        for n in (int(np.prod(shape)), nb):
+            a, b = fa[2][pos:pos + n].astype(np.float64), fl[2][pos:pos + n].astype(np.float64)
+            assert np.max(np.abs(a - b)) <= 1e-4 * np.max(np.abs(b)), (shape, n)
+            pos += n
+    assert rel(fa[3] - w0, fl[3] - w0) < 2e-3          # a second update, on weights that differ in the last place
