@@ -143,6 +143,11 @@ hipError_t launch_igemm_f32(const PtrTab& ws, const CPtrTab& wts, const IGemm& g
                             bool dgrad, int count, hipStream_t s);
 hipError_t launch_igemm_wgrad_f32(const PtrTab& ws, const PtrTab& grads, const IGemm& g, const VConv& v, size_t dy_off, int64_t w_off,
                                   int64_t b_off, int count, hipStream_t s);
+// The first convolution and the 3 x 3 / 2 max pooling behind it in one launch (conv_pool.hip): the convolution's output is not stored.
+// y_off / arg_off: the pooled tensor (elements) and its winners (bytes), which mark dead windows where ep.relu is set.
+bool conv_pool_ok(const IGemm& g, const PoolShape& ps);
+hipError_t launch_conv_pool(const PtrTab& ws, const CPtrTab& wts, const IGemm& g, const Epilogue& ep, const PoolShape& ps, size_t y_off, size_t arg_off,
+                            bool pool_relu, int count, hipStream_t s);
 hipError_t launch_igemm_frag(const PtrTab& ws, const CPtrTab& wts, const IGemm& g, const Epilogue& ep, int count, hipStream_t s);
 // dW and db of one layer (the bias gradient rides along as one extra im2col column of ones).
 hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm& g, const VConv& v, size_t dy_off, int64_t w_off,

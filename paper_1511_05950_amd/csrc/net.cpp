@@ -33,6 +33,8 @@ struct Op {
   bool dgrad_bt = false;       // fc: B operand is the flat weight matrix read transposed
   int64_t pack_fwd = -1, pack_bwd = -1;   // element offsets in the packed-filter region of a version slot
   int Kp = 0, Kpt = 0;
+  // first convolution that the max pooling behind it shares a kernel with: its output is not stored
+  bool with_pool = false;
   // fully connected layer whose weight gradient is kept as the factors x^T [in][NP] and dy^T [out][NP]
   bool factored = false;
   size_t fx_off = 0, fdy_off = 0;         // element offsets of the two factor copies in the workspace
@@ -408,6 +410,10 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
     if (!net->bf16)   // the fp32 kernels read the flat filter itself: its byte size bounds their loads
       op.gf.b_bytes = op.gd.b_bytes = (uint32_t)((int64_t)op.vc.K * op.vc.Creal * op.vc.ksr * op.vc.ksr * 4);
   }
+  if (net->bf16 && net->ops.size() > 1) {
+    Op &conv = net->ops[0], &pool = net->ops[1];
+    conv.with_pool = conv.kind == OP_CONV && conv.mfma && !conv.is_fc && pool.kind == OP_POOL_MAX && conv_pool_ok(conv.gf, pool.ps);
+  }
   size_t maxe = 0;
   for (const Tensor& t : net->tensors) maxe = t.elems > maxe ? t.elems : maxe;
   // the kernels address an activation tensor through 32-bit byte offsets with the top bit reserved for "out of range"
@@ -731,7 +737,15 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
   }
   // ---- forward
   TRY(launch_pack_input(bf, imgs, ws, T[0].off, count, net->mu, net->inpack, net->pixel_mean, stream));
-  for (const Op& op : net->ops) {
+  size_t first = 0;
+  if (net->ops[0].with_pool) {
+    const Op &conv = net->ops[0], &pool = net->ops[1];
+    const Epilogue ep{0, 0, conv.b_off, 1, conv.relu ? 1 : 0, 0, 0};
+    TRY(launch_conv_pool(ws, wts, conv.gf, ep, pool.ps, T[(size_t)pool.out_t].off, pool.arg_off, pool.relu, count, stream));
+    first = 2;
+  }
+  for (size_t k = first; k < net->ops.size(); k++) {
+    const Op& op = net->ops[k];
     const size_t xi = T[(size_t)op.in_t].off, yo = T[(size_t)op.out_t].off;
     switch (op.kind) {
       case OP_CONV:
