@@ -665,13 +665,12 @@ __global__ __launch_bounds__(256) void compact_flatten_kernel(PtrTab ws, Compact
 
 // ---------------------------------------------------------------- last fully connected layer, softmax, loss, input gradient
 // One workgroup per image, whose inputs stay in LDS; a wavefront takes two classes at a time.  rank_out: evaluation.
-constexpr int kHeadTh = 512;
-template <typename T, int V>
-__global__ __launch_bounds__(kHeadTh) void compact_head_kernel(PtrTab ws, CPtrTab wts, CPtrTab labels, CompactSrc src, CompactHead hd, int32_t* rank_out) {
+template <typename T, int V, int TH>
+__global__ __launch_bounds__(TH) void compact_head_kernel(PtrTab ws, CPtrTab wts, CPtrTab labels, CompactSrc src, CompactHead hd, int32_t* rank_out) {
   extern __shared__ __attribute__((aligned(16))) float compact_lds[];
   float* xs = compact_lds;                        // [in]
   float* zs = compact_lds + ((hd.in + 3) & ~3);   // [K] scores, then their gradient
-  __shared__ float red[kHeadTh / 64];
+  __shared__ float red[TH / 64];
   const int z = blockIdx.z, n = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   char* wsb = (char*)ws.p[z];
   const T* W = (const T*)wts.p[z] + hd.w_off;
@@ -679,7 +678,7 @@ __global__ __launch_bounds__(kHeadTh) void compact_head_kernel(PtrTab ws, CPtrTa
   const int in = hd.in, K = hd.K;
   if (src.kind == CSRC_FLAT) {
     const T* x = (const T*)wsb + src.off + (uint32_t)n * in;
-    for (int i = tid * V; i < in; i += kHeadTh * V) {
+    for (int i = tid * V; i < in; i += TH * V) {
       float f[V];
       ldv<T, V>(x + i, f);
       put<V>(xs + i, f);
@@ -687,7 +686,7 @@ __global__ __launch_bounds__(kHeadTh) void compact_head_kernel(PtrTab ws, CPtrTa
   } else {
     const int HW = src.H * src.W;
     T* xf = (T*)wsb + hd.flat_off + (uint32_t)n * in;
-    for (int i = tid * V; i < in; i += kHeadTh * V) {           // i = pixel * C + channel
+    for (int i = tid * V; i < in; i += TH * V) {           // i = pixel * C + channel
       const int hw = src.by_c(i), c = i - hw * src.C;
       const uint32_t e = (uint32_t)n * in + i;
       float val[V];
@@ -707,7 +706,7 @@ __global__ __launch_bounds__(kHeadTh) void compact_head_kernel(PtrTab ws, CPtrTa
   }
   const int y = ((const int32_t*)labels.p[z])[n];
   __syncthreads();
-  for (int k0 = wave * 2; k0 < K; k0 += 2 * (kHeadTh / 64)) {
+  for (int k0 = wave * 2; k0 < K; k0 += 2 * (TH / 64)) {
     const T *w0 = W + (uint32_t)k0 * in, *w1 = W + (uint32_t)min(k0 + 1, K - 1) * in;
     float a0 = 0.f, a1 = 0.f;
 #pragma unroll 4
@@ -740,14 +739,14 @@ __global__ __launch_bounds__(kHeadTh) void compact_head_kernel(PtrTab ws, CPtrTa
   if (rank_out) {
     int cnt = 0;
     const float zy = y_ok ? zs[y] : 0.f;
-    for (int j = tid; j < K; j += kHeadTh) cnt += (zs[j] > zy || (zs[j] == zy && j < y)) ? 1 : 0;
+    for (int j = tid; j < K; j += TH) cnt += (zs[j] > zy || (zs[j] == zy && j < y)) ? 1 : 0;
     for (int o = 32; o > 0; o >>= 1) cnt += __shfl_down(cnt, o, 64);
     if (lane == 0) red[wave] = (float)cnt;
     __syncthreads();
     if (tid == 0) {
       float tot = 0.f;
 #pragma unroll
-      for (int w = 0; w < kHeadTh / 64; w++) tot += red[w];
+      for (int w = 0; w < TH / 64; w++) tot += red[w];
       rank_out[(int64_t)z * hd.N + n] = y_ok ? (int)tot : K;
     }
     return;
@@ -755,14 +754,14 @@ __global__ __launch_bounds__(kHeadTh) void compact_head_kernel(PtrTab ws, CPtrTa
   __syncthreads();
   const float inv = 1.0f / sum, invN = 1.0f / (float)hd.N;
   T* dz = (T*)wsb + hd.dz_off + (uint32_t)n * K;
-  for (int j = tid; j < K; j += kHeadTh) {
+  for (int j = tid; j < K; j += TH) {
     const float d = stored((expf(zs[j] - m) * inv - (j == y ? 1.f : 0.f)) * invN, (const T*)nullptr);
     stf(dz + j, d);
     zs[j] = d;                                    // each score is read and replaced by its own thread
   }
   __syncthreads();
   T* dx = (T*)wsb + hd.dx_off + (uint32_t)n * in;
-  for (int i = tid * V; i < in; i += kHeadTh * V) {
+  for (int i = tid * V; i < in; i += TH * V) {
     float acc[V];
 #pragma unroll
     for (int v = 0; v < V; v++) acc[v] = 0.f;
@@ -1106,7 +1105,11 @@ hipError_t launch_compact_head(bool bf, const PtrTab& ws, const CPtrTab& wts, co
   const size_t lds = compact_head_lds(hd.in, hd.K);
   // four elements at a time where every row of the weights and of the inputs starts at a multiple of four
   const bool v4 = hd.in % 4 == 0 && hd.w_off % 4 == 0 && (src.kind == CSRC_FLAT || src.C % 4 == 0);
-#define X(T, V) hipLaunchKernelGGL((compact_head_kernel<T, V>), grid, dim3(kHeadTh), lds, s, ws, wts, labels, src, hd, rank_out)
+  // few images: as many lanes to each as help; many: half as many lanes leave a compute unit room for twice as many images (64 input channels of
+  // 4 x 4, 3 classes, 2 304 images: 28 us with 512 lanes, 19 with 256; 256 images 9.2 and 9.5; 64 x 4 x 4 and 10 classes 30 / 29 and 9.2 / 12.5)
+  const bool many = (int64_t)hd.N * count >= 1024;
+  auto go = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, s, ws, wts, labels, src, hd, rank_out); };
+#define X(T, V) many ? go(compact_head_kernel<T, V, 256>, 256) : go(compact_head_kernel<T, V, 512>, 512)
   if (bf) { if (v4) X(bf16_t, 4); else X(bf16_t, 1); }
   else { if (v4) X(float, 4); else X(float, 1); }
 #undef X

@@ -182,6 +182,8 @@ hipError_t launch_flatten_bwd(bool is_bf16, const PtrTab& ws, size_t dy_off, siz
 // loss_byte_off: N floats of per-image losses in the workspace (bytes from its base).
 hipError_t launch_softmax_ce(bool is_bf16, bool z_f32, const PtrTab& ws, const CPtrTab& labels, size_t z_off, size_t dz_off,
                              size_t loss_byte_off, int N, int K, float* loss_out, int count, hipStream_t s);
+// loss_out[l] = mean of learner l's per-image losses
+hipError_t launch_loss_mean(const PtrTab& ws, size_t loss_byte_off, int N, float* loss_out, int count, hipStream_t s);
 hipError_t launch_label_rank(bool is_bf16, bool z_f32, const PtrTab& ws, const CPtrTab& labels, size_t z_off, int N, int K,
                              int32_t* rank_out, int count, hipStream_t s);
 // ---- fully connected layers over all rows of a weight version (fc_rows.hip)

@@ -736,13 +736,32 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(PtrTab ws, CPtrTab labe
   if (threadIdx.x == 0) img_loss[n] = (y >= 0 && y < K) ? -(ldf(zn + y) - m - logf(sum)) : NAN;   // a bad label poisons the loss
 }
 
-__global__ void loss_mean_kernel(PtrTab ws, size_t loss_byte_off, int N, float* loss_out) {
-  const int l = blockIdx.x;
-  if (threadIdx.x != 0) return;
-  const float* img_loss = reinterpret_cast<const float*>((const char*)ws.p[l] + loss_byte_off);
+// Sums stay in image order: the losses come to LDS together (one dependent read after the other, 256 images took 11 us).
+constexpr int kLossChunk = 1024;
+__global__ __launch_bounds__(256) void loss_mean_kernel(PtrTab ws, size_t loss_byte_off, int N, float* loss_out) {
+  __shared__ __attribute__((aligned(16))) float part[kLossChunk];
+  const float* img_loss = reinterpret_cast<const float*>((const char*)ws.p[blockIdx.x] + loss_byte_off);
   float tot = 0.f;
-  for (int n = 0; n < N; n++) tot += img_loss[n];
-  loss_out[l] = tot / (float)N;
+  for (int n0 = 0; n0 < N; n0 += kLossChunk) {
+    const int len = min(kLossChunk, N - n0);
+    if (n0) __syncthreads();
+    for (int i = threadIdx.x; i < (len + 15) / 16 * 16; i += 256) part[i] = i < len ? img_loss[n0 + i] : -0.f;    // -0 changes no sum
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int i = 0; i < len; i += 16) {
+        float4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[k] = *reinterpret_cast<const float4*>(part + i + 4 * k);
+#pragma unroll
+        for (int k = 0; k < 4; k++) { tot += v[k].x; tot += v[k].y; tot += v[k].z; tot += v[k].w; }
+      }
+  }
+  if (threadIdx.x == 0) loss_out[blockIdx.x] = tot / (float)N;
+}
+
+hipError_t launch_loss_mean(const PtrTab& ws, size_t loss_byte_off, int N, float* loss_out, int count, hipStream_t s) {
+  hipLaunchKernelGGL(loss_mean_kernel, dim3(count), dim3(256), 0, s, ws, loss_byte_off, N, loss_out);
+  return hipGetLastError();
 }
 
 hipError_t launch_softmax_ce(bool is_bf16, bool z_f32, const PtrTab& ws, const CPtrTab& labels, size_t z_off, size_t dz_off,
@@ -751,8 +770,7 @@ hipError_t launch_softmax_ce(bool is_bf16, bool z_f32, const PtrTab& ws, const C
   if (is_bf16 && z_f32) hipLaunchKernelGGL((softmax_ce_kernel<bf16_t, float>), g, dim3(256), 0, s, ws, labels, z_off, dz_off, loss_byte_off, N, K);
   else if (is_bf16) hipLaunchKernelGGL((softmax_ce_kernel<bf16_t, bf16_t>), g, dim3(256), 0, s, ws, labels, z_off, dz_off, loss_byte_off, N, K);
   else hipLaunchKernelGGL((softmax_ce_kernel<float, float>), g, dim3(256), 0, s, ws, labels, z_off, dz_off, loss_byte_off, N, K);
-  if (loss_out) hipLaunchKernelGGL(loss_mean_kernel, dim3(count), dim3(64), 0, s, ws, loss_byte_off, N, loss_out);
-  return hipGetLastError();
+  return loss_out ? launch_loss_mean(ws, loss_byte_off, N, loss_out, count, s) : hipGetLastError();
 }
 
 // ------------------------------------------------------------------ evaluation: rank of the true class

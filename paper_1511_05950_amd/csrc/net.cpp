@@ -71,6 +71,9 @@ struct CompactPlan {
 
 struct Net {
   int mu = 0;
+  // layer by layer: the last fully connected layer, loss and its input gradient in one kernel, from operation `head` on (an average
+  // pooling, the flattening or the layer itself); -1: separate kernels
+  int head = -1;
   CompactPlan compact;
   bool bf16 = false;
   int classes = 0;
@@ -414,6 +417,21 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
     Op &conv = net->ops[0], &pool = net->ops[1];
     conv.with_pool = conv.kind == OP_CONV && conv.mfma && !conv.is_fc && pool.kind == OP_POOL_MAX && conv_pool_ok(conv.gf, pool.ps);
   }
+  {
+    // a last layer of few classes, which has no matrix-instruction kernel: one workgroup per image reads its weights twice
+    const int last = (int)net->ops.size() - 1;
+    const Op& fc = net->ops[(size_t)last];
+    if (fc.is_fc && !fc.mfma && last > 0 && compact_head_ok(fc.cs.C, fc.cs.K) && head_kernel_wins(fc.cs.C, fc.cs.K)) {
+      net->head = last;
+      if (net->ops[(size_t)last - 1].kind == OP_FLATTEN && net->ops[(size_t)last - 1].in_t != 0) {
+        net->head = last - 1;
+        const Op* pool = last > 1 ? &net->ops[(size_t)last - 2] : nullptr;
+        if (pool && pool->kind == OP_POOL_AVG && pool->in_t != 0) net->head = last - 2;
+      } else if (!net->ops[(size_t)last - 1].is_fc) {
+        net->head = -1;                                  // flattened images, or a layer of 1 x 1 pixels
+      }
+    }
+  }
   size_t maxe = 0;
   for (const Tensor& t : net->tensors) maxe = t.elems > maxe ? t.elems : maxe;
   // the kernels address an activation tensor through 32-bit byte offsets with the top bit reserved for "out of range"
@@ -744,7 +762,8 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
     TRY(launch_conv_pool(ws, wts, conv.gf, ep, pool.ps, T[(size_t)pool.out_t].off, pool.arg_off, pool.relu, count, stream));
     first = 2;
   }
-  for (size_t k = first; k < net->ops.size(); k++) {
+  const size_t layers = net->head >= 0 ? (size_t)net->head : net->ops.size();
+  for (size_t k = first; k < layers; k++) {
     const Op& op = net->ops[k];
     const size_t xi = T[(size_t)op.in_t].off, yo = T[(size_t)op.out_t].off;
     switch (op.kind) {
@@ -777,11 +796,48 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
   }
   // ---- loss and its gradient with respect to the class scores
   size_t dy = net->grad_a, dx = net->grad_b;
-  TRY(launch_softmax_ce(bf, net->scores_f32, ws, labs, T[(size_t)net->ops.back().out_t].off, dy, net->loss_off, net->mu, net->classes,
-                        out_loss_dev, count, stream));
-  if (out_rank_dev)
-    return launch_label_rank(bf, net->scores_f32, ws, labs, T[(size_t)net->ops.back().out_t].off, net->mu, net->classes, out_rank_dev,
-                             count, stream);
+  if (net->head >= 0) {
+    const Op &from = net->ops[(size_t)net->head], &fc = net->ops.back();
+    const Tensor& tin = T[(size_t)from.in_t];
+    CompactSrc src;
+    memset(&src, 0, sizeof(src));
+    src.off = tin.off;
+    bool relu = tin.relu;                                // of the values the input gradient is masked by
+    CompactHead hd;
+    memset(&hd, 0, sizeof(hd));
+    hd.HW = 1;
+    if (from.is_fc) {
+      src.kind = CSRC_FLAT;
+    } else {
+      src.kind = CSRC_TENSOR;
+      src.C = from.ps.C; src.H = from.ps.H; src.W = from.ps.W;
+      if (from.kind == OP_POOL_AVG) {
+        src.kind = CSRC_AVGPOOL;
+        src.YH = src.H; src.YW = src.W;
+        src.H = from.ps.OH; src.W = from.ps.OW;
+        src.pks = from.ps.ks; src.pst = from.ps.stride; src.relu = from.relu ? 1 : 0;
+        relu = from.relu;
+      }
+      src.by_c.set(src.C);
+      src.by_c4.set(src.C / 4);
+      hd.HW = src.H * src.W;
+    }
+    hd.N = net->mu; hd.in = fc.cs.C; hd.K = fc.cs.K;
+    hd.C = hd.in / hd.HW;
+    hd.w_off = fc.w_off; hd.b_off = fc.b_off;
+    hd.flat_off = T[(size_t)fc.in_t].off; hd.dz_off = dy; hd.dx_off = dx; hd.loss_off = net->loss_off;
+    hd.use_mask = relu ? 1 : 0;
+    hd.by_hw.set(hd.HW);
+    TRY(launch_compact_head(bf, ws, wts, labs, src, hd, out_rank_dev, count, stream));
+    if (out_loss_dev) TRY(launch_loss_mean(ws, net->loss_off, net->mu, out_loss_dev, count, stream));
+    if (out_rank_dev) return hipSuccess;
+  } else {
+    TRY(launch_softmax_ce(bf, net->scores_f32, ws, labs, T[(size_t)net->ops.back().out_t].off, dy, net->loss_off, net->mu, net->classes,
+                          out_loss_dev, count, stream));
+    if (out_rank_dev)
+      return launch_label_rank(bf, net->scores_f32, ws, labs, T[(size_t)net->ops.back().out_t].off, net->mu, net->classes, out_rank_dev,
+                               count, stream);
+  }
   // ---- backward
   auto fc_dgrad = [&](const Op& op, const Tensor& tin) -> hipError_t {
     IGemm gd = op.gd;
@@ -828,7 +884,10 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
           }
         } else {
           TRY(launch_conv_wgrad_simple(bf, ws, grads, tin.off, dy, op.w_off, op.b_off, op.cs, count, stream));
-          if (need_dx) TRY(launch_conv_dgrad_simple(bf, ws, wts, dy, dx, op.w_off, op.cs, tin.relu, tin.off, count, stream));
+          if (need_dx && k == (int)net->ops.size() - 1 && net->head >= 0) {
+            // the input gradient has been written: of the pooled tensor where a flattening comes next
+            if (k > 0 && net->ops[(size_t)k - 1].kind == OP_FLATTEN) k--;
+          } else if (need_dx) TRY(launch_conv_dgrad_simple(bf, ws, wts, dy, dx, op.w_off, op.cs, tin.relu, tin.off, count, stream));
         }
         break;
       case OP_POOL_MAX:
