@@ -204,6 +204,7 @@ __device__ __forceinline__ RowPos row_pos(const bf16_t* t, const IGemm& g, int m
   return r;
 }
 
+typedef int v2i_t __attribute__((ext_vector_type(2)));
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 // Bias, ReLU, ReLU mask of the input gradient, conversion and store of one wavefront's WM x WN accumulator tile whose
 // origin is (mw, nw).  `lds` is the workgroup's tile memory, free once every wavefront has passed the barrier inside.
@@ -1782,16 +1783,26 @@ __global__ __launch_bounds__(256, 1) void wgrad_wide_kernel(PtrTab ws, PtrTab gr
 // positions' places are double-buffered: the next tile's are requested before this one is multiplied, one barrier a tile.
 // Bound by the transposing LDS reads.  CIFAR-shaped net, 18 learners x 128 images: its three layers 96 / 79 / 36 us gathered,
 // 51 / 45 / 31 here.
+//
+// POOL: a first layer with a 3 x 3 / 2 max pooling behind it reads the pooled tensor's gradient and the winners, a third of the bytes, instead of
+// its own output's, the largest tensor of the network, which then is neither written nor read and of which this was the only reader.  A
+// thread owns 8 channels of a 2 x 2 block of the tile, reads the four windows that reach it (a tile ahead, in registers) and puts the four
+// results where the dy of the tile would have landed.  Four of the wavefronts do that in front of their products and four behind, so that
+// vector and matrix instructions of the two of a SIMD meet.  First layer above: pooling backward and this 54 + 54 us, 63 in one kernel (68 with
+// all wavefronts behind; 71 with a compare and a select for each channel and window instead of four channels' compares in one subtraction).
 struct StripArgs {
   int PW;                    // patch width in pixels
   int tiles, per;            // tiles of MT positions, and how many a workgroup takes
   int patch, buf;            // bytes of a patch and of a whole buffer (dy, patch, places) in LDS
   FastDiv by_pw, by_cpt, by_band;   // divisions by PW, by 8-channel chunks of a pixel and by OH + ks - 1 (rows of a whole image in the patch)
+  int PH, PWo;               // POOL: pooled size
+  size_t arg_off;            // and its winners (bytes)
 };
 
-template <int TM, int WN, int TN, int MT>
+template <int TM, int WN, int TN, int MT, bool POOL>
 __global__ __launch_bounds__(512, 2) void wgrad_strip_kernel(PtrTab ws, IGemm g, size_t dy_off, StripArgs h) {
   constexpr int WK = 8 / WN, NT = 512, DY = TM * MT * 64;
+  static_assert(TM * MT <= NT, "POOL: 8 channels of a 2 x 2 block a thread");
   extern __shared__ __attribute__((aligned(16))) char strip_lds[];
   char* lds = strip_lds;
   const int z = blockIdx.z / g.splits, sp = blockIdx.z % g.splits, cg = blockIdx.y;
@@ -1825,6 +1836,11 @@ __global__ __launch_bounds__(512, 2) void wgrad_strip_kernel(PtrTab ws, IGemm g,
   rsrc_dy.y = __builtin_amdgcn_readfirstlane((int)((uintptr_t)dy >> 32) & 0xffff);
   rsrc_dy.z = (int)((int64_t)g.M * g.Ncols * 2);
   rsrc_dy.w = 0x00020000;
+  // POOL: dy is the pooled tensor's
+  const uint32_t out_rows = POOL ? fastdiv((uint32_t)g.M, g.OW, g.mg_ow) : 0;
+  const int pooled = POOL ? (int)fastdiv(out_rows, g.OH, g.mg_oh) * h.PH * h.PWo * g.Ncols : 0;
+  const __amdgpu_buffer_rsrc_t rsrc_pooled = __builtin_amdgcn_make_buffer_rsrc((void*)dy, 0, pooled * 2, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_arg = __builtin_amdgcn_make_buffer_rsrc((char*)ws.p[z] + (POOL ? h.arg_off : 0), 0, pooled, 0x00020000);
   rsrc_x.x = __builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)x);
   rsrc_x.y = __builtin_amdgcn_readfirstlane((int)((uintptr_t)x >> 32) & 0xffff);
   rsrc_x.z = (int)g.a_bytes;
@@ -1838,10 +1854,73 @@ __global__ __launch_bounds__(512, 2) void wgrad_strip_kernel(PtrTab ws, IGemm g,
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds0 + dst), "v"(voff), "s"(rsrc) : "memory", "m0");
   };
 #pragma clang diagnostic pop
+  // POOL: this thread's 8 channels of a 2 x 2 block of the tile's positions
+  const int chunk = tid & (TM * 4 - 1), block = tid / (TM * 4), half = g.OW >> 1;
+  const int block_row = (int)fastdiv((uint32_t)block * 2, g.OW, g.mg_ow), block_col = block - block_row * half;
+  v4i_t wd[4];                 // the windows above left, above, left and its own: their gradients
+  v2i_t wa[4];                 // and winners
+  auto request_windows = [&](int t) {
+    const uint32_t gr = fastdiv((uint32_t)t * MT, g.OW, g.mg_ow) + 2 * block_row;      // (a tile begins with an even row)
+    const int n = (int)fastdiv(gr, g.OH, g.mg_oh), a = (int)(gr - (uint32_t)n * g.OH) >> 1;
+    const bool mine = tid < TM * MT && chunk * 8 < g.Ncols && gr < out_rows;
+#pragma unroll
+    for (int w = 0; w < 4; w++) {
+      const int oh = a - 1 + (w >> 1), ow = block_col - 1 + (w & 1);
+      const bool ok = mine && (unsigned)oh < (unsigned)h.PH && (unsigned)ow < (unsigned)h.PWo;
+      const int o = ((n * h.PH + oh) * h.PWo + ow) * g.Ncols + chunk * 8;
+      wd[w] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_pooled, ok ? o * 2 : (int)kOutOfRange, 0, 0);
+      wa[w] = __builtin_amdgcn_raw_buffer_load_b64(rsrc_arg, ok ? o : (int)kOutOfRange, 0, 0);
+    }
+  };
+  const bool early = wave >= 4;
+  // the same sums in the same order as pool_bwd_3x3s2_kernel
+  auto spread_windows = [&](int buf) {
+    if (tid >= TM * MT) return;
+    char* to = lds + buf + ((chunk >> 2) * MT + block_row * 2 * g.OW + 2 * block_col) * 64 + (chunk & 3) * 16;
+    // (255, a window that passes nothing on, becomes 15: no place either, and no borrow below)
+#pragma unroll
+    for (int w = 0; w < 4; w++) wa[w] &= 0x0f0f0f0f;
+    // channels 2 c and 2 c + 1 of window w where their winner is `place`, else zeros: the top bit of each byte that is equal to it,
+    // spread over 16 bits
+    auto passed = [&](int w, int place, uint32_t (&two)[4]) {
+#pragma unroll
+      for (int i = 0; i < 2; i++) {
+        const uint32_t eq = 0x80808080u - ((uint32_t)wa[w][i] ^ (0x01010101u * place));
+        two[2 * i] = __builtin_amdgcn_perm(eq << 8, eq, 0x08080a0au) & (uint32_t)wd[w][2 * i];
+        two[2 * i + 1] = __builtin_amdgcn_perm(eq << 8, eq, 0x09090b0bu) & (uint32_t)wd[w][2 * i + 1];
+      }
+    };
+    uint32_t own[4], left[4], above[4], corner[4];
+    auto put = [&](int q, const uint32_t (&v)[4]) {
+      *reinterpret_cast<uint4*>(to + ((q >> 1) * g.OW + (q & 1)) * 64) = make_uint4(v[0], v[1], v[2], v[3]);
+    };
+    auto lo = [](uint32_t p) { return __uint_as_float(p << 16); };
+    auto hi = [](uint32_t p) { return __uint_as_float(p & 0xffff0000u); };
+    passed(3, 4, own);
+    put(3, own);
+    passed(2, 5, left);
+    passed(3, 3, own);
+#pragma unroll
+    for (int c = 0; c < 4; c++) own[c] = pack2bf(lo(left[c]) + lo(own[c]), hi(left[c]) + hi(own[c]));
+    put(2, own);
+    passed(1, 7, above);
+    passed(3, 1, own);
+#pragma unroll
+    for (int c = 0; c < 4; c++) own[c] = pack2bf(lo(above[c]) + lo(own[c]), hi(above[c]) + hi(own[c]));
+    put(1, own);
+    passed(0, 8, corner);
+    passed(1, 6, above);
+    passed(2, 2, left);
+    passed(3, 0, own);
+#pragma unroll
+    for (int c = 0; c < 4; c++)
+      own[c] = pack2bf(lo(corner[c]) + lo(above[c]) + lo(left[c]) + lo(own[c]), hi(corner[c]) + hi(above[c]) + hi(left[c]) + hi(own[c]));
+    put(0, own);
+  };
   auto request = [&](int t, int buf) {
     const int m0 = t * MT, m_last = min(m0 + MT, g.M) - 1;
 #pragma unroll
-    for (int i = 0; i < TM * MT / 128; i++) {      // dy: [32-channel panel][position][64 bytes]
+    for (int i = 0; i < (POOL ? 0 : TM * MT / 128); i++) {      // dy: [32-channel panel][position][64 bytes]
       const int s = i * NT + tid, panel = s / (MT * 4), row = (s / 4) % MT, n = panel * 32 + (s & 3) * 8;
       dma(rsrc_dy, (uint32_t)(buf + (i * NT + wave * 64) * 16), n < g.Ncols ? ((m0 + row) * g.Ncols + n) * 2 : (int)kOutOfRange);
     }
@@ -1885,11 +1964,24 @@ __global__ __launch_bounds__(512, 2) void wgrad_strip_kernel(PtrTab ws, IGemm g,
   const int row = 8 * (lane >> 5) + (j16 >> 2), dy_lane = row * 64 + 32 * ((lane >> 4) & 1) + 8 * (j16 & 3);
   const int t_begin = sp * h.per, t_end = min(h.tiles, t_begin + h.per);
   int buf = 0;
-  if (t_begin < t_end) request(t_begin, 0);
+  if (t_begin < t_end) {
+    request(t_begin, 0);
+    if constexpr (POOL) {
+      request_windows(t_begin);
+      spread_windows(0);
+      request_windows(t_begin + 1);
+    }
+  }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll 1
   for (int t = t_begin; t < t_end; t++) {
-    if (t + 1 < t_end) request(t + 1, h.buf - buf);
+    if (t + 1 < t_end) {
+      if constexpr (POOL)
+        if (early) spread_windows(h.buf - buf);    // (before the next loads: the compiler would wait for those too)
+      request(t + 1, h.buf - buf);
+      if constexpr (POOL)
+        if (early) request_windows(t + 2);
+    }
     const char* D = lds + buf;
     const char* X = D + DY;
     const int* place = reinterpret_cast<const int*>(X + h.patch);
@@ -1942,7 +2034,13 @@ __global__ __launch_bounds__(512, 2) void wgrad_strip_kernel(PtrTab ws, IGemm g,
       multiply(a1, b1);
       interleave();
     }
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the next tile is there, this one read
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (POOL)
+      if (!early && t + 1 < t_end) {
+        spread_windows(h.buf - buf);
+        request_windows(t + 2);                    // on their way across the barrier
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the next tile is there, this one read
     buf = h.buf - buf;
   }
 
@@ -2086,7 +2184,7 @@ __global__ __launch_bounds__(64 * W) void wgrad_columns_kernel(PtrTab ws, PtrTab
 }
 
 template <int F>
-static void launch_strip_t(const PtrTab& ws, const IGemm& g, size_t dy_off, const StripPlan& p, int count, hipStream_t s) {
+static void launch_strip_t(const PtrTab& ws, const IGemm& g, size_t dy_off, const StripPlan& p, const PooledDy* pooled, int count, hipStream_t s) {
   constexpr StripForm f = kStripForms[F];
   StripArgs h;
   h.PW = p.PW;
@@ -2097,12 +2195,23 @@ static void launch_strip_t(const PtrTab& ws, const IGemm& g, size_t dy_off, cons
   h.by_pw.set(p.PW);
   h.by_cpt.set(g.CPT);
   h.by_band.set(g.OH + g.ks - 1);
-  hipLaunchKernelGGL((wgrad_strip_kernel<f.TM, f.WN, f.TN, f.MT>), dim3(1, (unsigned)p.groups, (unsigned)(count * p.splits)), dim3(512), p.lds, s, ws, g,
-                     dy_off, h);
+  h.PH = pooled ? pooled->OH : 0;
+  h.PWo = pooled ? pooled->OW : 0;
+  h.arg_off = pooled ? pooled->arg_off : 0;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(1, (unsigned)p.groups, (unsigned)(count * p.splits)), dim3(512), p.lds, s, ws, g, dy_off, h);
+  };
+  pooled ? go(wgrad_strip_kernel<f.TM, f.WN, f.TN, f.MT, true>) : go(wgrad_strip_kernel<f.TM, f.WN, f.TN, f.MT, false>);
+}
+
+bool wgrad_takes_pooled(const IGemm& g, const VConv& v, const PoolShape& ps, size_t scratch_bytes, int count) {
+  StripPlan p;
+  return (v.ks > 1 || v.s2d > 1) && ps.ks == 3 && ps.stride == 2 && ps.H == g.OH && ps.W == g.OW &&
+         strip_plan(StripLayer{g.M, g.Ncols, g.C, g.ks, g.OH, g.OW, g.W, g.pad, count, scratch_bytes}, &p) && strip_pools(p, g.OH, g.OW);
 }
 
 hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm& g_in, const VConv& v, size_t dy_off, int64_t w_off,
-                              int64_t b_off, size_t scratch_bytes, int count, hipStream_t s) {
+                              int64_t b_off, size_t scratch_bytes, const PooledDy* pooled, int count, hipStream_t s) {
   IGemm g = g_in;
   if (g.C % 8 || g.Ncols % 8) return hipErrorInvalidValue;
   const int cols = g.Kchunks * 8 + 1;          // im2col columns plus the bias column
@@ -2130,14 +2239,15 @@ hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm
   const int partial = (g.splits > 1 || conv) ? 1 : 0;
   StripPlan strip;
   const bool done = conv && strip_plan(StripLayer{g.M, g.Ncols, g.C, g.ks, g.OH, g.OW, g.W, g.pad, count, scratch_bytes}, &strip);
+  if (pooled && !done) return hipErrorInvalidValue;
   if (done) {
     g.splits = strip.splits;
     switch (strip.form) {
-      case 0: launch_strip_t<0>(ws, g, dy_off, strip, count, s); break;
-      case 1: launch_strip_t<1>(ws, g, dy_off, strip, count, s); break;
-      case 2: launch_strip_t<2>(ws, g, dy_off, strip, count, s); break;
-      case 3: launch_strip_t<3>(ws, g, dy_off, strip, count, s); break;
-      default: launch_strip_t<4>(ws, g, dy_off, strip, count, s); break;
+      case 0: launch_strip_t<0>(ws, g, dy_off, strip, pooled, count, s); break;
+      case 1: launch_strip_t<1>(ws, g, dy_off, strip, pooled, count, s); break;
+      case 2: launch_strip_t<2>(ws, g, dy_off, strip, pooled, count, s); break;
+      case 3: launch_strip_t<3>(ws, g, dy_off, strip, pooled, count, s); break;
+      default: launch_strip_t<4>(ws, g, dy_off, strip, pooled, count, s); break;
     }
   }
 #define SASGD_WGRAD(BMG, BNG, WMG, WNG)                                                                                          \

@@ -149,9 +149,15 @@ bool conv_pool_ok(const IGemm& g, const PoolShape& ps);
 hipError_t launch_conv_pool(const PtrTab& ws, const CPtrTab& wts, const IGemm& g, const Epilogue& ep, const PoolShape& ps, size_t y_off, size_t arg_off,
                             bool pool_relu, int count, hipStream_t s);
 hipError_t launch_igemm_frag(const PtrTab& ws, const CPtrTab& wts, const IGemm& g, const Epilogue& ep, int count, hipStream_t s);
-// dW and db of one layer (the bias gradient rides along as one extra im2col column of ones).
+// dW and db of one layer (the bias gradient rides along as one extra im2col column of ones).  pooled: dy_off is the gradient of the 3 x 3 / 2 max
+// pooling's output behind the layer, whose winners are here; only where wgrad_takes_pooled() says so.
+struct PooledDy {
+  int OH, OW;
+  size_t arg_off;    // bytes
+};
+bool wgrad_takes_pooled(const IGemm& g, const VConv& v, const PoolShape& ps, size_t scratch_bytes, int count);
 hipError_t launch_igemm_wgrad(const PtrTab& ws, const PtrTab& grads, const IGemm& g, const VConv& v, size_t dy_off, int64_t w_off,
-                              int64_t b_off, size_t scratch_bytes, int count, hipStream_t s);
+                              int64_t b_off, size_t scratch_bytes, const PooledDy* pooled, int count, hipStream_t s);
 
 // y = conv(x, w) + b, optional ReLU.  w_off / b_off: element offsets into the learner's flat weight vector.
 // out_f32: y is stored as fp32 whatever T is (class scores).

@@ -845,9 +845,18 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
     const Epilogue ep{dx, tin.off, 0, 0, 0, tin.relu ? 1 : 0, 0};
     return launch_fc_rows(wsV, wtsV, vtab, versions, gd, ep, true, net->scratch_off, net->scratch_bytes, stream);
   };
+  // the first convolution's gradient has one reader, which may take it through the max pooling behind
+  PooledDy pooled{0, 0, 0};
+  bool through_pool = false;
+  if (bf && net->ops.size() > 1 && net->ops[0].kind == OP_CONV && net->ops[0].mfma && !net->ops[0].is_fc && net->ops[1].kind == OP_POOL_MAX) {
+    const Op &conv = net->ops[0], &pool = net->ops[1];
+    pooled = PooledDy{pool.ps.OH, pool.ps.OW, pool.arg_off};
+    through_pool = wgrad_takes_pooled(conv.gf, conv.vc, pool.ps, net->scratch_bytes, count);
+  }
   for (int k = (int)net->ops.size() - 1; k >= 0; k--) {
     const Op& op = net->ops[(size_t)k];
     const Tensor& tin = T[(size_t)op.in_t];
+    if (k == 1 && through_pool) continue;       // (dy stays the pooled tensor's gradient)
     const bool need_dx = op.in_t != 0;          // the network input needs no gradient
     switch (op.kind) {
       case OP_CONV:
@@ -872,7 +881,8 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
         } else if (op.mfma) {
           IGemm gw = op.gf;
           gw.scratch_off = net->scratch_off;
-          TRY(launch_igemm_wgrad(ws, grads, gw, op.vc, dy, op.w_off, op.b_off, net->scratch_bytes, count, stream));
+          TRY(launch_igemm_wgrad(ws, grads, gw, op.vc, dy, op.w_off, op.b_off, net->scratch_bytes,
+                                 k == 0 && through_pool ? &pooled : nullptr, count, stream));
           if (need_dx && op.is_fc) {
             TRY(fc_dgrad(op, tin));
           } else if (need_dx) {
