@@ -78,7 +78,7 @@ typedef struct {
   int32_t lr_mode;      /* PER_GRADIENT: alpha0 / tau_l for each gradient (Section 2.4);
                            MEAN_STALENESS: alpha0 / mean_l(tau_l); CONSTANT: alpha0.  A staleness
                            of 0 uses alpha0 unmodulated in every mode.                               */
-  int32_t flags;        /* 0, or SASGD_FLAG_FLAT_FC_GRADIENT.  By default (BF16 compute, mu <= 32) the weight
+  int32_t flags;        /* 0, or SASGD_FLAG_FLAT_FC_GRADIENT.  By default (BF16 compute; mu <= 32, or 256 if n = 1) the weight
                            gradient of a fully connected layer is not written out: with a mini-batch of mu
                            images it is the rank-mu product dy^T x, so calcGradient keeps the two factors
                            (mu x out and mu x in values) and applyUpdate forms the product on the fly in the

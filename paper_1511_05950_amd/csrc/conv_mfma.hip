@@ -290,9 +290,8 @@ __device__ __forceinline__ void frag_epilogue(floatx16 (&acc)[WM / 32][WN / 32],
 }
 
 // ------------------------------------------------------------------ convolution forward / dgrad, B from fragments
-// Same tiling as igemm_kernel, but only the gathered im2col tile goes through LDS; the filter operand comes
-// from the fragment-packed copy, one coalesced 1 KiB read per MFMA operand, prefetched one step ahead.  This
-// halves the LDS traffic per MFMA, which is what bounds the LDS-only variant.
+// Only the gathered im2col tile goes through LDS; the filter operand comes from the fragment-packed copy, one coalesced 1 KiB read
+// per MFMA operand, prefetched one step ahead.  This halves the LDS traffic per MFMA, which bounds a kernel with both operands there.
 constexpr uint32_t kOutOfRange = 0x80000000u;   // buffer offset beyond any tensor: the load returns zeros
 
 // NT = threads per workgroup = 64 x number of wave tiles.
