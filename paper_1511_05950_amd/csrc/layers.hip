@@ -104,8 +104,10 @@ __global__ __launch_bounds__(256) void pack_input_pixel_kernel(CPtrTab images, P
 // Space-to-depth by 4 of a 3-channel image (the 11 x 11 / 4 first layer): a workgroup makes `width` pixels of one row of destination
 // pixels (input_row_piece).  A thread reads the three channels' aligned float4 (row 4Y + dh, columns 4X .. 4X + 3) and puts
 // their twelve values, channels (dh * 4 + dw) * 3 + c, into LDS; the pixels leave as they lie there.  Needs W % 4 == 0 and 16-byte
-// aligned images (and mean).  Bound by HBM: 18 learners x 16 images 3 x 224 x 224, 260 MB, in 48 us; a lane per pixel, which writes
-// its 96 bytes on its own, took 78.
+// aligned images (and mean).  Bound by HBM: 18 learners x 16 images 3 x 224 x 224, 260 MB, in 42 us inside a training step; a lane per pixel, which
+// writes its 96 bytes on its own, took 78.  The images are read once, past the caches (54 us with ordinary loads, which drive out of them
+// what the step wrote; one learner of 256 images 48 -> 37; level in a validation pass, 33 and 34, which writes little).
+typedef float float4v __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void pack_input_s2d4_kernel(CPtrTab images, PtrTab ws, size_t out_off, InPack ip, int width,
                                                               int pieces, const float* __restrict__ mean) {
   extern __shared__ __attribute__((aligned(16))) uint2 s2d_row[];       // [width][96 bytes]
@@ -121,7 +123,8 @@ __global__ __launch_bounds__(256) void pack_input_s2d4_kernel(CPtrTab images, Pt
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
       if (h < ip.H) {
         const uint32_t pix = c * plane + (uint32_t)h * (uint32_t)ip.W + 4 * (x0 + X);
-        v = *reinterpret_cast<const float4*>(src + pix);
+        const float4v once = __builtin_nontemporal_load(reinterpret_cast<const float4v*>(src + pix));
+        v = make_float4(once.x, once.y, once.z, once.w);
         if (mean) {
           const float4 mv = *reinterpret_cast<const float4*>(mean + pix);
           v.x -= mv.x; v.y -= mv.y; v.z -= mv.z; v.w -= mv.w;
