@@ -84,7 +84,8 @@ typedef struct {
                            (mu x out and mu x in values) and applyUpdate forms the product on the fly in the
                            same fp32 arithmetic.  The 4 bytes per weight of gradient written by the learner
                            and read by the server disappear; copyGradient / gradientPtr expand the product on
-                           demand.  The flag forces the written-out gradient instead.  (Calls of few images on small
+                           demand.  The flag forces the written-out gradient instead, and with mu > 32 so does
+                           gradientPtr for the learner it was called for.  (Calls of few images on small
                            networks with a layer of an odd size write it out as well; both kinds may meet in
                            one update.)
                            SASGD_FLAG_EAGER_UPDATES: applyUpdate enqueues its kernels before it returns.  By default
@@ -235,7 +236,9 @@ int sasgd_copyGradient(sasgd_ctx* ctx, int32_t learner, float* host_out);
 int sasgd_copyMomentum(sasgd_ctx* ctx, float* host_out);
 /* Device address of a learner's gradient buffer (float32 [P]); valid for the context's lifetime.
  * Fully connected weight gradients kept as factors (see flags) are expanded into the buffer by
- * this call and by copyGradient (enqueued on the context's stream). */
+ * this call and by copyGradient (enqueued on the context's stream).  With mu > 32 the buffer is the
+ * gradient once its address has been handed out: the learner's later gradients are written out, and what
+ * the caller changes in it before the update is what the update takes. */
 int sasgd_gradientPtr(sasgd_ctx* ctx, int32_t learner, float** out_dev);
 
 /* Accumulated device time of the two hot phases since the last reset, measured with HIP events

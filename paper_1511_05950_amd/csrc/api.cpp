@@ -413,11 +413,13 @@ int sasgd_calcGradient(sasgd_ctx* ctx, const int32_t* learners, int32_t count, f
   bool seen[kMaxLearners] = {false};
   LearnerBind binds[kMaxLearners];
   int ids[kMaxLearners];
+  bool write_out = false;
   for (int k = 0; k < count; k++) {
     const int l = learners[k];
     if (l < 0 || l >= ctx->cfg.lambda || seen[l]) return fail(ctx, SASGD_EINVAL, "calcGradient: bad or duplicate learner");
     seen[l] = true;
     const Learner& L = ctx->learners[(size_t)l];
+    write_out = write_out || (L.grad_lent && ctx->cfg.mu > kFactorRowsAlways);
     if (!L.images || !L.has_weights) return fail(ctx, SASGD_ESTATE, "calcGradient: learner has no mini-batch or no weights bound");
     if (L.grad_state == GRAD_PENDING) return fail(ctx, SASGD_ESTATE, "calcGradient: learner's previous gradient is still pending at the server");
     if (!version_in_ring(ctx, L.pulled_version)) return fail(ctx, SASGD_ERANGE, "calcGradient: pulled version has left the ring");
@@ -430,7 +432,7 @@ int sasgd_calcGradient(sasgd_ctx* ctx, const int32_t* learners, int32_t count, f
   }
   prof_begin(ctx, 0);
   bool factors = false;
-  hipError_t e = net_calc_gradient(ctx->net, ids, binds, count, out_loss_dev, nullptr, &factors, ctx->stream);
+  hipError_t e = net_calc_gradient(ctx->net, ids, binds, count, out_loss_dev, nullptr, write_out, &factors, ctx->stream);
   prof_end(ctx);
   if (e != hipSuccess) return fail_hip(ctx, e, "calcGradient");
   for (int k = 0; k < count; k++) {
@@ -472,7 +474,7 @@ int sasgd_evaluate(sasgd_ctx* ctx, const int32_t* learners, int32_t count, float
     binds[k].version = L.pulled_version;
     binds[k].grad = nullptr;             // the evaluation pass writes no gradient
   }
-  hipError_t e = net_calc_gradient(ctx->net, ids, binds, count, out_loss_dev, out_rank_dev, nullptr, ctx->stream);
+  hipError_t e = net_calc_gradient(ctx->net, ids, binds, count, out_loss_dev, out_rank_dev, false, nullptr, ctx->stream);
   if (e != hipSuccess) return fail_hip(ctx, e, "evaluate");
   // The bindings stay, but a binding that an evaluation has used no longer keeps its version in the ring: a training
   // loop evaluates and moves on, and must not be stopped by applyUpdate's eviction check many updates later.
@@ -758,9 +760,16 @@ int sasgd_gradientPtr(sasgd_ctx* ctx, int32_t learner, float** out_dev) {
     const int rc = flush_updates(ctx);
     if (rc != SASGD_OK) return rc;
   }
-  hipError_t e = expand_factored(ctx, ctx->learners[(size_t)learner]);
+  Learner& L = ctx->learners[(size_t)learner];
+  hipError_t e = expand_factored(ctx, L);
   if (e != hipSuccess) return fail_hip(ctx, e, "gradientPtr");
-  *out_dev = ctx->learners[(size_t)learner].grad;
+  L.grad_lent = true;
+  if (ctx->cfg.mu > kFactorRowsAlways) {       // from here on the buffer is the gradient, for the server too
+    L.has_factors = false;
+    for (Pending& p : ctx->pending)
+      if (p.learner == learner) p.factors_ws = nullptr;
+  }
+  *out_dev = L.grad;
   return SASGD_OK;
 }
 

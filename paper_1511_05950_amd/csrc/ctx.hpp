@@ -59,6 +59,7 @@ hipError_t static_sum_buffer(float** out);
 // Update of the fully connected layers (each: weights [out][in] followed by the bias [out]) whose gradients are kept as
 // factors, all layers in ONE launch.  theta_in / theta_out / v / shadow_out / grads address element 0 of the flat vector.
 constexpr int kMaxFactorRows = 256;      // images of a mini-batch whose weight gradients are kept as factors
+constexpr int kFactorRowsAlways = 32;    // up to here also where the caller holds the gradient buffer's address (sasgd_gradientPtr)
 constexpr int kMaxFactoredLayers = 16;   // further fully connected layers write their gradient out
 struct FcUpdateLaunch {
   const float* theta_in;
@@ -107,9 +108,10 @@ hipError_t net_prepare_version(Net* net, const void* flat, void* packed, hipStre
 hipError_t net_prepare_versions(Net* net, const void* const* flat, void* const* packed, int versions, hipStream_t stream);
 // out_rank_dev == nullptr: forward, loss, backward (gradients into binds[k].grad).
 // out_rank_dev != nullptr: evaluation pass, forward and loss only, plus the rank of each image's true class.
+// write_out: no gradient is left as factors.
 // *wrote_factors (unless null): the factored layers' weight gradients were left as factors; false: all gradients are written out.
 hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* binds, int count,
-                             float* out_loss_dev, int32_t* out_rank_dev, bool* wrote_factors, hipStream_t stream);
+                             float* out_loss_dev, int32_t* out_rank_dev, bool write_out, bool* wrote_factors, hipStream_t stream);
 // Fully connected layers whose weight gradient calcGradient can leave as factors in the learner's workspace
 // (bf16 element offsets from the workspace base): weights at w_off [out][in], bias right behind them.
 struct FactoredLayer {
@@ -136,6 +138,7 @@ struct Learner {
   void* workspace = nullptr;
   bool has_factors = false;    // the current gradient's factored layers lie in `workspace` as factors
   bool fc_expanded = false;    // those have been written out into `grad` as well
+  bool grad_lent = false;      // the caller has the address of `grad`
 };
 
 struct Pending;

@@ -343,7 +343,7 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
         // rank-N weight gradient kept as factors: worth it while the products per weight and pending gradient stay far
         // below what the update's streaming rate leaves room for; with more than 32 images where every update is a pass of its own
         const int c_upd = cfg.lambda / cfg.n;
-        if (op.mfma && net->bf16 && !(cfg.flags & SASGD_FLAG_FLAT_FC_GRADIENT) && N <= (cfg.n == 1 ? kMaxFactorRows : 32) && (int64_t)c_upd * N <= 1024 &&
+        if (op.mfma && net->bf16 && !(cfg.flags & SASGD_FLAG_FLAT_FC_GRADIENT) && N <= (cfg.n == 1 ? kMaxFactorRows : kFactorRowsAlways) && (int64_t)c_upd * N <= 1024 &&
             op.w_off % 4 == 0 && L.units % 4 == 0 && in % 8 == 0 && n_factored < kMaxFactoredLayers) {
           op.factored = true;
           op.NP = (N + 7) & ~7;
@@ -382,7 +382,7 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
     bool any_factored = false;
     for (const Op& op : net->ops) any_factored = any_factored || op.factored;
     // they write every gradient out: not where the factors of few images are kept and all layers have kernels of their own
-    if (any_factored && N <= 32 && !cp.any_odd()) cp.ok = false;
+    if (any_factored && N <= kFactorRowsAlways && !cp.any_odd()) cp.ok = false;
     // the cost is linear in the learners of a call, so that the largest call decides for all of them
     cp.always = cp.ok && compact_wins(cp, net->bf16, N, cfg.lambda, false) && compact_wins(cp, net->bf16, N, cfg.lambda, true);
     if (cp.always)
@@ -713,7 +713,7 @@ static hipError_t compact_gradient(Net* net, const PtrTab& ws, const CPtrTab& wt
 
 // Forward pass, loss and (unless out_rank_dev is given, which makes this an evaluation pass) backward pass.
 hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* binds, int count, float* out_loss_dev,
-                             int32_t* out_rank_dev, bool* wrote_factors, hipStream_t stream) {
+                             int32_t* out_rank_dev, bool write_out, bool* wrote_factors, hipStream_t stream) {
   PtrTab ws, grads;
   CPtrTab wts, imgs, labs;
   memset(&ws, 0, sizeof(ws)); memset(&grads, 0, sizeof(grads));
@@ -730,7 +730,7 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
   const bool compact = net->compact.ok && (net->compact.always || compact_wins(net->compact, bf, net->mu, count, out_rank_dev != nullptr));
   if (wrote_factors) {
     *wrote_factors = false;
-    for (const Op& op : net->ops) *wrote_factors = *wrote_factors || (op.factored && !compact);
+    for (const Op& op : net->ops) *wrote_factors = *wrote_factors || (op.factored && !compact && !write_out);
   }
   if (compact)
     return compact_gradient(net, ws, wts, imgs, labs, grads, count, out_loss_dev, out_rank_dev, stream);
@@ -875,7 +875,7 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
             Epilogue ep{dx, tin.off, 0, 0, 0, tin.relu ? 1 : 0, 1};
             TRY(launch_igemm_f32(ws, wts, gd, op.vc, ep, op.w_off, true, count, stream));
           }
-        } else if (op.mfma && op.factored) {
+        } else if (op.mfma && op.factored && !write_out) {
           TRY(launch_fc_save_factors(ws, grads, tin.off, dy, op.fx_off, op.fdy_off, op.b_off, op.cs.N, op.cs.C, op.cs.K, op.NP, count, stream));
           if (need_dx) TRY(fc_dgrad(op, tin));
         } else if (op.mfma) {

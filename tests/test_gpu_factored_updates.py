@@ -59,3 +59,51 @@ def test_update_from_factors(lam, mu):
             assert np.max(np.abs(a - b)) <= 1e-4 * np.max(np.abs(b)), (shape, n)
             pos += n
     assert rel(fa[3] - w0, fl[3] - w0) < 2e-3          # a second update, on weights that differ in the last place
+
+
+class Buffer:
+    """A learner's gradient buffer, whose address was asked for at some time, as a tensor."""
+
+    def __init__(self, ctx, learner):
+        self.__cuda_array_interface__ = {"data": (ctx.gradientPtr(learner), False), "shape": (ctx.P,), "typestr": "<f4", "version": 2}
+
+
+@pytest.mark.parametrize("asked", ["at_the_start", "after_calcGradient", "after_pushGradient"])
+def test_a_caller_that_holds_the_gradient_finds_and_changes_it_there(asked):
+    """Mini-batches of more than 32 images: a buffer whose address the caller has holds every later gradient without another call, and the
+    update takes what the caller made of it, as where all gradients are written out."""
+    from paper_1511_05950_amd import binding
+    lam, mu = 2, 40
+    w0 = wl.init_weights(NET, 15, std=0.05)
+    X, Y = torch.from_numpy(wl.images(NET, lam * mu, 16)).cuda(), torch.from_numpy(wl.labels(NET, lam * mu, 17)).cuda()
+    got = []
+    for flags in (0, binding.FLAG_FLAT_FC_GRADIENT):
+        ctx = binding.Sasgd(lam, mu, 1, 2, net=NET, compute="bf16", alpha0=0.05, momentum=0.5, weight_decay=1e-2, init_weights=w0, flags=flags)
+        assert (ctx.factoredParams() > 0) == (flags == 0)
+        held, seen = None, []
+        if asked == "at_the_start":
+            held = torch.as_tensor(Buffer(ctx, 0), device="cuda")
+        for update in range(2):
+            for k in range(lam):
+                ctx.getMinibatch(k, X[k * mu:(k + 1) * mu], Y[k * mu:(k + 1) * mu])
+                ctx.pullWeights(k, 0)
+            ctx.calcGradient(list(range(lam)))
+            if held is None and asked == "after_calcGradient":
+                held = torch.as_tensor(Buffer(ctx, 0), device="cuda")
+            for k in range(lam):
+                ctx.pushGradient(k)
+            if held is None:
+                held = torch.as_tensor(Buffer(ctx, 0), device="cuda")
+            seen.append(held.clone())
+            held.clamp_(-1e-4, 1e-4)                          # the caller's clipping
+            seen.append(held.clone())
+            ctx.sumGradients()
+            ctx.applyUpdate()
+            seen.append(torch.from_numpy(ctx.copyMomentum()))
+        got.append([s.cpu().numpy() for s in seen])
+        del held
+        ctx.destroy()
+    assert np.abs(got[0][0]).max() > 2e-4                     # there was something to clip
+    for k, (a, b) in enumerate(zip(*got)):
+        # (sums in another order where the factors had been taken; behind the first update, weights that differ in the last place)
+        assert rel(a, b) < (1e-5 if k < 3 else 2e-3), (asked, k)
