@@ -342,11 +342,13 @@ int net_create(const sasgd_config& cfg, Net** out, int64_t* out_P, size_t* out_p
         if (net->bf16) op.mfma = op.mfma && fc_rows_layer_ok(in);
         // rank-N weight gradient kept as factors: worth it while the products per weight and pending gradient stay far
         // below what the update's streaming rate leaves room for; with more than 32 images where every update is a pass of its own
-        const int c_upd = cfg.lambda / cfg.n;
+        // (and where the factors' rounded-up rows stay within a tensor's limit, below, as the layer's own tensors may)
+        const int c_upd = cfg.lambda / cfg.n, NP = (N + 7) & ~7;
         if (op.mfma && net->bf16 && !(cfg.flags & SASGD_FLAG_FLAT_FC_GRADIENT) && N <= (cfg.n == 1 ? kMaxFactorRows : kFactorRowsAlways) && (int64_t)c_upd * N <= 1024 &&
-            op.w_off % 4 == 0 && L.units % 4 == 0 && in % 8 == 0 && n_factored < kMaxFactoredLayers) {
+            op.w_off % 4 == 0 && L.units % 4 == 0 && in % 8 == 0 && n_factored < kMaxFactoredLayers &&
+            (int64_t)std::max(in, L.units) * NP * 4 < ((int64_t)1 << 31)) {
           op.factored = true;
-          op.NP = (N + 7) & ~7;
+          op.NP = NP;
           n_factored++;
         }
       }

@@ -42,3 +42,14 @@ def test_many_inputs(compute, shape, mu):
     net = {"name": "inputs", "input": shape, "classes": 4, "layers": [("fc", 8), ("fc", 4)]}
     for (g, rg, loss, rl) in one_gradient(net, mu, compute, seed=6, scale=0.002, lam=1):
         check_gradient(net, compute, g, rg, loss, rl, "many inputs")
+
+
+def test_inputs_that_fit_but_for_the_factors_rounding():
+    """249 images of 2 144 000 inputs: their tensors stay below 2 GiB in 32 bits, and those of rows rounded up to 256 would not.  The layer then
+    keeps no factors."""
+    from paper_1511_05950_amd import binding
+    net = {"name": "inputs", "input": (8, 500, 536), "classes": 4, "layers": [("fc", 8), ("fc", 4)]}
+    assert 249 * 2_144_000 * 4 < 2 ** 31 < 256 * 2_144_000 * 4
+    ctx = binding.Sasgd(1, 249, 1, 1, net=net, compute="bf16", init_weights=torch.zeros(wl.num_params(net), device="cuda"))
+    assert ctx.factoredParams() == 0
+    ctx.destroy()
