@@ -582,8 +582,8 @@ __global__ __launch_bounds__(256) void apply_update_fc_kernel(const float* theta
 // a wavefront owns 64 x 64 weights, each operand serves two products, the running sum stays in MFMA order and is turned around once,
 // at its end.  theta and v come half a tile at a time, the first half on its way during the sums.
 // Lone steps of the AlexNet-shaped net's 58.6 M weights, all layers, whose theta, v and bf16 copy alone take 175 us at the copy rate: 18
-// gradients of 16 images 335 us with 32 x 32 weights a wavefront, 219 here; 8 of 32 267 and 204; one of 256 images 341 and 195 (written out
-// by the weight-gradient kernel, 118 us, and read again, it took 200); 4 of 256 961 and 304.
+// gradients of 16 images 335 us with 32 x 32 weights a wavefront, 219 here; 8 of 32 267 and 205; one of 256 images 341 and 197 (written out
+// by the weight-gradient kernel, 118 us, and read again, it took 200); 4 of 256 961 and 298.
 typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
 typedef unsigned v2u_t __attribute__((ext_vector_type(2)));
 constexpr int kDeepTile = 128;                        // weights of a workgroup in each direction: 2 x 2 wavefronts
@@ -755,9 +755,11 @@ __global__ __launch_bounds__(256, 2) void apply_update_fc_deep_kernel(const floa
       if (++fst == per) { fst = 0; fl++; }
     };
 #pragma clang diagnostic pop
+    // (theta's and momentum's pieces in front: the waits below count the loads to LDS behind a stage and nothing that the compiler issues,
+    // however many instructions it makes of a fetch)
+    if (!EXPAND) fetch(0);
     request(0);
     request(kDeepStage);
-    if (!EXPAND) fetch(0);
     const char* L = reinterpret_cast<const char*>(lds);
     const int arow = (64 * (wave >> 1) + j) * 128, brow = kDeepTile * 128 + (64 * (wave & 1) + j) * 128;
     floatx16_t p[2][2];
@@ -771,9 +773,7 @@ __global__ __launch_bounds__(256, 2) void apply_update_fc_deep_kernel(const floa
     uint32_t at = 0;
 #pragma unroll 1
     for (int s = 0; s < total; s++) {
-      // this stage has landed (behind the first two: theta's and momentum's pieces, requested between them and the third)
-      if (!EXPAND && s < 2) asm volatile("s_waitcnt vmcnt(24)\n\ts_barrier" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+      asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");         // this stage has landed: eight loads of the next one are behind it
       const int kks = min(4, (NP - 64 * stg + 15) >> 4);
       auto read = [&](bf16x8_t (&a)[2], bf16x8_t (&b)[2], int kk) {
         const int place = ((2 * kk + h) ^ (j & 7)) * 16;

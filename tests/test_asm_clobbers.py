@@ -1,5 +1,6 @@
 """Inline assembly under csrc/: a statement that writes a register by name says so to the compiler, which may otherwise keep a value of its
-own there (the destination of an LDS load that it places itself, say)."""
+own there (the destination of an LDS load that it places itself, say).  A wait for
+loads to LDS counts those behind the awaited ones only, never loads that the compiler issues, in whatever number."""
 import glob
 import os
 import re
@@ -30,3 +31,12 @@ def test_the_scan_sees_a_missing_clobber():
     bad = r'asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(a), "v"(b), "s"(c) : "memory");'
     good = bad.replace('"memory"', '"memory", "m0"')
     assert [w <= n for w, n in written_and_named(bad)] == [False] and [w <= n for w, n in written_and_named(good)] == [True]
+
+
+def test_the_staged_update_waits_for_its_own_loads_only():
+    """vmcnt is the number of loads still on their way that a wait allows.  In the staged update from factors a stage is eight loads to LDS, of which
+    the next stage's are behind it: more may only be allowed where more of the kernel's own are certain to be."""
+    source = open(os.path.join(CSRC, "update.hip")).read()
+    kernel = source[source.index("void apply_update_fc_deep_kernel("):source.index("hipError_t launch_apply_update_fc(")]
+    allowed = [int(n) for n in re.findall(r"vmcnt\((\d+)\)", kernel)]
+    assert allowed and max(allowed) <= 8
