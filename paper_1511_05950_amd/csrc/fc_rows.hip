@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256, 1) void fc_rows_kernel(PtrTab ws, CPtrTab wts,
   auto load = [&](uint32_t stage, int l) {           // load l of a wavefront into the stage at byte `stage` of LDS
     if (l < LA) {
       const bf16_t* p = a_k < a_end[l] ? a_ptr[l] + a_k : zeros;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds0 + stage + (LA * wave + l) * 1024), "v"(p) : "m0");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds0 + stage + (LA * wave + l) * 1024), "v"(p) : "memory", "m0");
     } else {
       const int off = b_k[l - LA] < k_end ? b_off[l - LA] : (int)kOutOfRange;
       v4i_t rsrc;
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(256, 1) void fc_rows_kernel(PtrTab ws, CPtrTab wts,
       rsrc.z = 0x7fffffff;                           // rows and columns are checked here
       rsrc.w = 0x00020000;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::
-                   "s"(lds0 + stage + (A_ELEMS * 2 + (LB * wave + l - LA) * 1024)), "v"(off), "s"(rsrc) : "m0");
+                   "s"(lds0 + stage + (A_ELEMS * 2 + (LB * wave + l - LA) * 1024)), "v"(off), "s"(rsrc) : "memory", "m0");
       b_k[l - LA] += FRK;
     }
     if (l == L - 1) { a_k += FRK; b_base += b_step; }

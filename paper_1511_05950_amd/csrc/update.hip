@@ -749,8 +749,8 @@ __global__ __launch_bounds__(256, 2) void apply_update_fc_deep_kernel(const floa
 #pragma unroll
       for (int q = 0; q < 4; q++) {
         const uint32_t dst = lds0 + at + (4 * wave + q) * 1024;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst), "v"(ok ? ro[q] : (int)0x80000000u), "s"(rd) : "m0");
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst + kDeepTile * 128), "v"(ok ? rx[q] : (int)0x80000000u), "s"(rxs) : "m0");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst), "v"(ok ? ro[q] : (int)0x80000000u), "s"(rd) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst + kDeepTile * 128), "v"(ok ? rx[q] : (int)0x80000000u), "s"(rxs) : "memory", "m0");
       }
       if (++fst == per) { fst = 0; fl++; }
     };

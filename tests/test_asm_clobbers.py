@@ -1,5 +1,5 @@
 """Inline assembly under csrc/: a statement that writes a register by name says so to the compiler, which may otherwise keep a value of its
-own there (the destination of an LDS load that it places itself, say).  A wait for
+own there (the destination of an LDS load that it places itself, say), and one that loads to LDS says that it writes memory.  A wait for
 loads to LDS counts those behind the awaited ones only, never loads that the compiler issues, in whatever number."""
 import glob
 import os
@@ -31,6 +31,27 @@ def test_the_scan_sees_a_missing_clobber():
     bad = r'asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(a), "v"(b), "s"(c) : "memory");'
     good = bad.replace('"memory"', '"memory", "m0"')
     assert [w <= n for w, n in written_and_named(bad)] == [False] and [w <= n for w, n in written_and_named(good)] == [True]
+
+
+LDS_LOAD = re.compile(r"\b(?:buffer|global)_load_\w+.*\blds\b|\bglobal_load_lds_\w+")
+
+
+def lds_loads(source):
+    for m in STATEMENT.finditer(source):
+        parts = m.group(1).split(":")
+        if LDS_LOAD.search(re.sub(r"\\[nt]", " ", "".join(re.findall(r'"([^"]*)"', parts[0])))):
+            yield '"memory"' in parts[-1]
+
+
+def test_loads_to_lds_clobber_memory():
+    seen = 0
+    for path in sorted(glob.glob(os.path.join(CSRC, "*.h*"))):
+        for named in lds_loads(open(path).read()):
+            seen += 1
+            assert named, os.path.basename(path)
+    assert seen >= 5                             # the strip kernel's, two of the fully connected product, two of the update from factors
+    bad = r'asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(a), "v"(b), "s"(c) : "m0");'
+    assert list(lds_loads(bad)) == [False] and list(lds_loads(bad.replace('"m0");', '"memory", "m0");'))) == [True]
 
 
 def test_the_staged_update_waits_for_its_own_loads_only():
