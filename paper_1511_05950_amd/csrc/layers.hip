@@ -583,127 +583,252 @@ hipError_t launch_pool_bwd(bool is_bf16, bool is_max, const PtrTab& ws, size_t d
 }
 
 // ------------------------------------------------------------------ flatten (NHWC -> C,H,W order) and back
-// A workgroup turns 64 channels of one image around through LDS: reads and writes are whole 16-byte pieces of neighbouring addresses (an
-// element per lane with its three 64-bit divisions took 9 us for 256 images of 256 x 6 x 6, 5 here: a launch and one round trip).  `whole`
-// says that the channels come in such pieces and the tile fits; otherwise the elements of the same tiles go one by one.
-constexpr int kFlatC = 64;
+// A workgroup turns up to 64 channels of up to 64 positions of one image around through LDS, so that a call of any shape has a workgroup for every
+// 4 096 values (or 8 192, below), and both sides' accesses are of neighbouring addresses: channels on one side in whole 16-byte pieces where they come in such, positions
+// on the other where an image's do, or where the tile holds the whole image (its 64 channels lie one after the other then).
+// Bound by the launch and two round trips to memory in small calls, by HBM in large ones.  bf16, forward and backward in us, with a value a lane and
+// three 64-bit divisions / here: 64 channels of 32 x 32, 16 images 7 / 4 and 5 / 5, 576 images 148 / 25 and 115 / 30; 72 of 45 x 45, 576 images
+// 371 / 110 and 323 / 123; 256 of 6 x 6, 256 images 9.6 / 5.2 and 10.5 / 5.4.  (With a workgroup for all positions of 64 channels, the 16 images took 54 and 47.)
 template <typename T>
 struct FlatTile {
-  static constexpr int V = 16 / sizeof(T), kPitch = kFlatC + 16 / sizeof(T);     // elements
+  static constexpr int V = 16 / sizeof(T), kPitch = kFlat + 16 / sizeof(T);     // elements
 };
+__device__ __forceinline__ uint32_t flat_bits(bf16_t v) { return v; }
+__device__ __forceinline__ uint32_t flat_bits(float v) { return __float_as_uint(v); }
+__device__ __forceinline__ void flat_store(bf16_t* to, uint32_t v) { *to = (bf16_t)v; }
+__device__ __forceinline__ void flat_store(float* to, uint32_t v) { *to = __uint_as_float(v); }
 struct FlatArgs {
-  int C, HW, blocks, whole;      // channel blocks of an image
-  FastDiv by_hw;                 // whole: 64 HW squared stays far below 2^32
+  int C, HW, cblocks;            // blocks of channels
+  FastDiv by_c, by_p;            // channels and positions of a full tile
 };
 
-template <typename T>
+// A step of the workgroup's way over a tile: position and channel of this lane's value or piece, false behind the last one.  Neighbouring lanes
+// take neighbouring channels, or positions.
+template <int V>
+__device__ __forceinline__ bool flat_channels(const FlatArgs& a, int cn, int pn, int i, int& p, int& c) {
+  if (V > 1) { p = i / (kFlat / V); c = i % (kFlat / V) * V; }
+  else { p = a.by_c(i); c = i - p * min(a.C, kFlat); }
+  return p < pn && c < cn;
+}
+template <int V>
+__device__ __forceinline__ bool flat_positions(const FlatArgs& a, int cn, int pn, int i, int& p, int& c) {
+  if (V > 1) { c = i / (kFlat / V); p = i % (kFlat / V) * V; }
+  else { c = a.by_p(i); p = i - c * min(a.HW, kFlat); }
+  return p < pn && c < cn;
+}
+// All of a lane's reads (get) are on their way before the first is used (put): one after the other they take a memory latency each.  Of `all` steps
+// of all lanes.  (Values of 16 bits in registers of their own: a load into half a register waits for the other half's.)
+template <int STEPS, typename R, typename At, typename Get>
+__device__ __forceinline__ void flat_get(R (&v)[STEPS], int all, At at, Get get) {
+#pragma unroll
+  for (int k = 0; k < STEPS; k++) {
+    int p, c;
+    if (256 * k < all && at((int)threadIdx.x + 256 * k, p, c)) v[k] = get(p, c);
+  }
+}
+template <int STEPS, typename R, typename At, typename Put>
+__device__ __forceinline__ void flat_put(const R (&v)[STEPS], int all, At at, Put put) {
+#pragma unroll
+  for (int k = 0; k < STEPS; k++) {
+    int p, c;
+    if (256 * k < all && at((int)threadIdx.x + 256 * k, p, c)) put(p, c, v[k]);
+  }
+}
+
+template <typename T, bool PIECES, int ROWS>
 __global__ __launch_bounds__(256) void flatten_fwd_kernel(PtrTab ws, size_t x_off, size_t y_off, FlatArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char flat_lds[];
-  T* tile = reinterpret_cast<T*>(flat_lds);                      // [HW][kPitch]
-  constexpr int V = FlatTile<T>::V, PITCH = FlatTile<T>::kPitch;
-  const int n = (int)blockIdx.x / a.blocks, c0 = ((int)blockIdx.x - n * a.blocks) * kFlatC, cn = min(kFlatC, a.C - c0);
-  const T* x = (const T*)ws.p[blockIdx.z] + x_off + (int64_t)n * a.HW * a.C + c0;
-  T* y = (T*)ws.p[blockIdx.z] + y_off + ((int64_t)n * a.C + c0) * a.HW;
-  if (a.whole) {
-    for (int i = threadIdx.x; i < a.HW * (kFlatC / V); i += 256) {
-      const int hw = i / (kFlatC / V), c = i % (kFlatC / V) * V;
-      if (c < cn) *reinterpret_cast<uint4*>(tile + hw * PITCH + c) = *reinterpret_cast<const uint4*>(x + (int64_t)hw * a.C + c);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x * V; i < cn * a.HW; i += 256 * V) {
+  constexpr int V = FlatTile<T>::V, PITCH = FlatTile<T>::kPitch, POS = flat_positions_of(ROWS), ALL = kFlat * POS / 256;
+  constexpr bool BLOCK = ROWS == FLAT_BLOCK || ROWS == FLAT_BLOCK_128;
+  __shared__ __attribute__((aligned(16))) T tile[POS * PITCH];
+  const int n = blockIdx.y, c0 = (int)blockIdx.x % a.cblocks * kFlat, p0 = (int)blockIdx.x / a.cblocks * POS;
+  const int cn = min(kFlat, a.C - c0), pn = min(POS, a.HW - p0), wc = min(kFlat, a.C), wp = min(kFlat, a.HW);
+  const T* x = (const T*)ws.p[blockIdx.z] + x_off + ((int64_t)n * a.HW + p0) * a.C + c0;
+  T* y = (T*)ws.p[blockIdx.z] + y_off + ((int64_t)n * a.C + c0) * a.HW + p0;
+  if constexpr (PIECES) {
+    uint4 v[ALL / V];
+    auto at = [&](int i, int& p, int& c) { return flat_channels<V>(a, cn, pn, i, p, c); };
+    flat_get(v, pn * (kFlat / V), at, [&](int p, int c) { return *reinterpret_cast<const uint4*>(x + p * a.C + c); });
+    flat_put(v, pn * (kFlat / V), at, [&](int p, int c, const uint4& q) { *reinterpret_cast<uint4*>(tile + p * PITCH + c) = q; });
+  } else {
+    uint32_t v[ALL];
+    auto at = [&](int i, int& p, int& c) { return flat_channels<1>(a, cn, pn, i, p, c); };
+    flat_get(v, pn * wc, at, [&](int p, int c) { return flat_bits(x[p * a.C + c]); });
+    flat_put(v, pn * wc, at, [&](int p, int c, uint32_t q) { flat_store(tile + p * PITCH + c, q); });
+  }
+  __syncthreads();
+  if constexpr (ROWS == FLAT_ELEMENTS) {
+    uint32_t v[ALL];
+    auto at = [&](int i, int& p, int& c) { return flat_positions<1>(a, cn, pn, i, p, c); };
+    flat_get(v, cn * wp, at, [&](int p, int c) { return flat_bits(tile[p * PITCH + c]); });
+    flat_put(v, cn * wp, at, [&](int p, int c, uint32_t q) { flat_store(y + c * a.HW + p, q); });
+  } else {
+#pragma unroll
+    for (int k = 0; k < ALL / V; k++) {
+      const int i = (int)threadIdx.x + 256 * k;
       union { uint4 q; T e[V]; } o;
-      int c = a.by_hw(i), hw = i - c * a.HW;
+      int p, c;
+      if (BLOCK) {
+        c = a.by_p(i * V);
+        p = i * V - c * a.HW;
+        if (i * V >= cn * a.HW) continue;
+      } else if (!flat_positions<V>(a, cn, pn, i, p, c)) {
+        continue;
+      }
+      T* to = y + c * a.HW + p;
 #pragma unroll
       for (int e = 0; e < V; e++) {
-        o.e[e] = tile[hw * PITCH + c];
-        if (++hw == a.HW) { hw = 0; c++; }
+        o.e[e] = tile[p * PITCH + c];
+        if (++p == a.HW && BLOCK) { p = 0; c++; }
       }
-      *reinterpret_cast<uint4*>(y + i) = o.q;
-    }
-  } else {
-    for (int i = threadIdx.x; i < cn * a.HW; i += 256) {
-      const int c = i / a.HW, hw = i - c * a.HW;
-      y[i] = x[(int64_t)hw * a.C + c];
+      *reinterpret_cast<uint4*>(to) = o.q;
     }
   }
 }
 
-template <typename T>
+template <typename T, bool PIECES, int ROWS>
 __global__ __launch_bounds__(256) void flatten_bwd_kernel(PtrTab ws, size_t dy_off, size_t dx_off, FlatArgs a, int use_mask, size_t mask_off) {
-  extern __shared__ __attribute__((aligned(16))) char flat_lds[];
-  T* tile = reinterpret_cast<T*>(flat_lds);
-  constexpr int V = FlatTile<T>::V, PITCH = FlatTile<T>::kPitch;
-  const int n = (int)blockIdx.x / a.blocks, c0 = ((int)blockIdx.x - n * a.blocks) * kFlatC, cn = min(kFlatC, a.C - c0);
-  const int64_t at = (int64_t)n * a.HW * a.C + c0;
-  const T* dy = (const T*)ws.p[blockIdx.z] + dy_off + ((int64_t)n * a.C + c0) * a.HW;
-  T* dx = (T*)ws.p[blockIdx.z] + dx_off + at;
-  const T* mask = (const T*)ws.p[blockIdx.z] + mask_off + at;
-  if (a.whole) {
-    for (int i = threadIdx.x * V; i < cn * a.HW; i += 256 * V) {
-      union { uint4 q; T e[V]; } o;
-      o.q = *reinterpret_cast<const uint4*>(dy + i);
-      int c = a.by_hw(i), hw = i - c * a.HW;
+  constexpr int V = FlatTile<T>::V, PITCH = FlatTile<T>::kPitch, POS = flat_positions_of(ROWS), ALL = kFlat * POS / 256;
+  constexpr bool BLOCK = ROWS == FLAT_BLOCK || ROWS == FLAT_BLOCK_128;
+  __shared__ __attribute__((aligned(16))) T tile[POS * PITCH];
+  const int n = blockIdx.y, c0 = (int)blockIdx.x % a.cblocks * kFlat, p0 = (int)blockIdx.x / a.cblocks * POS;
+  const int cn = min(kFlat, a.C - c0), pn = min(POS, a.HW - p0), wc = min(kFlat, a.C), wp = min(kFlat, a.HW);
+  const int64_t first = ((int64_t)n * a.HW + p0) * a.C + c0;
+  const T* dy = (const T*)ws.p[blockIdx.z] + dy_off + ((int64_t)n * a.C + c0) * a.HW + p0;
+  T* dx = (T*)ws.p[blockIdx.z] + dx_off + first;
+  const T* mask = (const T*)ws.p[blockIdx.z] + mask_off + first;
+  constexpr int OUT = PIECES ? ALL / V : ALL;
+  union Piece { uint4 q; T e[V]; };
+  uint4 mq[PIECES ? ALL / V : 1];
+  uint32_t me[PIECES ? 1 : ALL];
+  auto out = [&](int i, int& p, int& c) { return flat_channels<PIECES ? V : 1>(a, cn, pn, i, p, c); };
+  const int out_steps = pn * (PIECES ? kFlat / V : wc);
+  if (use_mask) {
+    if constexpr (PIECES) flat_get(mq, out_steps, out, [&](int p, int c) { return *reinterpret_cast<const uint4*>(mask + p * a.C + c); });
+    else flat_get(me, out_steps, out, [&](int p, int c) { return flat_bits(mask[p * a.C + c]); });
+  }
+  if constexpr (ROWS == FLAT_ELEMENTS) {
+    uint32_t v[ALL];
+    auto at = [&](int i, int& p, int& c) { return flat_positions<1>(a, cn, pn, i, p, c); };
+    flat_get(v, cn * wp, at, [&](int p, int c) { return flat_bits(dy[c * a.HW + p]); });
+    flat_put(v, cn * wp, at, [&](int p, int c, uint32_t q) { flat_store(tile + p * PITCH + c, q); });
+  } else {
+    Piece v[ALL / V];
+    auto at = [&](int i, int& p, int& c) {
+      if (!BLOCK) return flat_positions<V>(a, cn, pn, i, p, c);
+      c = a.by_p(i * V);
+      p = i * V - c * a.HW;
+      return i * V < cn * a.HW;
+    };
+    flat_get(v, cn * (POS / V), at, [&](int p, int c) { Piece o; o.q = *reinterpret_cast<const uint4*>(dy + c * a.HW + p); return o; });
+    flat_put(v, cn * (POS / V), at, [&](int p, int c, const Piece& o) {
 #pragma unroll
       for (int e = 0; e < V; e++) {
-        tile[hw * PITCH + c] = o.e[e];
-        if (++hw == a.HW) { hw = 0; c++; }
+        tile[p * PITCH + c] = o.e[e];
+        if (++p == a.HW && BLOCK) { p = 0; c++; }
       }
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < a.HW * (kFlatC / V); i += 256) {
-      const int hw = i / (kFlatC / V), c = i % (kFlatC / V) * V;
-      if (c >= cn) continue;
-      union { uint4 q; T e[V]; } o, m;
-      o.q = *reinterpret_cast<const uint4*>(tile + hw * PITCH + c);
-      if (use_mask) {
-        m.q = *reinterpret_cast<const uint4*>(mask + (int64_t)hw * a.C + c);
+    });
+  }
+  __syncthreads();
 #pragma unroll
-        for (int e = 0; e < V; e++)
-          if (!(ldf(&m.e[e]) > 0.f)) o.e[e] = (T)0;
-      }
-      *reinterpret_cast<uint4*>(dx + (int64_t)hw * a.C + c) = o.q;
-    }
-  } else {
-    for (int i = threadIdx.x; i < a.HW * kFlatC; i += 256) {
-      const int hw = i / kFlatC, c = i % kFlatC;
-      if (c >= cn) continue;
-      float v = ldf(dy + c * a.HW + hw);
-      if (use_mask && !(ldf(mask + (int64_t)hw * a.C + c) > 0.f)) v = 0.f;
-      stf(dx + (int64_t)hw * a.C + c, v);
+  for (int k = 0; k < OUT; k++) {
+    int p, c;
+    if (256 * k >= out_steps || !out((int)threadIdx.x + 256 * k, p, c)) continue;
+    if constexpr (PIECES) {
+      Piece o, m;
+      o.q = *reinterpret_cast<const uint4*>(tile + p * PITCH + c);
+      m.q = mq[k];
+#pragma unroll
+      for (int e = 0; e < V; e++)
+        if (use_mask && !(ldf(&m.e[e]) > 0.f)) o.e[e] = (T)0;
+      *reinterpret_cast<uint4*>(dx + p * a.C + c) = o.q;
+    } else {
+      T v = tile[p * PITCH + c], m;
+      flat_store(&m, me[k]);
+      if (use_mask && !(ldf(&m) > 0.f)) v = (T)0;
+      dx[p * a.C + c] = v;
     }
   }
 }
 
-// Returns the LDS bytes of a launch (0: element by element).
-static size_t flat_args(bool is_bf16, int C, int H, int W, bool aligned, FlatArgs* a) {
-  a->C = C;
-  a->HW = H * W;
-  a->blocks = (C + kFlatC - 1) / kFlatC;
-  a->by_hw.set(a->HW);
-  const int v = is_bf16 ? 8 : 4;
-  const size_t bytes = (size_t)a->HW * (is_bf16 ? FlatTile<bf16_t>::kPitch * 2 : FlatTile<float>::kPitch * 4);
-  a->whole = aligned && C % v == 0 && bytes <= 64 * 1024;
-  return a->whole ? bytes : 0;
+// A value a lane straight from memory to memory: few values, whose time is one round trip (flatten_direct).
+template <typename T>
+__global__ __launch_bounds__(256) void flatten_fwd_direct_kernel(PtrTab ws, size_t x_off, size_t y_off, int C, int HW) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= C * HW) return;
+  const int c = (int)((unsigned)i / (unsigned)HW), p = i - c * HW;
+  const int64_t image = (int64_t)blockIdx.y * C * HW;
+  ((T*)ws.p[blockIdx.z] + y_off + image)[i] = ((const T*)ws.p[blockIdx.z] + x_off + image)[p * C + c];
+}
+template <typename T>
+__global__ __launch_bounds__(256) void flatten_bwd_direct_kernel(PtrTab ws, size_t dy_off, size_t dx_off, int C, int HW, int use_mask, size_t mask_off) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= C * HW) return;
+  const int p = (int)((unsigned)i / (unsigned)C), c = i - p * C;
+  const int64_t image = (int64_t)blockIdx.y * C * HW;
+  T v = ((const T*)ws.p[blockIdx.z] + dy_off + image)[c * HW + p];
+  if (use_mask && !(ldf((const T*)ws.p[blockIdx.z] + mask_off + image + i) > 0.f)) v = (T)0;
+  ((T*)ws.p[blockIdx.z] + dx_off + image)[i] = v;
+}
+
+// f(kernel of the form): the template arguments as types
+template <typename F>
+static void flat_form(bool pieces, int rows, F f) {
+  if (pieces) {
+    if (rows == FLAT_BLOCK) f(std::true_type{}, std::integral_constant<int, FLAT_BLOCK>{});
+    else if (rows == FLAT_BLOCK_128) f(std::true_type{}, std::integral_constant<int, FLAT_BLOCK_128>{});
+    else if (rows == FLAT_PIECES) f(std::true_type{}, std::integral_constant<int, FLAT_PIECES>{});
+    else f(std::true_type{}, std::integral_constant<int, FLAT_ELEMENTS>{});
+  } else {
+    if (rows == FLAT_PIECES) f(std::false_type{}, std::integral_constant<int, FLAT_PIECES>{});
+    else f(std::false_type{}, std::integral_constant<int, FLAT_ELEMENTS>{});
+  }
+}
+
+// (Tensors begin at multiples of 64 elements, so that whole rows of pieces are all that pieces take.)
+static FlatArgs flat_args(int C, int HW, const FlattenPlan& pl) {
+  FlatArgs a;
+  a.C = C;
+  a.HW = HW;
+  a.cblocks = (C + kFlat - 1) / kFlat;
+  a.by_c.set(std::min(C, kFlat));
+  a.by_p.set(std::min(HW, flat_positions_of(pl.rows)));
+  return a;
 }
 
 hipError_t launch_flatten_fwd(bool is_bf16, const PtrTab& ws, size_t x_off, size_t y_off, int N, int C, int H, int W, int count,
                               hipStream_t s) {
-  FlatArgs a;
-  const size_t lds = flat_args(is_bf16, C, H, W, x_off % 8 == 0 && y_off % 8 == 0, &a);
-  const dim3 g((unsigned)(N * a.blocks), 1, (unsigned)count);
-  if (is_bf16) hipLaunchKernelGGL(flatten_fwd_kernel<bf16_t>, g, dim3(256), lds, s, ws, x_off, y_off, a);
-  else hipLaunchKernelGGL(flatten_fwd_kernel<float>, g, dim3(256), lds, s, ws, x_off, y_off, a);
+  if (x_off % 8 || y_off % 8) return hipErrorInvalidValue;
+  const FlattenPlan pl = flatten_plan((int64_t)N * count, C, H * W, is_bf16);
+  const dim3 g((unsigned)pl.groups, (unsigned)N, (unsigned)count);
+  if (pl.direct) {
+    if (is_bf16) hipLaunchKernelGGL(flatten_fwd_direct_kernel<bf16_t>, g, dim3(256), 0, s, ws, x_off, y_off, C, H * W);
+    else hipLaunchKernelGGL(flatten_fwd_direct_kernel<float>, g, dim3(256), 0, s, ws, x_off, y_off, C, H * W);
+    return hipGetLastError();
+  }
+  const FlatArgs a = flat_args(C, H * W, pl);
+  flat_form(pl.pieces, pl.rows, [&](auto P, auto R) {
+    if (is_bf16) hipLaunchKernelGGL((flatten_fwd_kernel<bf16_t, decltype(P)::value, decltype(R)::value>), g, dim3(256), 0, s, ws, x_off, y_off, a);
+    else hipLaunchKernelGGL((flatten_fwd_kernel<float, decltype(P)::value, decltype(R)::value>), g, dim3(256), 0, s, ws, x_off, y_off, a);
+  });
   return hipGetLastError();
 }
 
 hipError_t launch_flatten_bwd(bool is_bf16, const PtrTab& ws, size_t dy_off, size_t dx_off, int N, int C, int H, int W, bool use_mask,
                               size_t mask_off, int count, hipStream_t s) {
-  FlatArgs a;
-  const size_t lds = flat_args(is_bf16, C, H, W, dy_off % 8 == 0 && dx_off % 8 == 0 && mask_off % 8 == 0, &a);
-  const dim3 g((unsigned)(N * a.blocks), 1, (unsigned)count);
+  if (dy_off % 8 || dx_off % 8 || mask_off % 8) return hipErrorInvalidValue;
+  const FlattenPlan pl = flatten_plan((int64_t)N * count, C, H * W, is_bf16);
+  const dim3 g((unsigned)pl.groups, (unsigned)N, (unsigned)count);
   const int um = use_mask ? 1 : 0;
-  if (is_bf16) hipLaunchKernelGGL(flatten_bwd_kernel<bf16_t>, g, dim3(256), lds, s, ws, dy_off, dx_off, a, um, mask_off);
-  else hipLaunchKernelGGL(flatten_bwd_kernel<float>, g, dim3(256), lds, s, ws, dy_off, dx_off, a, um, mask_off);
+  if (pl.direct) {
+    if (is_bf16) hipLaunchKernelGGL(flatten_bwd_direct_kernel<bf16_t>, g, dim3(256), 0, s, ws, dy_off, dx_off, C, H * W, um, mask_off);
+    else hipLaunchKernelGGL(flatten_bwd_direct_kernel<float>, g, dim3(256), 0, s, ws, dy_off, dx_off, C, H * W, um, mask_off);
+    return hipGetLastError();
+  }
+  const FlatArgs a = flat_args(C, H * W, pl);
+  flat_form(pl.pieces, pl.rows, [&](auto P, auto R) {
+    if (is_bf16) hipLaunchKernelGGL((flatten_bwd_kernel<bf16_t, decltype(P)::value, decltype(R)::value>), g, dim3(256), 0, s, ws, dy_off, dx_off, a, um, mask_off);
+    else hipLaunchKernelGGL((flatten_bwd_kernel<float, decltype(P)::value, decltype(R)::value>), g, dim3(256), 0, s, ws, dy_off, dx_off, a, um, mask_off);
+  });
   return hipGetLastError();
 }
 

@@ -301,6 +301,33 @@ inline int conv_pool_rows(int pooled_rows, int conv_rows, int64_t images, int re
   return best;
 }
 
+// ---- flattening in front of a fully connected layer
+// A value a lane, straight from memory to memory, or tiles of 64 channels x 64 positions that a workgroup turns around in LDS.  The tiles' second step
+// costs a call of few values 1 us; beyond half a million values the other one's scattered reads cost more (bf16, direct / tiles, forward in us: 64
+// channels of 13 x 13, 16 images 3.4 / 5.3; 128 of 20 x 20, 16 images 6.2 / 3.7; 64 of 25 x 25, 16 images 5.6 / 5.5).  Tiles of few channels
+// are small, and without whole 16-byte pieces of positions no faster at any size (8 of 45 x 45, 576 images 18.4 / 27.6; 16 of them 47.7 / 31.2).
+constexpr int kFlat = 64;
+// A tile's side of positions: of a channel one by one, in whole pieces, or all channels' in one run, where the tile holds the whole image; that of up to 128
+// positions too, which as 64 and a rest of single ones are slower (9 x 9, 184 channels, 432 images 17 us backward, 13 so).
+enum FlatRows { FLAT_ELEMENTS, FLAT_PIECES, FLAT_BLOCK, FLAT_BLOCK_128 };
+constexpr int flat_positions_of(int rows) { return rows == FLAT_BLOCK_128 ? 128 : kFlat; }
+struct FlattenPlan {
+  bool direct;
+  bool pieces;       // the tiles' side of channels in whole pieces
+  int rows;          // FlatRows
+  int64_t groups;    // workgroups of an image
+};
+inline FlattenPlan flatten_plan(int64_t images, int C, int HW, bool bf16) {
+  const int v = bf16 ? 8 : 4;
+  FlattenPlan p;
+  p.pieces = C % v == 0;
+  p.rows = p.pieces && HW <= kFlat ? FLAT_BLOCK : HW % v == 0 ? FLAT_PIECES : p.pieces && HW <= 2 * kFlat ? FLAT_BLOCK_128 : FLAT_ELEMENTS;
+  p.direct = images * C * HW <= 1 << 19 || (C <= 8 && HW % v != 0);
+  const int positions = flat_positions_of(p.rows);
+  p.groups = p.direct ? ((int64_t)C * HW + 255) / 256 : (int64_t)((C + kFlat - 1) / kFlat) * ((HW + positions - 1) / positions);
+  return p;
+}
+
 // ---- last layer, loss and its input gradient in one kernel
 // A workgroup per image reads the layer's weights twice, so for few of them only.  Against separate kernels for pooling, flattening, scores, loss,
 // input gradient and its re-layout: 1 024 inputs, 10 classes, bf16, 64 / 256 / 2 304 images 9 / 10 / 29 us instead of 27 / 28 / 47 (2 304 in fp32 24
