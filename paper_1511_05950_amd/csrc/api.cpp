@@ -111,6 +111,21 @@ void window_coefficients(int lr_mode, float a0, int c, const int32_t* tau, float
 }
 
 
+// Writes the fully connected weight gradients that the learner holds as factors into its flat gradient buffer.
+hipError_t expand_factored(sasgd_ctx* ctx, Learner& L) {
+  if (!ctx->net || !L.has_factors || L.fc_expanded || L.grad_timestamp < 0) return hipSuccess;
+  FactoredLayer fl[kMaxFactoredLayers];
+  const int nfl = net_factored_layers(ctx->net, fl, kMaxFactoredLayers);
+  for (int k = 0; k < nfl; k++) {
+    const FactoredLayer& F = fl[k];
+    hipError_t e = launch_fc_expand_factors((const bf16_t*)L.workspace + F.fx_off, (const bf16_t*)L.workspace + F.fdy_off,
+                                            L.grad + F.w_off, F.in, F.out, F.NP, ctx->stream);
+    if (e != hipSuccess) return e;
+  }
+  L.fc_expanded = true;
+  return hipSuccess;
+}
+
 // Device work of `n` consecutive updates ctx->deferred[0 .. n): one launch per piece of the vector (flat stretch or
 // factored fully connected layer) that applies the n steps in order, then the per-version filter repack.
 hipError_t enqueue_updates(sasgd_ctx* ctx, int n) {
@@ -164,9 +179,19 @@ hipError_t enqueue_updates(sasgd_ctx* ctx, int n) {
   FactoredLayer fl[kMaxFactoredLayers];
   bool factors = false;                // gradients that are all written out take the streaming kernel alone
   for (int l = 0; l < total; l++) factors = factors || src[l]->factors_ws;
-  const int nfl = factors ? net_factored_layers(ctx->net, fl, kMaxFactoredLayers) : 0;
+  int nfl = factors ? net_factored_layers(ctx->net, fl, kMaxFactoredLayers) : 0;
   prof_begin(ctx, 1, n);
   hipError_t e = hipSuccess;
+  // Factors of many images that meet written-out gradients are written out first and all are streamed: the kernel that reads both kinds makes one
+  // 32 x 32 product after the other, whose time grows with the images.  AlexNet-shaped net, three learners' gradients and one pushed from outside, us,
+  // that kernel / this: 64 images 417 / 553, 128 574 / 573, 176 601 / 618, 192 756 / 609, 256 892 / 635; one and one of 256 473 / 373.
+  bool written = false;
+  for (int l = 0; l < total; l++) written = written || !src[l]->factors_ws;
+  if (nfl > 0 && written && fl[0].N > kMixedFactorRows) {
+    for (int l = 0; l < total && e == hipSuccess; l++)
+      if (src[l]->factors_ws) e = expand_factored(ctx, ctx->learners[(size_t)src[l]->learner]);
+    nfl = 0;
+  }
   auto flat_range = [&](int64_t begin, int64_t end) {
     if (end <= begin) return hipSuccess;
     UpdateLaunch r = u;
@@ -708,21 +733,6 @@ int sasgd_copyWeights(sasgd_ctx* ctx, int64_t version, float* host_out) {
   }
   if (e != hipSuccess) return fail_hip(ctx, e, "copyWeights");
   return SASGD_OK;
-}
-
-// Writes the fully connected weight gradients that the learner holds as factors into its flat gradient buffer.
-static hipError_t expand_factored(sasgd_ctx* ctx, Learner& L) {
-  if (!ctx->net || !L.has_factors || L.fc_expanded || L.grad_timestamp < 0) return hipSuccess;
-  FactoredLayer fl[kMaxFactoredLayers];
-  const int nfl = net_factored_layers(ctx->net, fl, kMaxFactoredLayers);
-  for (int k = 0; k < nfl; k++) {
-    const FactoredLayer& F = fl[k];
-    hipError_t e = launch_fc_expand_factors((const bf16_t*)L.workspace + F.fx_off, (const bf16_t*)L.workspace + F.fdy_off,
-                                            L.grad + F.w_off, F.in, F.out, F.NP, ctx->stream);
-    if (e != hipSuccess) return e;
-  }
-  L.fc_expanded = true;
-  return hipSuccess;
 }
 
 int sasgd_copyGradient(sasgd_ctx* ctx, int32_t learner, float* host_out) {

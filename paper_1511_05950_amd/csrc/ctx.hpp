@@ -59,6 +59,7 @@ hipError_t static_sum_buffer(float** out);
 // Update of the fully connected layers (each: weights [out][in] followed by the bias [out]) whose gradients are kept as
 // factors, all layers in ONE launch.  theta_in / theta_out / v / shadow_out / grads address element 0 of the flat vector.
 constexpr int kMaxFactorRows = 256;      // images of a mini-batch whose weight gradients are kept as factors
+constexpr int kMixedFactorRows = 176;    // images up to which they are also read as factors beside written-out gradients (enqueue_updates)
 constexpr int kFactorRowsAlways = 32;    // up to here also where the caller holds the gradient buffer's address (sasgd_gradientPtr)
 constexpr int kMaxFactoredLayers = 16;   // further fully connected layers write their gradient out
 struct FcUpdateLaunch {

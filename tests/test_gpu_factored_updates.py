@@ -16,11 +16,11 @@ NET = {"name": "factors", "input": (3, 12, 12), "classes": 8,                   
        "layers": [("conv", 32, 3, 1, 1), ("avgpool", 3, 2), ("fc", 4104), ("relu",), ("fc", 264), ("relu",), ("fc", 8)]}
 
 
-def one_update(lam, mu, flags):
+def one_update(lam, mu, flags, net=NET):
     from paper_1511_05950_amd import binding
-    w0 = wl.init_weights(NET, 5, std=0.05)
-    X, Y = torch.from_numpy(wl.images(NET, lam * mu, 6)).cuda(), torch.from_numpy(wl.labels(NET, lam * mu, 7)).cuda()
-    ctx = binding.Sasgd(lam, mu, 1, 2, net=NET, compute="bf16", alpha0=0.05, momentum=0.5, weight_decay=1e-2, init_weights=w0, flags=flags)
+    w0 = wl.init_weights(net, 5, std=0.05)
+    X, Y = torch.from_numpy(wl.images(net, lam * mu, 6)).cuda(), torch.from_numpy(wl.labels(net, lam * mu, 7)).cuda()
+    ctx = binding.Sasgd(lam, mu, 1, 2, net=net, compute="bf16", alpha0=0.05, momentum=0.5, weight_decay=1e-2, init_weights=w0, flags=flags)
     assert (ctx.factoredParams() > 0) == (flags == 0)
     for update in range(2):
         for k in range(lam):
@@ -107,3 +107,51 @@ def test_a_caller_that_holds_the_gradient_finds_and_changes_it_there(asked):
     for k, (a, b) in enumerate(zip(*got)):
         # (sums in another order where the factors had been taken; behind the first update, weights that differ in the last place)
         assert rel(a, b) < (1e-5 if k < 3 else 2e-3), (asked, k)
+
+
+WIDER = {"name": "factors", "input": (3, 12, 12), "classes": 8,           # 1 152 -> 12 296 -> 264: layer by layer for one learner of 33 images too
+         "layers": [("conv", 32, 3, 1, 1), ("avgpool", 3, 2), ("fc", 12296), ("relu",), ("fc", 264), ("relu",), ("fc", 8)]}
+
+
+@pytest.mark.parametrize("mu", [33, 40, 64])
+def test_update_from_factors_of_one_learner(mu):
+    """Three and four k-blocks, which a lone gradient takes through the tiles of 32 x 32 weights; bounds as above."""
+    from paper_1511_05950_amd import binding
+    fa, fl = one_update(1, mu, 0, WIDER), one_update(1, mu, binding.FLAG_FLAT_FC_GRADIENT, WIDER)
+    w0 = fa[4].astype(np.float64)
+    assert rel(fa[0][0], fl[0][0]) < 1e-5 and rel(fa[1] - w0, fl[1] - w0) < 1e-5 and rel(fa[2], fl[2]) < 1e-5
+
+
+@pytest.mark.parametrize("mu", [40, 64, 176, 177, 256])
+@pytest.mark.parametrize("n_factored", [1, 3])
+def test_factors_of_many_images_beside_a_written_out_gradient(mu, n_factored):
+    """A window of learners' gradients and one pushed from outside in the middle of them, at both sides of the line beyond which the factors are written
+    out first; a second window finds the learners' buffers as the first one left them."""
+    from paper_1511_05950_amd import binding
+    lam = n_factored + 1
+    w0 = wl.init_weights(NET, 25, std=0.05)
+    X, Y = torch.from_numpy(wl.images(NET, lam * mu, 26)).cuda(), torch.from_numpy(wl.labels(NET, lam * mu, 27)).cuda()
+    outside = (torch.randn(wl.num_params(NET), generator=torch.Generator().manual_seed(28)) * 1e-3).cuda()
+    ctx = binding.Sasgd(lam, mu, 1, 2, net=NET, compute="bf16", alpha0=0.05, momentum=0.5, weight_decay=1e-2, init_weights=w0)
+    assert ctx.factoredParams() > 0
+    theta, v = w0.astype(np.float64), 0.0
+    for window in range(2):
+        ks = list(range(n_factored))
+        for k in ks:
+            ctx.getMinibatch(k, X[(k + window) * mu:(k + window + 1) * mu], Y[(k + window) * mu:(k + window + 1) * mu])
+            ctx.pullWeights(k, 0)
+        ctx.calcGradient(ks)
+        for k in ks[:1]:
+            ctx.pushGradient(k)
+        ctx.pushGradientExternal(outside, ctx.timestamp())
+        for k in ks[1:]:
+            ctx.pushGradient(k)
+        ctx.sumGradients()
+        ctx.applyUpdate()
+        got, got_v = ctx.copyWeights(), ctx.copyMomentum()
+        g = sum(ctx.copyGradient(k).astype(np.float64) for k in ks) + outside.cpu().numpy()     # (what the update read, written out)
+        v = 0.5 * v + 0.05 / lam * g + 0.05 * 1e-2 * theta
+        theta = theta - v
+        assert rel(got_v, v) < 1e-5 and rel(got, theta) < 1e-7, window          # (32-bit weights, each rounded once)
+        theta, v = got.astype(np.float64), got_v.astype(np.float64)
+    ctx.destroy()
