@@ -60,3 +60,23 @@ def test_fused_steps_leave_the_bits_of_single_updates(case):
     assert len(eager["old"]) > 0
     for a, b in zip(eager["old"], fused["old"]):
         assert same_bits(a, b)
+
+
+@pytest.mark.parametrize("c, n, mu", [(8, 2, 8), (8, 2, 16), (8, 3, 13), (20, 2, 5), (16, 2, 16), (3, 4, 24), (3, 4, 32), (5, 3, 27), (7, 2, 20)])
+def test_fused_steps_leave_the_bits_of_single_updates_in_large_tiles(c, n, mu):
+    """Long sums, which a lone update takes in tiles of 128 x 128 weights (operands straight from memory up to 16 images, through LDS beyond) and a fused
+    pass in tiles of 32 x 32: layers that end inside either, gradients and images in numbers that are no multiples of the stages."""
+    from paper_1511_05950_amd import binding
+    net = {"name": "fcnet", "input": (3, 12, 10), "classes": 8,                   # 240 -> 264 -> 136 -> 8
+           "layers": [("conv", 8, 3, 1, 1), ("relu",), ("maxpool", 3, 2), ("fc", 264), ("relu",), ("fc", 136), ("relu",), ("fc", 8)]}
+    assert c >= 8 if mu <= 16 else c * -(-mu // 16) >= 5              # where the large tiles begin
+    K = 12
+    args = dict(net=net, netarg=net, compute="bf16", lam=c * n, mu=mu, n=n, K=K, R=2 * n + 1, std=0.1)
+    sched = wl.uniform_schedule(K, c, n, 2 * n, 11)                   # old enough that several updates' gradients come from one call
+    eager = run(sched=sched, flags=binding.FLAG_EAGER_UPDATES, seed=310, **args)
+    fused = run(sched=sched, flags=0, seed=310, **args)
+    assert eager["passes"] == K and fused["passes"] < K
+    assert same_bits(eager["w"], fused["w"]) and same_bits(eager["v"], fused["v"])
+    assert len(eager["old"]) > 0
+    for a, b in zip(eager["old"], fused["old"]):
+        assert same_bits(a, b)
