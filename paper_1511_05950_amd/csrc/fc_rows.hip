@@ -319,7 +319,7 @@ __global__ __launch_bounds__(256) void fc_rows_finish_kernel(PtrTab ws, CPtrTab 
   const uint32_t per_member4 = (uint32_t)(((int64_t)g.M * g.Ncols) >> 2);
   for (uint32_t o4 = blockIdx.x * 256 + threadIdx.x; o4 < total4; o4 += gridDim.x * 256) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
+#pragma unroll 8
     for (int sp = 0; sp < g.splits; sp++) {   // loads of several splits in flight; the additions keep split order
       const float4 p = part[(size_t)sp * total4 + o4];
       v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;

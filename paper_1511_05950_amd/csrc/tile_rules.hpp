@@ -269,7 +269,11 @@ inline FcRowsChoice fc_rows_choice(int K, int N, int rows, int groups, size_t sc
   for (int tm = 1; tm <= 4; tm++) {
     if (tm > 1 && 64 * (tm - 1) >= rows) break;                   // a smaller tile holds them all
     const int64_t tiles = (int64_t)((rows + 64 * tm - 1) / (64 * tm)) * ((N + 127) / 128) * groups;
-    for (int sp = 1; sp <= 16; sp++) {
+    // A second pass is a launch more than it costs itself: a contraction of less than 18 stages is not worth it (512 -> 64, 14 rows of 7 versions 10.3 us
+    // with that launch, 7.7 without; 1 024 -> 1 024, 64 rows 11.6 and 11).  Beyond 16 splits each keeps nine stages: 184 320 -> 8, 78 rows 58 us with 16
+    // splits of two tiles, 25 with 126; 357 216 -> 88, 57 rows 176 and 47 (from 9 729 inputs on).
+    const int most = steps < 18 ? 1 : steps / 9 <= 16 ? 16 : steps / 9 < 128 ? steps / 9 : 128;
+    for (int sp = 1; sp <= most; sp++) {
       const int per = (steps + sp - 1) / sp;
       if (sp > 1 && (per < 2 || (steps + per - 1) / per != sp || part >= (int64_t)1 << 31 || (uint64_t)part * sp > scratch_bytes)) continue;
       const double work = (double)((tiles * sp + 255) / 256) * (per * kStage[tm - 1] + 0.48 + 0.64 * tm);
