@@ -51,12 +51,18 @@ struct FcRowsArgs {
 // and taller tiles were no faster.  One learner of 256 images, 9 216 -> 4 096 -> 4 096 -> 1 000 units, both directions with their second
 // passes: 280 us with operands staged through registers in 128 x 128 tiles of 32 contraction elements, 142 here; 18 learners of 16 images on one version
 // 335 us as three groups of six whose weights were streamed thrice, 157 here; each on its own version 851 and 845; 7 such 362 and 325.
-template <int TM, bool BT>
+//
+// TN = 1: 32 TM rows, the four wavefronts side by side, for versions of at most 32 rows.  ST: stages in LDS; contractions of one or two stages have
+// no more of them, so that more workgroups share a compute unit, and read the ReLU mask beside the operands.  Input gradients, us, kernels before the stages /
+// 64 rows, three stages / here: 24 units <- 48 600 inputs, 15 versions of 26 rows 22 / 46 / 25; 8 <- 42 336, 12 of 8 11 / 29 / 13; 24 <- 349 272, 275 rows 108 / 200 / 118.
+template <int TM, int TN, bool BT, int ST>
 __global__ __launch_bounds__(256, 1) void fc_rows_kernel(PtrTab ws, CPtrTab wts, GroupTab gt, IGemm g, Epilogue ep, FcRowsArgs fa) {
-  constexpr int BM = 64 * TM, TN = 2;
+  constexpr int WAVES_N = FRN / (32 * TN), BM = 32 * TM * (4 / WAVES_N);
   constexpr int A_ELEMS = BM * FRK, STAGE = A_ELEMS + FRN * FRK;
-  constexpr int LA = 2 * TM, LB = 4, L = LA + LB;          // loads of a wavefront per stage
-  __shared__ __attribute__((aligned(16))) bf16_t lds[3 * STAGE];
+  constexpr int LA = BM / 32, LB = 4, L = LA + LB;         // loads of a wavefront per stage
+  constexpr int PITCH = 32 * TN + 4;                       // floats of a row of results in LDS
+  constexpr int RESULTS = 4 * 32 * PITCH * 2;              // the wavefronts' results, in elements of 2 bytes
+  __shared__ __attribute__((aligned(16))) bf16_t lds[ST * STAGE > RESULTS ? ST * STAGE : RESULTS];
 
   // launch order is dealt round-robin to the eight XCDs: each takes a contiguous eighth of (split, column tile, row block), so
   // that its L2 holds the image rows of few splits, and the row blocks of a weight tile meet there
@@ -74,7 +80,7 @@ __global__ __launch_bounds__(256, 1) void fc_rows_kernel(PtrTab ws, CPtrTab wts,
   const int K = g.Kchunks * 8;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = (wave >> 1) * (32 * TM), wn0 = (wave & 1) * 64;
+  const int wm0 = wave / WAVES_N * (32 * TM), wn0 = wave % WAVES_N * (32 * TN);
 
   const int all_steps = (K + FRK - 1) / FRK;
   const int per = (all_steps + g.splits - 1) / g.splits;
@@ -210,35 +216,73 @@ __global__ __launch_bounds__(256, 1) void fc_rows_kernel(PtrTab ws, CPtrTab wts,
       __builtin_amdgcn_sched_barrier(0);
     }
   };
+  // results: eight columns of a row per lane, 32 rows of a wavefront's in PASSES pieces
+  constexpr int LANES = 4 * TN, ROWS = 64 / LANES, PASSES = 32 / ROWS;
+  const int c8 = 8 * (lane % LANES), n = n0 + wn0 + c8;
+  union Eight { uint4 q; bf16_t e[8]; };
+  auto result = [&](int i, int p, char*& base, int64_t& o) {       // where piece p of the i-th 32 rows belongs
+    const int row = min(m0 + wm0 + 32 * i + ROWS * p + lane / LANES, Mg - 1);
+    const int q = fa.by_mu(row);
+    base = (char*)ws.p[z0 + q];
+    o = (int64_t)(row - q * g.M) * g.Ncols + n;
+  };
+  auto mask_of = [&](int i, int p) {
+    char* base;
+    int64_t o;
+    result(i, p, base, o);
+    return *reinterpret_cast<const uint4*>((const bf16_t*)base + ep.mask_off + o);
+  };
+  constexpr bool SHORT = ST < 3;
+  Eight early[SHORT ? TM : 1][SHORT ? PASSES : 1];
+  if constexpr (SHORT) {
 #pragma unroll 1
-  for (int st = 0; st < 3; st++) {
+    for (int st = 0; st < steps; st++) {
 #pragma unroll
-    for (int l = 0; l < L; l++) load((uint32_t)(st * STAGE * 2), l);
-  }
-  landed_and_read<2 * L>();
-  read(a0, b0, 0, 0);
-  int s = 0;
+      for (int l = 0; l < L; l++) load((uint32_t)(st * STAGE * 2), l);
+    }
+    if (ep.use_mask && g.splits == 1 && n < g.Ncols)               // beside the operands
+#pragma unroll
+      for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int p = 0; p < PASSES; p++) early[i][p].q = mask_of(i, p);
+    landed_and_read<0>();
 #pragma unroll 1
-  for (; s + 3 <= steps; s += 3) {
-    step(0, STAGE);
-    step(STAGE, 2 * STAGE);
-    step(2 * STAGE, 0);
-  }
-  if (s < steps) {
-    step(0, STAGE);
-    if (s + 1 < steps) step(STAGE, 2 * STAGE);
+    for (int st = 0; st < steps; st++) {
+#pragma unroll
+      for (int kk = 0; kk < 4; kk++) {
+        read(a0, b0, st * STAGE, kk);
+        multiply(a0, b0);
+      }
+    }
+  } else {
+#pragma unroll 1
+    for (int st = 0; st < 3; st++) {
+#pragma unroll
+      for (int l = 0; l < L; l++) load((uint32_t)(st * STAGE * 2), l);
+    }
+    landed_and_read<2 * L>();
+    read(a0, b0, 0, 0);
+    int s = 0;
+#pragma unroll 1
+    for (; s + 3 <= steps; s += 3) {
+      step(0, STAGE);
+      step(STAGE, 2 * STAGE);
+      step(2 * STAGE, 0);
+    }
+    if (s < steps) {
+      step(0, STAGE);
+      if (s + 1 < steps) step(STAGE, 2 * STAGE);
+    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load is left on its way to this workgroup's LDS
 
   // lane holds column n = l % 32 and rows 8 (r / 4) + 4 (l / 32) + r % 4 of every 32 x 32 block
   if (g.splits == 1) {
     // turned around through LDS, 32 rows at a time, a wavefront's piece each: eight columns of a row per lane
-    constexpr int PITCH = 64 + 4;
     float* piece = reinterpret_cast<float*>(lds) + wave * (32 * PITCH);
     const bf16_t* bias = (const bf16_t*)wts.p[z0] + ep.bias_off;
-    const int c8 = 8 * (lane & 7), n = n0 + wn0 + c8;
     float bs[8];
-    union { uint4 q; bf16_t e[8]; } bq;
+    Eight bq;
     bq.q = make_uint4(0u, 0u, 0u, 0u);
     if (ep.has_bias && n < g.Ncols)
 #pragma unroll
@@ -256,23 +300,18 @@ __global__ __launch_bounds__(256, 1) void fc_rows_kernel(PtrTab ws, CPtrTab wts,
         for (int r = 0; r < 16; r++) piece[(8 * (r >> 2) + 4 * h + (r & 3)) * PITCH + 32 * j + m] = acc[i][j][r];
       __builtin_amdgcn_wave_barrier();
       asm volatile("" ::: "memory");
-      char* base[4];
-      int64_t o[4];
-      union { uint4 q; bf16_t e[8]; } mk[4];
+      char* base[PASSES];
+      int64_t o[PASSES];
+      Eight mk[PASSES];
 #pragma unroll
-      for (int p = 0; p < 4; p++) {
-        const int row = min(row0 + 8 * p + (lane >> 3), Mg - 1);
-        const int q = fa.by_mu(row);
-        base[p] = (char*)ws.p[z0 + q];
-        o[p] = (int64_t)(row - q * g.M) * g.Ncols + n;
-      }
+      for (int p = 0; p < PASSES; p++) result(i, p, base[p], o[p]);
       if (ep.use_mask && n < g.Ncols)
 #pragma unroll
-        for (int p = 0; p < 4; p++) mk[p].q = *reinterpret_cast<const uint4*>((const bf16_t*)base[p] + ep.mask_off + o[p]);
+        for (int p = 0; p < PASSES; p++) mk[p].q = SHORT ? early[SHORT ? i : 0][SHORT ? p : 0].q : mask_of(i, p);
 #pragma unroll
-      for (int p = 0; p < 4; p++) {
-        if (row0 + 8 * p + (lane >> 3) >= Mg || n >= g.Ncols) continue;
-        const float* f = piece + (8 * p + (lane >> 3)) * PITCH + c8;
+      for (int p = 0; p < PASSES; p++) {
+        if (row0 + ROWS * p + lane / LANES >= Mg || n >= g.Ncols) continue;
+        const float* f = piece + (ROWS * p + lane / LANES) * PITCH + c8;
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; e++) {
@@ -306,6 +345,75 @@ __global__ __launch_bounds__(256, 1) void fc_rows_kernel(PtrTab ws, CPtrTab wts,
       for (int r = 0; r < 16; r++)
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][r]), rsrc_p, at + (32 * i + 8 * (r >> 2) + (r & 3)) * g.Ncols * 4, 0, 0);
   }
+}
+
+// Forward products of few rows and a short contraction: 32 rows x 32 columns a workgroup, whose eight wavefronts take every eighth 64 contraction elements,
+// operands straight from memory, and add their sums in the order of the wavefronts.  Bound by the launch and a few round trips: a tile of the kernel
+// above waits for LDS stage by stage, 0.3 us each, and a second pass is another launch (figures at fc_rows_short).
+constexpr int kShortWaves = 8;
+__global__ __launch_bounds__(64 * kShortWaves) void fc_rows_short_kernel(PtrTab ws, CPtrTab wts, GroupTab gt, IGemm g, Epilogue ep, FcRowsArgs fa) {
+  __shared__ float sums[kShortWaves][16][64];
+  const int z0 = table_byte(gt.first, blockIdx.y), Mg = table_byte(gt.members, blockIdx.y) * g.M;
+  const bf16_t* zeros = (const bf16_t*)((const char*)ws.p[z0]) + g.zero_off;
+  const bf16_t* W = (const bf16_t*)wts.p[z0] + g.b_off;
+  const int K = g.Kchunks * 8, n0 = blockIdx.x * 32;
+  const int tid = threadIdx.x, lane = tid & 63, m = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // results of this thread: two neighbouring columns of a row
+  const int orow = tid >> 4, ocol = 2 * (tid & 15);
+  const bool stores = orow < Mg && n0 + ocol < g.Ncols;
+  const bf16_t* bias = (const bf16_t*)wts.p[z0] + ep.bias_off + n0 + ocol;
+  const float b0 = stores && ep.has_bias ? bf2f(bias[0]) : 0.f, b1 = stores && ep.has_bias ? bf2f(bias[1]) : 0.f;
+  const int oq = fa.by_mu(min(orow, Mg - 1));
+  // rows and columns behind the last one repeat it: not stored
+  const int row = min(m, Mg - 1), q = fa.by_mu(row);
+  const bf16_t* a_ptr = (const bf16_t*)ws.p[z0 + q] + g.a_off + (int64_t)(row - q * g.M) * K;
+  const bf16_t* b_ptr = W + (int64_t)min(n0 + m, g.Ncols - 1) * g.ldb;
+  auto fetch = [&](uint4 (&a)[4], uint4 (&b)[4], int c) {
+#pragma unroll
+    for (int kk = 0; kk < 4; kk++) {
+      const int k = c * 64 + 16 * kk + 8 * h;
+      a[kk] = *reinterpret_cast<const uint4*>(k < K ? a_ptr + k : zeros);
+      b[kk] = *reinterpret_cast<const uint4*>(k < K ? b_ptr + k : zeros);
+    }
+  };
+  floatx16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; r++) acc[r] = 0.f;
+  auto multiply = [&](const uint4 (&a)[4], const uint4 (&b)[4]) {
+#pragma unroll
+    for (int kk = 0; kk < 4; kk++) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[kk]), __builtin_bit_cast(bf16x8, b[kk]), acc, 0, 0, 0);
+  };
+  const int chunks = (K + 63) / 64;
+  uint4 a0[4], b0v[4], a1[4], b1v[4];
+  fetch(a0, b0v, wave);
+#pragma unroll 1
+  for (int c = wave; c < chunks; c += 2 * kShortWaves) {
+    fetch(a1, b1v, c + kShortWaves);               // (behind the last one: zeros)
+    multiply(a0, b0v);
+    fetch(a0, b0v, c + 2 * kShortWaves);
+    multiply(a1, b1v);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; r++) sums[wave][r][lane] = acc[r];
+  __syncthreads();
+  if (!stores) return;
+  // column n = l % 32 and rows 8 (r / 4) + 4 (l / 32) + r % 4 of the block lie in lane l's r-th
+  const int r = 4 * (orow >> 3) + (orow & 3), l = ocol + 32 * ((orow >> 2) & 1);
+  float v0 = 0.f, v1 = 0.f;
+#pragma unroll
+  for (int w = 0; w < kShortWaves; w++) {
+    const float2 p = *reinterpret_cast<const float2*>(&sums[w][r][l]);
+    v0 += p.x;
+    v1 += p.y;
+  }
+  v0 += b0;
+  v1 += b1;
+  if (ep.relu) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); }
+  bf16_t* out = (bf16_t*)ws.p[z0 + oq] + ep.out_off;
+  const int64_t o = (int64_t)(orow - oq * g.M) * g.Ncols + n0 + ocol;
+  if (ep.out_f32) *reinterpret_cast<float2*>(reinterpret_cast<float*>(out) + o) = make_float2(v0, v1);
+  else *reinterpret_cast<uint32_t*>(out + o) = pack2bf(v0, v1);
 }
 
 // Sum of the split partials of every group in split order, then bias / ReLU / mask / conversion; blockIdx.z = group.
@@ -358,13 +466,22 @@ __global__ __launch_bounds__(256) void fc_rows_finish_kernel(PtrTab ws, CPtrTab 
   }
 }
 
-template <int TM>
-static void launch_t(const PtrTab& ws, const CPtrTab& wts, const GroupTab& gt, int groups, int max_rows, const IGemm& g, const Epilogue& ep, bool dgrad, hipStream_t s) {
-  FcRowsArgs fa{(max_rows + 64 * TM - 1) / (64 * TM), (g.Ncols + FRN - 1) / FRN, {}};
+template <int TM, int TN, int ST>
+static void launch_st(const PtrTab& ws, const CPtrTab& wts, const GroupTab& gt, int groups, int max_rows, const IGemm& g, const Epilogue& ep, bool dgrad, hipStream_t s) {
+  constexpr int BM = 32 * TM * TN;
+  FcRowsArgs fa{(max_rows + BM - 1) / BM, (g.Ncols + FRN - 1) / FRN, {}};
   fa.by_mu.set(g.M);
   const dim3 grid((unsigned)(fa.row_blocks * fa.tiles * g.splits), (unsigned)groups);
-  if (dgrad) hipLaunchKernelGGL((fc_rows_kernel<TM, true>), grid, dim3(256), 0, s, ws, wts, gt, g, ep, fa);
-  else hipLaunchKernelGGL((fc_rows_kernel<TM, false>), grid, dim3(256), 0, s, ws, wts, gt, g, ep, fa);
+  if (dgrad) hipLaunchKernelGGL((fc_rows_kernel<TM, TN, true, ST>), grid, dim3(256), 0, s, ws, wts, gt, g, ep, fa);
+  else hipLaunchKernelGGL((fc_rows_kernel<TM, TN, false, ST>), grid, dim3(256), 0, s, ws, wts, gt, g, ep, fa);
+}
+
+template <int TM, int TN>
+static void launch_t(const PtrTab& ws, const CPtrTab& wts, const GroupTab& gt, int groups, int max_rows, const IGemm& g, const Epilogue& ep, bool dgrad, hipStream_t s) {
+  const int stages = (g.Kchunks * 8 + FRK - 1) / FRK, per = (stages + g.splits - 1) / g.splits;
+  if (per == 1) launch_st<TM, TN, 1>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
+  else if (per == 2) launch_st<TM, TN, 2>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
+  else launch_st<TM, TN, 3>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
 }
 
 hipError_t launch_fc_rows(const PtrTab& ws, const CPtrTab& wts, const GroupTab& gt, int groups, const IGemm& g_in, const Epilogue& ep, bool dgrad,
@@ -377,13 +494,21 @@ hipError_t launch_fc_rows(const PtrTab& ws, const CPtrTab& wts, const GroupTab& 
     if (gt.members[k] < 1 || gt.first[k] + gt.members[k] > kMaxLearners) return hipErrorInvalidValue;
     max_rows = std::max(max_rows, gt.members[k] * g.M);
   }
+  if (!dgrad && fc_rows_short(g.Kchunks * 8, g.Ncols, max_rows, groups)) {
+    if (ep.use_mask) return hipErrorInvalidValue;
+    FcRowsArgs fa{1, 1, {}};
+    fa.by_mu.set(g.M);
+    hipLaunchKernelGGL(fc_rows_short_kernel, dim3((unsigned)((g.Ncols + 31) / 32), (unsigned)groups), dim3(64 * kShortWaves), 0, s, ws, wts, gt, g, ep, fa);
+    return hipGetLastError();
+  }
   const FcRowsChoice c = fc_rows_choice(g.Kchunks * 8, g.Ncols, max_rows, groups, scratch_bytes);
   g.splits = c.splits;
   g.scratch_off = scratch_off;
-  if (c.tm == 1) launch_t<1>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
-  else if (c.tm == 2) launch_t<2>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
-  else if (c.tm == 3) launch_t<3>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
-  else launch_t<4>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
+  if (max_rows <= 32) launch_t<1, 1>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
+  else if (c.tm == 1) launch_t<1, 2>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
+  else if (c.tm == 2) launch_t<2, 2>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
+  else if (c.tm == 3) launch_t<3, 2>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
+  else launch_t<4, 2>(ws, wts, gt, groups, max_rows, g, ep, dgrad, s);
   if (g.splits > 1) {
     const int64_t pieces = ((int64_t)max_rows * g.Ncols) >> 2;
     hipLaunchKernelGGL(fc_rows_finish_kernel, dim3((unsigned)std::min<int64_t>((pieces + 255) / 256, 2048), 1, (unsigned)groups), dim3(256), 0, s, ws, wts,

@@ -288,6 +288,11 @@ inline FcRowsChoice fc_rows_choice(int K, int N, int rows, int groups, size_t sc
   return best;
 }
 
+// Forward products of at most 32 rows, few enough for a workgroup of 32 columns on every compute unit and up to 2 048 inputs have a kernel without LDS
+// (fc_rows_short_kernel).  us, with the launch of a second pass, tiles / that: 512 -> 1 024, one row 10.6 / 5.0; 1 152 -> 512 of 18 versions 16 rows each 13 / 12; 1 536
+// -> 64, 16 rows 10.8 / 7.4; 256 -> 4 096 of 7 versions 6.8 / 10.2; 1 024 -> 1 024 of 10, 32 rows 11.8 / 12.6; 4 096 -> 64, 16 rows 11.9 / 14.4.
+inline bool fc_rows_short(int K, int N, int rows, int groups) { return rows <= 32 && K <= 2048 && (int64_t)((N + 31) / 32) * groups <= 256; }
+
 // ---- first convolution and max pooling in one kernel
 // Pooled rows of a workgroup, which walks down them `conv_rows` convolution rows at a time (one row more than two per pooled row), with
 // `resident` workgroups on a compute unit, each of which slows the others by a quarter (CIFAR-shaped net, 256 / 576 / 1 152 / 2 304 images at one walk
