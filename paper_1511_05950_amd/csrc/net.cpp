@@ -33,7 +33,7 @@ struct Op {
   bool dgrad_bt = false;       // fc: B operand is the flat weight matrix read transposed
   int64_t pack_fwd = -1, pack_bwd = -1;   // element offsets in the packed-filter region of a version slot
   int Kp = 0, Kpt = 0;
-  // first convolution that the max pooling behind it shares a kernel with: its output is not stored
+  // first convolution that the max pooling behind it can share a kernel with (conv_pool_wins decides per call): its output is not stored then
   bool with_pool = false;
   // fully connected layer whose weight gradient is kept as the factors x^T [in][NP] and dy^T [out][NP]
   bool factored = false;
@@ -758,7 +758,7 @@ hipError_t net_calc_gradient(Net* net, const int* learners, const LearnerBind* b
   // ---- forward
   TRY(launch_pack_input(bf, imgs, ws, T[0].off, count, net->mu, net->inpack, net->pixel_mean, stream));
   size_t first = 0;
-  if (net->ops[0].with_pool) {
+  if (net->ops[0].with_pool && conv_pool_wins((int64_t)count * net->mu, net->ops[0].gf.OH * net->ops[0].gf.OW, net->ops[0].gf.C, net->ops[0].gf.Ncols, net->ops[0].gf.ks)) {
     const Op &conv = net->ops[0], &pool = net->ops[1];
     const Epilogue ep{0, 0, conv.b_off, 1, conv.relu ? 1 : 0, 0, 0};
     TRY(launch_conv_pool(ws, wts, conv.gf, ep, pool.ps, T[(size_t)pool.out_t].off, pool.arg_off, pool.relu, count, stream));

@@ -294,6 +294,17 @@ inline FcRowsChoice fc_rows_choice(int K, int N, int rows, int groups, size_t sc
 inline bool fc_rows_short(int K, int N, int rows, int groups) { return rows <= 32 && K <= 2048 && (int64_t)((N + 31) / 32) * groups <= 256; }
 
 // ---- first convolution and max pooling in one kernel
+// Is it the faster way for a call of `images`?  Up to 1 024 of them a launch and its round trips are saved whatever the shapes.  Beyond, small images
+// leave most of a workgroup's 256 positions empty (bf16, separate kernels / this, us: 96 filters 3 x 3 over 6 x 7 of 16 channels, 1 024 images 20 / 18, 2 048 24 / 31,
+// 4 096 33 / 59; 128 over 10 x 7, 4 096 50 / 70; 64 over 8 x 10, 4 096 34 / 33), and many input channels behind few filters or large windows leave little
+// but the patch's way to LDS (8 filters 2 x 2 over 16 x 16 of 64 channels, 7 680 images 120 / 151; 64 of 5 x 5 over 18 x 18 of 64 552 / 609; 16 of 3 x 3
+// over 32 x 40 of 64, 2 048 images 220 / 182).  Of 302 such layers at 2 to 7 680 images, 4 are behind by more than 3 % now, 43 without the rule.
+inline bool conv_pool_wins(int64_t images, int positions, int C, int Ncols, int ks) {
+  if (images <= 1024) return true;
+  if (positions <= 90) return false;
+  return C < 64 || (ks < 5 && (Ncols > 32 || (positions > 128 && (ks > 2 || positions > 400))));
+}
+
 // Pooled rows of a workgroup, which walks down them `conv_rows` convolution rows at a time (one row more than two per pooled row), with
 // `resident` workgroups on a compute unit, each of which slows the others by a quarter (CIFAR-shaped net, 256 / 576 / 1 152 / 2 304 images at one walk
 // an image: 19 / 26 / 41 / 73 us): as little time as possible.
