@@ -349,9 +349,13 @@ inline FlattenPlan flatten_plan(int64_t images, int C, int HW, bool bf16) {
 }
 
 // ---- last layer, loss and its input gradient in one kernel
-// A workgroup per image reads the layer's weights twice, so for few of them only.  Against separate kernels for pooling, flattening, scores, loss,
+// A workgroup per image reads the layer's weights twice, so for few of them only, and walks the classes one after the other for the input gradient, a lane
+// per four inputs: for few classes, or some more behind at least 64 inputs.  Against separate kernels for pooling, flattening, scores, loss,
 // input gradient and its re-layout: 1 024 inputs, 10 classes, bf16, 64 / 256 / 2 304 images 9 / 10 / 29 us instead of 27 / 28 / 47 (2 304 in fp32 24
-// instead of 41); 512 inputs, 50 classes behind a hidden layer, bf16, 2 304 images 33 instead of 48.
-inline bool head_kernel_wins(int in, int classes) { return (int64_t)in * classes <= 32768; }
+// instead of 41); 512 inputs, 50 classes behind a hidden layer, bf16, 2 304 images 33 instead of 48; whole heads, 1 024 inputs, 31 classes, 1 024 images 46
+// instead of 91; 64 and 301, 64 images 50 instead of 55; 8 and 101, 64 images 32 and 32; 8 and 301 50 instead of 40; 32 and 1 001 122 instead of 69.
+inline bool head_kernel_wins(int in, int classes) {
+  return (int64_t)in * classes <= 32768 && (classes <= 128 || (in >= 64 && classes <= 320));
+}
 
 }  // namespace sasgd
