@@ -975,29 +975,25 @@ __global__ __launch_bounds__(256) void fc_save_factors_kernel(PtrTab ws, PtrTab 
   const int n0 = (int)(blockIdx.y * 64u + (t % pieces) * 8u), u0 = (int)(t / pieces) * 8;
   if (u0 >= units || n0 >= NP) return;
   union { uint4 q; bf16_t h[8]; } src[8], dst[8];
-  const bool whole = units % 8 == 0;                                  // out is a multiple of 4 only
 #pragma unroll
   for (int k = 0; k < 8; k++) {
     src[k].q = make_uint4(0u, 0u, 0u, 0u);
     if (n0 + k >= N) continue;
-    const bf16_t* p = src_t + (int64_t)(n0 + k) * units + u0;
-    if (whole) src[k].q = *reinterpret_cast<const uint4*>(p);
-    else
-      for (int e = 0; e < 8; e++) src[k].h[e] = u0 + e < units ? p[e] : (bf16_t)0;
+    src[k].q = *reinterpret_cast<const uint4*>(src_t + (int64_t)(n0 + k) * units + u0);
   }
 #pragma unroll
   for (int e = 0; e < 8; e++)
 #pragma unroll
     for (int k = 0; k < 8; k++) dst[e].h[k] = src[k].h[e];
 #pragma unroll
-  for (int e = 0; e < 8; e++)
-    if (u0 + e < units) *reinterpret_cast<uint4*>(dst_t + (int64_t)(u0 + e) * NP + n0) = dst[e].q;
+  for (int e = 0; e < 8; e++) *reinterpret_cast<uint4*>(dst_t + (int64_t)(u0 + e) * NP + n0) = dst[e].q;
 }
 
 hipError_t launch_fc_save_factors(const PtrTab& ws, const PtrTab& grads, size_t x_off, size_t dy_off, size_t fx_off, size_t fdy_off,
                                   int64_t b_off, int N, int in, int out, int NP, int count, hipStream_t s) {
+  if (in % 8 || out % 8) return hipErrorInvalidValue;          // (the matrix kernels take no other layers)
   const int pieces = std::min(8, NP / 8);
-  auto blocks = [&](int units) { return ((units + 7) / 8 * pieces + 255) / 256; };
+  auto blocks = [&](int units) { return (units / 8 * pieces + 255) / 256; };
   const int per_bias = 256 / kSaveSegments;
   hipLaunchKernelGGL(fc_save_factors_kernel, dim3((unsigned)(blocks(in) + blocks(out) + (out + per_bias - 1) / per_bias), (unsigned)((NP + 63) / 64), (unsigned)count),
                      dim3(256), 0, s, ws, grads, x_off, dy_off, fx_off, fdy_off, b_off, N, in, out, NP, blocks(in), blocks(out));
