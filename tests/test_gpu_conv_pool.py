@@ -46,7 +46,7 @@ def test_against_oracle(name):
 @pytest.mark.parametrize("odd_values", [False, True], ids=["plain", "inf_nan_zero"])
 def test_same_bits_as_separate_kernels(relu_first, odd_values):
     """Images of eight channels of bf16 values behind a 1 x 1 convolution that copies them: the pooled one is the second layer there, in kernels
-    of its own, and everything behind it has the same bits.  Infinities, NaNs and images of zeros pass as they do there."""
+    of its own, and everything behind it has the same bits.  NaNs (infinite pixels become some in the copy) and images of zeros pass as they do there."""
     from paper_1511_05950_amd import binding
     tail = [("conv", 40, 3, 1, 1)] + ([R, P] if relu_first else [P, R])
     one, two = net(8, 25, 30, *tail), net(8, 25, 30, ("conv", 8, 1, 1, 0), *tail)
@@ -79,3 +79,44 @@ def test_same_bits_as_separate_kernels(relu_first, odd_values):
         np.testing.assert_array_equal(got[0][0].numpy(), got[1][0].numpy())
     for a, b in zip(got[0][1], got[1][1]):
         np.testing.assert_array_equal(a, b)                       # NaNs in the same places count as equal
+
+
+@pytest.mark.parametrize("tail", [(P,), (R, P), (P, R)], ids=["pool", "relu_pool", "pool_relu"])
+def test_infinities_reach_the_pooling(tail):
+    """As above, with pixels of 3e38 in one channel, which the copying convolution keeps as they are: the pooled one, whose filters weigh that channel
+    with 2 (even ones) or -2 everywhere, makes infinities of both signs.  Behind the pooling a 1 x 1 convolution with weights below zero (even channels)
+    or above and a ReLU make zeros of those of positive pixels, and the learner's loss is finite; of negative pixels' it is not.  Other learners
+    have NaN pixels, which that ReLU ends."""
+    from paper_1511_05950_amd import binding
+    behind = list(tail) + [("conv", 16, 1, 1, 0), R]
+    one, two = net(8, 25, 30, ("conv", 40, 3, 1, 1), *behind), net(8, 25, 30, ("conv", 8, 1, 1, 0), ("conv", 40, 3, 1, 1), *behind)
+    lam, mu = 16, 16
+    w, X, Y = draw_case(one, lam, mu, 9, 0.05)
+    first = w[:40 * 8 * 9].reshape(40, 8, 9)
+    first[0::2, 0], first[1::2, 0] = 2, -2
+    second = w[40 * 8 * 9 + 40:][:16 * 40].reshape(16, 40)
+    second[:, 0::2], second[:, 1::2] = -np.abs(second[:, 0::2]), np.abs(second[:, 1::2])
+    X = torch.from_numpy(X).bfloat16().float().view(lam, mu, 8, 25, 30)
+    g = torch.Generator().manual_seed(3)
+    spots = torch.rand((lam, mu, 25, 30), generator=g) < 2e-2
+    X[1::4, :, 0][spots[1::4]], X[2::4, :, 0][spots[2::4]] = 3e38, -3e38
+    X[3::4] = X[3::4].masked_fill(spots[3::4][:, :, None], float("nan"))
+    for k, reach in enumerate([(False, False, False), (True, True, False), (True, True, False), (False, False, True)]):   # what the pooling reads
+        y = torch.nn.functional.conv2d(X[k], torch.from_numpy(first).view(40, 8, 3, 3), torch.from_numpy(w[40 * 8 * 9:][:40]), padding=1)
+        assert (bool((y == np.inf).any()), bool((y == -np.inf).any()), bool(y.isnan().any())) == reach
+    X, Yd = X.view(lam * mu, 8, 25, 30).cuda(), torch.from_numpy(Y).cuda()
+    copy = np.concatenate([np.eye(8, dtype=np.float32).ravel(), np.zeros(8, np.float32), w])
+    got = []
+    for nt, theta in ((one, w), (two, copy)):
+        ctx = binding.Sasgd(lam, mu, lam, 2, net=nt, compute="bf16", init_weights=theta)
+        loss = torch.zeros(lam, device="cuda")
+        for k in range(lam):
+            ctx.getMinibatch(k, X[k * mu:(k + 1) * mu], Yd[k * mu:(k + 1) * mu])
+            ctx.pullWeights(k, 0)
+        ctx.calcGradient(list(range(lam)), loss)
+        got.append((loss.cpu().numpy(), [ctx.copyGradient(k)[40 * 8 * 9 + 40 - wl.num_params(one):] for k in range(lam)]))
+        ctx.destroy()
+    assert np.isfinite(got[0][0]).tolist() == [k % 4 != 2 for k in range(lam)]
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    for a, b in zip(got[0][1], got[1][1]):
+        np.testing.assert_array_equal(a, b)
