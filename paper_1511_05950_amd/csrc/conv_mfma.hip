@@ -1854,19 +1854,18 @@ __global__ __launch_bounds__(512, 2) void wgrad_strip_kernel(PtrTab ws, IGemm g,
   };
 #pragma clang diagnostic pop
   // POOL: this thread's 8 channels of a 2 x 2 block of the tile's positions
-  const int chunk = tid & (TM * 4 - 1), block = tid / (TM * 4), half = g.OW >> 1;
-  const int block_row = (int)fastdiv((uint32_t)block * 2, g.OW, g.mg_ow), block_col = block - block_row * half;
+  const PoolBlock block = pool_block(tid, TM, g.OW, [&](uint32_t n) { return fastdiv(n, g.OW, g.mg_ow); });
   v4i_t wd[4];                 // the windows above left, above, left and its own: their gradients
   v2i_t wa[4];                 // and winners
   auto request_windows = [&](int t) {
-    const uint32_t gr = fastdiv((uint32_t)t * MT, g.OW, g.mg_ow) + 2 * block_row;      // (a tile begins with an even row)
+    const uint32_t gr = fastdiv((uint32_t)t * MT, g.OW, g.mg_ow) + 2 * block.row;      // (a tile begins with an even row)
     const int n = (int)fastdiv(gr, g.OH, g.mg_oh), a = (int)(gr - (uint32_t)n * g.OH) >> 1;
-    const bool mine = tid < TM * MT && chunk * 8 < g.Ncols && gr < out_rows;
+    const bool mine = tid < TM * MT && block.chunk * 8 < g.Ncols && gr < out_rows;
 #pragma unroll
     for (int w = 0; w < 4; w++) {
-      const int oh = a - 1 + (w >> 1), ow = block_col - 1 + (w & 1);
+      const int oh = a - 1 + (w >> 1), ow = block.col - 1 + (w & 1);
       const bool ok = mine && (unsigned)oh < (unsigned)h.PH && (unsigned)ow < (unsigned)h.PWo;
-      const int o = ((n * h.PH + oh) * h.PWo + ow) * g.Ncols + chunk * 8;
+      const int o = ((n * h.PH + oh) * h.PWo + ow) * g.Ncols + block.chunk * 8;
       wd[w] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_pooled, ok ? o * 2 : (int)kOutOfRange, 0, 0);
       wa[w] = __builtin_amdgcn_raw_buffer_load_b64(rsrc_arg, ok ? o : (int)kOutOfRange, 0, 0);
     }
@@ -1875,7 +1874,7 @@ __global__ __launch_bounds__(512, 2) void wgrad_strip_kernel(PtrTab ws, IGemm g,
   // the same sums in the same order as pool_bwd_3x3s2_kernel
   auto spread_windows = [&](int buf) {
     if (tid >= TM * MT) return;
-    char* to = lds + buf + ((chunk >> 2) * MT + block_row * 2 * g.OW + 2 * block_col) * 64 + (chunk & 3) * 16;
+    char* to = lds + buf + ((block.chunk >> 2) * MT + block.first) * 64 + (block.chunk & 3) * 16;
     // (255, a window that passes nothing on, becomes 15: no place either, and no borrow below)
 #pragma unroll
     for (int w = 0; w < 4; w++) wa[w] &= 0x0f0f0f0f;

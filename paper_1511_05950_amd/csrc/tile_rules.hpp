@@ -249,6 +249,14 @@ inline bool strip_plan(const StripLayer& g, StripPlan* p) {
 // 2 x 2 blocks of one image each: rows in pairs, and a whole number of pairs a tile.  Wherever it can, it is no slower than the pooling
 // layer's kernel in front of it: of 16 calls of one learner x 64 images to 18 x 128, the whole calls took 0.4 to 12 % less.
 inline bool strip_pools(const StripPlan& p, int OH, int OW) { return OH % 2 == 0 && OW % 2 == 0 && kStripForms[p.form].MT % (2 * OW) == 0; }
+// A thread's part of such a tile there: 8 channels (of 32 * panels) of a 2 x 2 block, which are the output positions `first`, first + 1, first + OW
+// and first + OW + 1 of the tile and lie in the window of that block and those above, left and above left of it.  by_ow(n) is n / OW.
+struct PoolBlock { int chunk, row, col, first; };
+template <class ByOW>
+constexpr PoolBlock pool_block(int tid, int panels, int OW, ByOW by_ow) {
+  const int block = tid / (panels * 4), row = (int)by_ow((uint32_t)block * 2), col = block - row * (OW >> 1);
+  return {tid & (panels * 4 - 1), row, col, row * 2 * OW + 2 * col};
+}
 
 // ---- fully connected layers over all rows of a weight version, bf16
 // Tiles of 64 tm rows x 128 columns and splits of the contraction (K values, in stages of 64).  The least of: rounds of one

@@ -74,6 +74,38 @@ def test_threads_cover_a_tile(tm, mt):
         assert len(seen) == tm * 4 * mt and max(p for _, p in seen) == mt - 1
 
 
+BLOCKS = r"""
+#include <stdio.h>
+#include "tile_rules.hpp"
+int main() {
+  int tm, mt, ow;
+  if (scanf("%d %d %d", &tm, &mt, &ow) != 3) return 1;
+  for (int tid = 0; tid < tm * mt; tid++) {
+    const sasgd::PoolBlock b = sasgd::pool_block(tid, tm, ow, [&](uint32_t n) { return n / (uint32_t)ow; });
+    printf("%d %d %d %d\n", b.chunk, b.row, b.col, b.first);
+  }
+}
+"""
+
+
+def test_the_kernels_blocks_cover_a_tile(tmp_path):
+    """As above, of the function that places the kernel's threads."""
+    (tmp_path / "blocks.cpp").write_text(BLOCKS)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_1511_05950_amd", "csrc"), str(tmp_path / "blocks.cpp"), "-o", str(tmp_path / "blocks")], check=True)
+    for tm, mt in [(2, 256), (1, 512), (1, 256)]:
+        for ow in [k for k in range(2, mt // 2 + 1, 2) if mt % (2 * k) == 0]:
+            out = subprocess.run([str(tmp_path / "blocks")], input="%d %d %d" % (tm, mt, ow), capture_output=True, text=True, check=True).stdout
+            seen = set()
+            for chunk, row, col, first in (map(int, line.split()) for line in out.splitlines()):
+                for q in range(4):
+                    p = first + q // 2 * ow + q % 2
+                    seen.add((chunk, p))
+                    r, c = divmod(p, ow)
+                    windows = {(a, b) for a in range(-1, r + 1) for b in range(-1, c + 1) if 0 <= r - 2 * a <= 2 and 0 <= c - 2 * b <= 2}
+                    assert windows <= {(row + a, col + b) for a in (-1, 0) for b in (-1, 0)}
+            assert seen == {(chunk, p) for chunk in range(tm * 4) for p in range(mt)}
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("relu_first", [True, False])
 @pytest.mark.parametrize("name", sorted(CASES))
